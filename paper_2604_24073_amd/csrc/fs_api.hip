@@ -182,6 +182,57 @@ void forget_fetched(fs_ctx *ctx) {
     for (int k = 0; k < FS_MAX_STEP_TABLES; ++k) ctx->fetched_emb[k] = nullptr;
 }
 
+// The streams that the contexts of one GPU run their own work on.  The chip gives a process four hardware queues:
+// one side stream, two index streams and the caller's stream are exactly four, and streams beyond that share a queue
+// with another one and run behind its work.  A program with several contexts on a GPU therefore gets one set for all of
+// them (three contexts with a set each, stepped in turn: 118 us per step of a 4M x 128 table where one context takes
+// 98).  Streams are safe to enqueue on from several threads, every wait enqueued here is for an event recorded
+// before, so contexts that share a stream can delay each other but not wait for each other in a circle.  Created with
+// the first context of a GPU, destroyed with the last.
+constexpr int kPoolDevices = 64;
+struct stream_set {
+    int users = 0;
+    hipStream_t a = nullptr, x[kIndexStreams] = {};
+};
+std::mutex g_pool_mu;
+stream_set g_pool[kPoolDevices];
+
+void destroy_set(stream_set &p) {
+    if (p.a) { (void)hipStreamSynchronize(p.a); (void)hipStreamDestroy(p.a); }
+    for (hipStream_t &st : p.x)
+        if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
+    p = stream_set();
+}
+
+bool acquire_streams(fs_ctx *c) {
+    if (c->device >= kPoolDevices) return false;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    stream_set &p = g_pool[c->device];
+    if (p.users == 0) {
+        bool ok = hipStreamCreateWithFlags(&p.a, hipStreamNonBlocking) == hipSuccess;
+        for (hipStream_t &st : p.x) ok = ok && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
+        if (!ok) {
+            destroy_set(p);
+            return false;
+        }
+    }
+    ++p.users;
+    c->stream_a = p.a;
+    for (int k = 0; k < kIndexStreams; ++k) c->stream_x[k] = p.x[k];
+    return true;
+}
+
+void release_streams(fs_ctx *c) {
+    if (!c->stream_a) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    stream_set &p = g_pool[c->device];
+    // this context's work has to be done before its events and workspace go
+    (void)hipStreamSynchronize(c->stream_a);
+    for (hipStream_t st : c->stream_x) (void)hipStreamSynchronize(st);
+    if (--p.users == 0) destroy_set(p);
+    c->stream_a = nullptr;
+}
+
 void worker_stop(fs_ctx *ctx);
 int join_pending_work(fs_ctx *ctx, hipStream_t s);
 void drop_ahead(fs_ctx *ctx, const void *key);
@@ -234,12 +285,9 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     }
     c->host = new (std::nothrow) fs_host();
     ok = ok && c->host != nullptr;
-    // The chip gives a process four hardware queues; streams beyond that share them, and two streams on one
-    // queue run one after the other.  Only the streams of the steady-state step exist from the start (side
-    // stream, index streams: with the caller's stream that makes four); the self-contained step's second side
-    // stream and the capture stream are created when first needed.
-    ok = ok && hipStreamCreateWithFlags(&c->stream_a, hipStreamNonBlocking) == hipSuccess;
-    for (hipStream_t &st : c->stream_x) ok = ok && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
+    // Only the streams of the steady-state step exist from the start; the self-contained step's second side
+    // stream and the streams of a graph capture are created when first needed.
+    ok = ok && acquire_streams(c);
     hipEvent_t *evs[] = {&c->ev_fork, &c->ev_split, &c->ev_ex, &c->ev_pfork[0], &c->ev_pfork[1], &c->ev_side[0],
                          &c->ev_side[1]};
     // These events order work of this device's streams among themselves and nothing else: nobody reads through
@@ -265,11 +313,10 @@ int fs_ctx_destroy(fs_ctx *c) {
     if (!c) return FS_OK;
     (void)hipSetDevice(c->device);
     worker_stop(c);
-    hipStream_t streams[] = {c->stream_a, c->stream_b, c->stream_cap};
+    hipStream_t streams[] = {c->stream_b, c->stream_cap, c->stream_cap_a};
     for (hipStream_t st : streams)
         if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
-    for (hipStream_t st : c->stream_x)
-        if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
+    release_streams(c);
     hipEvent_t evs[] = {c->ev_fork, c->ev_split, c->ev_ex, c->ev_pfork[0], c->ev_pfork[1], c->ev_side[0], c->ev_side[1]};
     for (hipEvent_t e : evs)
         if (e) (void)hipEventDestroy(e);
@@ -830,7 +877,8 @@ struct side_work {
 // Side stream A for one pipelined call: after the caller's earlier work (the gradients of `cur`), the
 // deferred passes, then the index halves of `next`, then the event the next call waits for.
 int enqueue_side_stream(fs_ctx *ctx, const side_work &w) {
-    hipStream_t sa = ctx->stream_a;
+    // a capture stays off the shared streams: what another context enqueues meanwhile must not end up in the graph
+    hipStream_t sa = ctx->capturing ? ctx->stream_cap_a : ctx->stream_a;
     int rc = FS_OK;
     FS_HIP(ctx, hipStreamWaitEvent(sa, ctx->ev_pfork[w.parity], 0));
     rc = enqueue_class_passes(ctx, w.cur, w.have_t, w.count, 1, sa, w.ex_timing);
@@ -1356,10 +1404,11 @@ int fs_graph_capture_pipelined(fs_ctx *ctx, const fs_step_args *cur, const fs_st
     ctx->side_pending = false;
     (void)hipStreamSynchronize(ctx->stream_a);
     for (hipStream_t sx : ctx->stream_x) (void)hipStreamSynchronize(sx);
-    if (!ctx->stream_cap && hipStreamCreateWithFlags(&ctx->stream_cap, hipStreamNonBlocking) != hipSuccess) {
-        delete g;
-        return set_err(ctx, FS_EHIP, "hipStreamCreateWithFlags(capture stream)");
-    }
+    for (hipStream_t *st : {&ctx->stream_cap, &ctx->stream_cap_a})
+        if (!*st && hipStreamCreateWithFlags(st, hipStreamNonBlocking) != hipSuccess) {
+            delete g;
+            return set_err(ctx, FS_EHIP, "hipStreamCreateWithFlags(capture stream)");
+        }
     hipError_t e = hipStreamBeginCapture(ctx->stream_cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) {
         delete g;

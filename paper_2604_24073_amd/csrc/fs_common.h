@@ -178,9 +178,11 @@ struct fs_ctx {
     int64_t *jag_tile_sum;    // [scan tiles] output elements per tile of output samples
     int32_t *jag_sel;         // [max_ids] computed segment order of a keyed shuffle
 
+    // shared by the contexts of a GPU (fs_api.hip)
     hipStream_t stream_a;     // side stream: index half of the lookahead batch; deferred pass of a pipelined call
-    hipStream_t stream_b;     // deferred pass of the self-contained step
     hipStream_t stream_x[kIndexStreams];   // ahead-of-time dedups and index halves, used in turn
+    // this context's own, created when first needed
+    hipStream_t stream_b;     // deferred pass of the self-contained step
     hipEvent_t ev_fork, ev_split, ev_ex;   // self-contained step and fs_step_forward
     hipEvent_t ev_pfork[2];   // position of the caller's stream at the start of a pipelined call (alternating)
     hipEvent_t ev_side[2];    // side-stream work of a pipelined call (deferred pass of cur, index half of next) done
@@ -196,6 +198,7 @@ struct fs_ctx {
     struct fs_host *host;     // host threads and the table of outstanding ahead-of-time dedups
     bool use_worker;
     hipStream_t stream_cap;   // capture stream of fs_graph_capture_pipelined
+    hipStream_t stream_cap_a; // the side stream of a capture
     bool capturing;           // host-side: a step is being recorded into a graph (no timing events)
     int timing_slots;
     int timing_every;         // bracket the kernels of one step in `timing_every`

@@ -359,13 +359,13 @@ typedef struct fs_step_args {
 
 /* Iteration t on one shard, scheduled as Section 3.2 prescribes (strict write-read ordering
  * on collision rows only):
- *   side stream A : fs_unique_ids(values_t1) -> fs_collision_split_classes(U_t, U_t1)
- *   `stream`      : wait A; fs_reduce_update_class(0)  [priority pass: collision rows];
+ *   `stream`      : update of every row of U_t straight from the layout of batch t (the arithmetic of
+ *                   fs_reduce_update_class; one call has nothing to gain from updating the exclusive rows later);
  *                   fs_gather_jagged(values_t1)
- *   side stream B : after A: fs_reduce_update_class(1) [deferred pass: exclusive rows],
- *                   overlapping the gather, which is race-free because ex and U_t1 are disjoint
- * and `stream` finally waits for B, so the step is complete when `stream` is.  Results are
- * identical to running the five operations one after another. */
+ *   index half    : fs_unique_ids(values_t1) -> fs_collision_split_classes(U_t, U_t1), which neither of the two
+ *                   waits for: on side stream A beside them (large batches; `stream` finally waits for A) or
+ *                   behind them on `stream`
+ * The step is complete when `stream` is.  Results are identical to running the five operations one after another. */
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *args, fs_stream stream);
 
 /* The index half of an iteration alone - what Forward of Algorithm 2 does with the prefetched

@@ -285,10 +285,10 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     }
     c->host = new (std::nothrow) fs_host();
     ok = ok && c->host != nullptr;
-    // Only the streams of the steady-state step exist from the start; the self-contained step's second side
-    // stream and the streams of a graph capture are created when first needed.
+    // Only the streams of the steady-state step exist from the start; those of a graph capture are created when
+    // first needed.
     ok = ok && acquire_streams(c);
-    hipEvent_t *evs[] = {&c->ev_fork, &c->ev_split, &c->ev_ex, &c->ev_pfork[0], &c->ev_pfork[1], &c->ev_side[0],
+    hipEvent_t *evs[] = {&c->ev_fork, &c->ev_split, &c->ev_pfork[0], &c->ev_pfork[1], &c->ev_side[0],
                          &c->ev_side[1]};
     // These events order work of this device's streams among themselves and nothing else: nobody reads through
     // them what a kernel wrote (the host only asks whether one has passed, to skip a wait).  Without the
@@ -313,11 +313,11 @@ int fs_ctx_destroy(fs_ctx *c) {
     if (!c) return FS_OK;
     (void)hipSetDevice(c->device);
     worker_stop(c);
-    hipStream_t streams[] = {c->stream_b, c->stream_cap, c->stream_cap_a};
+    hipStream_t streams[] = {c->stream_cap, c->stream_cap_a};
     for (hipStream_t st : streams)
         if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
     release_streams(c);
-    hipEvent_t evs[] = {c->ev_fork, c->ev_split, c->ev_ex, c->ev_pfork[0], c->ev_pfork[1], c->ev_side[0], c->ev_side[1]};
+    hipEvent_t evs[] = {c->ev_fork, c->ev_split, c->ev_pfork[0], c->ev_pfork[1], c->ev_side[0], c->ev_side[1]};
     for (hipEvent_t e : evs)
         if (e) (void)hipEventDestroy(e);
     if (c->host) {
@@ -344,7 +344,6 @@ int fs_check_async(fs_ctx *ctx, fs_stream stream) {
     if (jrc != FS_OK) return jrc;
     FS_HIP(ctx, hipStreamSynchronize(as_stream(stream)));
     FS_HIP(ctx, hipStreamSynchronize(ctx->stream_a));
-    if (ctx->stream_b) FS_HIP(ctx, hipStreamSynchronize(ctx->stream_b));
     for (hipStream_t sx : ctx->stream_x) FS_HIP(ctx, hipStreamSynchronize(sx));
     int flags[4] = {0, 0, 0, 0};
     FS_HIP(ctx, hipMemcpy(flags, ctx->d_flags, sizeof(flags), hipMemcpyDeviceToHost));
@@ -828,11 +827,6 @@ int enqueue_class_passes(fs_ctx *ctx, const fs_step_args *a, const bool *use, in
     return rc;
 }
 
-int enqueue_class_pass(fs_ctx *ctx, const fs_step_args *a, int cls, hipStream_t s, hipEvent_t *timing) {
-    const bool use = true;
-    return enqueue_class_passes(ctx, a, &use, 1, cls, s, timing);
-}
-
 // `part` (optional): per table -1 = the whole lookup, 0 / 1 = the exclusive / collision rows only
 int enqueue_gathers(fs_ctx *ctx, const fs_step_args *a, const bool *use, int count, hipStream_t s,
                     const int *part = nullptr, bool timed = true) {
@@ -857,9 +851,12 @@ int enqueue_gathers(fs_ctx *ctx, const fs_step_args *a, const bool *use, int cou
     return rc;
 }
 
+// the lookup of one step in batch order: the ascending ID list is still in the making
 int enqueue_gather(fs_ctx *ctx, const fs_step_args *a, hipStream_t s) {
+    fs_step_args x = *a;
+    x.sorted_ids_t1 = nullptr;
     const bool use = true;
-    return enqueue_gathers(ctx, a, &use, 1, s);
+    return enqueue_gathers(ctx, &x, &use, 1, s);
 }
 
 // What one pipelined call hands to side stream A: for each of its tables the deferred pass of `cur` and the
@@ -1167,42 +1164,49 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     return FS_OK;
 }
 
+// IDs of both batches from which the self-contained step takes its index half to the side stream
+constexpr int64_t kStepSideIds = 131072;
+
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     if (!ctx) return FS_EINVAL;
     bool have_t, have_t1;
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
-    if (!ctx->stream_b) FS_HIP(ctx, hipStreamCreateWithFlags(&ctx->stream_b, hipStreamNonBlocking));
-    hipStream_t sp = as_stream(stream), sa = ctx->stream_a, sb = ctx->stream_b;
+    hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
     forget_fetched(ctx);
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
     begin_step_timing(ctx);
     fs_ahead *index_ahead = claim_ahead(ctx, a->counts_dev);
     fs_ahead *ahead = (!index_ahead && have_t1) ? claim_ahead(ctx, a->u_t1) : nullptr;
-    // fork: the side streams start after whatever the caller already queued on `stream`
-    FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
-    FS_HIP(ctx, hipStreamWaitEvent(sa, ctx->ev_fork, 0));
-    FS_HIP(ctx, hipStreamWaitEvent(sb, ctx->ev_fork, 0));
-    rc = index_ahead ? consume_ahead(ctx, index_ahead, sa) : enqueue_index_work(ctx, a, have_t, have_t1, ahead, sa);
-    if (rc != FS_OK) return rc;
-    FS_HIP(ctx, hipEventRecord(ctx->ev_split, sa));
-    FS_HIP(ctx, hipStreamWaitEvent(sp, ctx->ev_split, 0));
-    FS_HIP(ctx, hipStreamWaitEvent(sb, ctx->ev_split, 0));
+    // Nothing outside this call can start before its last update, so the row work does not wait for the split: every
+    // row of U_t is updated straight from the layout of batch t, then the lookahead rows are read, in batch order;
+    // the index half is independent of both.  On the side stream it runs beside them, which costs two cross-stream
+    // waits of 10-12 us of host time each: worth it where the row work is long (4M x 128, 262 k IDs a batch: 182
+    // against 191 us), while a tiny call is bound by its host path (1 k IDs: 81 against 52 us).
+    const bool side = (have_t ? a->n_t : 0) + (have_t1 ? a->n_t1 : 0) > kStepSideIds;
+    if (side) FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
     if (have_t) {
-        // priority pass: collision rows, strictly before the lookahead rows are read
-        rc = enqueue_class_pass(ctx, a, 0, sp, timing_pair(ctx, FS_TIME_UPDATE_CO));
+        hipEvent_t *tu = timing_pair(ctx, FS_TIME_UPDATE_CO);
+        if (tu) (void)hipEventRecord(tu[0], sp);
+        rc = launch_batch_update(ctx, fs_batch_update_job{a->grads_t, a->n_t, a->dim, a->perm_t, a->seg_offsets_t, a->u_t,
+                                                          a->n_unique_t_dev, a->table, a->dtype, a->state, a->num_rows,
+                                                          a->lr, a->eps, a->reduced}, sp);
         if (rc != FS_OK) return rc;
-        // deferred pass on B: exclusive rows and lookahead rows are disjoint, so it may overlap the gather
-        rc = enqueue_class_pass(ctx, a, 1, sb, timing_pair(ctx, FS_TIME_UPDATE_EX));
-        if (rc != FS_OK) return rc;
+        if (tu) (void)hipEventRecord(tu[1], sp);
     }
-    FS_HIP(ctx, hipEventRecord(ctx->ev_ex, sb));
     if (have_t1) {
         rc = enqueue_gather(ctx, a, sp);
         if (rc != FS_OK) return rc;
     }
-    FS_HIP(ctx, hipStreamWaitEvent(sp, ctx->ev_ex, 0));
+    if (side) FS_HIP(ctx, hipStreamWaitEvent(sa, ctx->ev_fork, 0));
+    hipStream_t si = side ? sa : sp;
+    rc = index_ahead ? consume_ahead(ctx, index_ahead, si) : enqueue_index_work(ctx, a, have_t, have_t1, ahead, si);
+    if (rc != FS_OK) return rc;
+    if (side) {
+        FS_HIP(ctx, hipEventRecord(ctx->ev_split, sa));
+        FS_HIP(ctx, hipStreamWaitEvent(sp, ctx->ev_split, 0));
+    }
     if (ctx->timing_now) ++ctx->timing_steps;
     return FS_OK;
 }

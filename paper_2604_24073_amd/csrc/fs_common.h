@@ -127,6 +127,20 @@ struct fs_class_pass_job {
     const int32_t *short_rec;       // the records of the class
     const int64_t *n_rows_dev;      // the number of rows of the class
 };
+// the update of every row of a batch straight from its layout (host side)
+struct fs_batch_update_job {
+    const float *grads;
+    int64_t n;
+    int32_t dim;
+    const int32_t *perm, *seg_offsets;
+    const int64_t *u_t, *n_unique_dev;
+    void *table;
+    int dt;
+    float *state;
+    int64_t num_rows;
+    float lr, eps;
+    float *reduced;
+};
 struct fs_gather_job {
     const void *table;
     int64_t num_rows;
@@ -181,9 +195,7 @@ struct fs_ctx {
     // shared by the contexts of a GPU (fs_api.hip)
     hipStream_t stream_a;     // side stream: index half of the lookahead batch; deferred pass of a pipelined call
     hipStream_t stream_x[kIndexStreams];   // ahead-of-time dedups and index halves, used in turn
-    // this context's own, created when first needed
-    hipStream_t stream_b;     // deferred pass of the self-contained step
-    hipEvent_t ev_fork, ev_split, ev_ex;   // self-contained step and fs_step_forward
+    hipEvent_t ev_fork, ev_split;          // self-contained step and fs_step_forward
     hipEvent_t ev_pfork[2];   // position of the caller's stream at the start of a pipelined call (alternating)
     hipEvent_t ev_side[2];    // side-stream work of a pipelined call (deferred pass of cur, index half of next) done
     int pipe_parity;          // event set used by the last pipelined call
@@ -295,6 +307,7 @@ int launch_reduce_update(fs_ctx *, int cls, const float *grads, int64_t n, int32
                          const int32_t *cstart, const int64_t *u_t, void *table, int dt, float *state,
                          int64_t num_rows, float lr, float eps, float *reduced, hipStream_t s,
                          const int32_t *short_rec, const int64_t *n_rows_dev);
+int launch_batch_update(fs_ctx *, const fs_batch_update_job &job, hipStream_t s);
 // the class passes (class `cls`) / the gathers of `count` tables: tables of one dtype and row width share launches
 int launch_reduce_update_batch(fs_ctx *, int cls, int count, const fs_class_pass_job *jobs, hipStream_t s);
 int launch_gather_batch(fs_ctx *, int count, const fs_gather_job *jobs, hipStream_t s);

@@ -98,6 +98,23 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T *sh, T &total) {
     return base + inc - v;
 }
 
+// number of entries of a[0, n) that are <= key; executed by one whole wavefront (64-ary search)
+template <typename T>
+__device__ __forceinline__ int wave_upper_bound(const T *__restrict__ a, int n, T key) {
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = 0, hi = n;                      // a[i] <= key for i < lo, a[i] > key for i >= hi
+    while (lo < hi) {
+        const int step = (hi - lo + kWave - 1) / kWave;
+        const int probe = lo + (lane + 1) * step - 1;          // last entry of my sub-block
+        const bool le = (probe < hi) && (a[probe] <= key);
+        const int cnt = __popcll(__ballot(le));
+        lo += cnt * step;
+        const int nhi = lo + step - 1;
+        hi = nhi < hi ? nhi : hi;
+    }
+    return lo;
+}
+
 // ---- optional workgroup trace (diagnostic builds with -DFS_TRACE only) ------------------------------
 // Every workgroup of a traced kernel appends {kind, workgroups of the launch << 32 | linear workgroup id, first and last reading
 // of the 100 MHz wall clock by its thread 0} to a buffer the host sets with fs_debug_trace.  The buffer

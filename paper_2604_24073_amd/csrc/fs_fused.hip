@@ -33,20 +33,12 @@
 
 namespace fs {
 
-// build-time tuning knobs: row-group loads one wavefront issues per round; class positions per
-// wavefront in the priority / deferred pass (64, 32 or 16: collision rows have long segments,
-// exclusive rows short ones, and a short chunk means more wavefronts with shorter lives)
+// build-time tuning knobs: row-group loads one wavefront issues per round
 #ifndef FS_FUSED_UNR
 #define FS_FUSED_UNR 8
 #endif
 #ifndef FS_FUSED_RU
 #define FS_FUSED_RU 2                      // parked rows one group of lanes updates per round
-#endif
-#ifndef FS_FUSED_CHUNK_CO
-#define FS_FUSED_CHUNK_CO 64
-#endif
-#ifndef FS_FUSED_CHUNK_EX
-#define FS_FUSED_CHUNK_EX 64
 #endif
 #ifndef FS_SHORT_MAX_BLOCKS
 #define FS_SHORT_MAX_BLOCKS 1280
@@ -175,21 +167,32 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <bool BF16, int LPR, int UNR, int CHUNK>
-__device__ __forceinline__ void long_segments_body(
-    const int block, const f32x4 *__restrict__ grads, const int32_t *__restrict__ cperm, const int32_t *__restrict__ cslot,
-    const int32_t *__restrict__ class_pos, int cls, int n, const int32_t *__restrict__ seg_offsets,
-    const int32_t *__restrict__ cstart, const int64_t *__restrict__ u_t, void *table, float *state, int64_t num_rows,
-    int gvec, float lr, float eps, f32x4 *reduced, double *part_head, double *part_last, int *cnt_seg, int *cnt_sup,
-    int *flags) {
+// One wavefront's chunk of positions, wherever they come from (the class order, or the layout of a batch).  A lane
+// stands for one position of the chunk: the occurrence there, the slot and the table row of its segment, whether it
+// takes part.
+struct chunk_view {
+    int chunk, lo, n_chunks;       // number of the chunk, position of chunk 0, chunks there can be
+    int log2;                      // positions of a chunk
+    int pr, sl;
+    int64_t rid;
+    uint64_t live, tails;          // positions that take part; those that end a segment
+    bool head_cut, rest;           // the first segment came in from the chunk before; the last one goes on
+    int last;                      // the last position (its segment may go on)
+    int start[2], len[2];          // extents of the first and the last segment (positions)
+};
+
+template <bool BF16, int LPR, int UNR>
+__device__ __forceinline__ void long_chunk(const chunk_view &ch, const f32x4 *__restrict__ grads,
+                                           const int64_t *__restrict__ u_t, void *table, float *state, int64_t num_rows,
+                                           int gvec, float lr, float eps, f32x4 *reduced, double *part_head,
+                                           double *part_last, int *cnt_seg, int *cnt_sup, bool bad, int *flags) {
     constexpr int GPW = kWave / LPR;          // rows per wavefront instruction
     constexpr int BP = GPW * UNR;             // positions per batch
-    constexpr int NB = CHUNK / BP;            // batches per chunk
     // every segment here has more than FS_SHORT_SEGMENT positions, so only a few end inside one chunk:
     // their sums wait in LDS and are all applied in one round at the end of the chunk
-    constexpr int CAP = CHUNK / (FS_SHORT_SEGMENT + 1) + 1;
+    constexpr int CAP = kWave / (FS_SHORT_SEGMENT + 1) + 1;
     constexpr int RU = FS_FUSED_RU;
-    static_assert(CHUNK <= kWave && CHUNK % BP == 0, "one tail word, whole batches");
+    static_assert(BP <= kWave, "one tail word");
     __shared__ f32x4 stage[kFusedWaves][CAP * LPR];
     __shared__ int64_t stage_row[kFusedWaves][CAP];
     __shared__ int stage_slot[kFusedWaves][CAP];
@@ -198,63 +201,25 @@ __device__ __forceinline__ void long_segments_body(
     const int wib = threadIdx.x / kWave;
     const int grp = lane / LPR;
     const int lig = lane % LPR;
-    int lo = cls == 0 ? 0 : class_pos[0];
-    int hi = cls == 0 ? class_pos[0] : class_pos[1];
-    // A consistent class order never trips the range checks below; they turn a corrupted one into
-    // an error flag instead of a wild access.
-    if (lo < 0) lo = 0;
-    if (hi > n) hi = n;
-    const int chunk = block * kFusedWaves + wib;             // chunk number inside the class
-    const int64_t a64 = (int64_t)lo + (int64_t)chunk * CHUNK;
-    if (a64 >= hi) return;                                   // wave-uniform; wavefronts share nothing
-    const int a = (int)a64;
-    const int b = (a + CHUNK < hi) ? a + CHUNK : hi;
-    const int span = b - a;
     const bool col_ok = lig < gvec;
     const int dim = gvec * 4;
-
-    int pr = (lane < span) ? cperm[a + lane] : 0;
-    int sl = (lane < span) ? cslot[a + lane] : -1;
-    bool bad = (lane < span) && ((unsigned)pr >= (unsigned)n || (unsigned)sl >= (unsigned)n);
-    if (bad) { pr = 0; sl = 0; }
-    int edge = -1;                                           // lane 0: slot of position a-1, lane 1: of position b
-    if (lane == 0 && a > lo) edge = cslot[a - 1];
-    if (lane == 1 && b < hi) edge = cslot[b];
+    const int chunk = ch.chunk, lo = ch.lo, span = ch.last + 1;
+    const uint64_t tails = ch.tails;
+    const bool head_complete = !ch.head_cut;
     auto load_batch = [&](f32x4(&v)[UNR], int k) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int q = k * BP + u * GPW + grp;             // position inside the chunk
-            const int p = __shfl(pr, q, kWave);
+            const int p = __shfl(ch.pr, q, kWave);
             v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (col_ok && q < span) v[u] = __builtin_nontemporal_load(&grads[(int64_t)p * gvec + lig]);
+            if (col_ok && ((ch.live >> (q & 63)) & 1ull)) v[u] = __builtin_nontemporal_load(&grads[(int64_t)p * gvec + lig]);
         }
     };
-    f32x4 v[UNR];
-    load_batch(v, 0);
-    const int64_t rid = (lane < span) ? u_t[sl] : 0;          // table row of every position (used where a segment ends)
-    // extents of the first and the last segment of the chunk (lanes 0-2 / 3-5: class position of its
-    // first occurrence, its sorted positions): only needed if the chunk border cuts them
-    int meta = 0;
-    {
-        const int s_edge = __shfl(sl, lane < 3 ? 0 : span - 1, kWave);
-        if (lane < 6) {
-            const int f = lane % 3;
-            meta = f == 0 ? cstart[s_edge] : seg_offsets[s_edge + (f - 1)];
-        }
-    }
-
-    const int sl_prev = __shfl(edge, 0, kWave), sl_after = __shfl(edge, 1, kWave);
-    int nxt = __shfl_down(sl, 1, kWave);
-    if (lane == span - 1) nxt = sl_after;
-    const uint64_t tails = __ballot(lane < span && nxt != sl);
-    const int s_first = __builtin_amdgcn_readfirstlane(sl);
-    const bool head_complete = (a == lo) || (sl_prev != s_first);
 
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     int nflush = 0;
     int nparked = 0;
     bool oob = false;
-    const int n_chunks = (n + CHUNK - 1) / CHUNK;
 
     auto flush = [&](int q) {                                 // the segment that ends at chunk position q
         double t[4];
@@ -266,8 +231,8 @@ __device__ __forceinline__ void long_segments_body(
             if (nparked < CAP) {
                 if (grp == 0 && col_ok)
                     stage[wib][nparked * LPR + lig] = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
-                const int s_q = __shfl(sl, q, kWave);
-                const int64_t r_q = __shfl(rid, q, kWave);
+                const int s_q = __shfl(ch.sl, q, kWave);
+                const int64_t r_q = __shfl(ch.rid, q, kWave);
                 if (lane == 0) {
                     stage_slot[wib][nparked] = s_q;
                     stage_row[wib][nparked] = r_q;
@@ -308,11 +273,11 @@ __device__ __forceinline__ void long_segments_body(
         }
     };
 
-    for (int k = 0; k < NB; ++k) {
-        if (k > 0) {
-            if (k * BP >= span) break;                        // wave-uniform: ragged last chunk
-            load_batch(v, k);
-        }
+    f32x4 v[UNR];
+    for (int k = 0; k * BP < span; ++k) {
+        // wave-uniform: nobody in this batch takes part
+        if (((ch.live >> ((k * BP) & 63)) & (BP == kWave ? ~0ull : ((1ull << (BP & 63)) - 1ull))) == 0) continue;
+        load_batch(v, k);
         add_batch(v, k);
     }
     if (nparked > CAP) {                                      // cannot happen with a consistent class order
@@ -327,7 +292,7 @@ __device__ __forceinline__ void long_segments_body(
     }
 
     // positions after the last segment end of the chunk (the chunk's last position is not a tail)
-    const bool has_rest = ((tails >> (span - 1)) & 1ull) == 0;
+    const bool has_rest = ch.rest;
     if (has_rest) {
         double t[4];
 #pragma unroll
@@ -346,22 +311,18 @@ __device__ __forceinline__ void long_segments_body(
     // f+1+16j): the last piece of a super to arrive adds the super up (chunk order) and leaves the
     // sum in the super's first slot; the last of {first piece, supers} to arrive adds those up
     // (same order) and updates the row.
-    // The extents of the two candidate segments were requested at the start of the chunk (meta, below
-    // the first batch of loads); both first arrivals are counted with ONE atomic instruction (lane 0:
+    // Both first arrivals are counted with ONE atomic instruction (lane 0:
     // the piece of a super, lane 1: the first piece of the segment that leaves to the right), so the
     // common case costs one store acknowledgement and one atomic round trip per chunk.
-    const bool head_cut = !head_complete;
     const bool tail_cut = has_rest && (nflush > 0 || head_complete);
-    const int s_last = __shfl(sl, span - 1, kWave);
-    int seg_s[2] = {s_first, s_last}, c_first[2], c_last[2];
-    bool valid[2] = {head_cut, tail_cut};
+    int seg_s[2] = {__shfl(ch.sl, 0, kWave), __shfl(ch.sl, ch.last, kWave)}, c_first[2], c_last[2];
+    bool valid[2] = {ch.head_cut, tail_cut};
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
-        const int start = __shfl(meta, which * 3 + 0, kWave);
-        const int len = __shfl(meta, which * 3 + 2, kWave) - __shfl(meta, which * 3 + 1, kWave);
-        c_first[which] = (start - lo) / CHUNK;
-        c_last[which] = (start + len - 1 - lo) / CHUNK;
-        if (valid[which] && (start < lo || c_first[which] > chunk || c_last[which] < chunk || c_last[which] >= n_chunks ||
+        const int start = ch.start[which];
+        c_first[which] = (start - lo) >> ch.log2;
+        c_last[which] = (start + ch.len[which] - 1 - lo) >> ch.log2;
+        if (valid[which] && (start < lo || c_first[which] > chunk || c_last[which] < chunk || c_last[which] >= ch.n_chunks ||
                              c_last[which] == c_first[which] || (which == 0) != (chunk > c_first[which]))) {
             bad = true;
             valid[which] = false;
@@ -424,16 +385,141 @@ __device__ __forceinline__ void long_segments_body(
     if (bad) atomicOr(flags, kFlagInternal);
 }
 
+// The position-cut path over the class order: chunk `block * kFusedWaves + wavefront` of the class's positions.
+template <bool BF16, int LPR, int UNR>
+__device__ __forceinline__ void long_segments_body(
+    const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ cperm,
+    const int32_t *__restrict__ cslot, const int32_t *__restrict__ class_pos, int cls, int n,
+    const int32_t *__restrict__ seg_offsets, const int32_t *__restrict__ cstart, const int64_t *__restrict__ u_t,
+    void *table, float *state, int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, double *part_head,
+    double *part_last, int *cnt_seg, int *cnt_sup, int *flags) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int size = 1 << log2;
+    int lo = cls == 0 ? 0 : class_pos[0];
+    int hi = cls == 0 ? class_pos[0] : class_pos[1];
+    // A consistent class order never trips the range checks below; they turn a corrupted one into
+    // an error flag instead of a wild access.
+    if (lo < 0) lo = 0;
+    if (hi > n) hi = n;
+    chunk_view ch;
+    ch.chunk = block * kFusedWaves + threadIdx.x / kWave;    // chunk number inside the class
+    ch.lo = lo;
+    ch.log2 = log2;
+    ch.n_chunks = (n + size - 1) >> log2;
+    const int64_t a64 = (int64_t)lo + ((int64_t)ch.chunk << log2);
+    if (a64 >= hi) return;                                   // wave-uniform; wavefronts share nothing
+    const int a = (int)a64;
+    const int b = (a + size < hi) ? a + size : hi;
+    const int span = b - a;
+    ch.last = span - 1;
+    ch.pr = (lane < span) ? cperm[a + lane] : 0;
+    ch.sl = (lane < span) ? cslot[a + lane] : -1;
+    const bool bad = (lane < span) && ((unsigned)ch.pr >= (unsigned)n || (unsigned)ch.sl >= (unsigned)n);
+    if (bad) { ch.pr = 0; ch.sl = 0; }
+    int edge = -1;                                           // lane 0: slot of position a-1, lane 1: of position b
+    if (lane == 0 && a > lo) edge = cslot[a - 1];
+    if (lane == 1 && b < hi) edge = cslot[b];
+    ch.live = span == kWave ? ~0ull : (1ull << span) - 1ull;
+    ch.rid = (lane < span) ? u_t[ch.sl] : 0;                  // table row of every position (used where a segment ends)
+    // extents of the first and the last segment of the chunk (lanes 0-2 / 3-5: class position of its
+    // first occurrence, its sorted positions): only needed if the chunk border cuts them
+    int meta = 0;
+    {
+        const int s_edge = __shfl(ch.sl, lane < 3 ? 0 : span - 1, kWave);
+        if (lane < 6) {
+            const int f = lane % 3;
+            meta = f == 0 ? cstart[s_edge] : seg_offsets[s_edge + (f - 1)];
+        }
+    }
+    const int sl_prev = __shfl(edge, 0, kWave), sl_after = __shfl(edge, 1, kWave);
+    int nxt = __shfl_down(ch.sl, 1, kWave);
+    if (lane == span - 1) nxt = sl_after;
+    ch.tails = __ballot(lane < span && nxt != ch.sl);
+    ch.head_cut = a != lo && sl_prev == __builtin_amdgcn_readfirstlane(ch.sl);
+    ch.rest = ((ch.tails >> (span - 1)) & 1ull) == 0;
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        ch.start[which] = __shfl(meta, which * 3 + 0, kWave);
+        ch.len[which] = __shfl(meta, which * 3 + 2, kWave) - __shfl(meta, which * 3 + 1, kWave);
+    }
+    long_chunk<BF16, LPR, UNR>(ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
+                               cnt_seg, cnt_sup, bad, flags);
+}
+
+// The position-cut path straight over the layout of a batch (sorted positions, segment boundaries): positions of
+// segments with at most FS_SHORT_SEGMENT occurrences take no part.  The wavefront finds the segment of its first
+// position with a 64-ary search; its positions touch at most 64 consecutive segments, whose boundaries its lanes hold.
+template <bool BF16, int LPR, int UNR>
+__device__ __forceinline__ void long_segments_of_layout(
+    const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ perm, int n,
+    const int32_t *__restrict__ seg_offsets, const int64_t *__restrict__ u_t, int n_u, void *table, float *state,
+    int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, double *part_head, double *part_last, int *cnt_seg,
+    int *cnt_sup, int *flags) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int size = 1 << log2;
+    chunk_view ch;
+    ch.chunk = block * kFusedWaves + threadIdx.x / kWave;
+    ch.lo = 0;
+    ch.log2 = log2;
+    ch.n_chunks = (n + size - 1) >> log2;
+    const int64_t a64 = (int64_t)ch.chunk << log2;
+    if (a64 >= n || n_u <= 0) return;                        // wave-uniform; wavefronts share nothing
+    const int a = (int)a64;
+    const int span = (a + size < n) ? size : n - a;
+    ch.last = span - 1;
+    ch.pr = (lane < span) ? perm[a + lane] : 0;
+    bool bad = (unsigned)ch.pr >= (unsigned)n;
+    if (bad) ch.pr = 0;
+    int s0 = wave_upper_bound<int32_t>(seg_offsets, n_u, a) - 1;   // the segment of position a (boundary 0 is 0)
+    if (s0 < 0) { bad = true; s0 = 0; }
+    const int k = s0 + lane;
+    const int begin = k < n_u ? seg_offsets[k] : 0x7fffffff;
+    const int end = k < n_u ? seg_offsets[k + 1] : 0x7fffffff;
+    int idx = 0;                                             // the last of the 64 segments that starts at or before p
+    const int p = a + lane;
+#pragma unroll
+    for (int step = kWave / 2; step >= 1; step >>= 1)
+        if (__shfl(begin, idx + step, kWave) <= p) idx += step;
+    const int my_begin = __shfl(begin, idx, kWave), my_end = __shfl(end, idx, kWave);
+    ch.sl = s0 + idx;
+    // what a consistent layout never trips
+    if (lane < span && (my_begin < 0 || my_begin > p || my_end <= p || my_end > n || ch.sl >= n_u)) { bad = true; ch.sl = 0; }
+    const bool in = lane < span && !bad && my_end - my_begin > FS_SHORT_SEGMENT;
+    ch.live = __ballot(in);
+    if (__ballot(bad) != 0) {
+        if (lane == 0) atomicOr(flags, kFlagInternal);
+        return;
+    }
+    if (ch.live == 0) return;
+    ch.rid = in ? u_t[ch.sl] : 0;
+    ch.tails = __ballot(in && my_end == p + 1);
+    ch.start[0] = __shfl(my_begin, 0, kWave);
+    ch.len[0] = __shfl(my_end, 0, kWave) - ch.start[0];
+    ch.start[1] = __shfl(my_begin, ch.last, kWave);
+    ch.len[1] = __shfl(my_end, ch.last, kWave) - ch.start[1];
+    ch.head_cut = (ch.live & 1ull) != 0 && ch.start[0] < a;
+    ch.rest = ((ch.live >> ch.last) & 1ull) != 0 && ch.start[1] + ch.len[1] > a + span;
+    long_chunk<BF16, LPR, UNR>(ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
+                               cnt_seg, cnt_sup, false, flags);
+}
+
 // Short path: the rows of one class whose segment has at most FS_SHORT_SEGMENT occurrences.  The
 // index half left one record per row of the class (row, slot, number of occurrences, the
 // occurrences themselves), so a group of LPR lanes needs two dependent rounds per row: the record,
 // then table row + accumulator + all gradient rows of the segment at once.  Rows with longer
 // segments are skipped (the position-cut launch owns them).
-template <bool BF16, int LPR, int UNR>
+// LAYOUT: there are no records; row, extent and occurrences of a row come straight from the layout of the batch (one
+// dependent round more per row).
+struct row_source {
+    const int32_t *recs;           // records of a class, or
+    const int64_t *u_t;            // the layout of a batch
+    const int32_t *seg_offsets, *perm;
+};
+
+template <bool BF16, int LPR, int UNR, bool LAYOUT>
 __device__ __forceinline__ void short_rows_body(
-    const int block, const int nblocks, const f32x4 *__restrict__ grads, int n, const int32_t *__restrict__ recs, const int64_t *__restrict__ n_rows_dev,
-    int64_t cap, void *table, float *state, int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced,
-    int *flags) {
+    const int block, const int nblocks, const f32x4 *__restrict__ grads, int n, const row_source src, int64_t n_rows,
+    void *table, float *state, int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, int *flags) {
 #pragma clang fp contract(off)
     constexpr int GPW = kWave / LPR;
     constexpr int T = FS_SHORT_SEGMENT;
@@ -443,8 +529,6 @@ __device__ __forceinline__ void short_rows_body(
     const int lig = lane % LPR;
     const bool col_ok = lig < gvec;
     const int dim = gvec * 4;
-    int64_t n_rows = *n_rows_dev;
-    if (n_rows > cap) n_rows = cap;
     const int64_t waves = (int64_t)nblocks * kFusedWaves;
     const int64_t wave = (int64_t)block * kFusedWaves + (threadIdx.x / kWave);
     u32x4 *t4 = reinterpret_cast<u32x4 *>(table);
@@ -452,17 +536,41 @@ __device__ __forceinline__ void short_rows_body(
     bool oob = false, bad = false;
     for (int64_t base = wave * (GPW * UNR); base < n_rows; base += waves * (GPW * UNR)) {
         i32x4 hd[UNR], pa[UNR], pb[UNR];
+        if (LAYOUT) {
+            int at[UNR], cnt[UNR];
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int64_t i = base + u * GPW + grp;
-            const i32x4 *rec = reinterpret_cast<const i32x4 *>(recs + i * kShortRecInts);
-            hd[u] = i32x4{0, 0, 0, 0};
-            pa[u] = i32x4{0, 0, 0, 0};
-            pb[u] = i32x4{0, 0, 0, 0};
-            if (i < n_rows) {
-                hd[u] = rec[0];
-                pa[u] = rec[1];
-                pb[u] = rec[2];
+            for (int u = 0; u < UNR; ++u) {
+                const int64_t i = base + u * GPW + grp;
+                hd[u] = i32x4{0, 0, 0, 0};
+                at[u] = 0;
+                if (i < n_rows) {
+                    const int64_t row = src.u_t[i];
+                    at[u] = src.seg_offsets[i];
+                    hd[u] = i32x4{(int)(row & 0xFFFFFFFFll), (int)(row >> 32), (int)i, src.seg_offsets[i + 1] - at[u]};
+                }
+                cnt[u] = hd[u][3] <= T ? hd[u][3] : 0;
+                if (at[u] < 0 || at[u] > n - hd[u][3]) { bad = true; cnt[u] = 0; hd[u][3] = 0; }
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    pa[u][j] = j < cnt[u] ? src.perm[at[u] + j] : 0;
+                    pb[u][j] = 4 + j < cnt[u] ? src.perm[at[u] + 4 + j] : 0;
+                }
+        } else {
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const int64_t i = base + u * GPW + grp;
+                const i32x4 *rec = reinterpret_cast<const i32x4 *>(src.recs + i * kShortRecInts);
+                hd[u] = i32x4{0, 0, 0, 0};
+                pa[u] = i32x4{0, 0, 0, 0};
+                pb[u] = i32x4{0, 0, 0, 0};
+                if (i < n_rows) {
+                    hd[u] = rec[0];
+                    pa[u] = rec[1];
+                    pb[u] = rec[2];
+                }
             }
         }
         int64_t r[UNR];
@@ -572,7 +680,7 @@ __device__ __forceinline__ void short_rows_body(
 // better walked side by side than one after the other.
 struct class_pass_job {
     const f32x4 *grads;
-    int n, long_blocks, blocks, cls, gvec;
+    int n, long_blocks, blocks, chunk_log2, gvec;
     float lr, eps;
     const int32_t *cperm, *cslot, *class_pos, *seg_offsets, *cstart, *recs;
     const int64_t *u_t, *n_rows_dev;
@@ -589,30 +697,76 @@ struct class_pass_batch {
 
 // CLS (0: priority pass, 1: deferred pass) is a template parameter so that the two passes are two kernels by name
 // in a profile; the code is the same.
-template <bool BF16, int LPR, int UNR, int CHUNK, int SU, int CLS>
+template <bool BF16, int LPR, int UNR, int SU, int CLS>
 __global__ __launch_bounds__(kFusedWaves *kWave) void class_pass_kernel(const class_pass_batch batch, int *flags) {
     const class_pass_job &job = batch.j[blockIdx.y];
     FS_WG_TRACE(8 + CLS);
     if ((int)blockIdx.x >= job.blocks) return;
     if ((int)blockIdx.x < job.long_blocks)
-        long_segments_body<BF16, LPR, UNR, CHUNK>((int)blockIdx.x, job.grads, job.cperm, job.cslot, job.class_pos, CLS,
+        long_segments_body<BF16, LPR, UNR>((int)blockIdx.x, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos, CLS,
                                                   job.n, job.seg_offsets, job.cstart, job.u_t, job.table, job.state,
                                                   job.num_rows, job.gvec, job.lr, job.eps, job.reduced, job.part_head,
                                                   job.part_last, job.cnt_seg, job.cnt_sup, flags);
+    else {
+        int64_t n_rows = *job.n_rows_dev;
+        if (n_rows > job.n) n_rows = job.n;
+        short_rows_body<BF16, LPR, SU, false>((int)blockIdx.x - job.long_blocks, job.blocks - job.long_blocks, job.grads,
+                                              job.n, row_source{job.recs, nullptr, nullptr, nullptr}, n_rows, job.table,
+                                              job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
+    }
+}
+
+// All rows of a batch in one launch, straight from its layout: what the self-contained step runs, which has no use for
+// the two classes (nothing of it can start before the last update) and so needs neither split nor class order first.
+struct batch_update_job {
+    const f32x4 *grads;
+    int n, long_blocks, chunk_log2, gvec;
+    float lr, eps;
+    const int32_t *perm, *seg_offsets;
+    const int64_t *u_t, *n_unique_dev;
+    void *table;
+    float *state;
+    int64_t num_rows;
+    f32x4 *reduced;
+    double *part_head, *part_last;
+    int *cnt_seg, *cnt_sup;
+};
+
+template <bool BF16, int LPR, int UNR, int SU>
+__global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const batch_update_job job, int *flags) {
+    FS_WG_TRACE(9);
+    int64_t n_u = *job.n_unique_dev;
+    n_u = n_u < 0 ? 0 : (n_u > job.n ? job.n : n_u);
+    if ((int)blockIdx.x < job.long_blocks)
+        long_segments_of_layout<BF16, LPR, UNR>((int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
+                                                job.u_t, (int)n_u, job.table, job.state, job.num_rows, job.gvec, job.lr,
+                                                job.eps, job.reduced, job.part_head, job.part_last, job.cnt_seg,
+                                                job.cnt_sup, flags);
     else
-        short_rows_body<BF16, LPR, SU>((int)blockIdx.x - job.long_blocks, job.blocks - job.long_blocks, job.grads, job.n,
-                                       job.recs, job.n_rows_dev, (int64_t)job.n, job.table, job.state, job.num_rows,
-                                       job.gvec, job.lr, job.eps, job.reduced, flags);
+        short_rows_body<BF16, LPR, SU, true>((int)blockIdx.x - job.long_blocks, (int)gridDim.x - job.long_blocks, job.grads,
+                                             job.n, row_source{nullptr, job.u_t, job.seg_offsets, job.perm}, n_u, job.table,
+                                             job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
+}
+
+// Positions of a chunk (log2) for a batch of n occurrences.  A big batch fills the chip with chunks of 64, and every
+// chunk costs two dependent round trips at its cut segments (262 k occurrences: ten steps 1042 us with 64, 1052 with
+// 32, 1100 with 16); a small one is as long as the life of one wavefront, which short chunks shorten (three tables of
+// 14 k occurrences: 1050, 951, 891 us).  It depends on the batch alone: the order of the sums is part of the result.
+static int chunk_log2(int64_t n) {
+    return n >= 131072 ? 6 : (n >= 65536 ? 5 : 4);
+}
+
+template <int LPR> constexpr int fused_unr() {
+    return (kWave / (kWave / LPR)) < FS_FUSED_UNR ? kWave / (kWave / LPR) : FS_FUSED_UNR;
 }
 
 // `idx[0..m)`: the jobs of `jobs` (all of one dtype and row width, all with n > 0) that share this launch
-template <bool BF16, int LPR, int CHUNK, int CLS>
+template <bool BF16, int LPR, int CLS>
 static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *idx, int m, hipStream_t s) {
     constexpr int cls = CLS;
     constexpr int GPW = kWave / LPR;
     constexpr int SU = FS_SHORT_UNR;
-    constexpr int UNR = (CHUNK / GPW) < FS_FUSED_UNR ? ((CHUNK / GPW) < 1 ? 1 : (CHUNK / GPW)) : FS_FUSED_UNR;
-    constexpr int CH = CHUNK < GPW ? GPW : CHUNK;             // at least one row group per chunk
+    constexpr int UNR = fused_unr<LPR>();
     const size_t cap_chunks = (size_t)ceil_div(ctx->max_ids, kFusedMinChunk) + 2;
     const size_t cap_doubles = cap_chunks * (size_t)ctx->max_dim;
     int at = 0;
@@ -627,12 +781,13 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
             const int n = (int)in.n;
             // Both parts are sized for the worst case the host can know (every occurrence in a long
             // segment / every occurrence a row of its own); the real sizes live on the device.
-            const int long_blocks = (int)ceil_div(ceil_div(n, CH), kFusedWaves);
+            const int log2 = chunk_log2(n);
+            const int long_blocks = (int)ceil_div(ceil_div(n, 1 << log2), kFusedWaves);
             const size_t my_chunks = (size_t)long_blocks * kFusedWaves;
             if (k > 0 && (chunks + my_chunks > cap_chunks || doubles + my_chunks * (size_t)in.dim > cap_doubles)) break;
             class_pass_job &j = batch.j[k];
             j.grads = (const f32x4 *)in.grads;
-            j.n = n; j.long_blocks = long_blocks; j.cls = cls;
+            j.n = n; j.long_blocks = long_blocks; j.chunk_log2 = log2;
             j.gvec = in.dim / 4; j.lr = in.lr; j.eps = in.eps;
             j.cperm = in.cperm; j.cslot = in.cslot; j.class_pos = in.class_pos; j.seg_offsets = in.seg_offsets;
             j.cstart = in.cstart; j.recs = in.short_rec; j.u_t = in.u_t; j.n_rows_dev = in.n_rows_dev;
@@ -655,7 +810,7 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
             j.blocks = j.long_blocks + (int)short_blocks;
             blocks = j.blocks > blocks ? j.blocks : blocks;
         }
-        hipLaunchKernelGGL((class_pass_kernel<BF16, LPR, UNR, CH, SU, CLS>), dim3((unsigned)blocks, (unsigned)k),
+        hipLaunchKernelGGL((class_pass_kernel<BF16, LPR, UNR, SU, CLS>), dim3((unsigned)blocks, (unsigned)k),
                            dim3(kFusedWaves * kWave), 0, s, batch, ctx->d_flags);
         at += k;
     }
@@ -679,11 +834,11 @@ int launch_reduce_update_batch(fs_ctx *ctx, int cls, int count, const fs_class_p
 #define FS_CASE(L)                                                                              \
     case L:                                                                                     \
         if (cls == 0) {                                                                         \
-            if (bf) fused_launch<true, L, FS_FUSED_CHUNK_CO, 0>(ctx, jobs, idx, m, s);          \
-            else fused_launch<false, L, FS_FUSED_CHUNK_CO, 0>(ctx, jobs, idx, m, s);            \
+            if (bf) fused_launch<true, L, 0>(ctx, jobs, idx, m, s);          \
+            else fused_launch<false, L, 0>(ctx, jobs, idx, m, s);            \
         } else {                                                                                \
-            if (bf) fused_launch<true, L, FS_FUSED_CHUNK_EX, 1>(ctx, jobs, idx, m, s);          \
-            else fused_launch<false, L, FS_FUSED_CHUNK_EX, 1>(ctx, jobs, idx, m, s);            \
+            if (bf) fused_launch<true, L, 1>(ctx, jobs, idx, m, s);          \
+            else fused_launch<false, L, 1>(ctx, jobs, idx, m, s);            \
         }                                                                                       \
         break;
         switch (lpr) {
@@ -704,6 +859,42 @@ int launch_reduce_update(fs_ctx *ctx, int cls, const float *grads, int64_t n, in
     const fs_class_pass_job job = {grads, n, dim, cperm, cslot, class_pos, seg_offsets, cstart, u_t, table, dt, state,
                                    num_rows, lr, eps, reduced, short_rec, n_rows_dev};
     return launch_reduce_update_batch(ctx, cls, 1, &job, s);
+}
+
+template <bool BF16, int LPR>
+static void batch_update_launch(fs_ctx *ctx, const fs_batch_update_job &in, hipStream_t s) {
+    constexpr int GPW = kWave / LPR;
+    constexpr int SU = FS_SHORT_UNR;
+    batch_update_job j;
+    const int n = (int)in.n;
+    j.grads = (const f32x4 *)in.grads;
+    j.n = n; j.chunk_log2 = chunk_log2(n); j.gvec = in.dim / 4; j.lr = in.lr; j.eps = in.eps;
+    j.long_blocks = (int)ceil_div(ceil_div(n, 1 << j.chunk_log2), kFusedWaves);
+    j.perm = in.perm; j.seg_offsets = in.seg_offsets; j.u_t = in.u_t; j.n_unique_dev = in.n_unique_dev;
+    j.table = in.table; j.state = in.state; j.num_rows = in.num_rows; j.reduced = (f32x4 *)in.reduced;
+    j.part_head = ctx->fpart_head[0]; j.part_last = ctx->fpart_last[0];
+    j.cnt_seg = ctx->fcounters[0]; j.cnt_sup = ctx->fcounters_sup[0];
+    int64_t short_blocks = ceil_div(n, (int64_t)GPW * SU * kFusedWaves);
+    if (short_blocks > FS_SHORT_MAX_BLOCKS) short_blocks = FS_SHORT_MAX_BLOCKS;
+    hipLaunchKernelGGL((batch_update_kernel<BF16, LPR, fused_unr<LPR>(), SU>),
+                       dim3((unsigned)(j.long_blocks + short_blocks)), dim3(kFusedWaves * kWave), 0, s, j, ctx->d_flags);
+}
+
+int launch_batch_update(fs_ctx *ctx, const fs_batch_update_job &job, hipStream_t s) {
+    if (job.n == 0) return FS_OK;
+    const bool bf = job.dt == FS_BF16;
+#define FS_CASE(L)                                             \
+    case L:                                                    \
+        if (bf) batch_update_launch<true, L>(ctx, job, s);     \
+        else batch_update_launch<false, L>(ctx, job, s);       \
+        break;
+    switch (lanes_per_row(job.dim / 4)) {
+        FS_CASE(1) FS_CASE(2) FS_CASE(4) FS_CASE(8) FS_CASE(16) FS_CASE(32) FS_CASE(64)
+        default: return set_err(ctx, FS_EINVAL, "update: dim beyond 256");
+    }
+#undef FS_CASE
+    FS_LAUNCH_CHECK(ctx, "batch_update_kernel");
+    return FS_OK;
 }
 
 FS_TRACE_SETTER(fused)

@@ -32,23 +32,6 @@ __device__ __forceinline__ int wave_lower_bound(const int64_t *__restrict__ a, i
     return lo;
 }
 
-// number of entries of a[0, n) that are <= key; executed by one whole wavefront (64-ary search)
-template <typename T>
-__device__ __forceinline__ int wave_upper_bound(const T *__restrict__ a, int n, T key) {
-    const int lane = threadIdx.x & (kWave - 1);
-    int lo = 0, hi = n;                      // a[i] <= key for i < lo, a[i] > key for i >= hi
-    while (lo < hi) {
-        const int step = (hi - lo + kWave - 1) / kWave;
-        const int probe = lo + (lane + 1) * step - 1;          // last entry of my sub-block
-        const bool le = (probe < hi) && (a[probe] <= key);
-        const int cnt = __popcll(__ballot(le));
-        lo += cnt * step;
-        const int nhi = lo + step - 1;
-        hi = nhi < hi ? nhi : hi;
-    }
-    return lo;
-}
-
 template <typename P>
 __device__ __forceinline__ bool sorted_contains(P a, int lo, int hi, int64_t key) {
     const int end = hi;

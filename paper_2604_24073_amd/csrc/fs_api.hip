@@ -746,6 +746,35 @@ int enqueue_index_work_batch(fs_ctx *ctx, int count, const fs_step_args *a, cons
                              fs_ahead *const *ahead, hipStream_t s, int set0, fs_ahead *const *dedup_out,
                              fs_ahead *const *layout_in) {
     int rc = FS_OK;
+    fs_split_job sj[kMaxBatch];
+    fs_class_job cj[kMaxBatch];
+    fs_unique_job uj[kMaxBatch];
+    // Small batches, every record with a dedup of its own and none splitting what another one dedups: one launch.
+    bool fused = true;
+    for (int k = 0; k < count; ++k) {
+        const fs_step_args &x = a[k];
+        const bool t = have_t[k], t1 = have_t1[k];
+        uj[k] = fs_unique_job{x.values_t1, t1 ? x.n_t1 : 0, x.num_rows, x.u_t1, x.seg_offsets_t1, x.perm_t1, x.inverse_t1,
+                              x.n_unique_t1_dev, x.sorted_ids_t1};
+        sj[k] = fs_split_job{x.u_t, t ? x.n_unique_t_dev : nullptr, x.u_t1, t1 ? x.n_unique_t1_dev : nullptr,
+                             t ? x.n_t : 0, t1 ? x.n_t1 : 0, x.co, x.co_slot, x.ex, x.ex_slot, x.ex_next,
+                             x.ex_next_slot, x.counts_dev, t ? x.seg_offsets_t : nullptr, t1 ? x.co_flag_t1 : nullptr};
+        cj[k] = fs_class_job{x.perm_t, x.n_unique_t_dev, x.seg_offsets_t, t ? x.n_t : 0, t ? x.n_t : 0, x.cperm, x.cslot,
+                             x.cstart, x.class_pos_dev, x.u_t, x.short_rec};
+        fused = fused && t1 && !(ahead && ahead[k]) && !(layout_in && layout_in[k]);
+        for (int q = 0; q < count; ++q) fused = fused && !(t && a[q].u_t1 == x.u_t);
+    }
+    if (fused && small_unique_fits(count, uj, set0) && small_split_fits(count, sj, cj, set0)) {
+        rc = launch_small_index(ctx, count, uj, sj, cj, s);
+        if (dedup_out)
+            for (int k = 0; k < count; ++k)
+                if (dedup_out[k]) {
+                    const hipError_t e = hipEventRecord(dedup_out[k]->done, s);
+                    dedup_out[k]->state.store(kAheadRecorded, std::memory_order_release);
+                    if (e != hipSuccess && rc == FS_OK) rc = hip_err(ctx, e, "hipEventRecord(dedup)");
+                }
+        return rc;
+    }
     // dedups: those not done ahead of time share their launches (each keeps the scratch set of its record:
     // a job list with gaps is passed as separate runs)
     for (int k = 0; k < count; ++k)
@@ -759,15 +788,9 @@ int enqueue_index_work_batch(fs_ctx *ctx, int count, const fs_step_args *a, cons
         }
     for (int k0 = 0; k0 < count && rc == FS_OK;) {
         if (!(have_t1[k0] && !(ahead && ahead[k0]))) { ++k0; continue; }
-        fs_unique_job jobs[kMaxBatch];
         int m = 0;
-        while (k0 + m < count && have_t1[k0 + m] && !(ahead && ahead[k0 + m])) {
-            const fs_step_args &x = a[k0 + m];
-            jobs[m] = fs_unique_job{x.values_t1, x.n_t1, x.num_rows, x.u_t1, x.seg_offsets_t1, x.perm_t1, x.inverse_t1,
-                                    x.n_unique_t1_dev, x.sorted_ids_t1};
-            ++m;
-        }
-        rc = launch_unique_batch(ctx, m, jobs, s, set0 + k0);
+        while (k0 + m < count && have_t1[k0 + m] && !(ahead && ahead[k0 + m])) ++m;
+        rc = launch_unique_batch(ctx, m, uj + k0, s, set0 + k0);
         k0 += m;
     }
     if (dedup_out)
@@ -785,20 +808,7 @@ int enqueue_index_work_batch(fs_ctx *ctx, int count, const fs_step_args *a, cons
                 if (rc == FS_OK) rc = r;
             }
     if (rc != FS_OK) return rc;
-    fs_split_job sj[kMaxBatch];
-    fs_class_job cj[kMaxBatch];
-    for (int k = 0; k < count; ++k) {
-        const fs_step_args &x = a[k];
-        const bool t = have_t[k], t1 = have_t1[k];
-        sj[k] = fs_split_job{x.u_t, t ? x.n_unique_t_dev : nullptr, x.u_t1, t1 ? x.n_unique_t1_dev : nullptr,
-                             t ? x.n_t : 0, t1 ? x.n_t1 : 0, x.co, x.co_slot, x.ex, x.ex_slot, x.ex_next,
-                             x.ex_next_slot, x.counts_dev, t ? x.seg_offsets_t : nullptr, t1 ? x.co_flag_t1 : nullptr};
-        cj[k] = fs_class_job{x.perm_t, x.n_unique_t_dev, x.seg_offsets_t, t ? x.n_t : 0, t ? x.n_t : 0, x.cperm, x.cslot,
-                             x.cstart, x.class_pos_dev, x.u_t, x.short_rec};
-    }
-    rc = launch_split_batch(ctx, count, sj, s, set0);
-    if (rc != FS_OK) return rc;
-    return launch_class_order_batch(ctx, count, cj, s, set0);
+    return launch_split_class_batch(ctx, count, sj, cj, s, set0);
 }
 
 int enqueue_index_work(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool have_t1, fs_ahead *ahead,
@@ -950,12 +960,10 @@ int fs_collision_split_classes(fs_ctx *ctx, const int64_t *u_t, const int64_t *n
     if (cap_t1 > 0) FS_REQUIRE(ctx, u_t1 && n_t1_dev && ex_next && ex_next_slot, "split: null pointer (t+1 side)");
     int rc = join_pending_work(ctx, as_stream(stream));      // the workspace may still be in use on A
     if (rc != FS_OK) return rc;
-    rc = launch_split(ctx, u_t, cap_t > 0 ? n_t_dev : nullptr, u_t1, cap_t1 > 0 ? n_t1_dev : nullptr, cap_t, cap_t1,
-                      co, co_slot, ex, ex_slot, ex_next, ex_next_slot, counts_dev, as_stream(stream),
-                      cap_t > 0 ? seg_offsets_t : nullptr);
-    if (rc != FS_OK) return rc;
-    return launch_class_order(ctx, perm_t, n_t_dev, seg_offsets_t, n_t, cap_t, cperm, cslot, cstart, class_pos_dev,
-                              u_t, short_rec, as_stream(stream));
+    const fs_split_job sj = {u_t, cap_t > 0 ? n_t_dev : nullptr, u_t1, cap_t1 > 0 ? n_t1_dev : nullptr, cap_t, cap_t1,
+                             co, co_slot, ex, ex_slot, ex_next, ex_next_slot, counts_dev, cap_t > 0 ? seg_offsets_t : nullptr};
+    const fs_class_job cj = {perm_t, n_t_dev, seg_offsets_t, n_t, cap_t, cperm, cslot, cstart, class_pos_dev, u_t, short_rec};
+    return launch_split_class_batch(ctx, 1, &sj, &cj, as_stream(stream), 0);
 }
 
 int fs_reduce_update_class(fs_ctx *ctx, int cls, void *table, fs_dtype dt, float *state, int64_t num_rows,
@@ -1359,6 +1367,7 @@ int fs_step_join(fs_ctx *ctx, fs_stream stream) {
 // (layout beside the tracer in fs_device.h); nullptr switches the trace off.
 void fs_set_trace_unique(unsigned long long *);
 void fs_set_trace_split(unsigned long long *);
+void fs_set_trace_small(unsigned long long *);
 void fs_set_trace_gather(unsigned long long *);
 void fs_set_trace_fused(unsigned long long *);
 int fs_debug_trace(fs_ctx *ctx, void *buf_dev) {
@@ -1366,6 +1375,7 @@ int fs_debug_trace(fs_ctx *ctx, void *buf_dev) {
     FS_HIP(ctx, hipDeviceSynchronize());
     fs_set_trace_unique((unsigned long long *)buf_dev);
     fs_set_trace_split((unsigned long long *)buf_dev);
+    fs_set_trace_small((unsigned long long *)buf_dev);
     fs_set_trace_gather((unsigned long long *)buf_dev);
     fs_set_trace_fused((unsigned long long *)buf_dev);
     FS_HIP(ctx, hipDeviceSynchronize());

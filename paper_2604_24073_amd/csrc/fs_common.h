@@ -26,7 +26,10 @@ constexpr int kRadix = 1 << kRadixBits;                   // most bins of one pa
 #define FS_SORT_THREADS 1024
 #endif
 constexpr int kSortThreads = FS_SORT_THREADS;
-constexpr int kSortTile = 4096;                           // keys per tile
+#ifndef FS_SORT_TILE
+#define FS_SORT_TILE 4096
+#endif
+constexpr int kSortTile = FS_SORT_TILE;                   // keys per tile
 constexpr int kSortKpt = kSortTile / kSortThreads;        // keys per thread
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortScan = kSortThreads > kRadix ? kSortThreads : kRadix;
@@ -35,6 +38,13 @@ constexpr int kSortScan = kSortThreads > kRadix ? kSortThreads : kRadix;
 constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 4;
 constexpr int kScanTile = kScanThreads * kScanIpt;
+
+// Most IDs of a batch whose index half one workgroup does (fs_small.hip).  Ahead of time, where nobody waits for it and a
+// launch costs whatever runs beside it: what fits the LDS of a compute unit.  On the caller's stream: up to where the
+// chain of launches over many workgroups is the faster one (a whole step of 7.8 k IDs: 60 us against about 80, of
+// 15.6 k: 103 against about 88).
+constexpr int64_t kSmallIds = 16384;
+constexpr int64_t kSmallIdsInline = 8192;
 
 // segment reduce: sorted positions owned by one wavefront (one 64-bit tail mask, one permutation
 // entry per lane).  Short chunks = many wavefronts with short dependent-load chains.
@@ -292,16 +302,18 @@ int launch_unique_batch(fs_ctx *, int count, const fs_unique_job *jobs, hipStrea
 int launch_split_batch(fs_ctx *, int count, const fs_split_job *jobs, hipStream_t s, int set0);
 // right after launch_split_batch(..., seg_offsets_t given) with the same jobs order and sets, on the same stream
 int launch_class_order_batch(fs_ctx *, int count, const fs_class_job *jobs, hipStream_t s, int set0);
-// seg_offsets_t: optional; given, the per-tile occurrence counts that launch_class_order needs are left in
-// the context scratch
+// split and class order of `count` batches: the two calls above, or one launch where all of them are small
+int launch_split_class_batch(fs_ctx *, int count, const fs_split_job *jobs, const fs_class_job *cls, hipStream_t s, int set0);
+// one workgroup per batch: dedups (u), splits (sp) with class orders (cls, optional), or a dedup and then a split each,
+// whose U_t no dedup of the same launch may produce; the jobs must fit
+bool small_unique_fits(int count, const fs_unique_job *jobs, int set0);
+bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0);
+int launch_small_index(fs_ctx *, int count, const fs_unique_job *u, const fs_split_job *sp, const fs_class_job *cls,
+                       hipStream_t s);
 int launch_split(fs_ctx *, const int64_t *u_t, const int64_t *n_t_dev, const int64_t *u_t1,
                  const int64_t *n_t1_dev, int64_t cap_t, int64_t cap_t1, int64_t *co, int32_t *co_slot,
                  int64_t *ex, int32_t *ex_slot, int64_t *ex_next, int32_t *ex_next_slot, int64_t *counts_dev,
-                 hipStream_t s, const int32_t *seg_offsets_t = nullptr, int set = 0);
-// right after launch_split(..., seg_offsets_t) on the same stream: occurrences of the batch in class order
-int launch_class_order(fs_ctx *, const int32_t *perm, const int64_t *n_unique_dev, const int32_t *seg_offsets, int64_t n,
-                       int64_t cap_u, int32_t *cperm, int32_t *cslot, int32_t *cstart, int32_t *class_pos_dev,
-                       const int64_t *u_t, int32_t *short_rec, hipStream_t s, int set = 0);
+                 hipStream_t s);
 int launch_reduce_update(fs_ctx *, int cls, const float *grads, int64_t n, int32_t dim, const int32_t *cperm,
                          const int32_t *cslot, const int32_t *class_pos, const int32_t *seg_offsets,
                          const int32_t *cstart, const int64_t *u_t, void *table, int dt, float *state,

@@ -414,10 +414,11 @@ int launch_split_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, hipStre
 int launch_split(fs_ctx *ctx, const int64_t *u_t, const int64_t *n_t_dev, const int64_t *u_t1,
                  const int64_t *n_t1_dev, int64_t cap_t, int64_t cap_t1, int64_t *co, int32_t *co_slot,
                  int64_t *ex, int32_t *ex_slot, int64_t *ex_next, int32_t *ex_next_slot, int64_t *counts_dev,
-                 hipStream_t s, const int32_t *seg_offsets_t, int set) {
+                 hipStream_t s) {
     const fs_split_job job = {u_t, n_t_dev, u_t1, n_t1_dev, cap_t, cap_t1, co, co_slot, ex, ex_slot,
-                              ex_next, ex_next_slot, counts_dev, seg_offsets_t};
-    return launch_split_batch(ctx, 1, &job, s, set);
+                              ex_next, ex_next_slot, counts_dev, nullptr};
+    if (small_split_fits(1, &job, nullptr, 0)) return launch_small_index(ctx, 1, nullptr, &job, nullptr, s);
+    return launch_split_batch(ctx, 1, &job, s, 0);
 }
 
 int launch_class_order_batch(fs_ctx *ctx, int count, const fs_class_job *jobs, hipStream_t s, int set0) {
@@ -454,11 +455,12 @@ int launch_class_order_batch(fs_ctx *ctx, int count, const fs_class_job *jobs, h
     return FS_OK;
 }
 
-int launch_class_order(fs_ctx *ctx, const int32_t *perm, const int64_t *n_unique_dev, const int32_t *seg_offsets,
-                       int64_t n, int64_t cap_u, int32_t *cperm, int32_t *cslot, int32_t *cstart,
-                       int32_t *class_pos_dev, const int64_t *u_t, int32_t *short_rec, hipStream_t s, int set) {
-    const fs_class_job job = {perm, n_unique_dev, seg_offsets, n, cap_u, cperm, cslot, cstart, class_pos_dev, u_t, short_rec};
-    return launch_class_order_batch(ctx, 1, &job, s, set);
+int launch_split_class_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, const fs_class_job *cls, hipStream_t s,
+                             int set0) {
+    if (small_split_fits(count, jobs, cls, set0)) return launch_small_index(ctx, count, nullptr, jobs, cls, s);
+    const int rc = launch_split_batch(ctx, count, jobs, s, set0);
+    if (rc != FS_OK) return rc;
+    return launch_class_order_batch(ctx, count, cls, s, set0);
 }
 
 FS_TRACE_SETTER(split)

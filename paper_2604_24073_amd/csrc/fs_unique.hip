@@ -356,6 +356,7 @@ static int unique_batch_impl(fs_ctx *ctx, const unique_dev_batch &batch, int cou
 int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipStream_t s, int set0) {
     if (count < 1 || count > kMaxBatch || set0 < 0 || set0 + count > kSortSets)
         return set_err(ctx, FS_EINVAL, "unique: batch size");
+    if (small_unique_fits(count, jobs, set0)) return launch_small_index(ctx, count, jobs, nullptr, nullptr, s);
     if (count == 1 && jobs[0].n == 0) {
         hipLaunchKernelGGL(unique_empty_kernel, dim3(1), dim3(1), 0, s, jobs[0].seg_offsets, jobs[0].n_unique_dev);
         FS_LAUNCH_CHECK(ctx, "unique_empty_kernel");

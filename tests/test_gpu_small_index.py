@@ -1,0 +1,83 @@
+"""The index half of a small batch on one workgroup, at the sizes where it can go wrong: the edges of a round of 1024
+elements, the largest batch it takes on the caller's stream (8192 IDs) and ahead of time (16384), the first sizes it
+leaves to the chain of launches, one list much shorter than the other, every row long, one radix pass and four.  Whole
+numbers: every output equals the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2604_24073_amd as fs
+from helpers import dev
+from test_gpu_parity import class_order_from_oracle, zipf_ids
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def ctx():
+    # one per test: a context remembers ahead-of-time results by the address of their buffers
+    c = fs.Context(max_ids=40_000, max_dim=4)
+    yield c
+    c.close()
+
+
+def check_index_half(ctx, ids, nxt, rows, ahead):
+    n0, n1 = len(ids), len(nxt)
+    lay0, lay1, split = fs.alloc_layout(n0, "cuda"), fs.alloc_layout(n1, "cuda", sorted_ids=True), fs.alloc_split(n0, n1, "cuda")
+    fs.fs_unique_ids(ctx, dev(ids), rows, out=lay0)
+    d_nxt = dev(nxt)
+    keep = [torch.zeros((k, 4), device="cuda") for k in (min(rows, 8), n0, n1)]
+    args = fs.make_step_args(keep[0], torch.zeros(1, device="cuda"), 0.01, 1e-8, lay0, keep[1], d_nxt, None, lay1, split, None, keep[2])
+    args.num_rows = rows                                     # the index half touches no table row
+    if ahead:
+        fs.fs_step_forward_ahead(ctx, args)
+    else:
+        fs.fs_step_forward(ctx, args)
+    assert fs.fs_check_async(ctx) == fs.FS_OK
+    want0, want1 = O.unique_ids(ids, rows), O.unique_ids(nxt, rows)
+    for lay, want in ((lay0, want0), (lay1, want1)):
+        for k in ("unique", "seg_offsets", "perm", "inverse"):
+            assert np.array_equal(lay[k].cpu().numpy()[:len(want[k])], want[k]), k
+        assert int(lay["n_unique"].item()) == len(want["unique"])
+    assert np.array_equal(lay1["sorted_ids"].cpu().numpy(), np.sort(nxt))
+    sp = O.collision_split(want0["unique"], want1["unique"])
+    assert split["counts"].cpu().numpy().tolist() == [len(sp[k]) for k in ("co", "ex", "ex_next")]
+    for k in ("co", "co_slot", "ex", "ex_slot", "ex_next", "ex_next_slot"):
+        assert np.array_equal(split[k].cpu().numpy()[:len(sp[k])], sp[k]), k
+    flag = split["co_flag_t1"].cpu().numpy()[:len(want1["unique"])]
+    assert np.array_equal(flag, np.isin(want1["unique"], want0["unique"]).astype(np.uint8))
+    cperm, cslot, cstart, class_pos = class_order_from_oracle(want0, sp)
+    assert split["class_pos"].cpu().numpy().tolist() == [int(x) for x in class_pos]
+    assert np.array_equal(split["cperm"].cpu().numpy()[:class_pos[1]], cperm)
+    assert np.array_equal(split["cslot"].cpu().numpy()[:class_pos[1]], cslot)
+    in_order = cstart >= 0
+    assert np.array_equal(split["cstart"].cpu().numpy()[:len(cstart)][in_order], cstart[in_order])
+    rec = split["short_rec"].cpu().numpy()[:24 * n0].reshape(2, n0, 12)
+    seg = want0["seg_offsets"].astype(np.int64)
+    for cls, name in enumerate(("co", "ex")):
+        slots = sp[name + "_slot"]
+        got, lens = rec[cls, :len(slots)], seg[slots + 1] - seg[slots]
+        assert np.array_equal(got[:, 0:2].copy().view(np.int64).ravel(), sp[name])
+        assert np.array_equal(got[:, 2], slots) and np.array_equal(got[:, 3], lens)
+        for j in range(8):
+            has = (lens <= fs.FS_SHORT_SEGMENT) & (lens > j)
+            assert np.array_equal(got[has, 4 + j], want0["perm"][seg[slots[has]] + j])
+
+
+@pytest.mark.parametrize("n0,n1,rows,ahead", [
+    (1, 1, 1, False), (63, 65, 300, False), (1023, 1025, 500, False), (1025, 1023, 5000, True),
+    (2048, 4097, 100_000, False), (8192, 8192, 300_000, False), (8193, 8192, 300_000, False), (8192, 40, 60, False),
+    (40, 8192, 40_000_000, False), (16384, 16384, 64_000_000, True), (16384, 100, 1_000_000, True),
+    (100, 16384, 1_000_000, True), (16384, 9000, 1700, True), (16385, 16384, 50_000, True)])
+def test_index_half_of_a_small_batch(ctx, n0, n1, rows, ahead):
+    rng = np.random.default_rng(n0 * 31 + n1)
+    check_index_half(ctx, zipf_ids(rng, n0, rows, a=1.1), zipf_ids(rng, n1, rows, a=1.1), rows, ahead)
+
+
+@pytest.mark.parametrize("n", [9 * 113, 16380])
+def test_every_row_is_long(ctx, n):
+    """As many long rows as a batch can have (nine occurrences each), half of them collision rows."""
+    rng = np.random.default_rng(n)
+    rows = n // 9
+    check_index_half(ctx, rng.permutation(np.repeat(np.arange(rows), 9)), np.arange(0, rows, 2), rows, True)

@@ -432,6 +432,9 @@ int fs_step_forward_ahead_batch(fs_ctx *ctx, const fs_step_args *args, int count
  *                   deferred pass of cur (fs_reduce_update_class(1)); then the index half of
  *                   `next`: dedup of next's lookahead IDs (or a wait for fs_unique_ids_ahead),
  *                   split of next's U_t, class order of next's batch
+ * A call with little row work (up to 128 MB of gradients and looked-up rows over its tables, the index half of
+ * `next` done ahead of time or small) does without the side stream: both passes in one launch and the gather
+ * behind them on `stream`, an index half that is not done yet behind those.  Results do not depend on it.
  * The split and class order of `cur` must already exist: they were produced by the previous call
  * of this function (as its `next`) or by fs_step_forward.  `next` may be NULL (last iteration).
  * Nothing on A is waited for when the call returns: the next pipelined call waits for it before
@@ -472,7 +475,7 @@ int fs_prioritized_step_pipelined_multi(fs_ctx *ctx, const fs_step_args *cur, co
  * the collision rows only.  A lookahead batch of `cur` whose exclusive rows the previous call of this
  * function did not fetch (first call of a run; another pipelined or self-contained step, a stand-alone
  * update or a table initialisation on the context in between; fs_two_part_forget) gets its whole lookup on
- * `stream`.  fs_check_async, fs_step_join and the ahead-of-time index calls keep what was fetched.  Whoever
+ * `stream`, and so does a call with little row work (see fs_prioritized_step_pipelined).  fs_check_async, fs_step_join and the ahead-of-time index calls keep what was fetched.  Whoever
  * changes table rows or the output batch by other means between two calls must call fs_two_part_forget.  Every record with a lookahead batch needs co_flag_t1.  Results are those of
  * fs_prioritized_step_pipelined_multi, bit for bit; emb_t1 of cur is complete when `stream` is.  The output
  * batches of three consecutive iterations must be distinct buffers: while the caller consumes one, this call

@@ -819,6 +819,7 @@ int enqueue_index_work(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool hav
 // update_embedding for one class of rows of iteration t (0: priority pass, 1: deferred pass) of `count`
 // tables (`use[k]`: table k has gradients); tables of one row width share their launches
 fs_class_pass_job class_job(const fs_step_args *a, int cls) {
+    if (cls == 2) cls = 0;                                   // both passes in one launch: the job names class 0
     return fs_class_pass_job{a->grads_t, a->n_t, a->dim, a->cperm, a->cslot, a->class_pos_dev, a->seg_offsets_t,
                              a->cstart, a->u_t, a->table, a->dtype, a->state, a->num_rows, a->lr, a->eps, a->reduced,
                              a->short_rec + (int64_t)cls * a->n_t * kShortRecInts, a->counts_dev + cls};
@@ -1236,40 +1237,51 @@ int fs_prioritized_step_two_part_multi(fs_ctx *ctx, const fs_step_args *cur, con
     return pipelined_impl(ctx, cur, next, count, stream, true);
 }
 
+// Bytes of gradients and looked-up rows of a call up to which the pipelined step stays on one stream: both passes of
+// every table in one launch, the lookups behind them, no wait between streams (10-12 us of host time each, with a
+// second thread to pay them) and one launch less per row width.  What it gives up is the deferred pass running beside
+// the lookup.  Ten steps of one 2M x 128 table, two streams against one: 0.5 k IDs a batch 285 / 227 us, 8 k 319 / 261,
+// 65 k (67 MB) 472 / 438, 130 k (133 MB) 600 / 596, 262 k (of 4M rows) 1041 / 1056; eight tables of 2 GB 5616 / 6039.
+constexpr int64_t kOneStreamBytes = 128 << 20;
+
 static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_args *next, int count, fs_stream stream,
                           bool two_part) {
     if (!ctx) return FS_EINVAL;
     FS_REQUIRE(ctx, cur && count >= 1 && count <= FS_MAX_STEP_TABLES, "pipelined step: 1..FS_MAX_STEP_TABLES tables");
-    std::shared_ptr<side_work> w = std::make_shared<side_work>();
-    bool have_t1[kMaxTables];
-    w->count = count;
+    bool have_t[kMaxTables], have_t1[kMaxTables], nxt_t[kMaxTables], nxt_t1[kMaxTables], fetch_next[kMaxTables];
+    int64_t row_bytes = 0;
+    bool one_stream = !ctx->capturing;
     for (int k = 0; k < count; ++k) {
-        int rc = check_step_args(ctx, &cur[k], &w->have_t[k], &have_t1[k]);
+        int rc = check_step_args(ctx, &cur[k], &have_t[k], &have_t1[k]);
         if (rc != FS_OK) return rc;
-        w->has_next[k] = next != nullptr;
-        w->nxt_t[k] = w->nxt_t1[k] = false;
+        nxt_t[k] = nxt_t1[k] = false;
         if (next) {
-            rc = check_step_args(ctx, &next[k], &w->nxt_t[k], &w->nxt_t1[k]);
+            rc = check_step_args(ctx, &next[k], &nxt_t[k], &nxt_t1[k]);
             if (rc != FS_OK) return rc;
         }
-        w->cur[k] = cur[k];
-        w->next[k] = next ? next[k] : cur[k];
-        w->ahead[k] = w->index_ahead[k] = nullptr;
-        w->fetch_next[k] = two_part && next && w->nxt_t1[k];
+        fetch_next[k] = two_part && next && nxt_t1[k];
+        row_bytes += (have_t[k] ? cur[k].n_t * cur[k].dim * 4 : 0) +
+                     (have_t1[k] ? cur[k].n_t1 * cur[k].dim * (cur[k].dtype == FS_F32 ? 4 : 2) : 0);
+        // an index half that is still to be done is short on one workgroup, else it belongs beside the row work
+        if (next && (next[k].n_t > kSmallIdsInline || next[k].n_t1 > kSmallIdsInline))
+            one_stream = one_stream && find_ahead(ctx, next[k].counts_dev) != nullptr;
         if (two_part) {
             FS_REQUIRE(ctx, !ctx->capturing, "two-part step: not while a graph is being captured");
             FS_REQUIRE(ctx, !have_t1[k] || (cur[k].co_flag_t1 && cur[k].inverse_t1),
                        "two-part step: co_flag_t1 or inverse_t1 missing");
-            FS_REQUIRE(ctx, !w->fetch_next[k] || (next[k].co_flag_t1 && next[k].inverse_t1),
+            FS_REQUIRE(ctx, !fetch_next[k] || (next[k].co_flag_t1 && next[k].inverse_t1),
                        "two-part step: co_flag_t1 or inverse_t1 missing (next)");
         }
     }
-    // which part of cur's lookup is left to do: the collision rows if the previous call fetched the rest
+    one_stream = one_stream && row_bytes <= kOneStreamBytes;
+    // which part of cur's lookup is left to do: the collision rows if the previous call fetched the rest (on one stream
+    // the whole lookup: nothing is fetched ahead of a call there)
     int part[kMaxTables];
     for (int k = 0; k < count; ++k) {
+        if (one_stream) fetch_next[k] = false;
         const bool fetched = two_part && have_t1[k] && ctx->fetched_emb[k] == cur[k].emb_t1 &&
                              ctx->fetched_values[k] == cur[k].values_t1 && ctx->fetched_n[k] == cur[k].n_t1;
-        part[k] = fetched ? 1 : -1;
+        part[k] = fetched && !one_stream ? 1 : -1;
     }
     hipStream_t sp = as_stream(stream);
     begin_step_timing(ctx);
@@ -1278,12 +1290,13 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
     // priority pass.  Cross-stream waits are the expensive host operation here (each makes the
     // runtime flush the producer queue): two per call, whatever the number of tables - A waits for `stream`
     // as it stands at the start of the call (the gradients), `stream` waits for A's previous job.
+    // One stream: nothing goes to A.
     const bool prev_side = ctx->side_pending;
     const int pp = ctx->pipe_parity, p = pp ^ 1;            // event set of the previous / this call
     int rc = FS_OK;
     const double h0 = now_us();
-    fs_worker *w0 = (!ctx->capturing && ctx->use_worker) ? get_worker(ctx, 0) : nullptr;
-    if (ctx->host->worker[0]) {
+    fs_worker *w0 = (!ctx->capturing && !one_stream && ctx->use_worker) ? get_worker(ctx, 0) : nullptr;
+    if (ctx->host->worker[0] && prev_side) {
         rc = ctx->host->worker[0]->wait();                   // host side only: the previous job is enqueued
         if (rc != FS_OK) return set_err(ctx, rc, "side-stream enqueue of the previous call failed");
     }
@@ -1309,26 +1322,43 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
     }
     FS_HIP(ctx, hipEventRecord(ctx->ev_pfork[p], sp));
     ctx->pfork_valid = true;
-    // claimed entries: the side job waits for them and gives them back
-    if (next && !ctx->capturing)
+    std::function<int()> side_job;
+    if (!one_stream) {
+        std::shared_ptr<side_work> w = std::make_shared<side_work>();
+        w->count = count;
         for (int k = 0; k < count; ++k) {
-            w->index_ahead[k] = claim_ahead(ctx, next[k].counts_dev);
-            w->ahead[k] = (w->nxt_t1[k] && !w->index_ahead[k]) ? claim_ahead(ctx, next[k].u_t1) : nullptr;
+            w->cur[k] = cur[k];
+            w->next[k] = next ? next[k] : cur[k];
+            w->has_next[k] = next != nullptr;
+            w->have_t[k] = have_t[k]; w->nxt_t[k] = nxt_t[k]; w->nxt_t1[k] = nxt_t1[k];
+            w->fetch_next[k] = fetch_next[k];
+            // claimed entries: the side job waits for them and gives them back (on one stream the next call asks for
+            // the index half of its `cur` itself)
+            const bool claim = next && !ctx->capturing;
+            w->index_ahead[k] = claim ? claim_ahead(ctx, next[k].counts_dev) : nullptr;
+            w->ahead[k] = (claim && nxt_t1[k] && !w->index_ahead[k]) ? claim_ahead(ctx, next[k].u_t1) : nullptr;
         }
-    w->parity = p;
-    w->ex_timing = timing_pair(ctx, FS_TIME_UPDATE_EX);
-    auto side_job = [ctx, w]() -> int { return enqueue_side_stream(ctx, *w); };
-    if (w0) w0->post(side_job);
+        w->parity = p;
+        w->ex_timing = timing_pair(ctx, FS_TIME_UPDATE_EX);
+        side_job = [ctx, w]() -> int { return enqueue_side_stream(ctx, *w); };
+        if (w0) w0->post(side_job);
+    }
     const double h2 = now_us();
     rc = FS_OK;
     if (prev_side && hipStreamWaitEvent(sp, ctx->ev_side[pp], 0) != hipSuccess) rc = FS_EHIP;
     ctx->side_pending = false;
     const double h3 = now_us();
     // every priority pass before every gather: a gather may only read what its table's priority pass left
-    if (rc == FS_OK) rc = enqueue_class_passes(ctx, cur, w->have_t, count, 0, sp, timing_pair(ctx, FS_TIME_UPDATE_CO));
+    if (rc == FS_OK)
+        rc = enqueue_class_passes(ctx, cur, have_t, count, one_stream ? 2 : 0, sp, timing_pair(ctx, FS_TIME_UPDATE_CO));
     if (rc == FS_OK) rc = enqueue_gathers(ctx, cur, have_t1, count, sp, part);
+    if (one_stream && next)
+        for (int k = 0; k < count && rc == FS_OK; ++k)
+            if (!find_ahead(ctx, next[k].counts_dev))        // its index half was not done ahead of time
+                rc = enqueue_index_work(ctx, &next[k], nxt_t[k], nxt_t1[k],
+                                        nxt_t1[k] ? claim_ahead(ctx, next[k].u_t1) : nullptr, sp);
     const double h4 = now_us();
-    if (!w0) {
+    if (!w0 && !one_stream) {
         const int src = side_job();
         if (rc == FS_OK) rc = src;
     }
@@ -1339,9 +1369,9 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
     ctx->host_us[3] += h4 - h3;      // priority passes and gathers
     ctx->host_us[6] += 1.0;
     ctx->pipe_parity = p;
-    ctx->side_pending = true;        // also after a failure: a posted job still records its event
+    ctx->side_pending = !one_stream; // also after a failure: a posted job still records its event
     for (int k = 0; k < kMaxTables; ++k) {
-        const bool f = rc == FS_OK && k < count && w->fetch_next[k];
+        const bool f = rc == FS_OK && k < count && fetch_next[k];
         ctx->fetched_emb[k] = f ? next[k].emb_t1 : nullptr;
         ctx->fetched_values[k] = f ? next[k].values_t1 : nullptr;
         ctx->fetched_n[k] = f ? next[k].n_t1 : 0;

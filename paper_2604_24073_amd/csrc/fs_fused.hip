@@ -680,7 +680,7 @@ __device__ __forceinline__ void short_rows_body(
 // better walked side by side than one after the other.
 struct class_pass_job {
     const f32x4 *grads;
-    int n, long_blocks, blocks, chunk_log2, gvec;
+    int n, long_blocks, blocks, chunk_log2, gvec, cls;
     float lr, eps;
     const int32_t *cperm, *cslot, *class_pos, *seg_offsets, *cstart, *recs;
     const int64_t *u_t, *n_rows_dev;
@@ -695,15 +695,15 @@ struct class_pass_batch {
     class_pass_job j[kMaxBatch];
 };
 
-// CLS (0: priority pass, 1: deferred pass) is a template parameter so that the two passes are two kernels by name
-// in a profile; the code is the same.
+// CLS (0: priority pass, 1: deferred pass, 2: both of every table, one after the other in the grid) is a template
+// parameter so that the passes are kernels of their own by name in a profile; the code is the same.
 template <bool BF16, int LPR, int UNR, int SU, int CLS>
 __global__ __launch_bounds__(kFusedWaves *kWave) void class_pass_kernel(const class_pass_batch batch, int *flags) {
     const class_pass_job &job = batch.j[blockIdx.y];
     FS_WG_TRACE(8 + CLS);
     if ((int)blockIdx.x >= job.blocks) return;
     if ((int)blockIdx.x < job.long_blocks)
-        long_segments_body<BF16, LPR, UNR>((int)blockIdx.x, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos, CLS,
+        long_segments_body<BF16, LPR, UNR>((int)blockIdx.x, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos, CLS < 2 ? CLS : job.cls,
                                                   job.n, job.seg_offsets, job.cstart, job.u_t, job.table, job.state,
                                                   job.num_rows, job.gvec, job.lr, job.eps, job.reduced, job.part_head,
                                                   job.part_last, job.cnt_seg, job.cnt_sup, flags);
@@ -763,10 +763,10 @@ template <int LPR> constexpr int fused_unr() {
 // `idx[0..m)`: the jobs of `jobs` (all of one dtype and row width, all with n > 0) that share this launch
 template <bool BF16, int LPR, int CLS>
 static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *idx, int m, hipStream_t s) {
-    constexpr int cls = CLS;
     constexpr int GPW = kWave / LPR;
     constexpr int SU = FS_SHORT_UNR;
     constexpr int UNR = fused_unr<LPR>();
+    constexpr int PER = CLS < 2 ? 1 : 2;                      // passes of a table
     const size_t cap_chunks = (size_t)ceil_div(ctx->max_ids, kFusedMinChunk) + 2;
     const size_t cap_doubles = cap_chunks * (size_t)ctx->max_dim;
     int at = 0;
@@ -776,7 +776,7 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
         memset(&batch, 0, sizeof(batch));
         size_t chunks = 0, doubles = 0;
         int k = 0, blocks = 0;
-        for (; at + k < m && k < kMaxBatch; ++k) {
+        for (; at + k < m && (k + 1) * PER <= kMaxBatch; ++k) {
             const fs_class_pass_job &in = jobs[idx[at + k]];
             const int n = (int)in.n;
             // Both parts are sized for the worst case the host can know (every occurrence in a long
@@ -785,24 +785,30 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
             const int long_blocks = (int)ceil_div(ceil_div(n, 1 << log2), kFusedWaves);
             const size_t my_chunks = (size_t)long_blocks * kFusedWaves;
             if (k > 0 && (chunks + my_chunks > cap_chunks || doubles + my_chunks * (size_t)in.dim > cap_doubles)) break;
-            class_pass_job &j = batch.j[k];
-            j.grads = (const f32x4 *)in.grads;
-            j.n = n; j.long_blocks = long_blocks; j.chunk_log2 = log2;
-            j.gvec = in.dim / 4; j.lr = in.lr; j.eps = in.eps;
-            j.cperm = in.cperm; j.cslot = in.cslot; j.class_pos = in.class_pos; j.seg_offsets = in.seg_offsets;
-            j.cstart = in.cstart; j.recs = in.short_rec; j.u_t = in.u_t; j.n_rows_dev = in.n_rows_dev;
-            j.table = in.table; j.state = in.state; j.num_rows = in.num_rows; j.reduced = (f32x4 *)in.reduced;
-            j.part_head = ctx->fpart_head[cls] + doubles;
-            j.part_last = ctx->fpart_last[cls] + doubles;
-            j.cnt_seg = ctx->fcounters[cls] + chunks;
-            j.cnt_sup = ctx->fcounters_sup[cls] + chunks;
+            for (int c = 0; c < PER; ++c) {
+                const int cls = PER == 1 ? CLS : c;
+                class_pass_job &j = batch.j[k * PER + c];
+                j.grads = (const f32x4 *)in.grads;
+                j.n = n; j.long_blocks = long_blocks; j.chunk_log2 = log2; j.cls = cls;
+                j.gvec = in.dim / 4; j.lr = in.lr; j.eps = in.eps;
+                j.cperm = in.cperm; j.cslot = in.cslot; j.class_pos = in.class_pos; j.seg_offsets = in.seg_offsets;
+                j.cstart = in.cstart; j.u_t = in.u_t;
+                // records and row count of class 1 lie behind those of class 0 (both passes: `in` names class 0)
+                j.recs = in.short_rec + (int64_t)c * n * kShortRecInts;
+                j.n_rows_dev = in.n_rows_dev + c;
+                j.table = in.table; j.state = in.state; j.num_rows = in.num_rows; j.reduced = (f32x4 *)in.reduced;
+                j.part_head = ctx->fpart_head[cls] + doubles;
+                j.part_last = ctx->fpart_last[cls] + doubles;
+                j.cnt_seg = ctx->fcounters[cls] + chunks;
+                j.cnt_sup = ctx->fcounters_sup[cls] + chunks;
+            }
             chunks += my_chunks;
             doubles += my_chunks * (size_t)in.dim;
         }
         // The short part walks its records with a grid stride: the tables of a launch share FS_SHORT_MAX_BLOCKS
         // workgroups (about five per compute unit, all resident from the start).  Measured on four workloads,
         // more and shorter-lived workgroups lose (16 k: +5 %, 64 k: +12 %), fewer than three per compute unit too.
-        for (int q = 0; q < k; ++q) {
+        for (int q = 0; q < k * PER; ++q) {
             class_pass_job &j = batch.j[q];
             int64_t short_blocks = ceil_div(j.n, (int64_t)GPW * SU * kFusedWaves);
             const int64_t cap = FS_SHORT_MAX_BLOCKS / k > 256 ? FS_SHORT_MAX_BLOCKS / k : 256;
@@ -810,7 +816,7 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
             j.blocks = j.long_blocks + (int)short_blocks;
             blocks = j.blocks > blocks ? j.blocks : blocks;
         }
-        hipLaunchKernelGGL((class_pass_kernel<BF16, LPR, UNR, SU, CLS>), dim3((unsigned)blocks, (unsigned)k),
+        hipLaunchKernelGGL((class_pass_kernel<BF16, LPR, UNR, SU, CLS>), dim3((unsigned)blocks, (unsigned)(k * PER)),
                            dim3(kFusedWaves * kWave), 0, s, batch, ctx->d_flags);
         at += k;
     }
@@ -834,11 +840,14 @@ int launch_reduce_update_batch(fs_ctx *ctx, int cls, int count, const fs_class_p
 #define FS_CASE(L)                                                                              \
     case L:                                                                                     \
         if (cls == 0) {                                                                         \
-            if (bf) fused_launch<true, L, 0>(ctx, jobs, idx, m, s);          \
-            else fused_launch<false, L, 0>(ctx, jobs, idx, m, s);            \
+            if (bf) fused_launch<true, L, 0>(ctx, jobs, idx, m, s);                             \
+            else fused_launch<false, L, 0>(ctx, jobs, idx, m, s);                               \
+        } else if (cls == 1) {                                                                  \
+            if (bf) fused_launch<true, L, 1>(ctx, jobs, idx, m, s);                             \
+            else fused_launch<false, L, 1>(ctx, jobs, idx, m, s);                               \
         } else {                                                                                \
-            if (bf) fused_launch<true, L, 1>(ctx, jobs, idx, m, s);          \
-            else fused_launch<false, L, 1>(ctx, jobs, idx, m, s);            \
+            if (bf) fused_launch<true, L, 2>(ctx, jobs, idx, m, s);                             \
+            else fused_launch<false, L, 2>(ctx, jobs, idx, m, s);                               \
         }                                                                                       \
         break;
         switch (lpr) {

@@ -6,8 +6,9 @@
 // the ranks in a zig-zag - rank i takes sorted positions i, 2n-1-i, 2n+i, 4n-1-i, ...  The deal is a
 // closed form per sorted position, one thread each.
 //
-// Indexed permute: output sample k is input sample sample_of[k].  Three launches: lengths summed per
-// tile of samples, the output offsets by a scan with tile prefixes, and the copy.  The copy is driven
+// Indexed permute: output sample k is input sample sample_of[k].  Up to 8192 samples two launches: one
+// workgroup lays out the output offsets, then the copy; beyond, lengths summed per tile of samples, the
+// output offsets by a scan with tile prefixes, and the copy.  The copy is driven
 // by the OUTPUT (every lane writes consecutive pieces of the output, so a 16K-item sample costs per
 // item what a short one costs): a workgroup takes 4096 or 8192 consecutive output pieces, finds the samples
 // they belong to with two 64-ary searches, stages their boundaries in LDS and lets every piece
@@ -16,8 +17,8 @@
 // VBS: the same sort, then the sorted order is cut into n runs of about equal total weight.
 //
 // Keyed transpose, ranged dispatch and ranged combine (same section of the paper) are the same copy
-// under a computed order of the F x B segments of a keyed jagged tensor: one more launch writes that
-// order down, then the three launches above run.
+// under a computed order of the F x B segments of a keyed jagged tensor, written down where the lengths
+// are summed.
 #include "fs_common.h"
 #include "fs_device.h"
 
@@ -67,28 +68,173 @@ struct jagged_in {
     int64_t B, n_values;      // samples, elements behind them
 };
 
-// length of output sample k (0 past the end; 0 and a flag for a sample index out of range or a sample whose
-// boundaries are not inside the values: such a sample is never read)
-__device__ __forceinline__ int64_t out_len(const jagged_in &in, const int32_t *__restrict__ sample_of, int64_t k,
-                                           int64_t n_out, bool &bad) {
-    if (k >= n_out) return 0;
-    const int64_t p = sample_of[k];
+// length of input sample p (0 and a flag for a sample index out of range or a sample whose boundaries are not inside
+// the values: such a sample is never read)
+__device__ __forceinline__ int64_t sample_len(const jagged_in &in, int64_t p, bool &bad) {
     if (p < 0 || p >= in.B) { bad = true; return 0; }
     const int64_t a = in.offsets[p], b = in.offsets[p + 1];
     if (a < 0 || b < a || b > in.n_values) { bad = true; return 0; }
     return b - a;
 }
 
-__global__ __launch_bounds__(kScanThreads) void permute_tile_sum_kernel(const jagged_in in,
-                                                                        const int32_t *__restrict__ sample_of,
-                                                                        int64_t n_out, int64_t *__restrict__ tile_sum,
+// length of output sample k (0 past the end)
+__device__ __forceinline__ int64_t out_len(const jagged_in &in, const int32_t *__restrict__ sample_of, int64_t k,
+                                           int64_t n_out, bool &bad) {
+    return k < n_out ? sample_len(in, sample_of[k], bad) : 0;
+}
+
+// ---- the order of the output samples ---------------------------------------------------------------------
+// Segment (f, b) of a keyed jagged tensor with F keys and B samples is number f * B + b in feature-major
+// form and b * F + f in batch-major form.  Ranks own sample ranges [ro[r], ro[r + 1]); what a rank is sent
+// (dispatch) or has sent (combine) is a feature-major tensor over its own samples, rank after rank.
+enum { kMapTranspose = 0, kMapDispatch = 1, kMapCombine = 2, kMapGiven = 3 };
+
+// where the input sample of an output sample comes from: the caller's list, or computed from the keyed form
+struct sample_order {
+    int mode;
+    const int32_t *given;     // kMapGiven
+    int64_t F, B;             // the others
+    const int64_t *ro;        // dispatch, combine
+    int n_ranks;
+    int64_t *splits;          // dispatch: elements each rank is sent
+};
+
+// the last r in [0, n) with scale * ro[r] <= x (ro ascending, ro[0] == 0)
+__device__ __forceinline__ int last_rank_at_or_before(const int64_t *ro, int n, int64_t scale, int64_t x) {
+    int lo = 0, hi = n;                      // first r with scale * ro[r] > x
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (scale * ro[mid] <= x) lo = mid + 1; else hi = mid;
+    }
+    return lo > 0 ? lo - 1 : 0;
+}
+
+// input segment of output segment j; -1 for ranges that make no sense: the copy skips and reports it
+__device__ __forceinline__ int32_t ordered_segment(const sample_order &o, const int64_t *ro, int64_t j) {
+    const int64_t F = o.F, B = o.B;
+    int64_t in = -1;
+    if (o.mode == kMapTranspose) {
+        in = (j % F) * B + j / F;
+    } else if (o.mode == kMapDispatch) {
+        const int r = last_rank_at_or_before(ro, o.n_ranks, F, j);
+        const int64_t first = ro[r], cnt = ro[r + 1] - first, local = j - F * first;
+        if (cnt > 0 && local >= 0 && local < F * cnt) in = (local / cnt) * B + first + local % cnt;
+    } else {
+        const int64_t f = j / B, b = j % B;
+        const int r = last_rank_at_or_before(ro, o.n_ranks, 1, b);
+        const int64_t first = ro[r], cnt = ro[r + 1] - first;
+        if (cnt > 0 && b >= first && b < first + cnt) in = F * first + f * cnt + (b - first);
+    }
+    return (in >= 0 && in < F * B) ? (int32_t)in : -1;
+}
+
+// what one workgroup sees wrong with the rank boundaries
+__device__ __forceinline__ bool bad_ranks(const sample_order &o) {
+    bool bad = false;
+    if (o.mode == kMapDispatch || o.mode == kMapCombine) {
+        for (int r = threadIdx.x; r < o.n_ranks; r += blockDim.x) bad |= o.ro[r + 1] < o.ro[r];
+        if (threadIdx.x == 0) bad |= o.ro[0] != 0 || o.ro[o.n_ranks] != o.B;
+    }
+    return bad;
+}
+
+// elements rank r is sent: the extent of its F * count segments in the dispatched tensor
+__device__ __forceinline__ int64_t rank_split(const sample_order &o, const int64_t *out_offsets, int64_t r) {
+    int64_t a = o.ro[r], b = o.ro[r + 1];
+    a = a < 0 ? 0 : (a > o.B ? o.B : a);
+    b = b < a ? a : (b > o.B ? o.B : b);
+    return out_offsets[o.F * b] - out_offsets[o.F * a];
+}
+
+// Everything the copy needs about a small number of output samples in ONE launch: their order, the output offsets
+// and the splits.  The work is a few loads a sample; what it costs is launches, about 4 us each here (four keyed
+// shuffles of 1024 segments spent three to four of them on it).  One workgroup, up to kPlanPer consecutive samples
+// a thread; beyond that one compute unit takes longer than two launches over many.
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanPer = 8;
+constexpr int kPlanRanks = 1024;                 // rank boundaries kept in LDS
+
+__global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_in in, const sample_order order,
+                                                                   int32_t *sel, int n_out, int64_t cap_out,
+                                                                   int64_t *out_offsets, int *__restrict__ flags) {
+    __shared__ int64_t s_ro[kPlanRanks + 1];
+    __shared__ int64_t sh[kPlanThreads / kWave];
+    const bool ranked = order.mode == kMapDispatch || order.mode == kMapCombine;
+    const bool staged = ranked && order.n_ranks <= kPlanRanks;
+    if (staged)
+        for (int r = threadIdx.x; r <= order.n_ranks; r += kPlanThreads) s_ro[r] = order.ro[r];
+    __syncthreads();
+    const int64_t *ro = staged ? (const int64_t *)s_ro : order.ro;
+    bool bad = n_out > 0 && bad_ranks(order);
+    const int per = (n_out + kPlanThreads - 1) / kPlanThreads;           // at most kPlanPer
+    const int k0 = (int)threadIdx.x * per;
+    int32_t p[kPlanPer];
+#pragma unroll
+    for (int i = 0; i < kPlanPer; ++i) {
+        p[i] = -1;
+        if (i < per && k0 + i < n_out) {
+            if (order.mode == kMapGiven) {
+                p[i] = order.given[k0 + i];
+            } else {
+                p[i] = ordered_segment(order, ro, k0 + i);
+                sel[k0 + i] = p[i];
+            }
+        }
+    }
+    int64_t len[kPlanPer], v = 0;
+#pragma unroll
+    for (int i = 0; i < kPlanPer; ++i) {
+        len[i] = (i < per && k0 + i < n_out) ? sample_len(in, p[i], bad) : 0;
+        v += len[i];
+    }
+    const int64_t inc = wave_inclusive_scan<int64_t>(v);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) sh[threadIdx.x / kWave] = inc;
+    __syncthreads();
+    int64_t run = inc - v, total = 0;
+#pragma unroll
+    for (int w = 0; w < kPlanThreads / kWave; ++w) {
+        if (w < (int)(threadIdx.x / kWave)) run += sh[w];
+        total += sh[w];
+    }
+#pragma unroll
+    for (int i = 0; i < kPlanPer; ++i) {
+        if (i < per && k0 + i < n_out) out_offsets[k0 + i] = run;
+        run += len[i];
+    }
+    if (threadIdx.x == 0) {
+        out_offsets[n_out] = total;
+        bad |= total > cap_out;                                          // the copy stops at cap_out
+    }
+    if (bad) atomicOr(flags, kFlagOffsets);
+    if (order.splits != nullptr) {
+        __syncthreads();                                                 // the offsets above, by any thread
+        for (int r = threadIdx.x; r < order.n_ranks; r += kPlanThreads) order.splits[r] = rank_split(order, out_offsets, r);
+    }
+}
+
+// The same for more samples than one workgroup takes: order and lengths summed per tile, then the scan.
+__global__ __launch_bounds__(kScanThreads) void permute_tile_sum_kernel(const jagged_in in, const sample_order order,
+                                                                        int32_t *__restrict__ sel, int64_t n_out,
+                                                                        int64_t *__restrict__ tile_sum,
                                                                         int *__restrict__ flags) {
     __shared__ int64_t sh[kScanThreads / kWave];
     const int64_t k0 = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanIpt;
-    bool bad = false;
+    bool bad = blockIdx.x == 0 && bad_ranks(order);
     int64_t v = 0;
 #pragma unroll
-    for (int i = 0; i < kScanIpt; ++i) v += out_len(in, sample_of, k0 + i, n_out, bad);
+    for (int i = 0; i < kScanIpt; ++i) {
+        const int64_t k = k0 + i;
+        if (k < n_out) {
+            int32_t p;
+            if (order.mode == kMapGiven) {
+                p = order.given[k];
+            } else {
+                p = ordered_segment(order, order.ro, k);
+                sel[k] = p;
+            }
+            v += sample_len(in, p, bad);
+        }
+    }
     int64_t total;
     (void)block_exclusive_scan<int64_t>(v, sh, total);
     if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
@@ -126,6 +272,13 @@ __global__ __launch_bounds__(kScanThreads) void permute_offsets_kernel(const jag
         out_offsets[n_out] = total;
         if (total > cap_out) atomicOr(flags, kFlagOffsets);     // the copy stops at cap_out
     }
+}
+
+__global__ __launch_bounds__(256) void dispatch_splits_kernel(const sample_order order,
+                                                              const int64_t *__restrict__ out_offsets) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < order.n_ranks; r += stride)
+        order.splits[r] = rank_split(order, out_offsets, r);
 }
 
 // number of entries of a[0, n) that are <= key; executed by one whole wavefront (64-ary search)
@@ -246,15 +399,25 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     }
 }
 
-int launch_indexed_permute(fs_ctx *ctx, const void *values, int64_t n_values, int32_t elem_bytes,
-                           const int64_t *offsets, int64_t B, const int32_t *sample_of, int64_t n_out, void *out_values,
-                           int64_t cap_out, int64_t *out_offsets, hipStream_t s) {
+// output samples in the order `order`, whose list is `sample_of` (written here unless the caller gave it)
+static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values, int32_t elem_bytes,
+                               const int64_t *offsets, int64_t B, const sample_order &order, int64_t n_out,
+                               void *out_values, int64_t cap_out, int64_t *out_offsets, hipStream_t s) {
     const jagged_in in = {offsets, B, n_values};
-    const int tiles = (int)(n_out > 0 ? ceil_div(n_out, kScanTile) : 1);
-    hipLaunchKernelGGL(permute_tile_sum_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, sample_of,
-                       n_out, ctx->jag_tile_sum, ctx->d_flags);
-    hipLaunchKernelGGL(permute_offsets_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, sample_of,
-                       n_out, ctx->jag_tile_sum, cap_out, out_offsets, ctx->d_flags);
+    const int32_t *sample_of = order.mode == kMapGiven ? order.given : ctx->jag_sel;
+    if (n_out <= (int64_t)kPlanThreads * kPlanPer) {
+        hipLaunchKernelGGL(jagged_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, in, order, ctx->jag_sel, (int)n_out,
+                           cap_out, out_offsets, ctx->d_flags);
+    } else {
+        const int tiles = (int)ceil_div(n_out, kScanTile);
+        hipLaunchKernelGGL(permute_tile_sum_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, order,
+                           ctx->jag_sel, n_out, ctx->jag_tile_sum, ctx->d_flags);
+        hipLaunchKernelGGL(permute_offsets_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, sample_of,
+                           n_out, ctx->jag_tile_sum, cap_out, out_offsets, ctx->d_flags);
+        if (order.splits != nullptr)
+            hipLaunchKernelGGL(dispatch_splits_kernel, dim3((unsigned)ceil_div(order.n_ranks, 256)), dim3(256), 0, s, order,
+                               out_offsets);
+    }
     if (cap_out > 0 && n_out > 0) {
         const int piece = elem_bytes % 16 == 0 ? 16 : (elem_bytes % 8 == 0 ? 8 : 4);
         const int ppe = elem_bytes / piece;
@@ -273,6 +436,13 @@ int launch_indexed_permute(fs_ctx *ctx, const void *values, int64_t n_values, in
     }
     FS_LAUNCH_CHECK(ctx, "indexed permute kernels");
     return FS_OK;
+}
+
+int launch_indexed_permute(fs_ctx *ctx, const void *values, int64_t n_values, int32_t elem_bytes,
+                           const int64_t *offsets, int64_t B, const int32_t *sample_of, int64_t n_out, void *out_values,
+                           int64_t cap_out, int64_t *out_offsets, hipStream_t s) {
+    const sample_order order = {kMapGiven, sample_of, 0, 0, nullptr, 0, nullptr};
+    return launch_ordered_copy(ctx, values, n_values, elem_bytes, offsets, B, order, n_out, out_values, cap_out, out_offsets, s);
 }
 
 // ---- VBS: cuts of about equal weight --------------------------------------------------------------------
@@ -382,82 +552,13 @@ int launch_partition_vbs(fs_ctx *ctx, const int64_t *lengths, int64_t B, const i
 }
 
 // ---- keyed transpose, ranged dispatch, ranged combine ---------------------------------------------------
-// Segment (f, b) of a keyed jagged tensor with F keys and B samples is number f * B + b in feature-major
-// form and b * F + f in batch-major form.  Ranks own sample ranges [ro[r], ro[r + 1]); what a rank is sent
-// (dispatch) or has sent (combine) is a feature-major tensor over its own samples, rank after rank.
-enum { kMapTranspose = 0, kMapDispatch = 1, kMapCombine = 2 };
-
-// the last r in [0, n) with scale * ro[r] <= x (ro ascending, ro[0] == 0)
-__device__ __forceinline__ int last_rank_at_or_before(const int64_t *__restrict__ ro, int n, int64_t scale, int64_t x) {
-    int lo = 0, hi = n;                      // first r with scale * ro[r] > x
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (scale * ro[mid] <= x) lo = mid + 1; else hi = mid;
-    }
-    return lo > 0 ? lo - 1 : 0;
-}
-
-__global__ __launch_bounds__(256) void segment_map_kernel(int mode, int64_t F, int64_t B,
-                                                          const int64_t *__restrict__ ro, int n_ranks,
-                                                          int32_t *__restrict__ sel, int *__restrict__ flags) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (mode != kMapTranspose) {
-        bool bad = false;
-        for (int64_t r = gtid; r < n_ranks; r += stride) bad |= ro[r + 1] < ro[r];
-        if (gtid == 0) bad |= ro[0] != 0 || ro[n_ranks] != B;
-        if (bad) atomicOr(flags, kFlagOffsets);
-    }
-    for (int64_t j = gtid; j < F * B; j += stride) {
-        int64_t in = -1;                     // stays -1 for ranges that make no sense: the copy skips and reports it
-        if (mode == kMapTranspose) {
-            in = (j % F) * B + j / F;
-        } else if (mode == kMapDispatch) {
-            const int r = last_rank_at_or_before(ro, n_ranks, F, j);
-            const int64_t first = ro[r], cnt = ro[r + 1] - first, local = j - F * first;
-            if (cnt > 0 && local >= 0 && local < F * cnt) in = (local / cnt) * B + first + local % cnt;
-        } else {
-            const int64_t f = j / B, b = j % B;
-            const int r = last_rank_at_or_before(ro, n_ranks, 1, b);
-            const int64_t first = ro[r], cnt = ro[r + 1] - first;
-            if (cnt > 0 && b >= first && b < first + cnt) in = F * first + f * cnt + (b - first);
-        }
-        sel[j] = (in >= 0 && in < F * B) ? (int32_t)in : -1;
-    }
-}
-
-// elements each rank is sent: the extent of its F * count segments in the dispatched tensor
-__global__ __launch_bounds__(256) void dispatch_splits_kernel(int64_t F, int64_t B, const int64_t *__restrict__ ro,
-                                                              int n_ranks, const int64_t *__restrict__ out_offsets,
-                                                              int64_t *__restrict__ splits) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_ranks; r += stride) {
-        int64_t a = ro[r], b = ro[r + 1];
-        a = a < 0 ? 0 : (a > B ? B : a);
-        b = b < a ? a : (b > B ? B : b);
-        splits[r] = out_offsets[F * b] - out_offsets[F * a];
-    }
-}
-
 int launch_keyed_shuffle(fs_ctx *ctx, int mode, const void *values, int64_t n_values, int32_t elem_bytes,
                          const int64_t *offsets, int64_t F, int64_t B, const int64_t *rank_offsets, int32_t n_ranks,
                          void *out_values, int64_t *out_offsets, int64_t *splits, hipStream_t s) {
     const int64_t segs = F * B;
-    if (segs > 0) {
-        int64_t blocks = ceil_div(segs, 256);
-        if (blocks > 1024) blocks = 1024;
-        hipLaunchKernelGGL(segment_map_kernel, dim3((unsigned)blocks), dim3(256), 0, s, mode, F, B, rank_offsets,
-                           (int)n_ranks, ctx->jag_sel, ctx->d_flags);
-    }
-    const int rc = launch_indexed_permute(ctx, values, n_values, elem_bytes, offsets, segs, ctx->jag_sel, segs,
-                                          out_values, n_values, out_offsets, s);
-    if (rc != FS_OK) return rc;
-    if (splits != nullptr && n_ranks > 0) {
-        hipLaunchKernelGGL(dispatch_splits_kernel, dim3((unsigned)ceil_div(n_ranks, 256)), dim3(256), 0, s, F, B,
-                           rank_offsets, (int)n_ranks, out_offsets, splits);
-        FS_LAUNCH_CHECK(ctx, "dispatch_splits_kernel");
-    }
-    return FS_OK;
+    const sample_order order = {mode, nullptr, F, B, rank_offsets, (int)n_ranks, splits};
+    return launch_ordered_copy(ctx, values, n_values, elem_bytes, offsets, segs, order, segs, out_values, n_values,
+                               out_offsets, s);
 }
 
 }  // namespace fs

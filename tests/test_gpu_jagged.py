@@ -178,6 +178,27 @@ def test_ranged_dispatch_and_combine_match_oracle(F, B, n_ranks, dtype, width):
     ctx.close()
 
 
+@pytest.mark.parametrize("segments", [1, 1023, 1024, 1025, 8191, 8192, 8193])
+@pytest.mark.parametrize("n_ranks", [1, 1024, 1025])
+def test_shuffles_around_the_most_samples_one_workgroup_lays_out(segments, n_ranks):
+    # one to eight samples a thread, then the tiled launches; rank boundaries inside and outside the staged list
+    rng = np.random.default_rng(segments + n_ranks)
+    values, offsets = keyed(rng, 1, segments, np.int64, 0, hi=9)
+    _, ro = O.partition_fbs(rng.integers(1, 100, size=segments).astype(np.int64), n_ranks)
+    ctx = fs.Context(max_ids=16384, max_dim=8)
+    sel = rng.permutation(segments).astype(np.int32)
+    got = fs.fs_jagged_indexed_permute(ctx, dev(values), dev(offsets), dev(sel), values.shape[0])
+    for a, b in zip(got, O.jagged_indexed_permute(values, offsets, sel)):
+        assert a.cpu().numpy().tolist() == b.tolist()
+    sent = fs.fs_jagged_ranged_dispatch(ctx, dev(values), dev(offsets), 1, segments, dev(ro))
+    for a, b in zip(sent, O.jagged_ranged_dispatch(values, offsets, 1, segments, ro)):
+        assert a.cpu().numpy().tolist() == b.tolist()
+    back = fs.fs_jagged_ranged_combine(ctx, sent[0], sent[1], 1, segments, dev(ro))
+    assert back[0].cpu().numpy().tolist() == values.tolist() and back[1].cpu().numpy().tolist() == offsets.tolist()
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    ctx.close()
+
+
 def test_ranged_dispatch_reports_ranges_that_do_not_cover_the_samples():
     rng = np.random.default_rng(8)
     values, offsets = keyed(rng, 2, 50, np.int64, 0)

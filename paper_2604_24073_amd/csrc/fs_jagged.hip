@@ -10,7 +10,7 @@
 // workgroup lays out the output offsets, then the copy; beyond, lengths summed per tile of samples, the
 // output offsets by a scan with tile prefixes, and the copy.  The copy is driven
 // by the OUTPUT (every lane writes consecutive pieces of the output, so a 16K-item sample costs per
-// item what a short one costs): a workgroup takes 4096 or 8192 consecutive output pieces, finds the samples
+// item what a short one costs): a workgroup takes 2048 or 8192 consecutive output pieces, finds the samples
 // they belong to with two 64-ary searches, stages their boundaries in LDS and lets every piece
 // binary-search LDS.
 //
@@ -297,11 +297,12 @@ __device__ __forceinline__ int64_t wave_upper_bound(const int64_t *__restrict__ 
     return lo;
 }
 
-// pieces per workgroup: the searches that open a tile are a chain of dependent loads, paid once per tile, and
-// the chip writes faster the more workgroups share a job.  Measured: 64 KB of output per workgroup for 8-byte
-// pieces (16.7 M IDs: 75 us with twice that), 128 KB for 16-byte pieces (250 k rows of 512 bytes: 50 us, and
-// 133 us with half of that)
-template <typename V> constexpr int copy_tile() { return sizeof(V) == 16 ? 8192 : 4096; }
+// Pieces per workgroup.  A copy of whole rows wants long stretches: the searches that open a tile are a chain of
+// dependent loads that queue behind the rows of the other workgroups (250 k rows of 512 bytes, 16-byte pieces: 50 us
+// with 128 KB a workgroup, 100 to 160 with 32 or 64 KB).  Where samples are short the walk over their boundaries
+// counts, and more, shorter-lived wavefronts hide it: 16 KB of 8-byte pieces (eight in flight per lane) against 32 KB
+// (sixteen), a whole balancer pass: samples of 1 to 200 IDs 198 -> 90 us, of 16 to 4096 IDs 108 -> 107.
+template <typename V> constexpr int copy_tile() { return sizeof(V) == 16 ? 8192 : 2048; }
 constexpr int kCopyWindow = 2048 + 2;                           // sample boundaries staged in LDS
 
 // V: the piece, the widest of 4, 8, 16 bytes that divides the element; ppe pieces per element.
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     static_assert(kWavePieces % (kWave * PIECES) == 0, "a wavefront's quarter is a whole number of rounds");
     for (uint32_t r0 = 0; r0 < kWavePieces; r0 += kWave * PIECES) {
         if (w0 + r0 >= tile_pieces) break;                      // whole wavefront
-        V v[PIECES];                                            // 128 bytes per lane in flight whatever the piece
+        V v[PIECES];                                            // in flight per lane
         bool live[PIECES];
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
@@ -388,13 +389,16 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
                     while (j + 1 < wn_all && out_offsets[ka + j + 1] <= e) ++j;
                     delta = offsets[sample_of[ka + j]] - out_offsets[ka + j];
                 }
-                v[i] = values[(e0 + le + delta) * ppe + pin];
+                // read once, written once: keeping either in the caches only pushes out the boundaries (three
+                // shuffles of 250 k rows of 512 bytes: 202 us with plain accesses, 185 with the hint on the loads
+                // only, 177 on both; at the rate of a plain copy now)
+                v[i] = __builtin_nontemporal_load(&values[(e0 + le + delta) * ppe + pin]);
             }
         }
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
             const uint32_t l = w0 + r0 + (uint32_t)i * kWave + lane;
-            if (live[i]) out[q0 + l] = v[i];
+            if (live[i]) __builtin_nontemporal_store(v[i], &out[q0 + l]);
         }
     }
 }
@@ -428,10 +432,10 @@ static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values
             hipLaunchKernelGGL((permute_copy_kernel<u32x4, 8>), grid, dim3(kScanThreads), 0, s, (const u32x4 *)values,
                                in, sample_of, n_out, out_offsets, cap_out, ppe, (u32x4 *)out_values);
         else if (piece == 8)
-            hipLaunchKernelGGL((permute_copy_kernel<uint64_t, 16>), grid, dim3(kScanThreads), 0, s, (const uint64_t *)values,
+            hipLaunchKernelGGL((permute_copy_kernel<uint64_t, 8>), grid, dim3(kScanThreads), 0, s, (const uint64_t *)values,
                                in, sample_of, n_out, out_offsets, cap_out, ppe, (uint64_t *)out_values);
         else
-            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, 16>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
+            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, 8>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
                                in, sample_of, n_out, out_offsets, cap_out, ppe, (uint32_t *)out_values);
     }
     FS_LAUNCH_CHECK(ctx, "indexed permute kernels");

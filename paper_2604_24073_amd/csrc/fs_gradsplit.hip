@@ -177,10 +177,9 @@ int launch_split_grads(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim, 
 // through part_pos they name rows of the packed parts instead: class 0 (collision rows) reads g_co, class 1 g_ex.
 __device__ __forceinline__ int part_row(int pos) { return pos >= 0 ? pos : -1 - pos; }
 
-__global__ __launch_bounds__(256) void gs_remap_cperm_kernel(const int32_t *__restrict__ cperm,
-                                                             const int32_t *__restrict__ class_pos, int n,
-                                                             const int32_t *__restrict__ part_pos,
-                                                             int32_t *__restrict__ cperm_parts, int *__restrict__ flags) {
+__device__ __forceinline__ void remap_cperm(const int32_t *__restrict__ cperm, const int32_t *__restrict__ class_pos, int n,
+                                            const int32_t *__restrict__ part_pos, int32_t *__restrict__ cperm_parts,
+                                            int *__restrict__ flags) {
     int n_pos = class_pos[1];
     if (n_pos > n) n_pos = n;
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -193,11 +192,10 @@ __global__ __launch_bounds__(256) void gs_remap_cperm_kernel(const int32_t *__re
     cperm_parts[p] = part_row(pos);
 }
 
-__global__ __launch_bounds__(256) void gs_remap_records_kernel(const int32_t *__restrict__ recs,
-                                                               const int64_t *__restrict__ counts_dev, int cap, int n,
-                                                               const int32_t *__restrict__ part_pos,
-                                                               int32_t *__restrict__ recs_parts, int *__restrict__ flags) {
-    const int cls = blockIdx.y;
+__device__ __forceinline__ void remap_records(int cls, const int32_t *__restrict__ recs,
+                                              const int64_t *__restrict__ counts_dev, int cap, int n,
+                                              const int32_t *__restrict__ part_pos, int32_t *__restrict__ recs_parts,
+                                              int *__restrict__ flags) {
     const int n_rows = clamp_i64(counts_dev + cls, cap);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_rows) return;
@@ -222,14 +220,26 @@ __global__ __launch_bounds__(256) void gs_remap_records_kernel(const int32_t *__
     for (int q = 0; q < kShortRecInts; ++q) dst[q] = w[q];
 }
 
+// Class order and the records of both classes in one launch (blockIdx.y: class of the records, 2: the order): each is
+// a few dependent loads per thread, so what a launch of its own costs is the launch.  One launch against two, the whole
+// start of Backward on 130 k rows of 1 KB: 118.2 -> 115.7 us.
+__global__ __launch_bounds__(256) void gs_remap_kernel(const int32_t *__restrict__ cperm, const int32_t *__restrict__ class_pos,
+                                                       const int32_t *__restrict__ recs,
+                                                       const int64_t *__restrict__ counts_dev, int cap, int n,
+                                                       const int32_t *__restrict__ part_pos,
+                                                       int32_t *__restrict__ cperm_parts, int32_t *__restrict__ recs_parts,
+                                                       int *__restrict__ flags) {
+    if (blockIdx.y == 2) remap_cperm(cperm, class_pos, n, part_pos, cperm_parts, flags);
+    else remap_records(blockIdx.y, recs, counts_dev, cap, n, part_pos, recs_parts, flags);
+}
+
 int launch_class_order_for_parts(fs_ctx *ctx, const int32_t *part_pos, int64_t n, int64_t cap_u, const int32_t *cperm,
                                  const int32_t *class_pos_dev, const int32_t *short_rec, const int64_t *counts_dev,
                                  int32_t *cperm_parts, int32_t *short_rec_parts, hipStream_t s) {
     if (n == 0) return FS_OK;
-    hipLaunchKernelGGL(gs_remap_cperm_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, cperm, class_pos_dev,
-                       (int)n, part_pos, cperm_parts, ctx->d_flags);
-    hipLaunchKernelGGL(gs_remap_records_kernel, dim3((unsigned)ceil_div(cap_u, 256), 2u), dim3(256), 0, s, short_rec,
-                       counts_dev, (int)cap_u, (int)n, part_pos, short_rec_parts, ctx->d_flags);
+    const int64_t most = n > cap_u ? n : cap_u;
+    hipLaunchKernelGGL(gs_remap_kernel, dim3((unsigned)ceil_div(most, 256), 3u), dim3(256), 0, s, cperm, class_pos_dev,
+                       short_rec, counts_dev, (int)cap_u, (int)n, part_pos, cperm_parts, short_rec_parts, ctx->d_flags);
     FS_LAUNCH_CHECK(ctx, "class order for parts");
     return FS_OK;
 }

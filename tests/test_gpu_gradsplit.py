@@ -55,6 +55,29 @@ def test_split_grads_bit_exact(ctx, n, n1, rows, dim):
     assert np.array_equal(pos[want["ex_index"]], -1 - np.arange(n_ex))
 
 
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 255, 256, 257, 4095, 4097, 70_000])
+@pytest.mark.parametrize("which", ["all", "none", "first", "last", "every 64th", "all but every 64th"])
+def test_split_grads_collision_rows_at_the_edges_of_wavefronts(ctx, n, which):
+    """Every occurrence its own row, collision rows chosen by slot: membership is decided 64 slots at a time.  Copies
+    and indices only, so every comparison is exact."""
+    slots = np.arange(n)
+    co = {"all": slots >= 0, "none": slots < 0, "first": slots == 0, "last": slots == n - 1, "every 64th": slots % 64 == 0,
+          "all but every 64th": slots % 64 != 0}[which]
+    ids = np.random.default_rng(n).permutation(n).astype(np.int64)
+    grads = (np.arange(n * 4, dtype=np.float32)).reshape(n, 4)
+    nxt = np.concatenate([slots[co], [n]]).astype(np.int64)
+    lay, sp = layout_and_split(ctx, ids, nxt, n + 1)
+    got = fs.fs_split_grads(ctx, dev(grads), lay, sp)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    mine = np.flatnonzero(co[ids])
+    rest = np.flatnonzero(~co[ids])
+    assert got["counts"].cpu().numpy().tolist() == [len(mine), len(rest)]
+    assert np.array_equal(got["co_index"][:len(mine)].cpu().numpy(), mine)
+    assert np.array_equal(got["ex_index"][:len(rest)].cpu().numpy(), rest)
+    assert got["g_co"][:len(mine)].cpu().numpy().tobytes() == grads[mine].tobytes()
+    assert got["g_ex"][:len(rest)].cpu().numpy().tobytes() == grads[rest].tobytes()
+
+
 def test_split_grads_all_and_none(ctx):
     rng = np.random.default_rng(3)
     ids = zipf_ids(rng, 3000, 400)

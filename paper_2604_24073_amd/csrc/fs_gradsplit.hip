@@ -127,6 +127,10 @@ __global__ void gs_empty_kernel(int64_t *counts_dev) {
     counts_dev[1] = 0;
 }
 
+// Bound: HBM, every gradient row read and written once.  The parts are what the next kernels read (the class passes,
+// or whatever packs them for an exchange), so they are stored with plain stores and stay in the caches as far as they
+// fit; the gradients are not needed again and are read around them.  Plain against non-temporal stores, the whole start
+// of Backward on 130 k rows of 1 KB: 113.5 -> 111.1 us.
 template <int LPR, int UNR>
 __global__ __launch_bounds__(256) void gs_copy_kernel(const u32x4 *__restrict__ grads, int n, int gvec,
                                                       const int32_t *__restrict__ part_pos, u32x4 *__restrict__ g_co,
@@ -155,7 +159,7 @@ __global__ __launch_bounds__(256) void gs_copy_kernel(const u32x4 *__restrict__ 
             if (live[u]) {
                 const bool co = pos[u] >= 0;
                 const int64_t r = co ? pos[u] : -1 - pos[u];
-                store_streaming(v[u], (co ? g_co : g_ex) + r * gvec + lig);
+                ((co ? g_co : g_ex) + r * gvec)[lig] = v[u];
             }
     }
 }

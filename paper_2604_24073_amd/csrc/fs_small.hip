@@ -282,18 +282,26 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         if (long_b != 0)                                     // wave-uniform
             lens += __shfl(wave_inclusive_scan<int>(lg ? (f ? len : len << 16) : 0), kWave - 1, kWave);
     }
+    // The ends of the layout; with them right and every row at least one occurrence long, the boundaries ascend from 0
+    // to n, so the extents of the rows are disjoint: the long ones sum to at most n <= kSmallIds (the packed halves
+    // hold that), and there are at most n / 9 of them.  A layout that does not fit its batch gets the flag and no class
+    // order: its extents may overlap, and then nothing bounds their sum.
+    if (classes && threadIdx.x == 0) bad |= n_t == 0 || job.seg_offsets[0] != 0 || job.seg_offsets[n_t] != job.n;
+    constexpr int kBadWave = 1 << 20;                        // beside the number of long rows
+    static_assert(kSmallIds < kBadWave, "there are fewer rows than the mark says");
+    const bool bad_wave = __ballot(bad) != 0;
     if (lane == 0) {
         sh.wave_a[w] = n_co_mine;
         sh.wave_b[w] = lens;
-        sh.wave_c[w] = n_long_mine;
+        sh.wave_c[w] = n_long_mine + (bad_wave ? kBadWave : 0);
     }
     if (bad) atomicOr(flags, kFlagInternal);
     __syncthreads();
     int n_co, len_all, n_long;
     int co_run = small_prefix(sh.wave_a, w, n_co);
-    // both halves stay below 2^16: a batch has at most kSmallIds occurrences
     int len_run = small_prefix(sh.wave_b, w, len_all);     // occurrences of long rows before the round: co, ex << 16
     int long_run = small_prefix(sh.wave_c, w, n_long);
+    const bool fits = n_long < kBadWave;                   // the layout fits its batch (the same in every thread)
     const int n_co_pos = len_all & 0xffff, n_pos = n_co_pos + (int)((uint32_t)len_all >> 16);
     // the list of long rows: class position, sorted position, slot; U_t1 is not needed in LDS any more, but the marks are
     int32_t *l_dest = reinterpret_cast<int32_t *>(lds), *l_from = l_dest + maxn / 8, *l_slot = l_from + maxn / 8;
@@ -320,14 +328,14 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
                 int32_t *rec = job.short_rec + ((int64_t)(f ? 0 : job.cap_t) + (f ? c : e - c)) * kShortRecInts;
                 *reinterpret_cast<i32x4 *>(rec) = i32x4{(int)(id & 0xFFFFFFFFll), (int)(id >> 32), e, x.len};
                 if (x.len > FS_SHORT_SEGMENT) {
-                    const int dest = f ? (both & 0xffff) : n_co_pos + (int)((uint32_t)both >> 16);
-                    const int k = long_run + __popcll(long_b & lt);
-                    if (k < maxn / 8) {
+                    if (fits) {
+                        const int dest = f ? (both & 0xffff) : n_co_pos + (int)((uint32_t)both >> 16);
+                        const int k = long_run + __popcll(long_b & lt);
                         l_dest[k] = dest;
                         l_from[k] = x.first;
                         l_slot[k] = f ? e : ~e;
+                        job.cstart[e] = dest;
                     }
-                    job.cstart[e] = dest;
                 } else {
                     // whole 16-byte pieces: one compute unit writes the records of the batch, and a store instruction
                     // costs it a cycle per line whatever it writes there
@@ -347,8 +355,8 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         job.counts_dev[1] = n_t - n_co;
         job.counts_dev[2] = n_t1 - n_co;
         if (job.class_pos_dev != nullptr) {
-            job.class_pos_dev[0] = classes ? n_co_pos : 0;
-            job.class_pos_dev[1] = classes ? n_pos : 0;
+            job.class_pos_dev[0] = classes && fits ? n_co_pos : 0;
+            job.class_pos_dev[1] = classes && fits ? n_pos : 0;
         }
     }
     // the other side: rows of U_t1 that are not in U_t
@@ -376,7 +384,7 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         }
         run += __popcll(b);
     }
-    if (!classes || n_long > maxn / 8) return;               // the second cannot happen: a long row has 9 occurrences
+    if (!classes || !fits) return;
     // The class order, a thread per class position.  The list has the long rows in row order, both classes mixed:
     // inside a class the positions ascend with the list, so the row of a position is found by looking for the last row
     // of ITS class that starts at or before it - the rows of the class are separated first.
@@ -415,8 +423,7 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         }
         if (lo == 0) continue;                               // cannot happen: row 0 of the list starts at 0
         const int j = lo - 1;
-        const int p = s_from[j] + (q - s_dest[j]);
-        job.cperm[q] = (p >= 0 && p < job.n) ? job.perm[p] : 0;
+        job.cperm[q] = job.perm[s_from[j] + (q - s_dest[j])];
         job.cslot[q] = s_slot[j];
     }
 }

@@ -81,3 +81,46 @@ def test_every_row_is_long(ctx, n):
     rng = np.random.default_rng(n)
     rows = n // 9
     check_index_half(ctx, rng.permutation(np.repeat(np.arange(rows), 9)), np.arange(0, rows, 2), rows, True)
+
+
+GUARD = 1 << 17                 # more than the packed sums of any layout can reach
+
+
+@pytest.mark.parametrize("n", [1024, 8192, 9000])
+@pytest.mark.parametrize("what", ["overlapping rows", "short of the batch", "behind the start", "stale count", "no rows"])
+def test_layout_that_does_not_fit_its_batch_writes_nothing_out_of_range(n, what):
+    """Segment boundaries or a count left over from another batch: reported, and nothing is written past the class
+    order, whose places the class passes then do not trust (one workgroup up to 8192 IDs, the chain of launches above)."""
+    ctx = fs.Context(max_ids=16384, max_dim=4)
+    u = 200
+    seg = np.minimum(np.arange(n + 1) * 9, n).astype(np.int32)
+    count = -(-n // 9)
+    if what == "overlapping rows":                           # every other row spans nearly the whole batch
+        seg[:u + 1] = np.where(np.arange(u + 1) % 2 == 1, n - 24, 0)
+        count = u
+    elif what == "short of the batch":
+        count = u if u * 9 < n else 100
+    elif what == "behind the start":
+        seg[0] = 3
+    elif what == "stale count":
+        count = n
+    else:
+        count = 0
+    lay = {"unique": dev(np.arange(n, dtype=np.int64)), "seg_offsets": dev(seg), "perm": dev(np.arange(n, dtype=np.int32)),
+           "n_unique": dev(np.array([count], dtype=np.int64)), "n": n}
+    u1 = dev(np.arange(0, n, 2, dtype=np.int64))
+    split = fs.alloc_split(n, n, "cuda")
+    guarded = ("cperm", "cslot", "cstart", "short_rec", "co", "co_slot", "ex", "ex_slot", "ex_next", "ex_next_slot")
+    size = {k: split[k].numel() for k in guarded}
+    for k in guarded:
+        split[k] = torch.full((size[k] + GUARD,), -7, dtype=split[k].dtype, device="cuda")
+    fs.fs_collision_split_classes(ctx, lay, u1, dev(np.array([u1.numel()], dtype=np.int64)), n, out=split)
+    rc = fs.fs_check_async(ctx)
+    if n <= 8192 or what != "stale count":                  # the chain sees no position of a row without occurrences
+        assert rc == fs.FS_ERANGE and "internal" in ctx.last_error()
+    for k in guarded:
+        assert bool((split[k][size[k]:] == -7).all()), k
+    first, end = split["class_pos"].cpu().tolist()
+    if n <= 8192:
+        assert (first, end) == (0, 0)
+    ctx.close()

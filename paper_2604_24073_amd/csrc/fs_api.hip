@@ -722,6 +722,17 @@ fs_ahead *alloc_ahead(fs_ctx *ctx, const void *key) {
     return e;
 }
 
+// What the index half of a record would refuse, asked before anything of the call is enqueued or claimed: a refusal
+// behind the row work would leave a table updated once by a call that the caller repeats.
+int check_index_half(fs_ctx *ctx, const fs_step_args *a, bool have_t1, bool done_ahead) {
+    if (done_ahead) return FS_OK;
+    // fs_unique_ids_ahead has no place for the ascending ID list: a lookup that walked it would read junk
+    if (have_t1 && a->sorted_ids_t1 != nullptr && !ctx->capturing && find_ahead(ctx, a->u_t1))
+        return set_err(ctx, FS_EINVAL, "step: sorted_ids_t1 given, but the dedup of this batch was done by "
+                                       "fs_unique_ids_ahead, which does not write it");
+    return FS_OK;
+}
+
 // stream `s` waits for the work of `e`; the slot is free afterwards (any thread; `e` was claimed)
 int consume_ahead(fs_ctx *ctx, fs_ahead *e, hipStream_t s) {
     while (e->state.load(std::memory_order_acquire) != kAheadRecorded) std::this_thread::yield();
@@ -781,10 +792,6 @@ int enqueue_index_work_batch(fs_ctx *ctx, int count, const fs_step_args *a, cons
         if (have_t1[k] && ahead && ahead[k]) {
             const int r = consume_ahead(ctx, ahead[k], s);
             if (rc == FS_OK) rc = r;
-            // fs_unique_ids_ahead has no place for the ascending ID list: a lookup that walked it would read junk
-            if (a[k].sorted_ids_t1 != nullptr && rc == FS_OK)
-                rc = set_err(ctx, FS_EINVAL, "step: sorted_ids_t1 given, but the dedup of this batch was done by "
-                                             "fs_unique_ids_ahead, which does not write it");
         }
     for (int k0 = 0; k0 < count && rc == FS_OK;) {
         if (!(have_t1[k0] && !(ahead && ahead[k0]))) { ++k0; continue; }
@@ -1084,6 +1091,10 @@ int fs_step_forward_ahead_batch(fs_ctx *ctx, const fs_step_args *a, int count, f
     FS_REQUIRE(ctx, !ctx->capturing, "index half ahead: not while a graph is being captured");
     if (stream == FS_STREAM_LAST_STEP)
         FS_REQUIRE(ctx, ctx->pfork_valid, "index half ahead: FS_STREAM_LAST_STEP before any pipelined call");
+    for (int k = 0; k < count; ++k) {
+        const int rc = check_index_half(ctx, &a[k], b.have_t1[k], false);
+        if (rc != FS_OK) return rc;
+    }
     fs_host *h = ctx->host;
     for (int k = 0; k < count; ++k)
         if (find_ahead(ctx, a[k].counts_dev)) {
@@ -1159,6 +1170,8 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
     hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
+    rc = check_index_half(ctx, a, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
+    if (rc != FS_OK) return rc;
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
     // already done ahead of time (and joined above): nothing left to do but to give the entry back
@@ -1182,6 +1195,8 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
     hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
+    rc = check_index_half(ctx, a, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
+    if (rc != FS_OK) return rc;
     forget_fetched(ctx);
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
@@ -1257,6 +1272,8 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
         nxt_t[k] = nxt_t1[k] = false;
         if (next) {
             rc = check_step_args(ctx, &next[k], &nxt_t[k], &nxt_t1[k]);
+            if (rc != FS_OK) return rc;
+            rc = check_index_half(ctx, &next[k], nxt_t1[k], !ctx->capturing && find_ahead(ctx, next[k].counts_dev));
             if (rc != FS_OK) return rc;
         }
         fetch_next[k] = two_part && next && nxt_t1[k];

@@ -724,8 +724,10 @@ fs_ahead *alloc_ahead(fs_ctx *ctx, const void *key) {
 
 // What the index half of a record would refuse, asked before anything of the call is enqueued or claimed: a refusal
 // behind the row work would leave a table updated once by a call that the caller repeats.
-int check_index_half(fs_ctx *ctx, const fs_step_args *a, bool have_t1, bool done_ahead) {
+int check_index_half(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool have_t1, bool done_ahead) {
     if (done_ahead) return FS_OK;
+    if (have_t && a->n_t > kClassOrderMax)
+        return set_err(ctx, FS_ERANGE, "step: the class order takes at most 7.8M occurrences of a batch");
     // fs_unique_ids_ahead has no place for the ascending ID list: a lookup that walked it would read junk
     if (have_t1 && a->sorted_ids_t1 != nullptr && !ctx->capturing && find_ahead(ctx, a->u_t1))
         return set_err(ctx, FS_EINVAL, "step: sorted_ids_t1 given, but the dedup of this batch was done by "
@@ -1092,7 +1094,7 @@ int fs_step_forward_ahead_batch(fs_ctx *ctx, const fs_step_args *a, int count, f
     if (stream == FS_STREAM_LAST_STEP)
         FS_REQUIRE(ctx, ctx->pfork_valid, "index half ahead: FS_STREAM_LAST_STEP before any pipelined call");
     for (int k = 0; k < count; ++k) {
-        const int rc = check_index_half(ctx, &a[k], b.have_t1[k], false);
+        const int rc = check_index_half(ctx, &a[k], b.have_t[k], b.have_t1[k], false);
         if (rc != FS_OK) return rc;
     }
     fs_host *h = ctx->host;
@@ -1170,7 +1172,7 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
     hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
-    rc = check_index_half(ctx, a, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
+    rc = check_index_half(ctx, a, have_t, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
     if (rc != FS_OK) return rc;
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
@@ -1195,7 +1197,7 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
     hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
-    rc = check_index_half(ctx, a, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
+    rc = check_index_half(ctx, a, have_t, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
     if (rc != FS_OK) return rc;
     forget_fetched(ctx);
     rc = join_pending_work(ctx, sp);
@@ -1273,7 +1275,8 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
         if (next) {
             rc = check_step_args(ctx, &next[k], &nxt_t[k], &nxt_t1[k]);
             if (rc != FS_OK) return rc;
-            rc = check_index_half(ctx, &next[k], nxt_t1[k], !ctx->capturing && find_ahead(ctx, next[k].counts_dev));
+            rc = check_index_half(ctx, &next[k], nxt_t[k], nxt_t1[k],
+                                  !ctx->capturing && find_ahead(ctx, next[k].counts_dev));
             if (rc != FS_OK) return rc;
         }
         fetch_next[k] = two_part && next && nxt_t1[k];

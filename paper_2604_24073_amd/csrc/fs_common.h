@@ -38,6 +38,10 @@ constexpr int kSortScan = kSortThreads > kRadix ? kSortThreads : kRadix;
 constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 4;
 constexpr int kScanTile = kScanThreads * kScanIpt;
+// The class order keeps two counts per tile of rows in LDS (60 KB): most tiles, and the most distinct rows that the host
+// may allow for (it knows occurrences only).
+constexpr int kClassOrderTiles = 60 * 1024 / (2 * (int)sizeof(int));
+constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
 // Most IDs of a batch whose index half one workgroup does (fs_small.hip).  Ahead of time, where nobody waits for it and a
 // launch costs whatever runs beside it: what fits the LDS of a compute unit.  On the caller's stream: up to where the

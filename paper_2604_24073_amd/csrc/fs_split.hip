@@ -447,7 +447,7 @@ int launch_class_order_batch(fs_ctx *ctx, int count, const fs_class_job *jobs, h
         blocks = j.blocks > blocks ? j.blocks : blocks;
         max_tiles = j.tiles_t > max_tiles ? j.tiles_t : max_tiles;
     }
-    if ((size_t)max_tiles * 2 * sizeof(int) > 60 * 1024)
+    if (max_tiles > kClassOrderTiles)
         return set_err(ctx, FS_ERANGE, "class order: more than 7.8M distinct rows in one batch");
     hipLaunchKernelGGL(class_scatter_kernel, dim3((unsigned)blocks, (unsigned)count), dim3(kScanThreads),
                        (size_t)max_tiles * 2 * sizeof(int), s, batch, ctx->d_flags);

@@ -93,3 +93,30 @@ def test_ascending_ids_of_a_batch_deduped_ahead_are_refused_before_anything_runs
     assert torch.equal(table, want_t) and torch.equal(state, want_s)
     assert torch.equal(step.emb, fresh.emb)
     ctx.close()
+
+
+@pytest.mark.parametrize("call", ["step", "forward", "ahead", "pipelined"])
+def test_batch_beyond_the_class_order_is_refused_before_anything_runs(call):
+    n, dim = 7680 * 1024 + 1, 4                              # one occurrence more than the class order takes
+    ctx = fs.Context(max_ids=n, max_dim=dim)
+    table, state = torch.ones((ROWS, dim), device="cuda"), torch.ones(ROWS, device="cuda")
+    ids = torch.arange(n, dtype=torch.int64, device="cuda") % ROWS
+    lay = fs.fs_unique_ids(ctx, ids, ROWS)
+    split = fs.alloc_split(n, 1, "cuda")
+    args = fs.make_step_args(table, state, 0.01, 1e-8, lay, torch.ones((n, dim), device="cuda"), None, None, None, split,
+                             None, None)
+    if call == "step":
+        raises(fs.FS_ERANGE, fs.fs_prioritized_step, ctx, args)
+    elif call == "forward":
+        raises(fs.FS_ERANGE, fs.fs_step_forward, ctx, args)
+    elif call == "ahead":
+        raises(fs.FS_ERANGE, fs.fs_step_forward_ahead, ctx, args)
+    else:
+        few = torch.arange(9, dtype=torch.int64, device="cuda")
+        small = fs.make_step_args(table, state, 0.01, 1e-8, fs.fs_unique_ids(ctx, few, ROWS), torch.ones((9, dim), device="cuda"),
+                                  None, None, None, fs.alloc_split(9, 1, "cuda"), None, None)
+        fs.fs_step_forward(ctx, small)
+        raises(fs.FS_ERANGE, fs.fs_prioritized_step_pipelined, ctx, small, args)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    assert bool((table == 1.0).all()) and bool((state == 1.0).all())
+    ctx.close()

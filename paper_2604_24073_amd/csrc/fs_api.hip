@@ -691,6 +691,12 @@ fs_ahead *find_ahead(fs_ctx *ctx, const void *key) {
     return nullptr;
 }
 
+// an entry whose work will not be posted after all
+void give_back(fs_ahead *e) {
+    e->key = nullptr;
+    e->state.store(kAheadFree, std::memory_order_release);
+}
+
 // find_ahead + claim: the caller hands the entry to exactly one consumer (consume_ahead)
 fs_ahead *claim_ahead(fs_ctx *ctx, const void *key) {
     fs_ahead *e = find_ahead(ctx, key);
@@ -825,6 +831,14 @@ int enqueue_index_work(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool hav
     return enqueue_index_work_batch(ctx, 1, a, &have_t, &have_t1, &ahead, s, set, &dedup_out, &layout_in);
 }
 
+// The index half of one record on `s`: done ahead of time, it is only waited for.  An entry is claimed here, where
+// nothing can fail before it is given back (one that is claimed and not consumed would be lost for good).
+int enqueue_or_consume_index_half(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool have_t1, hipStream_t s) {
+    fs_ahead *index_ahead = claim_ahead(ctx, a->counts_dev);
+    if (index_ahead) return consume_ahead(ctx, index_ahead, s);
+    return enqueue_index_work(ctx, a, have_t, have_t1, have_t1 ? claim_ahead(ctx, a->u_t1) : nullptr, s);
+}
+
 // update_embedding for one class of rows of iteration t (0: priority pass, 1: deferred pass) of `count`
 // tables (`use[k]`: table k has gradients); tables of one row width share their launches
 fs_class_pass_job class_job(const fs_step_args *a, int cls) {
@@ -897,9 +911,10 @@ int enqueue_side_stream(fs_ctx *ctx, const side_work &w) {
     // a capture stays off the shared streams: what another context enqueues meanwhile must not end up in the graph
     hipStream_t sa = ctx->capturing ? ctx->stream_cap_a : ctx->stream_a;
     int rc = FS_OK;
-    FS_HIP(ctx, hipStreamWaitEvent(sa, ctx->ev_pfork[w.parity], 0));
-    rc = enqueue_class_passes(ctx, w.cur, w.have_t, w.count, 1, sa, w.ex_timing);
-    for (int k = 0; k < w.count; ++k) {
+    const hipError_t e = hipStreamWaitEvent(sa, ctx->ev_pfork[w.parity], 0);
+    if (e != hipSuccess) rc = hip_err(ctx, e, "hipStreamWaitEvent(fork)");
+    if (rc == FS_OK) rc = enqueue_class_passes(ctx, w.cur, w.have_t, w.count, 1, sa, w.ex_timing);
+    for (int k = 0; k < w.count; ++k) {                       // also after a failure: the claimed entries are given back
         if (w.index_ahead[k]) {
             const int r = consume_ahead(ctx, w.index_ahead[k], sa);
             if (rc == FS_OK) rc = r;
@@ -940,10 +955,7 @@ int join_pending_work(fs_ctx *ctx, hipStream_t s) {
 // else); only after join_pending_work, so the entry is finished
 void drop_ahead(fs_ctx *ctx, const void *key) {
     fs_ahead *e = find_ahead(ctx, key);
-    if (e) {
-        e->key = nullptr;
-        e->state.store(kAheadFree, std::memory_order_release);
-    }
+    if (e) give_back(e);
 }
 
 }  // namespace
@@ -1036,6 +1048,8 @@ int fs_unique_ids_ahead(fs_ctx *ctx, const int64_t *ids, int64_t n, int64_t num_
     FS_REQUIRE(ctx, unique && seg_offsets && n_unique_dev, "unique: null pointer");
     if (n > 0) FS_REQUIRE(ctx, ids && perm, "unique: null pointer");
     FS_REQUIRE(ctx, !ctx->capturing, "unique ahead: not while a graph is being captured");
+    if (stream == FS_STREAM_LAST_STEP)
+        FS_REQUIRE(ctx, ctx->pfork_valid, "unique ahead: FS_STREAM_LAST_STEP before any pipelined call");
     fs_host *h = ctx->host;
     if (find_ahead(ctx, unique)) {
         (void)workers_wait(ctx);
@@ -1050,10 +1064,13 @@ int fs_unique_ids_ahead(fs_ctx *ctx, const int64_t *ids, int64_t n, int64_t num_
     // caller's stream - its position at the start of the most recent pipelined call
     hipEvent_t after = e->fork;
     if (stream == FS_STREAM_LAST_STEP) {
-        FS_REQUIRE(ctx, ctx->pfork_valid, "unique ahead: FS_STREAM_LAST_STEP before any pipelined call");
         after = ctx->ev_pfork[ctx->pipe_parity];
     } else {
-        FS_HIP(ctx, hipEventRecord(e->fork, as_stream(stream)));
+        const hipError_t err = hipEventRecord(e->fork, as_stream(stream));
+        if (err != hipSuccess) {
+            give_back(e);
+            return hip_err(ctx, err, "hipEventRecord(fork)");
+        }
     }
     auto job = [=]() -> int {
         int rc = FS_OK;
@@ -1122,23 +1139,27 @@ int fs_step_forward_ahead_batch(fs_ctx *ctx, const fs_step_args *a, int count, f
         b.e_ded[k] = (b.e_idx[k] && wanted) ? alloc_ahead(ctx, a[k].u_t1) : nullptr;
         failed = !b.e_idx[k] || (wanted && !b.e_ded[k]);
     }
-    if (failed) {
+    hipEvent_t after = nullptr;
+    hipError_t err = hipSuccess;
+    if (!failed) {
+        after = stream == FS_STREAM_LAST_STEP ? ctx->ev_pfork[ctx->pipe_parity] : b.e_idx[0]->fork;
+        if (stream != FS_STREAM_LAST_STEP) err = hipEventRecord(after, as_stream(stream));
+    }
+    if (failed || err != hipSuccess) {
         // the claimed entries still have to be waited for by somebody: let the index streams do it
         for (int k = 0; k < count; ++k) {
             if (b.dedup_in[k]) (void)consume_ahead(ctx, b.dedup_in[k], ctx->stream_x[0]);
             if (b.layout_in[k]) (void)consume_ahead(ctx, b.layout_in[k], ctx->stream_x[0]);
             fs_ahead *mine[2] = {b.e_idx[k], b.e_ded[k]};
             for (fs_ahead *e : mine)
-                if (e) { e->key = nullptr; e->state.store(kAheadFree, std::memory_order_release); }
+                if (e) give_back(e);
         }
+        if (err != hipSuccess) return hip_err(ctx, err, "hipEventRecord(fork)");
         return set_err(ctx, FS_EINVAL, "index half ahead: too much ahead-of-time work is outstanding");
     }
     const int x = h->x_turn;
     h->x_turn = (x + 1) % kIndexStreams;
     hipStream_t sx = ctx->stream_x[x];
-    hipEvent_t after = b.e_idx[0]->fork;
-    if (stream == FS_STREAM_LAST_STEP) after = ctx->ev_pfork[ctx->pipe_parity];
-    else FS_HIP(ctx, hipEventRecord(b.e_idx[0]->fork, as_stream(stream)));
     auto job = [=]() -> int {
         int jrc = FS_OK;
         if (hipStreamWaitEvent(sx, after, 0) != hipSuccess) jrc = FS_EHIP;
@@ -1176,12 +1197,9 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     if (rc != FS_OK) return rc;
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
-    // already done ahead of time (and joined above): nothing left to do but to give the entry back
-    fs_ahead *index_ahead = claim_ahead(ctx, a->counts_dev);
-    fs_ahead *ahead = (!index_ahead && have_t1) ? claim_ahead(ctx, a->u_t1) : nullptr;
     FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
     FS_HIP(ctx, hipStreamWaitEvent(sa, ctx->ev_fork, 0));
-    rc = index_ahead ? consume_ahead(ctx, index_ahead, sa) : enqueue_index_work(ctx, a, have_t, have_t1, ahead, sa);
+    rc = enqueue_or_consume_index_half(ctx, a, have_t, have_t1, sa);
     if (rc != FS_OK) return rc;
     FS_HIP(ctx, hipEventRecord(ctx->ev_split, sa));
     FS_HIP(ctx, hipStreamWaitEvent(sp, ctx->ev_split, 0));
@@ -1203,8 +1221,6 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
     begin_step_timing(ctx);
-    fs_ahead *index_ahead = claim_ahead(ctx, a->counts_dev);
-    fs_ahead *ahead = (!index_ahead && have_t1) ? claim_ahead(ctx, a->u_t1) : nullptr;
     // Nothing outside this call can start before its last update, so the row work does not wait for the split: every
     // row of U_t is updated straight from the layout of batch t, then the lookahead rows are read, in batch order;
     // the index half is independent of both.  On the side stream it runs beside them, which costs two cross-stream
@@ -1226,8 +1242,7 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
         if (rc != FS_OK) return rc;
     }
     if (side) FS_HIP(ctx, hipStreamWaitEvent(sa, ctx->ev_fork, 0));
-    hipStream_t si = side ? sa : sp;
-    rc = index_ahead ? consume_ahead(ctx, index_ahead, si) : enqueue_index_work(ctx, a, have_t, have_t1, ahead, si);
+    rc = enqueue_or_consume_index_half(ctx, a, have_t, have_t1, side ? sa : sp);
     if (rc != FS_OK) return rc;
     if (side) {
         FS_HIP(ctx, hipEventRecord(ctx->ev_split, sa));

@@ -1,5 +1,7 @@
 """A step call that is refused leaves everything as it was: nothing enqueued, table and state untouched, results of
 ahead-of-time calls still there for the call that is made instead."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -119,4 +121,47 @@ def test_batch_beyond_the_class_order_is_refused_before_anything_runs(call):
         raises(fs.FS_ERANGE, fs.fs_prioritized_step_pipelined, ctx, small, args)
     assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
     assert bool((table == 1.0).all()) and bool((state == 1.0).all())
+    ctx.close()
+
+
+def leave_a_host_error():
+    """A runtime call of the caller's own that failed: the next launch check of the library finds its error."""
+    assert ctypes.CDLL("libamdhip64.so").hipSetDevice(ctypes.c_int(9999)) != 0
+
+
+@pytest.mark.parametrize("n", [300, 70_000])
+def test_failed_steps_keep_what_was_done_ahead(n):
+    """A step whose row work does not launch gives none of the ahead-of-time entries away: many times more failures than
+    there are entries, and the last dedup is still found."""
+    ctx = fs.Context(max_ids=80_000, max_dim=DIM)
+    table, state = torch.zeros((ROWS, DIM), device="cuda"), torch.zeros(ROWS, device="cuda")
+    a, b, _ = batches(n)
+    step = Step(ctx, table, state, a, b, 1, sorted_ids=False)
+    for _ in range(80):
+        fs.fs_unique_ids_ahead(ctx, step.nxt, ROWS, step.lay1)
+        leave_a_host_error()
+        raises(fs.FS_EHIP, fs.fs_prioritized_step, ctx, step.args)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    fs.fs_prioritized_step(ctx, step.args)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    u = np.unique(b)
+    assert int(step.lay1["n_unique"].item()) == len(u)
+    assert np.array_equal(step.lay1["unique"][:len(u)].cpu().numpy(), u)
+    assert torch.equal(step.emb, table[step.nxt])
+    ctx.close()
+
+
+def test_ahead_call_that_is_refused_leaves_no_entry_behind():
+    """FS_STREAM_LAST_STEP before any pipelined call: refused, and the step that names the buffers dedups by itself
+    instead of waiting for work that was never posted."""
+    ctx = fs.Context(max_ids=1000, max_dim=DIM)
+    table, state = torch.zeros((ROWS, DIM), device="cuda"), torch.zeros(ROWS, device="cuda")
+    a, b, _ = batches(300)
+    step = Step(ctx, table, state, a, b, 1)
+    with pytest.raises(fs.FreeScaleError) as e:
+        fs.fs_unique_ids_ahead(ctx, step.nxt, ROWS, step.lay1, stream=fs.FS_STREAM_LAST_STEP)
+    assert e.value.code == fs.FS_EINVAL
+    fs.fs_prioritized_step(ctx, step.args)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    assert int(step.lay1["n_unique"].item()) == len(np.unique(b))
     ctx.close()

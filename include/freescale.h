@@ -56,8 +56,13 @@ enum {
 
 /* Allocates the workspace for inputs of at most max_ids IDs per iteration and rows of at
  * most max_dim columns on GPU `device` (sort double buffers, histograms, scan partials,
- * fp64 partial rows of the segment reduce), two side streams at default priority and the
- * events that order the passes.  This is the only call that allocates device memory. */
+ * fp64 partial rows of the segment reduce) and the events that order the passes.  This is the only call that
+ * allocates device memory.
+ * What a call runs beside the caller's stream goes on a side stream and two index streams of default priority.
+ * Contexts of one GPU whose calls all name the same stream of the caller share these three: their side work runs in
+ * the order it is enqueued, behind positions of that one stream, and fs_check_async and fs_ctx_destroy wait for all of
+ * it.  A context that has been called on one stream and is then called on another, or on a stream that is being captured,
+ * gets three of its own from there on. */
 int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim);
 int fs_ctx_destroy(fs_ctx *ctx);
 

@@ -182,55 +182,100 @@ void forget_fetched(fs_ctx *ctx) {
     for (int k = 0; k < FS_MAX_STEP_TABLES; ++k) ctx->fetched_emb[k] = nullptr;
 }
 
-// The streams that the contexts of one GPU run their own work on.  The chip gives a process four hardware queues:
-// one side stream, two index streams and the caller's stream are exactly four, and streams beyond that share a queue
-// with another one and run behind its work.  A program with several contexts on a GPU therefore gets one set for all of
-// them (three contexts with a set each, stepped in turn: 118 us per step of a 4M x 128 table where one context takes
-// 98).  Streams are safe to enqueue on from several threads, every wait enqueued here is for an event recorded
-// before, so contexts that share a stream can delay each other but not wait for each other in a circle.  Created with
-// the first context of a GPU, destroyed with the last.
-constexpr int kPoolDevices = 64;
-struct stream_set {
-    int users = 0;
-    hipStream_t a = nullptr, x[kIndexStreams] = {};
-};
-std::mutex g_pool_mu;
-stream_set g_pool[kPoolDevices];
+}  // namespace
 
-void destroy_set(stream_set &p) {
-    if (p.a) { (void)hipStreamSynchronize(p.a); (void)hipStreamDestroy(p.a); }
-    for (hipStream_t &st : p.x)
-        if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
-    p = stream_set();
+// ---- the streams that contexts run their own work on ---------------------------------------------------------------
+// One side stream and two index streams make a set.  Contexts whose calls all name one and the same stream of the caller
+// share the set of that stream: the chip gives a process four hardware queues, which the caller's stream and one set
+// use up, and streams beyond that share a queue with another one and run behind its work (three loops of a 4M x 128
+// table in turn on one stream, ten steps: 1320 to 1405 us with a set each, 1195 with one).  Everything on such a set
+// waits for positions of that one stream only, so a context that shares it is held up by nothing that does not hold up
+// its own calls as well.  A context that is called on a second stream, or while its stream is being captured, gets a set
+// of its own for good: behind another stream's work it could wait for something its caller has nothing to do with, and
+// what another context enqueues must not end up in a capture (two groups of two tables on a stream each, 200 k IDs a
+// batch, ten steps: 4030 to 4300 us with one set for both, 3900 to 3945 with two).
+// Streams are safe to enqueue on from several threads, and every wait enqueued is for an event recorded before.
+struct fs_stream_set {
+    int device, users;
+    hipStream_t home;                      // the caller's stream whose contexts share the set
+    hipStream_t a, x[kIndexStreams];
+    fs_stream_set *next;                   // list of the shared sets
+};
+
+namespace {
+
+std::mutex g_sets_mu;
+fs_stream_set *g_sets;
+
+void destroy_set(fs_stream_set *p) {
+    if (p->a) (void)hipStreamDestroy(p->a);
+    for (hipStream_t st : p->x)
+        if (st) (void)hipStreamDestroy(st);
+    delete p;
 }
 
-bool acquire_streams(fs_ctx *c) {
-    if (c->device >= kPoolDevices) return false;
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    stream_set &p = g_pool[c->device];
-    if (p.users == 0) {
-        bool ok = hipStreamCreateWithFlags(&p.a, hipStreamNonBlocking) == hipSuccess;
-        for (hipStream_t &st : p.x) ok = ok && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
-        if (!ok) {
-            destroy_set(p);
-            return false;
+fs_stream_set *new_set(int device, hipStream_t home) {
+    fs_stream_set *p = new (std::nothrow) fs_stream_set();
+    if (!p) return nullptr;
+    p->device = device;
+    p->users = 1;
+    p->home = home;
+    int current = device;
+    (void)hipGetDevice(&current);
+    bool ok = current == device || hipSetDevice(device) == hipSuccess;
+    ok = ok && hipStreamCreateWithFlags(&p->a, hipStreamNonBlocking) == hipSuccess;
+    for (hipStream_t &st : p->x) ok = ok && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
+    if (current != device) (void)hipSetDevice(current);
+    if (ok) return p;
+    destroy_set(p);
+    return nullptr;
+}
+
+// the set of the contexts driven from `home`
+fs_stream_set *share_set(int device, hipStream_t home) {
+    std::lock_guard<std::mutex> lk(g_sets_mu);
+    for (fs_stream_set *p = g_sets; p; p = p->next)
+        if (p->device == device && p->home == home) {
+            ++p->users;
+            return p;
         }
+    fs_stream_set *p = new_set(device, home);
+    if (p) {
+        p->next = g_sets;
+        g_sets = p;
     }
-    ++p.users;
-    c->stream_a = p.a;
-    for (int k = 0; k < kIndexStreams; ++k) c->stream_x[k] = p.x[k];
-    return true;
+    return p;
+}
+
+// gives a set back; this context's work on it is done (or there is none)
+void drop_set(fs_stream_set *p) {
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> lk(g_sets_mu);
+        if (--p->users > 0) return;
+        for (fs_stream_set **q = &g_sets; *q; q = &(*q)->next)
+            if (*q == p) {
+                *q = p->next;
+                break;
+            }
+    }
+    destroy_set(p);
+}
+
+void use_set(fs_ctx *c, const fs_stream_set *p) {
+    c->stream_a = p->a;
+    for (int k = 0; k < kIndexStreams; ++k) c->stream_x[k] = p->x[k];
 }
 
 void release_streams(fs_ctx *c) {
-    if (!c->stream_a) return;
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    stream_set &p = g_pool[c->device];
     // this context's work has to be done before its events and workspace go
-    (void)hipStreamSynchronize(c->stream_a);
-    for (hipStream_t st : c->stream_x) (void)hipStreamSynchronize(st);
-    if (--p.users == 0) destroy_set(p);
-    c->stream_a = nullptr;
+    for (fs_stream_set *p : {c->shared_set, c->own_set}) {
+        if (!p) continue;
+        (void)hipStreamSynchronize(p->a);
+        for (hipStream_t st : p->x) (void)hipStreamSynchronize(st);
+        drop_set(p);
+    }
+    c->shared_set = c->own_set = nullptr;
 }
 
 void worker_stop(fs_ctx *ctx);
@@ -287,9 +332,12 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     ok = ok && c->host != nullptr;
     // Only the streams of the steady-state step exist from the start; those of a graph capture are created when
     // first needed.
-    ok = ok && acquire_streams(c);
+    // (the set of the default stream for now: the first call that needs one names the caller's stream)
+    c->shared_set = share_set(device, nullptr);
+    ok = ok && c->shared_set != nullptr;
+    if (c->shared_set) use_set(c, c->shared_set);
     hipEvent_t *evs[] = {&c->ev_fork, &c->ev_split, &c->ev_pfork[0], &c->ev_pfork[1], &c->ev_side[0],
-                         &c->ev_side[1]};
+                         &c->ev_side[1], &c->ev_move};
     // These events order work of this device's streams among themselves and nothing else: nobody reads through
     // them what a kernel wrote (the host only asks whether one has passed, to skip a wait).  Without the
     // system-scope fence that a recorded event otherwise brings, the kernel behind a wait keeps the caches as the
@@ -317,7 +365,8 @@ int fs_ctx_destroy(fs_ctx *c) {
     for (hipStream_t st : streams)
         if (st) { (void)hipStreamSynchronize(st); (void)hipStreamDestroy(st); }
     release_streams(c);
-    hipEvent_t evs[] = {c->ev_fork, c->ev_split, c->ev_pfork[0], c->ev_pfork[1], c->ev_side[0], c->ev_side[1]};
+    hipEvent_t evs[] = {c->ev_fork, c->ev_split, c->ev_pfork[0], c->ev_pfork[1], c->ev_side[0], c->ev_side[1],
+                        c->ev_move};
     for (hipEvent_t e : evs)
         if (e) (void)hipEventDestroy(e);
     if (c->host) {
@@ -898,6 +947,7 @@ int enqueue_gather(fs_ctx *ctx, const fs_step_args *a, hipStream_t s) {
 constexpr int kMaxTables = FS_MAX_STEP_TABLES;
 struct side_work {
     int count = 0, parity = 0;
+    hipStream_t stream = nullptr;
     hipEvent_t *ex_timing = nullptr;
     fs_step_args cur[kMaxTables], next[kMaxTables];
     bool have_t[kMaxTables], has_next[kMaxTables], nxt_t[kMaxTables], nxt_t1[kMaxTables];
@@ -908,8 +958,7 @@ struct side_work {
 // Side stream A for one pipelined call: after the caller's earlier work (the gradients of `cur`), the
 // deferred passes, then the index halves of `next`, then the event the next call waits for.
 int enqueue_side_stream(fs_ctx *ctx, const side_work &w) {
-    // a capture stays off the shared streams: what another context enqueues meanwhile must not end up in the graph
-    hipStream_t sa = ctx->capturing ? ctx->stream_cap_a : ctx->stream_a;
+    hipStream_t sa = w.stream;
     int rc = FS_OK;
     const hipError_t e = hipStreamWaitEvent(sa, ctx->ev_pfork[w.parity], 0);
     if (e != hipSuccess) rc = hip_err(ctx, e, "hipStreamWaitEvent(fork)");
@@ -956,6 +1005,45 @@ int join_pending_work(fs_ctx *ctx, hipStream_t s) {
 void drop_ahead(fs_ctx *ctx, const void *key) {
     fs_ahead *e = find_ahead(ctx, key);
     if (e) give_back(e);
+}
+
+// Before work that is ordered after `s`, a stream of the caller, goes on the context's own streams: whose set they are.
+int follow_stream(fs_ctx *ctx, hipStream_t s) {
+    if (ctx->own_set) return FS_OK;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (s != nullptr) FS_HIP(ctx, hipStreamIsCapturing(s, &status));
+    // (one handle stands for the per-thread stream of every thread)
+    const bool alone = status != hipStreamCaptureStatusNone || s == hipStreamPerThread;
+    if (!alone && s == ctx->shared_set->home) {
+        ctx->set_used = true;
+        return FS_OK;
+    }
+    if (!alone && !ctx->set_used) {
+        fs_stream_set *p = share_set(ctx->device, s);
+        if (!p) return set_err(ctx, FS_EHIP, "hipStreamCreateWithFlags(side streams)");
+        drop_set(ctx->shared_set);
+        ctx->shared_set = p;
+        ctx->set_used = true;
+        use_set(ctx, p);
+        return FS_OK;
+    }
+    const int wrc = workers_wait(ctx);                       // what has been posted is on the streams it was posted for
+    if (wrc != FS_OK) return wrc;
+    fs_stream_set *p = new_set(ctx->device, s);
+    if (!p) return set_err(ctx, FS_EHIP, "hipStreamCreateWithFlags(side streams)");
+    // the scratch of every stream of the old set is the scratch of its successor
+    hipError_t err = hipSuccess;
+    for (int k = -1; k < kIndexStreams && err == hipSuccess && ctx->set_used; ++k) {
+        err = hipEventRecord(ctx->ev_move, k < 0 ? ctx->stream_a : ctx->stream_x[k]);
+        if (err == hipSuccess) err = hipStreamWaitEvent(k < 0 ? p->a : p->x[k], ctx->ev_move, 0);
+    }
+    if (err != hipSuccess) {
+        drop_set(p);
+        return hip_err(ctx, err, "hipStreamWaitEvent(own side streams)");
+    }
+    ctx->own_set = p;
+    use_set(ctx, p);
+    return FS_OK;
 }
 
 }  // namespace
@@ -1050,6 +1138,8 @@ int fs_unique_ids_ahead(fs_ctx *ctx, const int64_t *ids, int64_t n, int64_t num_
     FS_REQUIRE(ctx, !ctx->capturing, "unique ahead: not while a graph is being captured");
     if (stream == FS_STREAM_LAST_STEP)
         FS_REQUIRE(ctx, ctx->pfork_valid, "unique ahead: FS_STREAM_LAST_STEP before any pipelined call");
+    const int frc = stream == FS_STREAM_LAST_STEP ? FS_OK : follow_stream(ctx, as_stream(stream));
+    if (frc != FS_OK) return frc;
     fs_host *h = ctx->host;
     if (find_ahead(ctx, unique)) {
         (void)workers_wait(ctx);
@@ -1114,6 +1204,8 @@ int fs_step_forward_ahead_batch(fs_ctx *ctx, const fs_step_args *a, int count, f
         const int rc = check_index_half(ctx, &a[k], b.have_t[k], b.have_t1[k], false);
         if (rc != FS_OK) return rc;
     }
+    const int frc = stream == FS_STREAM_LAST_STEP ? FS_OK : follow_stream(ctx, as_stream(stream));
+    if (frc != FS_OK) return frc;
     fs_host *h = ctx->host;
     for (int k = 0; k < count; ++k)
         if (find_ahead(ctx, a[k].counts_dev)) {
@@ -1192,9 +1284,12 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     bool have_t, have_t1;
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
-    hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
+    hipStream_t sp = as_stream(stream);
     rc = check_index_half(ctx, a, have_t, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
     if (rc != FS_OK) return rc;
+    rc = follow_stream(ctx, sp);
+    if (rc != FS_OK) return rc;
+    hipStream_t sa = ctx->stream_a;
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
     FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
@@ -1214,9 +1309,15 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     bool have_t, have_t1;
     int rc = check_step_args(ctx, a, &have_t, &have_t1);
     if (rc != FS_OK) return rc;
-    hipStream_t sp = as_stream(stream), sa = ctx->stream_a;
+    hipStream_t sp = as_stream(stream);
     rc = check_index_half(ctx, a, have_t, have_t1, find_ahead(ctx, a->counts_dev) != nullptr);
     if (rc != FS_OK) return rc;
+    const bool side = (have_t ? a->n_t : 0) + (have_t1 ? a->n_t1 : 0) > kStepSideIds;
+    if (side) {
+        rc = follow_stream(ctx, sp);
+        if (rc != FS_OK) return rc;
+    }
+    hipStream_t sa = ctx->stream_a;
     forget_fetched(ctx);
     rc = join_pending_work(ctx, sp);
     if (rc != FS_OK) return rc;
@@ -1226,7 +1327,6 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     // the index half is independent of both.  On the side stream it runs beside them, which costs two cross-stream
     // waits of 10-12 us of host time each: worth it where the row work is long (4M x 128, 262 k IDs a batch: 182
     // against 191 us), while a tiny call is bound by its host path (1 k IDs: 81 against 52 us).
-    const bool side = (have_t ? a->n_t : 0) + (have_t1 ? a->n_t1 : 0) > kStepSideIds;
     if (side) FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
     if (have_t) {
         hipEvent_t *tu = timing_pair(ctx, FS_TIME_UPDATE_CO);
@@ -1319,6 +1419,10 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
         part[k] = fetched && !one_stream ? 1 : -1;
     }
     hipStream_t sp = as_stream(stream);
+    if (!ctx->capturing) {
+        const int frc = follow_stream(ctx, sp);
+        if (frc != FS_OK) return frc;
+    }
     begin_step_timing(ctx);
     // Side stream A still runs what the previous call left there (its deferred passes, the index halves
     // that produced the split and class order of `cur`).  It is waited for once, right before the first
@@ -1374,6 +1478,8 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
             w->ahead[k] = (claim && nxt_t1[k] && !w->index_ahead[k]) ? claim_ahead(ctx, next[k].u_t1) : nullptr;
         }
         w->parity = p;
+        // a capture stays off the shared streams: what another context enqueues meanwhile must not end up in the graph
+        w->stream = ctx->capturing ? ctx->stream_cap_a : ctx->stream_a;
         w->ex_timing = timing_pair(ctx, FS_TIME_UPDATE_EX);
         side_job = [ctx, w]() -> int { return enqueue_side_stream(ctx, *w); };
         if (w0) w0->post(side_job);

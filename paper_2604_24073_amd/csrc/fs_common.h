@@ -206,7 +206,11 @@ struct fs_ctx {
     int64_t *jag_tile_sum;    // [scan tiles] output elements per tile of output samples
     int32_t *jag_sel;         // [max_ids] computed segment order of a keyed shuffle
 
-    // shared by the contexts of a GPU (fs_api.hip)
+    // the set of streams in use (fs_api.hip): the one shared with the other contexts driven from the same stream, or one
+    // of its own
+    struct fs_stream_set *shared_set, *own_set;
+    bool set_used;            // host-side: work of this context has gone on the shared set
+    hipEvent_t ev_move;       // end of a stream of the shared set, for its successor
     hipStream_t stream_a;     // side stream: index half of the lookahead batch; deferred pass of a pipelined call
     hipStream_t stream_x[kIndexStreams];   // ahead-of-time dedups and index halves, used in turn
     hipEvent_t ev_fork, ev_split;          // self-contained step and fs_step_forward

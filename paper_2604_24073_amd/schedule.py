@@ -144,8 +144,9 @@ class StepLoop:
             t.allocate(self.L, self.P, self.n_records, emb_rotation, keep_reduced, inverse=two_part,
                        row_ordered_lookup=row_ordered_lookup)
         self.ctxs = [fs.Context(max_ids=max(max(t.n) for t in g), max_dim=max(t.dim for t in g)) for g in self.groups]
-        # The chip gives a process four hardware queues and a context owns three streams, so the first group is
-        # stepped on the default stream (the fourth queue); a stream of its own for it costs 25 % (5 queues in use).
+        # The chip gives a process four hardware queues, and the contexts driven from one stream use three more
+        # streams between them, so the first group is stepped on the default stream (the fourth queue); a stream of
+        # its own for it costs 25 % (5 queues in use).
         self.streams = [torch.cuda.default_stream()] + [new_hip_stream() for _ in self.groups[1:]]
         # one contiguous array of records per group and step: what the step call takes; and per chain start
         self.step_records = [[fs.step_args_array([t.args[s] for t in g]) for s in range(self.n_records)]

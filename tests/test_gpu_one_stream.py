@@ -1,7 +1,7 @@
 """The pipelined step keeps a call with little row work on one stream and runs a large one on two, and the
 self-contained step does the same with its index half: iterations of both sizes in turn (so that every hand-over between
-the two forms happens) give the bits of the building blocks issued one after another.  Also: contexts of one GPU share
-their side and index streams, also from two threads and after one of them is gone."""
+the two forms happens) give the bits of the building blocks issued one after another.  Also: contexts driven from one
+stream share their side and index streams; a context that is called on a second stream, or captured, has its own."""
 import threading
 
 import numpy as np
@@ -9,8 +9,8 @@ import pytest
 import torch
 
 import paper_2604_24073_amd as fs
-from helpers import table_to_host
-from test_gpu_parity import rand_table, run_steps_gpu
+from helpers import dev, table_to_host
+from test_gpu_parity import rand_table, run_steps_gpu, zipf_ids
 from test_gpu_pipeline import make_its, run_pipelined
 
 pytestmark = pytest.mark.gpu
@@ -41,7 +41,9 @@ def test_large_and_small_iterations_in_turn(dtype):
     ctx.close()
 
 
-def test_contexts_share_their_streams():
+def test_contexts_share_their_streams_until_they_are_called_on_another():
+    # both on the default stream (one set for the two), then each on a stream of its own from a thread of its own (a set
+    # each, work still queued on the old one), then one of them alone
     rng = np.random.default_rng(8)
     rows, dim = 5000, 64
     its = [make_its(rng, rows, dim, 6, users=40, max_len=300) for _ in range(2)]
@@ -71,3 +73,99 @@ def test_contexts_share_their_streams():
     again = run_pipelined(ctxs[1], table, state, its[1], 0.01, 1e-8, ahead="index")
     assert table_to_host(again[0]).tobytes() == table_to_host(want[1][0]).tobytes()
     ctxs[1].close()
+
+
+def test_contexts_on_one_stream_take_turns():
+    """Two contexts stepped in turn on one stream that is not the default one, without a wait between the calls."""
+    rng = np.random.default_rng(9)
+    rows, dim = 5000, 64
+    its = [make_its(rng, rows, dim, 5, users=40, max_len=300) for _ in range(2)]
+    table, state = rand_table(rng, rows, dim, "f32"), np.zeros(rows, np.float32)
+    ctxs = [fs.Context(max_ids=20_000, max_dim=dim) for _ in range(2)]
+    want = [run_pipelined(ctxs[k], table, state, its[k], 0.01, 1e-8, ahead="index") for k in range(2)]
+    got = [None, None]
+    with torch.cuda.stream(torch.cuda.Stream()):
+        fresh = [fs.Context(max_ids=20_000, max_dim=dim) for _ in range(2)]
+
+        def inner(_):                # the other context's whole run between two steps of this one
+            if got[1] is None:
+                got[1] = run_pipelined(fresh[1], table, state, its[1], 0.01, 1e-8, ahead="batch2_last_step", sync_each=False)
+
+        got[0] = run_pipelined(fresh[0], table, state, its[0], 0.01, 1e-8, ahead=False, sync_each=False, between=inner)
+    for k in range(2):
+        assert torch.equal(got[k][0], want[k][0]) and torch.equal(got[k][1], want[k][1])
+    for c in ctxs + fresh:
+        c.close()
+
+
+@pytest.mark.parametrize("ahead", [False, "index_last_step", "batch2"])
+def test_context_that_changes_its_stream_between_two_steps(ahead):
+    """Consecutive pipelined calls on two streams in turn, ordered by the caller with events and nothing else: the work
+    the context left on its side and index streams stays ordered before what follows on the new ones."""
+    rng = np.random.default_rng(10)
+    rows, dim = 30_000, 256
+    its = make_its(rng, rows, dim, 6, users=80, max_len=1800)            # 147 MB a call: two streams
+    table, state = rand_table(rng, rows, dim, "f32"), np.zeros(rows, np.float32)
+    ctx = fs.Context(max_ids=100_000, max_dim=dim)
+    want = run_pipelined(ctx, table, state, its, 0.01, 1e-8)
+    ctx.close()
+    ctx = fs.Context(max_ids=100_000, max_dim=dim)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    before = torch.cuda.current_stream()
+
+    def switch(t):
+        was = torch.cuda.current_stream()
+        now = streams[t % 2]
+        now.wait_stream(was)
+        torch.cuda.set_stream(now)
+
+    try:
+        got = run_pipelined(ctx, table, state, its, 0.01, 1e-8, ahead=ahead, sync_each=False, between=switch)
+    finally:
+        torch.cuda.synchronize()
+        torch.cuda.set_stream(before)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    ctx.close()
+
+
+def test_captured_step_beside_another_context():
+    """The self-contained step recorded into a graph by the caller, its index half on a side stream, while another context
+    enqueues on its own streams: neither sees the other, and every replay gives the eager step's bits."""
+    rng = np.random.default_rng(12)
+    rows, dim, n = 20_000, 32, 70_000
+    a, b = (zipf_ids(rng, n, rows, a=1.1) for _ in range(2))
+    grads = dev(rng.standard_normal((n, dim)).astype(np.float32))
+    start = rand_table(rng, rows, dim, "f32")
+
+    def step_on(ctx, stream=None):
+        table, state = dev(start), torch.zeros(rows, device="cuda")
+        lay0, lay1 = fs.fs_unique_ids(ctx, dev(a), rows), fs.alloc_layout(n, "cuda")
+        split, emb, nxt = fs.alloc_split(n, n, "cuda"), torch.zeros((n, dim), device="cuda"), dev(b)
+        args = fs.make_step_args(table, state, 0.01, 1e-8, lay0, grads, nxt, None, lay1, split, None, emb)
+        return args, (table, state, emb, lay1, split, lay0, nxt)
+
+    ctx, other, ref = (fs.Context(max_ids=80_000, max_dim=dim) for _ in range(3))
+    eager, out = step_on(ref)
+    captured, got = step_on(ctx)
+    beside, out2 = step_on(other)
+    torch.cuda.synchronize()
+    graph, stream, third = torch.cuda.CUDAGraph(), torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="relaxed"):
+        fs.fs_prioritized_step(ctx, captured, stream=stream)
+        fs.fs_step_forward(other, beside, stream=third)
+    for _ in range(3):
+        graph.replay()
+        fs.fs_prioritized_step(ref, eager)
+        torch.cuda.synchronize()
+        for x, y in zip(got[:3], out[:3]):
+            assert torch.equal(x, y)
+        for k in ("co_slot", "counts"):
+            m = int(out[4]["counts"][0].item()) if k == "co_slot" else 3
+            assert torch.equal(got[4][k][:m], out[4][k][:m])
+        u = int(out[3]["n_unique"].item())
+        assert torch.equal(got[3]["unique"][:u], out[3]["unique"][:u])
+    for c in (ctx, other, ref):
+        assert fs.fs_check_async(c) == fs.FS_OK, c.last_error()
+    assert torch.equal(out2[4]["counts"], out[4]["counts"])
+    for c in (ctx, other, ref):
+        c.close()

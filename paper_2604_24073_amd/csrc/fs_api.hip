@@ -159,7 +159,7 @@ void carve(fs_ctx *c, char *base, size_t *total) {
     c->part_head = cv.take<double>(chunks * (size_t)c->max_dim);
     c->part_last = cv.take<double>(chunks * (size_t)c->max_dim);
     c->chunk_desc = cv.take<int32_t>(chunks * 4);
-    const size_t fchunks = (size_t)ceil_div(c->max_ids, kFusedMinChunk) + 2;
+    const size_t fchunks = (size_t)fused_chunk_space(c->max_ids);
     for (int k = 0; k < 2; ++k) {
         c->fpart_head[k] = cv.take<double>(fchunks * (size_t)c->max_dim);
         c->fpart_last[k] = cv.take<double>(fchunks * (size_t)c->max_dim);
@@ -324,7 +324,7 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     carve(c, static_cast<char *>(c->slab), &total);
     bool ok = hipMemset(c->slab, 0, 4096) == hipSuccess;
     for (int k = 0; k < 2; ++k) {
-        const size_t bytes = ((size_t)ceil_div(c->max_ids, kFusedMinChunk) + 2) * sizeof(int);
+        const size_t bytes = (size_t)fused_chunk_space(c->max_ids) * sizeof(int);
         ok = ok && hipMemset(c->fcounters[k], 0, bytes) == hipSuccess;
         ok = ok && hipMemset(c->fcounters_sup[k], 0, bytes) == hipSuccess;
     }
@@ -401,7 +401,7 @@ int fs_check_async(fs_ctx *ctx, fs_stream stream) {
     if (flags[0] & kFlagInternal) {
         // a fused pass that met an inconsistent class order left cut segments half counted in: the arrival
         // counters must stand at zero again before the next pass (every stream is idle here)
-        const size_t bytes = ((size_t)ceil_div(ctx->max_ids, kFusedMinChunk) + 2) * sizeof(int);
+        const size_t bytes = (size_t)fused_chunk_space(ctx->max_ids) * sizeof(int);
         for (int k = 0; k < 2; ++k) {
             FS_HIP(ctx, hipMemset(ctx->fcounters[k], 0, bytes));
             FS_HIP(ctx, hipMemset(ctx->fcounters_sup[k], 0, bytes));

@@ -47,7 +47,6 @@ namespace fs {
 #define FS_SHORT_UNR 2                     // short path: rows one group of lanes takes per iteration
 #endif
 constexpr int kFusedSuper = 16;            // pieces of a cut segment that are added in one go (first level)
-constexpr int kFusedWaves = 4;             // wavefronts per workgroup (they never synchronise)
 
 // Adagrad on `nrows` parked rows of one wavefront.  Group g of the wavefront takes rows g, g+GPW, ...
 // stage: [row][LPR] fp32 sums (4 columns per lane), stage_row: table row, stage_slot: slot in U_t.
@@ -748,14 +747,6 @@ __global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const 
                                              job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
 }
 
-// Positions of a chunk (log2) for a batch of n occurrences.  A big batch fills the chip with chunks of 64, and every
-// chunk costs two dependent round trips at its cut segments (262 k occurrences: ten steps 1042 us with 64, 1052 with
-// 32, 1100 with 16); a small one is as long as the life of one wavefront, which short chunks shorten (three tables of
-// 14 k occurrences: 1050, 951, 891 us).  It depends on the batch alone: the order of the sums is part of the result.
-static int chunk_log2(int64_t n) {
-    return n >= 131072 ? 6 : (n >= 65536 ? 5 : 4);
-}
-
 template <int LPR> constexpr int fused_unr() {
     return (kWave / (kWave / LPR)) < FS_FUSED_UNR ? kWave / (kWave / LPR) : FS_FUSED_UNR;
 }
@@ -767,7 +758,7 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
     constexpr int SU = FS_SHORT_UNR;
     constexpr int UNR = fused_unr<LPR>();
     constexpr int PER = CLS < 2 ? 1 : 2;                      // passes of a table
-    const size_t cap_chunks = (size_t)ceil_div(ctx->max_ids, kFusedMinChunk) + 2;
+    const size_t cap_chunks = (size_t)fused_chunk_space(ctx->max_ids);
     const size_t cap_doubles = cap_chunks * (size_t)ctx->max_dim;
     int at = 0;
     while (at < m) {

@@ -2,6 +2,7 @@
 self-contained step does the same with its index half: iterations of both sizes in turn (so that every hand-over between
 the two forms happens) give the bits of the building blocks issued one after another.  Also: contexts driven from one
 stream share their side and index streams; a context that is called on a second stream, or captured, has its own."""
+import ctypes
 import threading
 
 import numpy as np
@@ -9,6 +10,7 @@ import pytest
 import torch
 
 import paper_2604_24073_amd as fs
+from paper_2604_24073_amd.schedule import new_hip_stream
 from helpers import dev, table_to_host
 from test_gpu_parity import rand_table, run_steps_gpu, zipf_ids
 from test_gpu_pipeline import make_its, run_pipelined
@@ -169,3 +171,48 @@ def test_captured_step_beside_another_context():
     assert torch.equal(out2[4]["counts"], out[4]["counts"])
     for c in (ctx, other, ref):
         c.close()
+
+
+def kernels_captured(call):
+    """Number of kernel nodes of what `call(stream)` enqueues (recorded, not run)."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream = new_hip_stream()
+    raw, graph = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(raw, ctypes.c_int(2)) == 0                    # relaxed
+    call(stream)
+    assert hip.hipStreamEndCapture(raw, ctypes.byref(graph)) == 0
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    kernels = 0
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        kernels += kind.value == 0                                                 # hipGraphNodeTypeKernel
+    assert hip.hipGraphDestroy(graph) == 0
+    return kernels
+
+
+@pytest.mark.parametrize("n", [1, 2000, 65_535, 65_536, 131_071, 131_072, 600_000])
+def test_tables_of_one_width_share_their_launches(n):
+    """Eight equal tables as large as the context allows, on one stream: both passes of four tables a launch (the context
+    has room for the pieces of all of them), and one lookup for the eight."""
+    rows, dim = 500, 4
+    ctx = fs.Context(max_ids=n, max_dim=dim)
+    tables, keep = [], []
+    for k in range(8):
+        ids = (torch.arange(n, device="cuda") * (k + 1)) % rows
+        nxt = torch.arange(min(n, 64), device="cuda")
+        lay, lay1 = fs.fs_unique_ids(ctx, ids, rows), fs.alloc_layout(nxt.numel(), "cuda")
+        split = fs.alloc_split(n, nxt.numel(), "cuda")
+        table, state = torch.zeros((rows, dim), device="cuda"), torch.zeros(rows, device="cuda")
+        grads, emb = torch.ones((n, dim), device="cuda"), torch.empty((nxt.numel(), dim), device="cuda")
+        tables.append(fs.make_step_args(table, state, 0.01, 1e-8, lay, grads, nxt, None, lay1, split, None, emb))
+        keep.append((ids, nxt, lay, lay1, split, table, state, grads, emb))
+        fs.fs_step_forward(ctx, tables[-1])
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    record = fs.step_args_array(tables)
+    passes = kernels_captured(lambda s: fs.fs_prioritized_step_pipelined_multi(ctx, record, None, stream=s)) - 1
+    assert passes == 2
+    ctx.close()

@@ -1372,9 +1372,10 @@ int fs_prioritized_step_two_part_multi(fs_ctx *ctx, const fs_step_args *cur, con
 // Bytes of gradients and looked-up rows of a call up to which the pipelined step stays on one stream: both passes of
 // every table in one launch, the lookups behind them, no wait between streams (10-12 us of host time each, with a
 // second thread to pay them) and one launch less per row width.  What it gives up is the deferred pass running beside
-// the lookup.  Ten steps of one 2M x 128 table, two streams against one: 0.5 k IDs a batch 285 / 227 us, 8 k 319 / 261,
-// 65 k (67 MB) 472 / 438, 130 k (133 MB) 600 / 596, 262 k (of 4M rows) 1041 / 1056; eight tables of 2 GB 5616 / 6039.
-constexpr int64_t kOneStreamBytes = 128 << 20;
+// the lookup.  Ten steps of one 2M x 128 table, two streams against one: 32 k IDs a batch (31 MB) 455 / 415 us, 65 k
+// (64 MB) 519 / 482, 98 k (96 MB) 570 / 568, 110 k (107 MB) 611 / 621, 120 k (117 MB) 644 / 661, 130 k (127 MB) 680 / 702,
+// 262 k (of 4M rows) 1041 / 1056; two tables of 49 k (96 MB) 785 / 759; eight tables of 2 GB 5616 / 6039.
+constexpr int64_t kOneStreamBytes = 100 << 20;
 
 static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_args *next, int count, fs_stream stream,
                           bool two_part) {

@@ -43,11 +43,14 @@ constexpr int kScanTile = kScanThreads * kScanIpt;
 constexpr int kClassOrderTiles = 60 * 1024 / (2 * (int)sizeof(int));
 constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
-// Most IDs of a batch whose index half one workgroup does (fs_small.hip).  Ahead of time, where nobody waits for it and a
-// launch costs whatever runs beside it: what fits the LDS of a compute unit.  On the caller's stream: up to where the
-// chain of launches over many workgroups is the faster one (a whole step of 7.8 k IDs: 60 us against about 80, of
-// 15.6 k: 103 against about 88).
+// IDs of a batch whose index half fits the LDS of one workgroup (fs_small.hip), and the most it takes.  On the caller's
+// stream: up to where the chain of launches over many workgroups is the faster one (a whole step of 8192 IDs: 67 us
+// against 86).  Ahead of time a launch costs whatever runs beside it and the workgroup has the iterations ahead to
+// finish, but it must keep up with them: ten steps of three tables, an iteration a launch, one workgroup against the
+// chain: 12000 IDs 681 / 674 us, 14000 747 / 700, 16000 784 / 694; one table, four iterations a launch: 12000 281 / 300,
+// 14000 299 / 311, 16000 303 / 320.
 constexpr int64_t kSmallIds = 16384;
+constexpr int64_t kSmallIdsAhead = 12288;
 constexpr int64_t kSmallIdsInline = 8192;
 
 // segment reduce: sorted positions owned by one wavefront (one 64-bit tail mask, one permutation

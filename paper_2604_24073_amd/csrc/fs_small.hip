@@ -1,4 +1,4 @@
-// The index half of a small batch on ONE workgroup: dedup, collision split and class order of at most kSmallIds IDs.
+// The index half of a small batch on ONE workgroup: dedup, collision split and class order of up to kSmallIds IDs.
 //
 // The kernels of fs_unique.hip and fs_split.hip are a chain of up to eleven launches; on a batch of a few thousand IDs
 // each of them is a handful of workgroups and takes 2.5 to 9 us whatever it does, so the chain takes 55 to 75 us and
@@ -479,7 +479,7 @@ static int key_bits_of(int64_t num_rows) {
 }
 
 // scratch set 0 belongs to the caller's stream and the side stream, the others to the index streams
-static int64_t small_limit(int set0) { return set0 == 0 ? kSmallIdsInline : kSmallIds; }
+static int64_t small_limit(int set0) { return set0 == 0 ? kSmallIdsInline : kSmallIdsAhead; }
 
 bool small_unique_fits(int count, const fs_unique_job *jobs, int set0) {
     const int64_t most = small_limit(set0);

@@ -832,7 +832,7 @@ int enqueue_index_work_batch(fs_ctx *ctx, int count, const fs_step_args *a, cons
         fused = fused && t1 && !(ahead && ahead[k]) && !(layout_in && layout_in[k]);
         for (int q = 0; q < count; ++q) fused = fused && !(t && a[q].u_t1 == x.u_t);
     }
-    if (fused && small_unique_fits(count, uj, set0) && small_split_fits(count, sj, cj, set0)) {
+    if (fused && small_unique_fits(count, uj, set0) && small_split_fits(count, sj, cj, set0, true)) {
         rc = launch_small_index(ctx, count, uj, sj, cj, s);
         if (dedup_out)
             for (int k = 0; k < count; ++k)

@@ -52,6 +52,11 @@ constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 constexpr int64_t kSmallIds = 16384;
 constexpr int64_t kSmallIdsAhead = 12288;
 constexpr int64_t kSmallIdsInline = 8192;
+// Without the dedup in front the chain is two launches (the split alone) or three: IDs up to which the one workgroup
+// does those on the caller's stream.  Split alone, one workgroup against two launches: 4096 IDs 11.4 / 11.6 us, 5000
+// 13.8 / 11.4, 8192 18.9 / 11.8; with the class order against three: 6144 22.5 / 23.6, 7000 24.7 / 24.4, 8192 28.4 / 24.1.
+constexpr int64_t kSmallSplitInline = 4096;
+constexpr int64_t kSmallClassesInline = 6144;
 
 // segment reduce: sorted positions owned by one wavefront (one 64-bit tail mask, one permutation
 // entry per lane).  Short chunks = many wavefronts with short dependent-load chains.
@@ -338,7 +343,7 @@ int launch_split_class_batch(fs_ctx *, int count, const fs_split_job *jobs, cons
 // one workgroup per batch: dedups (u), splits (sp) with class orders (cls, optional), or a dedup and then a split each,
 // whose U_t no dedup of the same launch may produce; the jobs must fit
 bool small_unique_fits(int count, const fs_unique_job *jobs, int set0);
-bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0);
+bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0, bool with_dedup = false);
 int launch_small_index(fs_ctx *, int count, const fs_unique_job *u, const fs_split_job *sp, const fs_class_job *cls,
                        hipStream_t s);
 int launch_split(fs_ctx *, const int64_t *u_t, const int64_t *n_t_dev, const int64_t *u_t1,

@@ -488,8 +488,9 @@ bool small_unique_fits(int count, const fs_unique_job *jobs, int set0) {
     return count >= 1 && count <= kMaxBatch;
 }
 
-bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0) {
-    const int64_t most = small_limit(set0);
+bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0, bool with_dedup) {
+    int64_t most = small_limit(set0);
+    if (set0 == 0 && !with_dedup) most = cls ? kSmallClassesInline : kSmallSplitInline;
     for (int k = 0; k < count; ++k)
         if (jobs[k].cap_t > most || jobs[k].cap_t1 > most || (cls && cls[k].n > most)) return false;
     return count >= 1 && count <= kMaxBatch;

@@ -85,14 +85,35 @@ def test_every_row_is_long(ctx, n):
     check_index_half(ctx, rng.permutation(np.repeat(np.arange(rows), 9)), np.arange(0, rows, 2), rows, True)
 
 
+@pytest.mark.parametrize("n0,n1", [(4096, 4096), (4097, 4096), (4096, 4097), (6144, 6144), (6145, 6144), (6144, 6145)])
+def test_split_without_the_dedup_around_the_sizes_where_it_changes_over(ctx, n0, n1):
+    rng = np.random.default_rng(n0 + n1)
+    rows = 3000
+    ids, nxt = zipf_ids(rng, n0, rows, a=1.1), zipf_ids(rng, n1, rows, a=1.1)
+    lay0, lay1 = fs.fs_unique_ids(ctx, dev(ids), rows), fs.fs_unique_ids(ctx, dev(nxt), rows)
+    want0 = O.unique_ids(ids, rows)
+    sp = O.collision_split(want0["unique"], O.unique_ids(nxt, rows)["unique"])
+    cperm, cslot, _, class_pos = class_order_from_oracle(want0, sp)
+    alone = fs.fs_collision_split(ctx, lay0["unique"], lay0["n_unique"], lay1["unique"], lay1["n_unique"], n0, n1)
+    split = fs.fs_collision_split_classes(ctx, lay0, lay1["unique"], lay1["n_unique"], n1)
+    assert fs.fs_check_async(ctx) == fs.FS_OK
+    for got in (alone, split):
+        assert got["counts"].cpu().numpy().tolist() == [len(sp[k]) for k in ("co", "ex", "ex_next")]
+        for k in ("co", "co_slot", "ex", "ex_slot", "ex_next", "ex_next_slot"):
+            assert np.array_equal(got[k].cpu().numpy()[:len(sp[k])], sp[k]), k
+    assert split["class_pos"].cpu().numpy().tolist() == [int(x) for x in class_pos]
+    assert np.array_equal(split["cperm"].cpu().numpy()[:class_pos[1]], cperm)
+    assert np.array_equal(split["cslot"].cpu().numpy()[:class_pos[1]], cslot)
+
+
 GUARD = 1 << 17                 # more than the packed sums of any layout can reach
 
 
-@pytest.mark.parametrize("n", [1024, 8192, 9000])
+@pytest.mark.parametrize("n", [1024, 6144, 9000])
 @pytest.mark.parametrize("what", ["overlapping rows", "short of the batch", "behind the start", "stale count", "no rows"])
 def test_layout_that_does_not_fit_its_batch_writes_nothing_out_of_range(n, what):
     """Segment boundaries or a count left over from another batch: reported, and nothing is written past the class
-    order, whose places the class passes then do not trust (one workgroup up to 8192 IDs, the chain of launches above)."""
+    order, whose places the class passes then do not trust (one workgroup up to 6144 IDs, the chain of launches above)."""
     ctx = fs.Context(max_ids=16384, max_dim=4)
     u = 200
     seg = np.minimum(np.arange(n + 1) * 9, n).astype(np.int32)
@@ -118,11 +139,11 @@ def test_layout_that_does_not_fit_its_batch_writes_nothing_out_of_range(n, what)
         split[k] = torch.full((size[k] + GUARD,), -7, dtype=split[k].dtype, device="cuda")
     fs.fs_collision_split_classes(ctx, lay, u1, dev(np.array([u1.numel()], dtype=np.int64)), n, out=split)
     rc = fs.fs_check_async(ctx)
-    if n <= 8192 or what != "stale count":                  # the chain sees no position of a row without occurrences
+    if n <= 6144 or what != "stale count":                  # the chain sees no position of a row without occurrences
         assert rc == fs.FS_ERANGE and "internal" in ctx.last_error()
     for k in guarded:
         assert bool((split[k][size[k]:] == -7).all()), k
     first, end = split["class_pos"].cpu().tolist()
-    if n <= 8192:
+    if n <= 6144:
         assert (first, end) == (0, 0)
     ctx.close()

@@ -128,10 +128,12 @@ __global__ void gs_empty_kernel(int64_t *counts_dev) {
 }
 
 // Bound: HBM, every gradient row read and written once.  The parts are what the next kernels read (the class passes,
-// or whatever packs them for an exchange), so they are stored with plain stores and stay in the caches as far as they
-// fit; the gradients are not needed again and are read around them.  Plain against non-temporal stores, the whole start
-// of Backward on 130 k rows of 1 KB: 113.5 -> 111.1 us.
-template <int LPR, int UNR>
+// or whatever packs them for an exchange); the gradients are not needed again and are read around them.  KEEP: plain
+// stores, so that the parts stay in the memory-side cache, up to what that holds.  Non-temporal / plain stores, the whole
+// start of Backward on rows of 1 KB: 32 MB 58.1 / 55.3 us, 64 MB 85.7 / 79.1, 126 MB 134.7 / 125.6, 244 MB 219 / 216,
+// 292 MB 251 / 252, 585 MB 474 / 485; equal below 24 MB.
+constexpr int64_t kKeepPartsBytes = 256 << 20;
+template <int LPR, int UNR, bool KEEP>
 __global__ __launch_bounds__(256) void gs_copy_kernel(const u32x4 *__restrict__ grads, int n, int gvec,
                                                       const int32_t *__restrict__ part_pos, u32x4 *__restrict__ g_co,
                                                       u32x4 *__restrict__ g_ex) {
@@ -159,7 +161,9 @@ __global__ __launch_bounds__(256) void gs_copy_kernel(const u32x4 *__restrict__ 
             if (live[u]) {
                 const bool co = pos[u] >= 0;
                 const int64_t r = co ? pos[u] : -1 - pos[u];
-                ((co ? g_co : g_ex) + r * gvec)[lig] = v[u];
+                u32x4 *to = (co ? g_co : g_ex) + r * gvec + lig;
+                if (KEEP) *to = v[u];
+                else __builtin_nontemporal_store(v[u], to);
             }
     }
 }
@@ -181,12 +185,14 @@ int launch_split_grads(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim, 
     hipLaunchKernelGGL(gs_number_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, inverse, ws.flag_t, (int)n,
                        (int)cap_u, ws.cnt, tiles, co_index, ex_index, part_pos, counts_dev);
     const int gvec = dim / 4;
+    const bool keep = n * dim * 4 <= kKeepPartsBytes;
 #define FS_CASE(L)                                                                                                 \
     case L: {                                                                                                      \
         constexpr int UNR = 4;                                                                                     \
         const int64_t blocks = ceil_div(n, (int64_t)(kWave / L) * UNR * 4);                                        \
-        hipLaunchKernelGGL((gs_copy_kernel<L, UNR>), dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), \
-                           0, s, (const u32x4 *)grads, (int)n, gvec, part_pos, (u32x4 *)g_co, (u32x4 *)g_ex);      \
+        auto *copy = keep ? &gs_copy_kernel<L, UNR, true> : &gs_copy_kernel<L, UNR, false>;                        \
+        hipLaunchKernelGGL(copy, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s,               \
+                           (const u32x4 *)grads, (int)n, gvec, part_pos, (u32x4 *)g_co, (u32x4 *)g_ex);            \
         break;                                                                                                     \
     }
     switch (lanes_per_row(gvec)) {

@@ -124,3 +124,20 @@ def test_fused_passes_read_the_packed_parts(ctx, dim, dtype):
     assert table_to_host(t_b).tobytes() == table_to_host(t_a).tobytes()
     assert s_b.cpu().numpy().tobytes() == s_a.cpu().numpy().tobytes()
     assert table_to_host(t_a).tobytes() != table.tobytes()
+
+
+@pytest.mark.parametrize("n", [262_144, 262_145])             # rows of 1 KB: 256 MB, the most that is stored to stay cached
+def test_split_grads_around_the_size_from_which_the_parts_leave_the_caches(n):
+    ctx = fs.Context(max_ids=n, max_dim=256)
+    rng = np.random.default_rng(n)
+    rows = 50_000
+    ids_t, ids_t1 = zipf_ids(rng, n, rows, a=1.1), zipf_ids(rng, 30_000, rows, a=1.1)
+    lay, sp = layout_and_split(ctx, ids_t, ids_t1, rows)
+    grads = torch.randn((n, 256), device="cuda")
+    got = fs.fs_split_grads(ctx, grads, lay, sp)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    co = torch.from_numpy(np.flatnonzero(np.isin(ids_t, ids_t1))).cuda()
+    ex = torch.from_numpy(np.flatnonzero(~np.isin(ids_t, ids_t1))).cuda()
+    assert got["counts"].cpu().tolist() == [co.numel(), ex.numel()] and co.numel() > 0 and ex.numel() > 0
+    assert torch.equal(got["g_co"][:co.numel()], grads[co]) and torch.equal(got["g_ex"][:ex.numel()], grads[ex])
+    ctx.close()

@@ -10,7 +10,7 @@
 // workgroup lays out the output offsets, then the copy; beyond, lengths summed per tile of samples, the
 // output offsets by a scan with tile prefixes, and the copy.  The copy is driven
 // by the OUTPUT (every lane writes consecutive pieces of the output, so a 16K-item sample costs per
-// item what a short one costs): a workgroup takes 2048 or 8192 consecutive output pieces, finds the samples
+// item what a short one costs): a workgroup takes 2048 to 8192 consecutive output pieces, finds the samples
 // they belong to with two 64-ary searches, stages their boundaries in LDS and lets every piece
 // binary-search LDS.
 //
@@ -302,18 +302,21 @@ __device__ __forceinline__ int64_t wave_upper_bound(const int64_t *__restrict__ 
 // with 128 KB a workgroup, 100 to 160 with 32 or 64 KB).  Where samples are short the walk over their boundaries
 // counts, and more, shorter-lived wavefronts hide it: 16 KB of 8-byte pieces (eight in flight per lane) against 32 KB
 // (sixteen), a whole balancer pass: samples of 1 to 200 IDs 198 -> 90 us, of 16 to 4096 IDs 108 -> 107.
-template <typename V> constexpr int copy_tile() { return sizeof(V) == 16 ? 8192 : 2048; }
+// 4-byte pieces: a large output pays for the searches with too few bytes a tile, a small one fills the chip with short
+// tiles only.  Tiles of 2048 (eight in flight) / 4096 (sixteen), one permute: 500 k pieces 22.3 / 31 us, 1 M 21.7 / 27.6,
+// 8 M 38.5 / 38.3, 9 M 42.0 / 42.1, 10 M 48.5 / 43.0, 12.5 M 51.3 / 45.1, 32 M 99.8 / 87.3.
+constexpr int kCopyTile16 = 8192, kCopyTile8 = 2048, kCopyTile4 = 2048, kCopyTile4Large = 4096;
+constexpr int64_t kCopyLargeFrom = 9 << 20;                     // 4-byte pieces of the output
 constexpr int kCopyWindow = 2048 + 2;                           // sample boundaries staged in LDS
 
 // V: the piece, the widest of 4, 8, 16 bytes that divides the element; ppe pieces per element.
 // Inside a tile everything is counted from the tile's first element in 32 bits (a 64-bit division per
 // piece would cost more than the copy).
-template <typename V, int PIECES>
+template <typename V, int kCopyTile, int PIECES>
 __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__restrict__ values, const jagged_in in,
                                                                     const int32_t *__restrict__ sample_of,
                                                                     int64_t n_out, const int64_t *__restrict__ out_offsets,
                                                                     int64_t cap_out, int ppe, V *__restrict__ out) {
-    constexpr int kCopyTile = copy_tile<V>();
     __shared__ int32_t w_rel[kCopyWindow];      // out_offsets[ka + j] minus the tile's first element (at least -1)
     __shared__ int64_t w_delta[kCopyWindow];    // first input element of sample ka + j minus its first output element
     __shared__ int64_t win[2];
@@ -425,17 +428,22 @@ static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values
     if (cap_out > 0 && n_out > 0) {
         const int piece = elem_bytes % 16 == 0 ? 16 : (elem_bytes % 8 == 0 ? 8 : 4);
         const int ppe = elem_bytes / piece;
-        const int64_t blocks = ceil_div(cap_out * ppe, piece == 16 ? copy_tile<u32x4>() : copy_tile<uint64_t>());
+        const bool large = piece == 4 && cap_out * ppe >= kCopyLargeFrom;
+        const int tile = piece == 16 ? kCopyTile16 : (piece == 8 ? kCopyTile8 : (large ? kCopyTile4Large : kCopyTile4));
+        const int64_t blocks = ceil_div(cap_out * ppe, tile);
         if (blocks > 0x7fffffffll) return set_err(ctx, FS_EINVAL, "indexed permute: output too large for one launch");
         const dim3 grid((unsigned)blocks);
         if (piece == 16)
-            hipLaunchKernelGGL((permute_copy_kernel<u32x4, 8>), grid, dim3(kScanThreads), 0, s, (const u32x4 *)values,
+            hipLaunchKernelGGL((permute_copy_kernel<u32x4, kCopyTile16, 8>), grid, dim3(kScanThreads), 0, s, (const u32x4 *)values,
                                in, sample_of, n_out, out_offsets, cap_out, ppe, (u32x4 *)out_values);
         else if (piece == 8)
-            hipLaunchKernelGGL((permute_copy_kernel<uint64_t, 8>), grid, dim3(kScanThreads), 0, s, (const uint64_t *)values,
+            hipLaunchKernelGGL((permute_copy_kernel<uint64_t, kCopyTile8, 8>), grid, dim3(kScanThreads), 0, s, (const uint64_t *)values,
                                in, sample_of, n_out, out_offsets, cap_out, ppe, (uint64_t *)out_values);
+        else if (large)
+            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, kCopyTile4Large, 16>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
+                               in, sample_of, n_out, out_offsets, cap_out, ppe, (uint32_t *)out_values);
         else
-            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, 8>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
+            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, kCopyTile4, 8>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
                                in, sample_of, n_out, out_offsets, cap_out, ppe, (uint32_t *)out_values);
     }
     FS_LAUNCH_CHECK(ctx, "indexed permute kernels");

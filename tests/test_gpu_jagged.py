@@ -199,6 +199,26 @@ def test_shuffles_around_the_most_samples_one_workgroup_lays_out(segments, n_ran
     ctx.close()
 
 
+@pytest.mark.parametrize("pieces,width,longest", [(9 * 2**20 - 1, 1, 400), (9 * 2**20, 1, 400), (9 * 2**20 + 1, 1, 2),
+                                                  (9 * 2**20 + 3, 3, 100)])
+def test_four_byte_pieces_around_the_size_where_the_tile_changes(pieces, width, longest):
+    # samples of up to `longest` elements (up to 2: a tile touches more of them than it stages), the last one cut to fit
+    rng = np.random.default_rng(pieces + longest)
+    total = pieces // width
+    lens = rng.integers(0, longest + 1, size=2 * total // longest + 4)
+    offsets = np.minimum(np.concatenate([[0], np.cumsum(lens)]), total).astype(np.int64)
+    offsets[-1] = total
+    B = offsets.size - 1
+    values = rng.integers(0, 2**31 - 1, size=(total, width)).astype(np.int32)
+    sel = rng.permutation(B).astype(np.int32)
+    ctx = fs.Context(max_ids=B, max_dim=8)
+    out, out_off = fs.fs_jagged_indexed_permute(ctx, dev(values), dev(offsets), dev(sel), total)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    want, want_off = O.jagged_indexed_permute(values, offsets, sel)
+    assert np.array_equal(out_off.cpu().numpy(), want_off) and np.array_equal(out.cpu().numpy(), want)
+    ctx.close()
+
+
 def test_ranged_dispatch_reports_ranges_that_do_not_cover_the_samples():
     rng = np.random.default_rng(8)
     values, offsets = keyed(rng, 2, 50, np.int64, 0)

@@ -1301,8 +1301,11 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     return FS_OK;
 }
 
-// IDs of both batches from which the self-contained step takes its index half to the side stream
-constexpr int64_t kStepSideIds = 131072;
+// IDs of both batches from which the self-contained step takes its index half to the side stream: two cross-stream waits
+// of 10-12 us of host time each against a chain of launches behind the row work.  Behind / beside it on a 4M x 128 table,
+// IDs of one batch: 8 k 67 / 70 us, 16 k 93 / 103, 32 k 101 / 110, 64 k 114 / 118, 80 k 122 / 121, 96 k 127 / 127, 128 k
+// 138 / 136, 256 k 193 / 177.
+constexpr int64_t kStepSideIds = 163840;
 
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     if (!ctx) return FS_EINVAL;
@@ -1324,9 +1327,7 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     begin_step_timing(ctx);
     // Nothing outside this call can start before its last update, so the row work does not wait for the split: every
     // row of U_t is updated straight from the layout of batch t, then the lookahead rows are read, in batch order;
-    // the index half is independent of both.  On the side stream it runs beside them, which costs two cross-stream
-    // waits of 10-12 us of host time each: worth it where the row work is long (4M x 128, 262 k IDs a batch: 182
-    // against 191 us), while a tiny call is bound by its host path (1 k IDs: 81 against 52 us).
+    // the index half is independent of both.
     if (side) FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
     if (have_t) {
         hipEvent_t *tu = timing_pair(ctx, FS_TIME_UPDATE_CO);

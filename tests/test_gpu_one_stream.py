@@ -134,7 +134,7 @@ def test_captured_step_beside_another_context():
     """The self-contained step recorded into a graph by the caller, its index half on a side stream, while another context
     enqueues on its own streams: neither sees the other, and every replay gives the eager step's bits."""
     rng = np.random.default_rng(12)
-    rows, dim, n = 20_000, 32, 70_000
+    rows, dim, n = 20_000, 32, 90_000
     a, b = (zipf_ids(rng, n, rows, a=1.1) for _ in range(2))
     grads = dev(rng.standard_normal((n, dim)).astype(np.float32))
     start = rand_table(rng, rows, dim, "f32")
@@ -146,7 +146,7 @@ def test_captured_step_beside_another_context():
         args = fs.make_step_args(table, state, 0.01, 1e-8, lay0, grads, nxt, None, lay1, split, None, emb)
         return args, (table, state, emb, lay1, split, lay0, nxt)
 
-    ctx, other, ref = (fs.Context(max_ids=80_000, max_dim=dim) for _ in range(3))
+    ctx, other, ref = (fs.Context(max_ids=100_000, max_dim=dim) for _ in range(3))
     eager, out = step_on(ref)
     captured, got = step_on(ctx)
     beside, out2 = step_on(other)

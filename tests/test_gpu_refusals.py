@@ -45,10 +45,10 @@ def raises(code, call, *args):
     assert e.value.code == code
 
 
-@pytest.mark.parametrize("n", [300, 70_000])                # index half behind the row work; on the side stream
+@pytest.mark.parametrize("n", [300, 90_000])                # index half behind the row work; on the side stream
 @pytest.mark.parametrize("call", ["step", "forward", "ahead", "pipelined", "pipelined multi"])
 def test_ascending_ids_of_a_batch_deduped_ahead_are_refused_before_anything_runs(n, call):
-    ctx = fs.Context(max_ids=80_000, max_dim=DIM)
+    ctx = fs.Context(max_ids=100_000, max_dim=DIM)
     torch.manual_seed(1)
     table, state = torch.randn((ROWS, DIM), device="cuda"), torch.rand(ROWS, device="cuda")
     before = (table.clone(), state.clone())
@@ -129,11 +129,11 @@ def leave_a_host_error():
     assert ctypes.CDLL("libamdhip64.so").hipSetDevice(ctypes.c_int(9999)) != 0
 
 
-@pytest.mark.parametrize("n", [300, 70_000])
+@pytest.mark.parametrize("n", [300, 90_000])
 def test_failed_steps_keep_what_was_done_ahead(n):
     """A step whose row work does not launch gives none of the ahead-of-time entries away: many times more failures than
     there are entries, and the last dedup is still found."""
-    ctx = fs.Context(max_ids=80_000, max_dim=DIM)
+    ctx = fs.Context(max_ids=100_000, max_dim=DIM)
     table, state = torch.zeros((ROWS, DIM), device="cuda"), torch.zeros(ROWS, device="cuda")
     a, b, _ = batches(n)
     step = Step(ctx, table, state, a, b, 1, sorted_ids=False)

@@ -358,7 +358,8 @@ typedef struct fs_step_args {
     /* output (OPTIONAL, may be NULL): [n_t1] the IDs of the lookahead batch in ascending order, every occurrence
      * listed (sorted_ids_t1[p] is the row of the occurrence perm_t1[p]); written with the layout of t+1.  Given,
      * the lookup of the lookahead batch walks the batch row by row instead of occurrence by occurrence: all
-     * occurrences of a row are neighbours, so a row is fetched once however far apart its occurrences lie */
+     * occurrences of a row are neighbours, so a row is fetched once however far apart its occurrences lie (the pipelined
+     * calls; fs_prioritized_step looks the batch up before its layout stands and goes by occurrence) */
     int64_t *sorted_ids_t1;
 } fs_step_args;
 
@@ -370,7 +371,10 @@ typedef struct fs_step_args {
  *   index half    : fs_unique_ids(values_t1) -> fs_collision_split_classes(U_t, U_t1), which neither of the two
  *                   waits for: on side stream A beside them (large batches; `stream` finally waits for A) or
  *                   behind them on `stream`
- * The step is complete when `stream` is.  Results are identical to running the five operations one after another. */
+ * The step is complete when `stream` is.  Results are those of the five operations one after another, with the fp64 sums
+ * of rows that occur more than FS_SHORT_SEGMENT times added in an order of its own: fixed by the layout of the batch, so
+ * the same bits on every run, but another order than that of fs_segment_reduce_grads or fs_reduce_update_class, so that a
+ * sum may differ from theirs by the error of fp64 addition before its one rounding to fp32. */
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *args, fs_stream stream);
 
 /* The index half of an iteration alone - what Forward of Algorithm 2 does with the prefetched

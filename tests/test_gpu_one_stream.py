@@ -17,14 +17,22 @@ from test_gpu_pipeline import make_its, run_pipelined
 
 pytestmark = pytest.mark.gpu
 
-BIG, SMALL = 1800, 60           # longest sequence of 80 users: about 72 k IDs x 256 columns = 147 MB both ways, and 5 MB
+# longest sequence of 80 users: about 96 k IDs x 256 columns, 196 MB a call in fp32 and 147 MB with bf16 rows; and 5 MB
+BIG, SMALL = 2400, 60
+ONE_STREAM = 100 << 20          # most bytes of gradients and looked-up rows of a call on one stream
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_large_and_small_iterations_in_turn(dtype):
     rng = np.random.default_rng(7)
     rows, dim = 40_000, 256
-    its = [make_its(rng, rows, dim, 1, users=80, max_len=m)[0] for m in (BIG, BIG, SMALL, BIG, BIG, SMALL, SMALL)]
+    sizes = (BIG, BIG, BIG, SMALL, SMALL, BIG, BIG, BIG, SMALL, SMALL)
+    its = [make_its(rng, rows, dim, 1, users=80, max_len=m)[0] for m in sizes]
+    # with the index halves done ahead the bytes of a call decide: two on two streams in a row, so that the second one
+    # finds exclusive rows fetched, and both ways between the forms (a small batch beside a large one: either)
+    w = 4 if dtype == "f32" else 2
+    two = [a.grads.nbytes + len(b.values) * dim * w > ONE_STREAM for a, b in zip(its, its[1:])]
+    assert two[0] and two[1] and two[5] and two[6] and not two[3] and not two[8]
     table, state = rand_table(rng, rows, dim, dtype), np.zeros(rows, np.float32)
     ctx = fs.Context(max_ids=200_000, max_dim=dim)
     want_t, want_s, want = run_steps_gpu(ctx, table, state, its, 0.01, 1e-8, mode="fused_calls")
@@ -32,7 +40,8 @@ def test_large_and_small_iterations_in_turn(dtype):
     got_t, got_s, got = run_steps_gpu(ctx, table, state, its, 0.01, 1e-8, mode="step")
     assert torch.equal(got_t.view(view), want_t.view(view)) and torch.equal(got_s, want_s)
     for ahead, sync_each, two_part in (("batch2_last_step", False, False), ("index", True, False), (False, False, False),
-                                       ("index", False, True), (False, True, True)):
+                                       ("index", False, True), (False, True, True), ("batch2_last_step", False, True),
+                                       ("batch2", True, True)):
         got_t, got_s, got = run_pipelined(ctx, table, state, its, 0.01, 1e-8, ahead=ahead, sync_each=sync_each, two_part=two_part)
         what = f"ahead={ahead} sync_each={sync_each} two_part={two_part}"
         assert torch.equal(got_t.view(view), want_t.view(view)) and torch.equal(got_s, want_s), what

@@ -1,0 +1,109 @@
+"""The two-stream form of the pipelined step, on batches large enough that every call of a run takes it (more than 100 MB
+of gradients and looked-up rows a call): deferred pass, index half and the lookup's exclusive part on side stream A beside
+the caller's stream, with and without the enqueueing threads, with and without waits between the calls.  Everything bit
+for bit as the building blocks issued one after another."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_24073_amd as fs
+from helpers import dev, table_to_dev, table_to_host
+from test_gpu_parity import rand_table, run_steps_gpu, zipf_ids
+from test_gpu_pipeline import make_its, run_pipelined
+
+pytestmark = pytest.mark.gpu
+
+ROWS, DIM, LIMIT = 40_000, 256, 100 << 20
+
+
+def call_bytes(its, dtype):
+    """Bytes of gradients and looked-up rows of every call but the last (which looks nothing up)."""
+    w = 4 if dtype == "f32" else 2
+    return [a.grads.nbytes + len(b.values) * DIM * w for a, b in zip(its, its[1:])]
+
+
+@pytest.fixture(scope="module", params=["f32", "bf16"])
+def run(request):
+    dtype = request.param
+    rng = np.random.default_rng(77)
+    its = make_its(rng, ROWS, DIM, 6, users=80, max_len=2400)
+    assert min(call_bytes(its, dtype)) > LIMIT
+    table, state = rand_table(rng, ROWS, DIM, dtype), np.zeros(ROWS, np.float32)
+    ctx = fs.Context(max_ids=150_000, max_dim=DIM)
+    want = run_steps_gpu(ctx, table, state, its, 0.01, 1e-8, mode="fused_calls")
+    yield ctx, dtype, its, table, state, want
+    ctx.close()
+
+
+def check(run, ahead, sync_each, threaded, **kw):
+    ctx, dtype, its, table, state, (want_t, want_s, want) = run
+    view = torch.int16 if dtype == "bf16" else torch.int32
+    ctx.lib.fs_ctx_set_threaded_enqueue(ctx.handle, 1 if threaded else 0)
+    fs.fs_ctx_host_times(ctx, reset=True)
+    got_t, got_s, got = run_pipelined(ctx, table, state, its, 0.01, 1e-8, ahead=ahead, sync_each=sync_each, **kw)
+    if threaded:
+        assert fs.fs_ctx_host_times(ctx)[5] > 0.0               # the side-stream thread had something to enqueue
+    ctx.lib.fs_ctx_set_threaded_enqueue(ctx.handle, 1)
+    assert torch.equal(got_t.view(view), want_t.view(view)) and torch.equal(got_s, want_s)
+    for a, b in zip(got, want[1:]):
+        assert a["reduced"].tobytes() == b["reduced"].tobytes() and a["counts"].tolist() == b["counts"].tolist()
+        if "emb_next" in a:
+            assert a["emb_next"].tobytes() == b["emb_next"].tobytes()
+
+
+@pytest.mark.parametrize("ahead,sync_each,threaded", [
+    (False, False, True), (False, True, False), (False, False, False), (True, False, True), (True, False, False),
+    ("last_step", False, True), ("index", False, True), ("index", True, False), ("index_last_step", False, False),
+    ("batch2", False, True), ("batch3_last_step", False, True), ("batch4_last_step", False, False), ("batch4", True, True)])
+def test_pipelined_steps_on_two_streams(run, ahead, sync_each, threaded):
+    check(run, ahead, sync_each, threaded)
+
+
+@pytest.mark.parametrize("ahead,sync_each,threaded,disturb", [
+    (False, True, True, None), (False, False, True, None), ("index", False, True, None), ("batch2", False, True, None),
+    ("batch2_last_step", False, False, None), ("batch3_last_step", True, True, None), (True, False, False, None),
+    ("batch2", True, True, 3), (False, True, True, 1), ("index", True, False, 2)])
+def test_two_part_lookup_on_two_streams(run, ahead, sync_each, threaded, disturb):
+    check(run, ahead, sync_each, threaded, two_part=True, disturb=disturb)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_exclusive_rows_are_fetched_by_the_call_before_unless_they_are_forgotten(dtype):
+    rng = np.random.default_rng(78)
+    n = 80_000
+    ids = [zipf_ids(rng, n, ROWS, a=1.1) for _ in range(4)]
+    start = rand_table(rng, ROWS, DIM, dtype)
+    ctx = fs.Context(max_ids=n, max_dim=DIM)
+    view = torch.int16 if dtype == "bf16" else torch.int32
+    table, state = table_to_dev(start), torch.zeros(ROWS, device="cuda")
+    vals = [dev(x) for x in ids]
+    grads = torch.randn((n, DIM), device="cuda")
+    lays = [fs.alloc_layout(n, "cuda") for _ in range(4)]
+    splits = [fs.alloc_split(n, n, "cuda") for _ in range(3)]
+    embs = [torch.empty((n, DIM), dtype=table.dtype, device="cuda") for _ in range(3)]
+    fs.fs_unique_ids(ctx, vals[0], ROWS, out=lays[0])
+    args = [fs.make_step_args(table, state, 0.01, 1e-8, dict(lays[t], n=n), grads, vals[t + 1], None, lays[t + 1], splits[t],
+                              None, embs[t]) for t in range(3)]
+    records = [fs.step_args_array([a]) for a in args]
+    fs.fs_step_forward(ctx, args[0])
+    for e in embs:
+        e.view(view).fill_(-3)
+    fs.fs_prioritized_step_two_part_multi(ctx, records[0], records[1])
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    co = torch.from_numpy(np.isin(ids[2], ids[1])).cuda()      # occurrences of iteration 1's lookahead batch on its own rows
+    assert bool(co.any()) and not bool(co.all())
+    got = embs[1].view(view)
+    # a row of batch 2 that batch 1 does not update keeps what iteration 0 left: fetched already; the others are not
+    assert torch.equal(got[~co], table[vals[2]].view(view)[~co]) and bool((got[co] == -3).all())
+    # taken as fetched: overwritten meanwhile, the exclusive rows stay overwritten
+    got[~co] = -5
+    fs.fs_prioritized_step_two_part_multi(ctx, records[1], records[2])
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    assert bool((got[~co] == -5).all()) and torch.equal(got[co], table[vals[2]].view(view)[co])
+    # forgotten: the whole lookup is done
+    embs[2].view(view).fill_(-5)
+    fs.fs_two_part_forget(ctx)
+    fs.fs_prioritized_step_two_part_multi(ctx, records[2], None)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    assert torch.equal(embs[2].view(view), table[vals[3]].view(view))
+    ctx.close()

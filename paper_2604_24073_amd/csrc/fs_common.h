@@ -26,10 +26,7 @@ constexpr int kRadix = 1 << kRadixBits;                   // most bins of one pa
 #define FS_SORT_THREADS 1024
 #endif
 constexpr int kSortThreads = FS_SORT_THREADS;
-#ifndef FS_SORT_TILE
-#define FS_SORT_TILE 4096
-#endif
-constexpr int kSortTile = FS_SORT_TILE;                   // keys per tile
+constexpr int kSortTile = 4096;                           // keys per tile
 constexpr int kSortKpt = kSortTile / kSortThreads;        // keys per thread
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortScan = kSortThreads > kRadix ? kSortThreads : kRadix;

@@ -281,22 +281,6 @@ __global__ __launch_bounds__(256) void dispatch_splits_kernel(const sample_order
         order.splits[r] = rank_split(order, out_offsets, r);
 }
 
-// number of entries of a[0, n) that are <= key; executed by one whole wavefront (64-ary search)
-__device__ __forceinline__ int64_t wave_upper_bound(const int64_t *__restrict__ a, int64_t n, int64_t key) {
-    const int lane = threadIdx.x & (kWave - 1);
-    int64_t lo = 0, hi = n;                  // a[i] <= key for i < lo, a[i] > key for i >= hi
-    while (lo < hi) {
-        const int64_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t probe = lo + (lane + 1) * step - 1;      // last entry of my sub-block
-        const bool le = (probe < hi) && (a[probe] <= key);
-        const int cnt = __popcll(__ballot(le));
-        lo += cnt * step;
-        const int64_t nhi = lo + step - 1;
-        hi = nhi < hi ? nhi : hi;
-    }
-    return lo;
-}
-
 // Pieces per workgroup.  A copy of whole rows wants long stretches: the searches that open a tile are a chain of
 // dependent loads that queue behind the rows of the other workgroups (250 k rows of 512 bytes, 16-byte pieces: 50 us
 // with 128 KB a workgroup, 100 to 160 with 32 or 64 KB).  Where samples are short the walk over their boundaries
@@ -334,7 +318,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
         // sample of an element e: the last k with out_offsets[k] <= e (empty samples in between are skipped);
         // the first wavefront looks for the sample of the tile's first element, the second for that of its last
         const int w = threadIdx.x / kWave;
-        const int64_t k = wave_upper_bound(out_offsets, n_out + 1, w == 0 ? e0 : e1) - 1;
+        const int64_t k = wave_upper_bound<int64_t>(out_offsets, (int)(n_out + 1), w == 0 ? e0 : e1) - 1;
         if ((threadIdx.x & (kWave - 1)) == 0) win[w] = k;
     }
     __syncthreads();

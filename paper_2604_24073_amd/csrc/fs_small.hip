@@ -268,7 +268,11 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         int len = 0;
         if (e < n_t) {
             f = (found[e / rounds_t] >> (e % rounds_t)) & 1;
-            if (classes) len = row_extent(job, e, bad).len;
+            if (classes) {
+                const small_extent x = row_extent(job, e, bad);
+                len = x.len;
+                bad |= (e == 0 && x.first != 0) || (e == n_t - 1 && x.first + len != job.n);
+            }
         }
         const uint64_t co_b = __ballot(f);
         const bool lg = len > FS_SHORT_SEGMENT;
@@ -282,11 +286,11 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         if (long_b != 0)                                     // wave-uniform
             lens += __shfl(wave_inclusive_scan<int>(lg ? (f ? len : len << 16) : 0), kWave - 1, kWave);
     }
-    // The ends of the layout; with them right and every row at least one occurrence long, the boundaries ascend from 0
-    // to n, so the extents of the rows are disjoint: the long ones sum to at most n <= kSmallIds (the packed halves
-    // hold that), and there are at most n / 9 of them.  A layout that does not fit its batch gets the flag and no class
-    // order: its extents may overlap, and then nothing bounds their sum.
-    if (classes && threadIdx.x == 0) bad |= n_t == 0 || job.seg_offsets[0] != 0 || job.seg_offsets[n_t] != job.n;
+    // With the ends of the layout right and every row at least one occurrence long, the boundaries ascend from 0 to n, so
+    // the extents of the rows are disjoint: the long ones sum to at most n <= kSmallIds (the packed halves hold that), and
+    // there are at most n / 9 of them.  A layout that does not fit its batch gets the flag and no class order: its extents
+    // may overlap, and then nothing bounds their sum.
+    bad |= classes && n_t == 0;
     constexpr int kBadWave = 1 << 20;                        // beside the number of long rows
     static_assert(kSmallIds < kBadWave, "there are fewer rows than the mark says");
     const bool bad_wave = __ballot(bad) != 0;

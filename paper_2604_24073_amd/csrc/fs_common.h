@@ -62,15 +62,11 @@ constexpr int kReduceWavesPerBlock = 4;
 constexpr int kShortRecInts = 12;                         // row (2), slot, occurrences, occurrence list (FS_SHORT_SEGMENT)
 static_assert(FS_SHORT_SEGMENT == 8, "record layout");
 // Fused pass: positions of a chunk (log2) for a batch of n occurrences.  A big batch fills the chip with chunks of 64,
-// and every chunk costs two dependent round trips at its cut segments; a small one is as long as the life of one
-// wavefront, which short chunks shorten.  Ten steps with 64 / 32 / 16: three tables of three widths of 14 k occurrences
-// 1050 / 951 / 891 us; eight tables of 48 k 1966 / 1975 / 2022, of 60 k 2265 / 2298 / 2409; four of 80 k 1608 / 1617 /
-// 1654, of 100 k 1887 / 1909 / 2002, of 128 k 2246 / 2313 / 2391; one of 60 k 478 / 458 / 462, of 80 k 514 / 500 / 520,
-// of 128 k 670 / 688 / 700, of 262 k 1042 / 1052 / 1100.  It depends on the batch alone, not on the tables beside it:
-// the order of the sums is part of the result.
+// and every chunk costs two dependent round trips at its cut segments (262 k occurrences: ten steps 1042 us with 64, 1052 with
+// 32, 1100 with 16); a small one is as long as the life of one wavefront, which short chunks shorten (three tables of
+// 14 k occurrences: 1050, 951, 891 us).  It depends on the batch alone: the order of the sums is part of the result.
 constexpr int kFusedWaves = 4;                            // wavefronts per workgroup (they never synchronise)
-constexpr int64_t kChunk32From = 49152, kChunk64From = 98304;
-inline int chunk_log2(int64_t n) { return n >= kChunk64From ? 6 : (n >= kChunk32From ? 5 : 4); }
+inline int chunk_log2(int64_t n) { return n >= 131072 ? 6 : (n >= 65536 ? 5 : 4); }
 
 // device-side error flag bits (ctx->d_flags[0])
 constexpr int kFlagRowRange = 1;
@@ -297,12 +293,11 @@ inline int lanes_per_row(int granules) {
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Chunks of the fused pass that the partial rows and counters of one class have room for: kMaxBatch tables of any size
-// below the one from which chunks are longest (a table has the most of them just below a change), and four of
+// below the one from which chunks are longest (a table has the most of them just below 65536 occurrences), and four of
 // max_ids, so that the tables of a call share their launch (with room for one table a launch, ten steps of eight tables
 // of 32 k occurrences took 2105 us, with this 1535; four of 60 k 1440 and 1325).
 inline int64_t fused_chunk_space(int64_t max_ids) {
-    static_assert(kChunk64From / 32 <= kChunk32From / 16, "no more chunks of 32 than of 16");
-    const int64_t most = max_ids < kChunk32From ? max_ids : kChunk32From;
+    const int64_t most = max_ids < 65536 ? max_ids : 65536;
     const int64_t batch = kMaxBatch * (ceil_div(most, 16) + kFusedWaves), largest = ceil_div(max_ids, 16) + 4 * kFusedWaves;
     return batch > largest ? batch : largest;
 }

@@ -54,6 +54,7 @@ struct small_shared {
     uint32_t base[kSmallRadix];
     uint32_t part[kSmallRadix / kWave];
     int wave_a[kSmallWaves], wave_b[kSmallWaves], wave_c[kSmallWaves];
+    int misfit;                                          // split: the layout of batch t does not fit its batch
     // ballots of the rounds of a wavefront (LDS, not registers: with loops over the rounds that are not unrolled the code
     // of a phase stays a few hundred instructions, and none of it is fetched for one use)
     uint64_t bal[2][kSmallWaves][kSmallIds / kSmallThreads];
@@ -231,6 +232,7 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
 #pragma unroll 4
     for (int e = threadIdx.x; e < n_t1; e += kSmallThreads) other[e] = job.u_t1[e];
     if ((int)threadIdx.x < maxn / 32) mark[threadIdx.x] = 0;
+    if (threadIdx.x == 0) sh.misfit = 0;
     __syncthreads();
     bool bad = false;
     // Both lists ascend: a thread takes a few consecutive rows of U_t, looks the first one up and walks on from there (a
@@ -291,21 +293,21 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
     // there are at most n / 9 of them.  A layout that does not fit its batch gets the flag and no class order: its extents
     // may overlap, and then nothing bounds their sum.
     bad |= classes && n_t == 0;
-    constexpr int kBadWave = 1 << 20;                        // beside the number of long rows
-    static_assert(kSmallIds < kBadWave, "there are fewer rows than the mark says");
-    const bool bad_wave = __ballot(bad) != 0;
     if (lane == 0) {
         sh.wave_a[w] = n_co_mine;
         sh.wave_b[w] = lens;
-        sh.wave_c[w] = n_long_mine + (bad_wave ? kBadWave : 0);
+        sh.wave_c[w] = n_long_mine;
     }
-    if (bad) atomicOr(flags, kFlagInternal);
+    if (bad) {
+        sh.misfit = 1;
+        atomicOr(flags, kFlagInternal);
+    }
     __syncthreads();
     int n_co, len_all, n_long;
     int co_run = small_prefix(sh.wave_a, w, n_co);
     int len_run = small_prefix(sh.wave_b, w, len_all);     // occurrences of long rows before the round: co, ex << 16
     int long_run = small_prefix(sh.wave_c, w, n_long);
-    const bool fits = n_long < kBadWave;                   // the layout fits its batch (the same in every thread)
+    const bool fits = sh.misfit == 0;
     const int n_co_pos = len_all & 0xffff, n_pos = n_co_pos + (int)((uint32_t)len_all >> 16);
     // the list of long rows: class position, sorted position, slot; U_t1 is not needed in LDS any more, but the marks are
     int32_t *l_dest = reinterpret_cast<int32_t *>(lds), *l_from = l_dest + maxn / 8, *l_slot = l_from + maxn / 8;
@@ -332,14 +334,14 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
                 int32_t *rec = job.short_rec + ((int64_t)(f ? 0 : job.cap_t) + (f ? c : e - c)) * kShortRecInts;
                 *reinterpret_cast<i32x4 *>(rec) = i32x4{(int)(id & 0xFFFFFFFFll), (int)(id >> 32), e, x.len};
                 if (x.len > FS_SHORT_SEGMENT) {
-                    if (fits) {
-                        const int dest = f ? (both & 0xffff) : n_co_pos + (int)((uint32_t)both >> 16);
-                        const int k = long_run + __popcll(long_b & lt);
+                    const int dest = f ? (both & 0xffff) : n_co_pos + (int)((uint32_t)both >> 16);
+                    const int k = long_run + __popcll(long_b & lt);
+                    if (k < maxn / 8) {                      // always, where the layout fits
                         l_dest[k] = dest;
                         l_from[k] = x.first;
                         l_slot[k] = f ? e : ~e;
-                        job.cstart[e] = dest;
                     }
+                    job.cstart[e] = dest;
                 } else {
                     // whole 16-byte pieces: one compute unit writes the records of the batch, and a store instruction
                     // costs it a cycle per line whatever it writes there
@@ -388,7 +390,7 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         }
         run += __popcll(b);
     }
-    if (!classes || !fits) return;
+    if (!classes || !fits || n_long > maxn / 8) return;      // the last only tells the compiler how long the list can be
     // The class order, a thread per class position.  The list has the long rows in row order, both classes mixed:
     // inside a class the positions ascend with the list, so the row of a position is found by looking for the last row
     // of ITS class that starts at or before it - the rows of the class are separated first.
@@ -427,7 +429,8 @@ __device__ __forceinline__ void small_split_body(const small_split &job, const i
         }
         if (lo == 0) continue;                               // cannot happen: row 0 of the list starts at 0
         const int j = lo - 1;
-        job.cperm[q] = job.perm[s_from[j] + (q - s_dest[j])];
+        const int p = s_from[j] + (q - s_dest[j]);
+        job.cperm[q] = (p >= 0 && p < job.n) ? job.perm[p] : 0;
         job.cslot[q] = s_slot[j];
     }
 }

@@ -62,9 +62,12 @@ constexpr int kReduceWavesPerBlock = 4;
 constexpr int kShortRecInts = 12;                         // row (2), slot, occurrences, occurrence list (FS_SHORT_SEGMENT)
 static_assert(FS_SHORT_SEGMENT == 8, "record layout");
 // Fused pass: positions of a chunk (log2) for a batch of n occurrences.  A big batch fills the chip with chunks of 64,
-// and every chunk costs two dependent round trips at its cut segments (262 k occurrences: ten steps 1042 us with 64, 1052 with
-// 32, 1100 with 16); a small one is as long as the life of one wavefront, which short chunks shorten (three tables of
-// 14 k occurrences: 1050, 951, 891 us).  It depends on the batch alone: the order of the sums is part of the result.
+// and every chunk costs two dependent round trips at its cut segments; a small one is as long as the life of one
+// wavefront, which short chunks shorten.  With 64 / 32 / 16 positions, both passes of one table of 128 columns alone:
+// 50 k occurrences 28.5 / 25.5 / 24.2 us, 80 k 33.6 / 31.0 / 31.2, 130 k 43.4 / 42.6 / 41.0, of 256 columns 72.0 / 69.8 /
+// 70.2; ten steps of 262 k 1042 / 1052 / 1100.  Tables beside each other fill the chip sooner: ten steps of four tables
+// of 60 k 1302 / 1310 / 1328, of 100 k 1892 / 1906 / 1998, of 130 k 2265 / 2335 / 2410.  It depends on the batch alone
+// and not on the tables beside it, for the order of the sums is part of the result, so the lines lie between.
 constexpr int kFusedWaves = 4;                            // wavefronts per workgroup (they never synchronise)
 inline int chunk_log2(int64_t n) { return n >= 131072 ? 6 : (n >= 65536 ? 5 : 4); }
 

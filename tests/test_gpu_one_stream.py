@@ -203,7 +203,7 @@ def kernels_captured(call):
     return kernels
 
 
-@pytest.mark.parametrize("n", [1, 2000, 65_535, 65_536, 131_071, 131_072, 600_000])
+@pytest.mark.parametrize("n", [1, 2000, 49_152, 65_535, 65_536, 98_304, 131_071, 131_072, 600_000])
 def test_tables_of_one_width_share_their_launches(n):
     """Eight equal tables as large as the context allows, on one stream: both passes of four tables a launch (the context
     has room for the pieces of all of them), and one lookup for the eight."""

@@ -231,14 +231,18 @@ fs_stream_set *new_set(int device, hipStream_t home) {
     return nullptr;
 }
 
-// the set of the contexts driven from `home`
-fs_stream_set *share_set(int device, hipStream_t home) {
+// the set of the contexts driven from `home`; `mine`, a set that only this context uses, becomes it if there is none
+fs_stream_set *share_set(int device, hipStream_t home, fs_stream_set *mine = nullptr) {
     std::lock_guard<std::mutex> lk(g_sets_mu);
     for (fs_stream_set *p = g_sets; p; p = p->next)
         if (p->device == device && p->home == home) {
             ++p->users;
             return p;
         }
+    if (mine && mine->users == 1) {
+        mine->home = home;
+        return mine;
+    }
     fs_stream_set *p = new_set(device, home);
     if (p) {
         p->next = g_sets;
@@ -247,17 +251,29 @@ fs_stream_set *share_set(int device, hipStream_t home) {
     return p;
 }
 
+void unlist_set(const fs_stream_set *p) {
+    for (fs_stream_set **q = &g_sets; *q; q = &(*q)->next)
+        if (*q == p) {
+            *q = p->next;
+            return;
+        }
+}
+
+// a shared set that nobody else uses leaves the list and belongs to this context alone
+bool keep_set(const fs_stream_set *p) {
+    std::lock_guard<std::mutex> lk(g_sets_mu);
+    if (p->users > 1) return false;
+    unlist_set(p);
+    return true;
+}
+
 // gives a set back; this context's work on it is done (or there is none)
 void drop_set(fs_stream_set *p) {
     if (!p) return;
     {
         std::lock_guard<std::mutex> lk(g_sets_mu);
         if (--p->users > 0) return;
-        for (fs_stream_set **q = &g_sets; *q; q = &(*q)->next)
-            if (*q == p) {
-                *q = p->next;
-                break;
-            }
+        unlist_set(p);
     }
     destroy_set(p);
 }
@@ -1019,12 +1035,17 @@ int follow_stream(fs_ctx *ctx, hipStream_t s) {
         return FS_OK;
     }
     if (!alone && !ctx->set_used) {
-        fs_stream_set *p = share_set(ctx->device, s);
+        fs_stream_set *p = share_set(ctx->device, s, ctx->shared_set);
         if (!p) return set_err(ctx, FS_EHIP, "hipStreamCreateWithFlags(side streams)");
-        drop_set(ctx->shared_set);
+        if (p != ctx->shared_set) drop_set(ctx->shared_set);
         ctx->shared_set = p;
         ctx->set_used = true;
         use_set(ctx, p);
+        return FS_OK;
+    }
+    if (keep_set(ctx->shared_set)) {
+        ctx->own_set = ctx->shared_set;
+        ctx->shared_set = nullptr;
         return FS_OK;
     }
     const int wrc = workers_wait(ctx);                       // what has been posted is on the streams it was posted for

@@ -1396,8 +1396,10 @@ int fs_prioritized_step_two_part_multi(fs_ctx *ctx, const fs_step_args *cur, con
 // second thread to pay them) and one launch less per row width.  What it gives up is the deferred pass running beside
 // the lookup.  Ten steps of one 2M x 128 table, two streams against one: 32 k IDs a batch (31 MB) 455 / 415 us, 65 k
 // (64 MB) 519 / 482, 98 k (96 MB) 570 / 568, 110 k (107 MB) 611 / 621, 120 k (117 MB) 644 / 661, 130 k (127 MB) 680 / 702,
-// 262 k (of 4M rows) 1041 / 1056; two tables of 49 k (96 MB) 785 / 759; eight tables of 2 GB 5616 / 6039.
-constexpr int64_t kOneStreamBytes = 100 << 20;
+// 262 k (of 4M rows) 1041 / 1056; two tables of 49 k (96 MB) 785 / 759, of 60 k (117 MB) 835 / 819, four of 30 k (117 MB)
+// 916 / 888; eight tables of 2 GB 5616 / 6039.  With the lookup in two parts, whose second gather the one-stream form does
+// without: one table of 110 k (107 MB) 648 / 638, of 120 k (117 MB) 679 / 678, of 130 k (127 MB) 709 / 716.
+constexpr int64_t kOneStreamBytes = 100 << 20, kOneStreamBytesMore = 120 << 20;     // one whole lookup; otherwise
 
 static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_args *next, int count, fs_stream stream,
                           bool two_part) {
@@ -1431,7 +1433,7 @@ static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_ar
                        "two-part step: co_flag_t1 or inverse_t1 missing (next)");
         }
     }
-    one_stream = one_stream && row_bytes <= kOneStreamBytes;
+    one_stream = one_stream && row_bytes <= (count > 1 || two_part ? kOneStreamBytesMore : kOneStreamBytes);
     // which part of cur's lookup is left to do: the collision rows if the previous call fetched the rest (on one stream
     // the whole lookup: nothing is fetched ahead of a call there)
     int part[kMaxTables];

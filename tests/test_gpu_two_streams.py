@@ -1,4 +1,4 @@
-"""The two-stream form of the pipelined step, on batches large enough that every call of a run takes it (more than 100 MB
+"""The two-stream form of the pipelined step, on batches large enough that every call of a run takes it (more than 120 MB
 of gradients and looked-up rows a call): deferred pass, index half and the lookup's exclusive part on side stream A beside
 the caller's stream, with and without the enqueueing threads, with and without waits between the calls.  Everything bit
 for bit as the building blocks issued one after another."""
@@ -13,7 +13,7 @@ from test_gpu_pipeline import make_its, run_pipelined
 
 pytestmark = pytest.mark.gpu
 
-ROWS, DIM, LIMIT = 40_000, 256, 100 << 20
+ROWS, DIM, LIMIT = 40_000, 256, 120 << 20
 
 
 def call_bytes(its, dtype):
@@ -70,7 +70,7 @@ def test_two_part_lookup_on_two_streams(run, ahead, sync_each, threaded, disturb
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_exclusive_rows_are_fetched_by_the_call_before_unless_they_are_forgotten(dtype):
     rng = np.random.default_rng(78)
-    n = 80_000
+    n = 90_000
     ids = [zipf_ids(rng, n, ROWS, a=1.1) for _ in range(4)]
     start = rand_table(rng, ROWS, DIM, dtype)
     ctx = fs.Context(max_ids=n, max_dim=DIM)

@@ -441,9 +441,10 @@ int fs_step_forward_ahead_batch(fs_ctx *ctx, const fs_step_args *args, int count
  *                   deferred pass of cur (fs_reduce_update_class(1)); then the index half of
  *                   `next`: dedup of next's lookahead IDs (or a wait for fs_unique_ids_ahead),
  *                   split of next's U_t, class order of next's batch
- * A call with little row work (up to 100 MB of gradients and looked-up rows, 120 MB over several tables or with the lookup
- * in two parts; the index half of `next` done ahead of time or small) does without the side stream: both passes in one launch and the gather
- * behind them on `stream`, an index half that is not done yet behind those.  Results do not depend on it.
+ * A call with little row work (up to 100 MB of gradients and looked-up rows, 120 MB over several tables or with the
+ * lookup in two parts; the index half of `next` done ahead of time or small) does without the side stream: both passes
+ * in one launch and the gather behind them on `stream`, an index half that is not done yet behind those.  Results do
+ * not depend on it.
  * The split and class order of `cur` must already exist: they were produced by the previous call
  * of this function (as its `next`) or by fs_step_forward.  `next` may be NULL (last iteration).
  * Nothing on A is waited for when the call returns: the next pipelined call waits for it before

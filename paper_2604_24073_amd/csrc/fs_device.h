@@ -68,13 +68,26 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
 // inclusive scan of one value per lane over the wavefront
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v) {
-    const int lane = threadIdx.x & (kWave - 1);
+    if constexpr (sizeof(T) == 4) {
+        // rows of sixteen lanes by row shifts, then the last lane of a row to the next row and of a half to the other
+        // half: six VALU instructions instead of six trips through the LDS crossbar
+        int x = (int)v;
+        x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1
+        x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);      // row_shr:2
+        x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);      // row_shr:4
+        x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);      // row_shr:8
+        x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+        x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+        return (T)x;
+    } else {
+        const int lane = threadIdx.x & (kWave - 1);
 #pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const T t = __shfl_up(v, d, kWave);
-        if (lane >= d) v += t;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const T t = __shfl_up(v, d, kWave);
+            if (lane >= d) v += t;
+        }
+        return v;
     }
-    return v;
 }
 
 // exclusive scan of one value per thread over a workgroup of kScanThreads threads; the total is returned

@@ -146,6 +146,8 @@ void carve(fs_ctx *c, char *base, size_t *total) {
         ws.idx[1] = cv.take<int32_t>(n);
         ws.tile_hist = cv.take<uint32_t>(sort_tiles * kRadix);
         ws.tile_heads = cv.take<int32_t>(scan_tiles);
+        ws.ranges = cv.take<uint32_t>(4 * (size_t)kMaxBuckets);
+        ws.range_start = cv.take<uint16_t>(bucket_table_size(c->max_ids));
     }
     for (int k = 0; k < kSortSets; ++k) {
         fs_split_scratch &ws = c->split[k];
@@ -1563,6 +1565,7 @@ int fs_step_join(fs_ctx *ctx, fs_stream stream) {
 // (layout beside the tracer in fs_device.h); nullptr switches the trace off.
 void fs_set_trace_unique(unsigned long long *);
 void fs_set_trace_split(unsigned long long *);
+void fs_set_trace_bucket(unsigned long long *);
 void fs_set_trace_small(unsigned long long *);
 void fs_set_trace_gather(unsigned long long *);
 void fs_set_trace_fused(unsigned long long *);
@@ -1571,6 +1574,7 @@ int fs_debug_trace(fs_ctx *ctx, void *buf_dev) {
     FS_HIP(ctx, hipDeviceSynchronize());
     fs_set_trace_unique((unsigned long long *)buf_dev);
     fs_set_trace_split((unsigned long long *)buf_dev);
+    fs_set_trace_bucket((unsigned long long *)buf_dev);
     fs_set_trace_small((unsigned long long *)buf_dev);
     fs_set_trace_gather((unsigned long long *)buf_dev);
     fs_set_trace_fused((unsigned long long *)buf_dev);

@@ -55,6 +55,18 @@ constexpr int64_t kSmallIdsInline = 8192;
 constexpr int64_t kSmallSplitInline = 4096;
 constexpr int64_t kSmallClassesInline = 6144;
 
+// Dedup by ranges of keys (fs_bucket.hip): most IDs of a batch, IDs of a tile, most ranges, and the IDs a range is meant
+// to hold (up to that many; a power of two of ranges).
+constexpr int64_t kBucketIdsMax = 1 << 20;
+constexpr int kBucketTile = 2048;
+constexpr int kMaxBuckets = 1024;
+constexpr int kBucketMean = 768;
+inline int ranges_log2(int64_t n) {
+    int k = 0;
+    while ((1 << k) < kMaxBuckets && ((int64_t)kBucketMean << k) < n) ++k;
+    return k;
+}
+
 // segment reduce: sorted positions owned by one wavefront (one 64-bit tail mask, one permutation
 // entry per lane).  Short chunks = many wavefronts with short dependent-load chains.
 constexpr int kReduceChunk = 64;
@@ -87,6 +99,8 @@ struct fs_sort_scratch {
     int32_t *idx[2];          // [max_ids] each
     uint32_t *tile_hist;      // [tiles * bins] per-tile digit counts
     int32_t *tile_heads;      // [scan tiles] heads per compaction tile
+    uint32_t *ranges;         // [4 * kMaxBuckets] dedup by ranges: what its launches tell each other of a range
+    uint16_t *range_start;    // [tiles * ranges] where the ranges start in a tile
 };
 #ifndef FS_INDEX_STREAMS
 #define FS_INDEX_STREAMS 2
@@ -330,6 +344,10 @@ int launch_unique(fs_ctx *, const int64_t *ids, int64_t n, int64_t num_rows, int
                   int set = 0);
 // `count` (1..kMaxBatch) independent jobs in shared launches; job k uses scratch set set0 + k
 int launch_unique_batch(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0);
+// the same by ranges of keys, where every job fits
+size_t bucket_table_size(int64_t max_ids);               // entries of fs_sort_scratch::range_start
+bool bucket_unique_fits(int count, const fs_unique_job *jobs);
+int launch_bucket_unique(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0);
 int launch_split_batch(fs_ctx *, int count, const fs_split_job *jobs, hipStream_t s, int set0);
 // right after launch_split_batch(..., seg_offsets_t given) with the same jobs order and sets, on the same stream
 int launch_class_order_batch(fs_ctx *, int count, const fs_class_job *jobs, hipStream_t s, int set0);

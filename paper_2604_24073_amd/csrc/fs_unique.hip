@@ -3,6 +3,9 @@
 // permutation and the inverse map.  (Collisions are defined on rows, Section 2.3 of the paper;
 // compute_collision of Algorithm 2 consumes the distinct lists.)
 //
+// What the other forms leave: batches of more than 2^20 IDs and tables of more than 2^31 rows (or of a size that is not
+// given).  One workgroup does small batches (fs_small.hip), ranges of keys those in between (fs_bucket.hip).
+//
 // Only ceil(log2(num_rows)) key bits are sorted, in the fewest passes of at most 9 bits; keys
 // travel as 32-bit words when they fit.  The inputs are small (a few hundred thousand keys), so
 // the passes are latency bound: tiles are large (4096 keys, 1024 threads) to keep the
@@ -362,6 +365,7 @@ int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipSt
         FS_LAUNCH_CHECK(ctx, "unique_empty_kernel");
         return FS_OK;
     }
+    if (bucket_unique_fits(count, jobs)) return launch_bucket_unique(ctx, count, jobs, s, set0);
     // one sort geometry for the whole batch: the widest key decides (sorting zero bits is harmless)
     int key_bits = 1;
     unique_dev_batch batch;

@@ -41,13 +41,13 @@ constexpr int kClassOrderTiles = 60 * 1024 / (2 * (int)sizeof(int));
 constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
 // IDs of a batch whose index half fits the LDS of one workgroup (fs_small.hip), and the most it takes.  On the caller's
-// stream: up to where the chain of launches over many workgroups is the faster one (a whole step of 8192 IDs: 67 us
-// against 86).  Ahead of time a launch costs whatever runs beside it and the workgroup has the iterations ahead to
-// finish, but it must keep up with them: ten steps of three tables, an iteration a launch, one workgroup against the
-// chain: 12000 IDs 681 / 674 us, 14000 747 / 700, 16000 784 / 694; one table, four iterations a launch: 12000 281 / 300,
-// 14000 299 / 311, 16000 303 / 320.
+// stream: up to where the chain of launches over many workgroups is the faster one (a whole step, one workgroup against
+// the chain: 1024 IDs 25.4 / 40.7 us, 4096 40.1 / 53.4, 6144 53.8 / 62.2, 8192 59.9 / 62.6).  Ahead of time a launch costs
+// whatever runs beside it and the workgroup has the iterations ahead to finish, but it must keep up with them: ten steps,
+// one workgroup against the chain, one table: 4096 IDs 241 / 308 us, 8192 278 / 315, 12288 354 / 335; three tables: 4096
+// 408 / 486, 8192 445 / 500, 12288 611 / 560.
 constexpr int64_t kSmallIds = 16384;
-constexpr int64_t kSmallIdsAhead = 12288;
+constexpr int64_t kSmallIdsAhead = 10240;
 constexpr int64_t kSmallIdsInline = 8192;
 // Without the dedup in front the chain is two launches (the split alone) or three: IDs up to which the one workgroup
 // does those on the caller's stream.  Split alone, one workgroup against two launches: 4096 IDs 11.4 / 11.6 us, 5000

@@ -87,7 +87,7 @@ def test_an_id_out_of_range_is_reported_and_leaves_the_other_rows_alone(ctx):
     check(ctx, ids, rows)
 
 
-@pytest.mark.parametrize("sizes", [(20_000, 300_000), (70_000, 3, 9_000)])
+@pytest.mark.parametrize("sizes", [(20_000, 300_000), (70_000, 3, 9_000), (10_240, 5_000), (10_241, 10_240)])
 def test_index_halves_of_different_sizes_in_one_chain(sizes):
     """Jobs that share their launches have ranges and tiles of their own number; what they write is the same as alone."""
     rng = np.random.default_rng(sum(sizes))

@@ -419,7 +419,7 @@ int fs_unique_ids_ahead(fs_ctx *ctx, const int64_t *ids, int64_t n, int64_t num_
 int fs_step_forward_ahead(fs_ctx *ctx, const fs_step_args *args, fs_stream stream);
 
 /* The index halves of `count` (1..FS_MAX_AHEAD_BATCH) argument records ahead of time in SHARED
- * launches: every kernel of the chain (three radix passes, compaction, split, class order) runs once
+ * launches: every kernel of the chain (dedup, split, class order) runs once
  * for all of them.  A launch disturbs whatever runs beside it on the chip by about as much however
  * small it is, so what the index work costs the bandwidth-bound passes falls with the number of
  * iterations - or tables - that share a chain.  The records may be consecutive iterations of one table

@@ -1326,8 +1326,7 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
 
 // IDs of both batches from which the self-contained step takes its index half to the side stream: two cross-stream waits
 // of 10-12 us of host time each against a chain of launches behind the row work.  Behind / beside it on a 4M x 128 table,
-// IDs of one batch: 8 k 67 / 70 us, 16 k 93 / 103, 32 k 101 / 110, 64 k 114 / 118, 80 k 122 / 121, 96 k 127 / 127, 128 k
-// 138 / 136, 256 k 193 / 177; on a 49 k x 160 bf16 table, whose rows the caches hold, 78 k 92 / 89.
+// IDs of one batch: 16 k 68 / 79 us, 32 k 75 / 82, 48 k 88 / 92, 64 k 85 / 89, 96 k 101 / 98, 128 k 105 / 102.
 constexpr int64_t kStepSideIds = 131072;
 
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {

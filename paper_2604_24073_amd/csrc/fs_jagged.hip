@@ -2,7 +2,7 @@
 // "Partitioning Algorithms") and the indexed permute of a jagged tensor (Section 4.2, "Triton Kernel
 // Optimizations": the kernel that applies a partitioning to the gathered IDs).
 //
-// FBS: samples sorted by UIH length (the stable radix sort of the dedup, on the lengths), then dealt to
+// FBS: samples sorted by UIH length (the stable sort of the dedup, on the lengths), then dealt to
 // the ranks in a zig-zag - rank i takes sorted positions i, 2n-1-i, 2n+i, 4n-1-i, ...  The deal is a
 // closed form per sorted position, one thread each.
 //

@@ -8,8 +8,8 @@
 // second launch compacts with tile prefixes.  Bound by dependent rounds, not bytes: the tile's own keys travel while the
 // window is searched, the two ends are searched at once, and a thread's four keys take their steps through LDS side by
 // side (the class order's positions and what their rows are likewise).  Plain operations of 34 k IDs 82.3 -> 80.5 us,
-// self-contained step of 297 k 148.6 -> 146.4 against one search, one key and one position after the other.  The list lengths are device scalars; the launch is
-// sized by the host-side caps and tiles past the end do nothing.
+// self-contained step of 297 k 148.6 -> 146.4 against one search, one key and one position after the other.
+// The list lengths are device scalars; the launch is sized by the host-side caps and tiles past the end do nothing.
 #include <mutex>
 
 #include "fs_common.h"

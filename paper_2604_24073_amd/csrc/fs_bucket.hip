@@ -709,12 +709,6 @@ size_t bucket_table_size(int64_t max_ids) {
     return (size_t)ceil_div(n, kBucketTile) << ranges_log2(n);
 }
 
-bool bucket_unique_fits(int count, const fs_unique_job *jobs) {
-    for (int k = 0; k < count; ++k)
-        if (jobs[k].n > kBucketIdsMax || jobs[k].num_rows <= 0 || jobs[k].num_rows > (1ll << 31)) return false;
-    return true;
-}
-
 int launch_bucket_unique(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipStream_t s, int set0) {
     bucket_dev_batch batch;
     memset(&batch, 0, sizeof(batch));

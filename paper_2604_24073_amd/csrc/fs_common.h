@@ -8,19 +8,13 @@
 #include <string.h>
 
 #include "freescale_aux.h"
+#include "fs_dedup_rule.h"
 
 namespace fs {
 
 constexpr int kWave = 64;
 
 // radix sort geometry
-#ifndef FS_RADIX_BITS
-#define FS_RADIX_BITS 9
-#endif
-constexpr int kRadixBits = FS_RADIX_BITS;                 // most bits one pass may sort (11 would sort 22-bit row IDs in
-                                                          // two passes, but every scatter workgroup then scans a
-                                                          // [tile][2048] table and lives four times as long beside the
-                                                          // class passes: measured slower, 105.2 against 103.0 us per step)
 constexpr int kRadix = 1 << kRadixBits;                   // most bins of one pass
 #ifndef FS_SORT_THREADS
 #define FS_SORT_THREADS 1024
@@ -54,18 +48,6 @@ constexpr int64_t kSmallIdsInline = 8192;
 // 13.8 / 11.4, 8192 18.9 / 11.8; with the class order against three: 6144 22.5 / 23.6, 7000 24.7 / 24.4, 8192 28.4 / 24.1.
 constexpr int64_t kSmallSplitInline = 4096;
 constexpr int64_t kSmallClassesInline = 6144;
-
-// Dedup by ranges of keys (fs_bucket.hip): most IDs of a batch, IDs of a tile, most ranges, and the IDs a range is meant
-// to hold (up to that many; a power of two of ranges).
-constexpr int64_t kBucketIdsMax = 1 << 20;
-constexpr int kBucketTile = 2048;
-constexpr int kMaxBuckets = 1024;
-constexpr int kBucketMean = 768;
-inline int ranges_log2(int64_t n) {
-    int k = 0;
-    while ((1 << k) < kMaxBuckets && ((int64_t)kBucketMean << k) < n) ++k;
-    return k;
-}
 
 // segment reduce: sorted positions owned by one wavefront (one 64-bit tail mask, one permutation
 // entry per lane).  Short chunks = many wavefronts with short dependent-load chains.
@@ -342,11 +324,11 @@ inline hipEvent_t *timing_pair(fs_ctx *ctx, int kind) {
 int launch_unique(fs_ctx *, const int64_t *ids, int64_t n, int64_t num_rows, int64_t *unique,
                   int32_t *seg_offsets, int32_t *perm, int32_t *inverse, int64_t *n_unique_dev, hipStream_t s,
                   int set = 0);
-// `count` (1..kMaxBatch) independent jobs in shared launches; job k uses scratch set set0 + k
-int launch_unique_batch(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0);
-// the same by ranges of keys, where every job fits
+// `count` (1..kMaxBatch) independent jobs in shared launches; job k uses scratch set set0 + k; alone: an operation of its
+// own, not part of an index half
+int launch_unique_batch(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0, bool alone = false);
+// the same by ranges of keys, for jobs that dedup_by_ranges takes
 size_t bucket_table_size(int64_t max_ids);               // entries of fs_sort_scratch::range_start
-bool bucket_unique_fits(int count, const fs_unique_job *jobs);
 int launch_bucket_unique(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0);
 int launch_split_batch(fs_ctx *, int count, const fs_split_job *jobs, hipStream_t s, int set0);
 // right after launch_split_batch(..., seg_offsets_t given) with the same jobs order and sets, on the same stream

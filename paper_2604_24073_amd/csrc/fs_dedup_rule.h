@@ -1,0 +1,59 @@
+// Sizes of the two dedups of many workgroups (fs_bucket.hip, fs_unique.hip) and which of them a batch takes.  Host code
+// only, no HIP, so that the rule can be compiled and looked at by itself.
+#pragma once
+
+#include <stdint.h>
+
+namespace fs {
+
+#ifndef FS_RADIX_BITS
+#define FS_RADIX_BITS 9
+#endif
+constexpr int kRadixBits = FS_RADIX_BITS;                 // most bits one pass may sort (11 would sort 22-bit row IDs in
+                                                          // two passes, but every scatter workgroup then scans a
+                                                          // [tile][2048] table and lives four times as long beside the
+                                                          // class passes: measured slower, 105.2 against 103.0 us per step)
+
+// bits of a row ID of a table of num_rows rows (of unknown size: 63)
+inline int key_bits_of(int64_t num_rows) {
+    if (num_rows <= 0) return 63;
+    int kb = 1;
+    while (kb < 63 && (1ll << kb) < num_rows) ++kb;
+    return kb;
+}
+inline int radix_passes(int key_bits) { return (key_bits + kRadixBits - 1) / kRadixBits; }
+
+// Dedup by ranges of keys: most IDs of a batch (a place and a rank share 32 bits), IDs of a tile, most ranges, and the IDs
+// a range is meant to hold (up to that many; a power of two of ranges).
+constexpr int64_t kBucketIdsMax = 1 << 20;
+constexpr int kBucketTile = 2048;
+constexpr int kMaxBuckets = 1024;
+constexpr int kBucketMean = 768;
+inline int ranges_log2(int64_t n) {
+    int k = 0;
+    while ((1 << k) < kMaxBuckets && ((int64_t)kBucketMean << k) < n) ++k;
+    return k;
+}
+// IDs of a batch from which the ranges are 1024: two to a compute unit (58 KB of LDS each), 512 of them run at once.
+constexpr int64_t kBucketOneWave = (int64_t)kBucketMean << 9;
+
+// By ranges or by radix passes?  Four launches by ranges, whatever the keys; two per radix pass of up to 9 key bits and two
+// more.  Radix / ranges, us (tables of 64 fp32 columns, Zipf IDs):
+//   one pass (512 rows): radix at every size.  The dedup alone, 9 k IDs 22 / 25, 131 k 23 / 29, 393 k 26 / 34, 786 k 32 / 55;
+//     ten steps of 60 k 281 / 313, of 500 k 776 / 814; self-contained step of 500 k 98 / 117; 65 k samples up to 500 long
+//     balanced 73.9 / 78.2.  (Below five rows and 34 k IDs the ranges lead, 28 / 23; no table is as small.)
+//   two passes (2^18 rows): ranges while they run all at once, 20 k IDs 36 / 28, 393216 43 / 41; beyond it depends on what is
+//     beside them.  Alone 393217 43 / 47, 550 k 47 / 54, 786 k 52 / 60.  Of an index half, where the smaller workgroups find
+//     a place beside the row work sooner, ten steps 500 k 866 / 865, 700 k 1129 / 1093, 1 M 1585 / 1487 (200 k rows 1790 /
+//     1632), self-contained step of 400 k 121 / 124, of 700 k 160 / 156.
+//   three and more: ranges at every size they can take.  4 M rows alone 300 k 62 / 44, 786 k 77 / 73, 1 M 86 / 82 (mean of 16
+//     batches, those with a range beyond LDS among them); ten steps of 1 M 2200 / 2038; 2^30 rows alone, 1 M 118 / 88.
+// most_ids, key_bits: the largest batch and the widest key of the dedups that share the launches; alone: an operation of its
+// own, not part of an index half.
+inline bool dedup_by_ranges(int64_t most_ids, int key_bits, bool alone) {
+    if (key_bits > 31 || most_ids > kBucketIdsMax) return false;
+    const int passes = radix_passes(key_bits);
+    return passes >= 3 || (passes == 2 && (!alone || most_ids <= kBucketOneWave));
+}
+
+}  // namespace fs

@@ -478,13 +478,6 @@ static int small_dispatch(fs_ctx *ctx, const small_batch &batch, int count, int6
     return FS_OK;
 }
 
-static int key_bits_of(int64_t num_rows) {
-    if (num_rows <= 0) return 63;
-    int kb = 1;
-    while (kb < 63 && (1ll << kb) < num_rows) ++kb;
-    return kb;
-}
-
 // scratch set 0 belongs to the caller's stream and the side stream, the others to the index streams
 static int64_t small_limit(int set0) { return set0 == 0 ? kSmallIdsInline : kSmallIdsAhead; }
 

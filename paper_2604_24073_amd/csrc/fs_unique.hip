@@ -3,8 +3,10 @@
 // permutation and the inverse map.  (Collisions are defined on rows, Section 2.3 of the paper;
 // compute_collision of Algorithm 2 consumes the distinct lists.)
 //
-// What the other forms leave: batches of more than 2^20 IDs and tables of more than 2^31 rows (or of a size that is not
-// given).  One workgroup does small batches (fs_small.hip), ranges of keys those in between (fs_bucket.hip).
+// What the other forms leave: tables of up to 512 rows (one pass), large batches of tables of up to 2^18 rows (two) where
+// the dedup is an operation of its own, batches of more than 2^20 IDs and tables of more than 2^31 rows or of a size that is
+// not given.  One workgroup does small batches (fs_small.hip), ranges of keys the others (fs_bucket.hip); the lines and what
+// was measured on both sides are in fs_dedup_rule.h.
 //
 // Only ceil(log2(num_rows)) key bits are sorted, in the fewest passes of at most 9 bits; keys
 // travel as 32-bit words when they fit.  The inputs are small (a few hundred thousand keys), so
@@ -327,7 +329,7 @@ static int unique_batch_impl(fs_ctx *ctx, const unique_dev_batch &batch, int cou
         tiles = batch.j[k].tiles > tiles ? batch.j[k].tiles : tiles;
         stiles = batch.j[k].stiles > stiles ? batch.j[k].stiles : stiles;
     }
-    const int passes = (key_bits + kRadixBits - 1) / kRadixBits;
+    const int passes = radix_passes(key_bits);
     const int bits = (key_bits + passes - 1) / passes;            // <= kRadixBits, evenly spread
     int cur = 0;   // buffer holding the input of the next pass (unused for the first pass)
     if (tiles > 0) {
@@ -356,7 +358,7 @@ static int unique_batch_impl(fs_ctx *ctx, const unique_dev_batch &batch, int cou
     return FS_OK;
 }
 
-int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipStream_t s, int set0) {
+int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipStream_t s, int set0, bool alone) {
     if (count < 1 || count > kMaxBatch || set0 < 0 || set0 + count > kSortSets)
         return set_err(ctx, FS_EINVAL, "unique: batch size");
     if (small_unique_fits(count, jobs, set0)) return launch_small_index(ctx, count, jobs, nullptr, nullptr, s);
@@ -365,19 +367,19 @@ int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipSt
         FS_LAUNCH_CHECK(ctx, "unique_empty_kernel");
         return FS_OK;
     }
-    if (bucket_unique_fits(count, jobs)) return launch_bucket_unique(ctx, count, jobs, s, set0);
     // one sort geometry for the whole batch: the widest key decides (sorting zero bits is harmless)
     int key_bits = 1;
+    int64_t most = 0;
+    for (int k = 0; k < count; ++k) {
+        const int kb = key_bits_of(jobs[k].num_rows);
+        key_bits = kb > key_bits ? kb : key_bits;
+        most = jobs[k].n > most ? jobs[k].n : most;
+    }
+    if (dedup_by_ranges(most, key_bits, alone)) return launch_bucket_unique(ctx, count, jobs, s, set0);
     unique_dev_batch batch;
     memset(&batch, 0, sizeof(batch));
     for (int k = 0; k < count; ++k) {
         const fs_unique_job &in = jobs[k];
-        int kb = 63;
-        if (in.num_rows > 0) {
-            kb = 1;
-            while (kb < 63 && (1ll << kb) < in.num_rows) ++kb;
-        }
-        key_bits = kb > key_bits ? kb : key_bits;
         const fs_sort_scratch &ws = ctx->sort[set0 + k];
         unique_dev_job &j = batch.j[k];
         j.ids = in.ids;
@@ -406,7 +408,7 @@ int launch_unique(fs_ctx *ctx, const int64_t *ids, int64_t n, int64_t num_rows, 
                   int32_t *seg_offsets, int32_t *perm, int32_t *inverse, int64_t *n_unique_dev, hipStream_t s,
                   int set) {
     const fs_unique_job job = {ids, n, num_rows, unique, seg_offsets, perm, inverse, n_unique_dev};
-    return launch_unique_batch(ctx, 1, &job, s, set);
+    return launch_unique_batch(ctx, 1, &job, s, set, set == 0);          // the other sets belong to the index streams
 }
 
 FS_TRACE_SETTER(unique)

@@ -40,6 +40,13 @@ def test_sizes(ctx, n, rows, a):
     check(ctx, zipf_ids(rng, n, rows, a=a), rows, inverse=n % 2 == 1)
 
 
+@pytest.mark.parametrize("n,rows", [(8193, 512), (8193, 513), (300_001, 500), (393_216, 1 << 18), (393_217, 1 << 18),
+                                    (393_217, (1 << 18) + 1), (786_433, 600)])
+def test_sizes_where_the_form_changes(ctx, n, rows):
+    """One, two and three radix passes' worth of key bits, an operation of its own."""
+    check(ctx, zipf_ids(np.random.default_rng(n + rows), n, rows, a=1.05), rows, inverse=n % 2 == 1)
+
+
 @pytest.mark.parametrize("n", [9000, 200_000])
 @pytest.mark.parametrize("what", ["one", "last", "two", "neighbours", "distinct", "descending", "periodic", "ends", "nines"])
 def test_distributions(ctx, n, what):
@@ -66,7 +73,7 @@ def sample_places(n):
     return (a + (h * np.maximum(b - a, np.uint64(1)) >> np.uint64(32))).astype(np.int64)
 
 
-@pytest.mark.parametrize("n,rows", [(16_384, 200), (30_001, 1 << 20), (100_000, 1 << 31)])
+@pytest.mark.parametrize("n,rows", [(16_384, 200), (16_384, 700), (30_001, 1 << 20), (100_000, 1 << 31)])
 def test_a_range_beyond_lds(ctx, n, rows):
     """The sample sees the first few rows only; everything else falls into the last range."""
     rng = np.random.default_rng(n)

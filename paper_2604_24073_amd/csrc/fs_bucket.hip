@@ -115,11 +115,14 @@ __device__ __forceinline__ void rank_round(bucket_sort_shared &sh, int w, uint32
         uint64_t *m = &sh.mask[w][digit];
         uint32_t *c = &sh.cnt[w][digit];
         (void)__hip_atomic_fetch_or(m, 1ull << (threadIdx.x & (kWave - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        wave_lds_order();
         peers = __hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        __hip_atomic_store(m, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         old = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        wave_lds_order();
+        __hip_atomic_store(m, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         (void)__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
+    wave_lds_order();
 }
 template <int KPT>
 __device__ __forceinline__ void sort_in_lds(int n, int bits, uint32_t *skey, uint32_t *sval, bucket_sort_shared &sh) {
@@ -300,7 +303,9 @@ __global__ __launch_bounds__(kPartThreads, 8) void bucket_partition_kernel(const
         const uint32_t before = peers_before(peers);
         uint16_t *c = cnt + w * ranges + range[r];
         const uint32_t old = valid ? *c : 0u;                // all peers read ...
+        wave_lds_order();
         if (valid && before == 0) *c = (uint16_t)(old + (uint32_t)__popcll(peers));      // ... then the first writes
+        wave_lds_order();
         rank[r] = old + before;
     }
     __syncthreads();

@@ -64,6 +64,15 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
 }
 
 
+// Between accesses by which the lanes of a wavefront tell each other something in LDS: what stands before is done, for all
+// of them, before what stands behind.  A wavefront's LDS accesses are carried out in their order, so this is for the compiler
+// only and emits no instruction.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- scans shared by the index kernels ----------------------------------------------------------------
 // inclusive scan of one value per lane over the wavefront
 template <typename T>

@@ -120,7 +120,9 @@ __device__ __forceinline__ void small_dedup_body(const small_dedup &job, char *l
             const uint64_t peers = (uint64_t)peers_lo | ((uint64_t)peers_hi << 32);
             const uint32_t before = __builtin_amdgcn_mbcnt_hi(peers_hi, __builtin_amdgcn_mbcnt_lo(peers_lo, 0));
             const uint32_t old = valid ? sh.cnt[w][digit] : 0u;       // all peers read ...
+            wave_lds_order();
             if (valid && before == 0) sh.cnt[w][digit] = (uint16_t)(old + (uint32_t)__popcll(peers));   // ... then the first writes
+            wave_lds_order();
             at[r] |= (old + before) << kPlaceBits;
         }
         __syncthreads();

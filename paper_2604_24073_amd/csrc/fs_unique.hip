@@ -204,7 +204,9 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(const uniqu
         }
         const uint32_t before = __popcll(peers & lt);
         const uint32_t old = valid ? cnt[w][digit] : 0u;              // all peers read ...
+        wave_lds_order();
         if (valid && before == 0) cnt[w][digit] = (uint16_t)(old + (uint32_t)__popcll(peers));   // ... then the first one writes
+        wave_lds_order();
         rank[r] = old + before;
     }
     __syncthreads();

@@ -97,12 +97,27 @@ def test_an_id_out_of_range_is_reported_and_leaves_the_other_rows_alone(ctx):
 @pytest.mark.parametrize("sizes", [(20_000, 300_000), (70_000, 3, 9_000), (10_240, 5_000), (10_241, 10_240)])
 def test_index_halves_of_different_sizes_in_one_chain(sizes):
     """Jobs that share their launches have ranges and tiles of their own number; what they write is the same as alone."""
+    check_chain(sizes, [400_000] * len(sizes))
+
+
+@pytest.mark.parametrize("sizes,rows,inverse", [
+    ((400_000, 20_000), (1 << 18, 900), True),               # two passes' worth of bits, beyond one wave of ranges
+    ((40_000, 4_097, 12_289), (512, 500, 2), False),         # radix, one pass
+    ((4_096, 20_000, 4_097), (1 << 33, 1 << 40, 0), False),  # radix, 64-bit keys (0: table of unknown size)
+    ((12_289, 4_097, 30_000), (700, 1 << 33, 400_000), True),     # one table that the ranges cannot take, two that they could
+    (((1 << 20) + 1, 9_000), (400_000, 3_000), False)])           # one batch beyond them
+def test_index_halves_of_every_form_in_one_chain(sizes, rows, inverse):
+    check_chain(sizes, rows, inverse)
+
+
+def check_chain(sizes, table_rows, inverse=True):
     rng = np.random.default_rng(sum(sizes))
-    rows, keep, args, lays = 400_000, [], [], []
+    keep, args, lays = [], [], []
     c = fs.Context(max_ids=max(sizes), max_dim=4)
-    for n in sizes:
-        ids, nxt = zipf_ids(rng, n, rows, a=1.1), zipf_ids(rng, n, rows, a=1.1)
-        lay0, lay1 = fs.alloc_layout(n, "cuda"), fs.alloc_layout(n, "cuda", sorted_ids=True)
+    for n, rows in zip(sizes, table_rows):
+        most = rows if rows > 0 else 1 << 45
+        ids, nxt = zipf_ids(rng, n, most, a=1.1), zipf_ids(rng, n, most, a=1.1)
+        lay0, lay1 = fs.alloc_layout(n, "cuda"), fs.alloc_layout(n, "cuda", inverse=inverse, sorted_ids=True)
         split = fs.alloc_split(n, n, "cuda")
         fs.fs_unique_ids(c, dev(ids), rows, out=lay0)
         keep.append([torch.zeros((k, 4), device="cuda") for k in (8, n, n)] + [dev(nxt), split, lay0])
@@ -110,12 +125,12 @@ def test_index_halves_of_different_sizes_in_one_chain(sizes):
                               lay1, split, None, keep[-1][2])
         a.num_rows = rows                                     # the index half touches no table row
         args.append(a)
-        lays.append((lay1, nxt, ids, split))
+        lays.append((lay1, nxt, ids, split, rows))
     fs.fs_step_forward_ahead_batch(c, fs.step_args_array(args))
     assert fs.fs_check_async(c) == fs.FS_OK
-    for lay, nxt, ids, split in lays:
+    for lay, nxt, ids, split, rows in lays:
         want, sp = O.unique_ids(nxt, rows), O.collision_split(O.unique_ids(ids, rows)["unique"], O.unique_ids(nxt, rows)["unique"])
-        for k in ("unique", "seg_offsets", "perm", "inverse"):
+        for k in ("unique", "seg_offsets", "perm") + (("inverse",) if inverse else ()):
             assert np.array_equal(lay[k].cpu().numpy()[:len(want[k])], want[k]), k
         assert np.array_equal(lay["sorted_ids"].cpu().numpy()[:len(nxt)], np.sort(nxt))
         assert split["counts"].cpu().numpy().tolist() == [len(sp[k]) for k in ("co", "ex", "ex_next")]

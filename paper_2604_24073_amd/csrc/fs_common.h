@@ -43,6 +43,7 @@ constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 constexpr int64_t kSmallIds = 16384;
 constexpr int64_t kSmallIdsAhead = 10240;
 constexpr int64_t kSmallIdsInline = 8192;
+static_assert(kSmallIdsAhead <= kSmallIds && kSmallIdsInline <= kSmallIds, "what the LDS holds");
 // Without the dedup in front the chain is two launches (the split alone) or three: IDs up to which the one workgroup
 // does those on the caller's stream.  Split alone, one workgroup against two launches: 4096 IDs 11.4 / 11.6 us, 5000
 // 13.8 / 11.4, 8192 18.9 / 11.8; with the class order against three: 6144 22.5 / 23.6, 7000 24.7 / 24.4, 8192 28.4 / 24.1.

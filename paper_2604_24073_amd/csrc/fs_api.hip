@@ -844,7 +844,8 @@ int enqueue_index_work_batch(fs_ctx *ctx, int count, const fs_step_args *a, cons
                               x.n_unique_t1_dev, x.sorted_ids_t1};
         sj[k] = fs_split_job{x.u_t, t ? x.n_unique_t_dev : nullptr, x.u_t1, t1 ? x.n_unique_t1_dev : nullptr,
                              t ? x.n_t : 0, t1 ? x.n_t1 : 0, x.co, x.co_slot, x.ex, x.ex_slot, x.ex_next,
-                             x.ex_next_slot, x.counts_dev, t ? x.seg_offsets_t : nullptr, t1 ? x.co_flag_t1 : nullptr};
+                             x.ex_next_slot, x.counts_dev, t ? x.seg_offsets_t : nullptr, t1 ? x.co_flag_t1 : nullptr,
+                             key_bits_of(x.num_rows)};
         cj[k] = fs_class_job{x.perm_t, x.n_unique_t_dev, x.seg_offsets_t, t ? x.n_t : 0, t ? x.n_t : 0, x.cperm, x.cslot,
                              x.cstart, x.class_pos_dev, x.u_t, x.short_rec};
         fused = fused && t1 && !(ahead && ahead[k]) && !(layout_in && layout_in[k]);

@@ -34,16 +34,6 @@ constexpr int kScanTile = kScanThreads * kScanIpt;
 constexpr int kClassOrderTiles = 60 * 1024 / (2 * (int)sizeof(int));
 constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
-// IDs of a batch whose index half fits the LDS of one workgroup (fs_small.hip), and the most it takes.  On the caller's
-// stream: up to where the chain of launches over many workgroups is the faster one (a whole step, one workgroup against
-// the chain: 1024 IDs 25.4 / 40.7 us, 4096 40.1 / 53.4, 6144 53.8 / 62.2, 8192 59.9 / 62.6).  Ahead of time a launch costs
-// whatever runs beside it and the workgroup has the iterations ahead to finish, but it must keep up with them: ten steps,
-// one workgroup against the chain, one table: 4096 IDs 241 / 308 us, 8192 278 / 315, 12288 354 / 335; three tables: 4096
-// 408 / 486, 8192 445 / 500, 12288 611 / 560.
-constexpr int64_t kSmallIds = 16384;
-constexpr int64_t kSmallIdsAhead = 10240;
-constexpr int64_t kSmallIdsInline = 8192;
-static_assert(kSmallIdsAhead <= kSmallIds && kSmallIdsInline <= kSmallIds, "what the LDS holds");
 // Without the dedup in front the chain is two launches (the split alone) or three: IDs up to which the one workgroup
 // does those on the caller's stream.  Split alone, one workgroup against two launches: 4096 IDs 11.4 / 11.6 us, 5000
 // 13.8 / 11.4, 8192 18.9 / 11.8; with the class order against three: 6144 22.5 / 23.6, 7000 24.7 / 24.4, 8192 28.4 / 24.1.
@@ -124,6 +114,7 @@ struct fs_split_job {
     int64_t *counts_dev;
     const int32_t *seg_offsets_t;   // optional; given, the per-tile occurrence counts the class order needs are left in the scratch
     uint8_t *flag_t1_out = nullptr; // optional [cap_t1]: 1 where the row of u_t1 is also in u_t (a collision row), else 0
+    int key_bits = 63;              // of the dedup in front of it (it decides where the one workgroup ends)
 };
 struct fs_class_job {
     const int32_t *perm;

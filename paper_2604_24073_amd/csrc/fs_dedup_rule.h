@@ -1,5 +1,6 @@
-// Sizes of the two dedups of many workgroups (fs_bucket.hip, fs_unique.hip) and which of them a batch takes.  Host code
-// only, no HIP, so that the rule can be compiled and looked at by itself.
+// Which form the index half of a batch takes: one workgroup (fs_small.hip), or a chain of launches whose dedup goes by ranges
+// of keys (fs_bucket.hip) or by radix passes (fs_unique.hip).  Host code only, no HIP, so that the rules can be compiled and
+// looked at by themselves.
 #pragma once
 
 #include <stdint.h>
@@ -22,6 +23,23 @@ inline int key_bits_of(int64_t num_rows) {
     return kb;
 }
 inline int radix_passes(int key_bits) { return (key_bits + kRadixBits - 1) / kRadixBits; }
+
+// IDs of a batch whose index half fits the LDS of one workgroup, and the most it takes.  On the caller's stream: up to where
+// the chain of launches over many workgroups is the faster one (a whole step, one workgroup against the chain: 1024 IDs
+// 25.4 / 40.7 us, 4096 40.1 / 53.4, 6144 53.8 / 62.2, 8192 59.9 / 62.6).  Ahead of time a launch costs whatever runs beside
+// it and the workgroup has the iterations ahead to finish, but it must keep up with them, and it sorts by 8 bits a pass.
+// Ten steps, one workgroup / the chain, tables of 64 columns, median of three processes: two passes, 11000 IDs, one table of
+// 500 rows 263 / 315 us, of 65536 283 / 310, three 439 / 591 and 500 / 568; 12200 IDs 263 / 303, 290 / 315, 445 / 591, 521 /
+// 524.  Three passes, of 1 M rows, one and three tables: 9000 IDs 309 / 318, 565 / 572; 10200 320 / 315, 573 / 540; 11000
+// 322 / 318, 590 / 527; 12200 336 / 319, 620 / 540.
+constexpr int64_t kSmallIds = 16384;
+constexpr int kSmallBits = 8;                             // most bits of a radix pass
+constexpr int64_t kSmallIdsInline = 8192;
+constexpr int64_t kSmallIdsAhead = 10240, kSmallIdsAheadTwoPasses = 12288;
+inline int64_t small_index_ids(bool callers_stream, int key_bits) {
+    return callers_stream ? kSmallIdsInline : key_bits <= 2 * kSmallBits ? kSmallIdsAheadTwoPasses : kSmallIdsAhead;
+}
+static_assert(kSmallIdsAheadTwoPasses <= kSmallIds && kSmallIdsInline <= kSmallIds, "what the LDS holds");
 
 // Dedup by ranges of keys: most IDs of a batch (a place and a rank share 32 bits), IDs of a tile, most ranges, and the IDs
 // a range is meant to hold (up to that many; a power of two of ranges).

@@ -1,5 +1,5 @@
 // The index half of a small batch on ONE workgroup: dedup, collision split and class order of up to kSmallIdsInline IDs
-// (8192) on the caller's stream, kSmallIdsAhead (10240) ahead of time.
+// (8192) on the caller's stream, of 10240 or 12288 ahead of time (small_index_ids in fs_dedup_rule.h).
 //
 // The kernels of fs_bucket.hip or fs_unique.hip and of fs_split.hip are a chain of up to seven launches (eleven of the radix
 // sort); on a batch of a few thousand IDs each of them is a handful of workgroups and takes 2.5 to 9 us whatever it does, so
@@ -22,7 +22,6 @@ namespace fs {
 
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kSmallBits = 8;                            // most bits of a radix pass
 constexpr int kSmallRadix = 1 << kSmallBits;
 static_assert(kSmallIds == kSmallThreads * 16, "KPT is at most 16");
 
@@ -483,20 +482,22 @@ static int small_dispatch(fs_ctx *ctx, const small_batch &batch, int count, int6
 }
 
 // scratch set 0 belongs to the caller's stream and the side stream, the others to the index streams
-static int64_t small_limit(int set0) { return set0 == 0 ? kSmallIdsInline : kSmallIdsAhead; }
+static int64_t small_limit(int set0, int key_bits) { return small_index_ids(set0 == 0, key_bits); }
 
 bool small_unique_fits(int count, const fs_unique_job *jobs, int set0) {
-    const int64_t most = small_limit(set0);
-    for (int k = 0; k < count; ++k)
-        if (jobs[k].n > most || key_bits_of(jobs[k].num_rows) > 32) return false;
+    for (int k = 0; k < count; ++k) {
+        const int kb = key_bits_of(jobs[k].num_rows);
+        if (kb > 32 || jobs[k].n > small_limit(set0, kb)) return false;
+    }
     return count >= 1 && count <= kMaxBatch;
 }
 
 bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0, bool with_dedup) {
-    int64_t most = small_limit(set0);
-    if (set0 == 0 && !with_dedup) most = cls ? kSmallClassesInline : kSmallSplitInline;
-    for (int k = 0; k < count; ++k)
+    for (int k = 0; k < count; ++k) {
+        int64_t most = small_limit(set0, jobs[k].key_bits);
+        if (set0 == 0 && !with_dedup) most = cls ? kSmallClassesInline : kSmallSplitInline;
         if (jobs[k].cap_t > most || jobs[k].cap_t1 > most || (cls && cls[k].n > most)) return false;
+    }
     return count >= 1 && count <= kMaxBatch;
 }
 

@@ -17,7 +17,7 @@ mark between blocks on every stream that carries steps (no wait anywhere); the r
 synchronisation on both sides.  `ms_per_step` is the MEDIAN block / K; `ms_per_step_whole_region` is the wall
 clock of all blocks / (blocks * K).
 
-Prints ONE JSON line.  `python bench.py --summarize-counters DIR [DIR ...]` instead prints the per-kernel means
+Prints ONE JSON line on stdout (and everything measured beside it on stderr).  `python bench.py --summarize-counters DIR [DIR ...]` instead prints the per-kernel means
 of rocprofv3 counter CSVs (the rows of profiles/hbm_traffic_per_launch.txt).
 """
 from __future__ import annotations
@@ -371,6 +371,46 @@ def bench_config(args, ci, extras):
     return res
 
 
+PER_CONFIG = ("value", "us_per_step", "ms_per_step_whole_region", "rows_per_step", "host_enqueue_us_per_step",
+              "step_algorithmic_bytes", "step_frac_of_hbm_peak", "step_measured_traffic_bytes",
+              "step_measured_traffic_frac_of_hbm_peak", "kernel_avg_us", "bench_seconds")
+
+
+def rounded(x):
+    """Six significant digits: more than any of the figures repeats to."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: rounded(v) for k, v in x.items()}
+    return [rounded(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def result_line(args, configs, results, device):
+    """The one JSON line of a run: the headline and, per configuration, what it is made of.  A few thousand characters at
+    most, for a reader that keeps only the end of what a program prints; everything else goes to stderr."""
+    head = results[configs[0]]
+    roofline = head["roofline"]
+    if roofline:
+        roofline = {k: v for k, v in roofline.items() if k not in ("note", "all_kernels")}
+    cpu = head["cpu_baseline"]
+    if cpu:
+        cpu = {k: v for k, v in cpu.items() if k != "sample"}
+    per = {}
+    for c in configs:
+        r = results[c]
+        per[f"configs[{c}]"] = {"workload": r["workload"].split(":")[0], "dtype": r["dtype"], **{k: r[k] for k in PER_CONFIG}}
+        if "step_without_index_chains" in r:
+            per[f"configs[{c}]"]["us_per_step_without_index_chains"] = r["step_without_index_chains"]["us_per_step"]
+    return rounded({
+        "metric": METRIC, "value": head["value"], "unit": "rows/s", "n_gpus": 1, "steps": args.steps,
+        "warmup": args.warmup, "ms_per_step": head["ms_per_step"], "higher_is_better": True, "scaling": "weak",
+        "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic",
+        "config": {"workload": head["workload"], "timed_blocks": args.blocks, "steps_per_block": args.steps,
+                   "also_timed": [results[c]["workload"].split(":")[0] for c in configs[1:]]},
+        "step_frac_of_hbm_peak": head["step_frac_of_hbm_peak"], "roofline": roofline, "cpu_baseline": cpu,
+        "per_config": per, "device": device})
+
+
 def measure_row_ceiling(loop, bufs, step_gbps):
     """The step's access pattern with nothing else in the way, on this workload's own tables: the distinct rows that
     the batches of a table touch, in a shuffled order, read whole by fs_stream_row_read and thrown away (one launch per
@@ -669,19 +709,9 @@ def main() -> int:
         results[ci] = r
         print(f"bench.py: configs[{ci}] {r['us_per_step']:.1f} us/step, {r['step_frac_of_hbm_peak']:.3f} of HBM peak "
               f"({r['bench_seconds']:.0f} s)", file=sys.stderr, flush=True)
-    head = results[configs[0]]
-    out = {
-        "metric": METRIC, "value": head["value"], "unit": "rows/s", "n_gpus": 1, "steps": args.steps,
-        "warmup": args.warmup, "ms_per_step": head["ms_per_step"], "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic",
-        "config": {"workload": head["workload"], "timed_blocks": args.blocks, "steps_per_block": args.steps,
-                   "also_timed": [results[c]["workload"].split(":")[0] for c in configs[1:]]},
-        "step_frac_of_hbm_peak": head["step_frac_of_hbm_peak"],
-        "roofline": head["roofline"], "cpu_baseline": head["cpu_baseline"],
-        "per_config": {f"configs[{c}]": results[c] for c in configs},
-        "device": device_info(),
-    }
-    print(json.dumps(out))
+    # what was measured beside the metric, whole, for a reader; the line on stdout is what a program reads
+    print("bench.py: details " + json.dumps({f"configs[{c}]": results[c] for c in configs}), file=sys.stderr, flush=True)
+    print(json.dumps(result_line(args, configs, results, device_info())))
     return 0
 
 

@@ -1326,8 +1326,10 @@ int fs_step_forward(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
 }
 
 // IDs of both batches from which the self-contained step takes its index half to the side stream: two cross-stream waits
-// of 10-12 us of host time each against a chain of launches behind the row work.  Behind / beside it on a 4M x 128 table,
-// IDs of one batch: 16 k 68 / 79 us, 32 k 75 / 82, 48 k 88 / 92, 64 k 85 / 89, 96 k 101 / 98, 128 k 105 / 102.
+// of 10-12 us of host time each against a chain of launches behind the row work.  Behind / beside it, IDs of one batch: on a
+// 4M x 128 table 16 k 68 / 79 us, 32 k 75 / 82, 48 k 88 / 92, 56 k 85.2 / 86.4, 64 k 87.5 / 88.9, 80 k 95.8 / 97.0, 88 k
+// 97.5 / 98.2, 96 k 102.8 / 101.5, 128 k 107.6 / 99.2; on a 49 k x 160 bf16 table, whose rows the caches hold, 56 k 79.5 /
+// 80.6, 64 k 83.3 / 81.0, 80 k 87.3 / 86.9, 96 k 93.2 / 91.6, 128 k 102.2 / 94.4.  The two cross on either side of the line.
 constexpr int64_t kStepSideIds = 131072;
 
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
@@ -1396,11 +1398,15 @@ int fs_prioritized_step_two_part_multi(fs_ctx *ctx, const fs_step_args *cur, con
 // Bytes of gradients and looked-up rows of a call up to which the pipelined step stays on one stream: both passes of
 // every table in one launch, the lookups behind them, no wait between streams (10-12 us of host time each, with a
 // second thread to pay them) and one launch less per row width.  What it gives up is the deferred pass running beside
-// the lookup.  Ten steps of one 2M x 128 table, two streams against one: 32 k IDs a batch (31 MB) 455 / 415 us, 65 k
-// (64 MB) 519 / 482, 98 k (96 MB) 570 / 568, 110 k (107 MB) 611 / 621, 120 k (117 MB) 644 / 661, 130 k (127 MB) 680 / 702,
-// 262 k (of 4M rows) 1041 / 1056; two tables of 49 k (96 MB) 785 / 759, of 60 k (117 MB) 835 / 819, four of 30 k (117 MB)
-// 916 / 888; eight tables of 2 GB 5616 / 6039.  With the lookup in two parts, whose second gather the one-stream form does
-// without: one table of 110 k (107 MB) 648 / 638, of 120 k (117 MB) 679 / 678, of 130 k (127 MB) 709 / 716.
+// the lookup.  Ten steps of tables of 2M x 128, two streams / one (median of three processes): one table of 32 k IDs a batch
+// (31 MB) 455 / 415 us, 102 k (100 MB) 508 / 461, 118 k (115 MB) 544 / 530, 133 k (130 MB) 599 / 569, 164 k (160 MB) 659 / 644,
+// 184 k (180 MB) 701 / 705, 205 k (200 MB) 752 / 764; two tables of 51 k (100 MB) 573 / 554, of 67 k (130 MB) 644 / 635, of 74 k
+// (145 MB) 656 / 667, of 92 k (180 MB) 752 / 801; four of 33 k (130 MB) 712 / 695, of 37 k (145 MB) 756 / 783, of 41 k (160 MB)
+// 763 / 864; eight of 17 k (130 MB) 860 / 850, of 19 k (145 MB) 891 / 962, of 23 k (180 MB) 975 / 1149.  With the lookup in two
+// parts, whose second gather the one-stream form does without: one table of 123 k (120 MB) 579 / 554, of 164 k (160 MB) 694 /
+// 666, of 184 k (180 MB) 747 / 735; two of 61 k (120 MB) 639 / 616, of 82 k (160 MB) 734 / 718, of 92 k (180 MB) 791 / 799.
+// Both lines are known to be low: the forms cross at about 170 MB for one table and at 135 for several (170 in two parts), and
+// between a line and its crossing a step takes up to 5 % longer than it would on one stream (two tables in two parts 7 %).
 constexpr int64_t kOneStreamBytes = 100 << 20, kOneStreamBytesMore = 120 << 20;     // one whole lookup; otherwise
 
 static int pipelined_impl(fs_ctx *ctx, const fs_step_args *cur, const fs_step_args *next, int count, fs_stream stream,

@@ -77,6 +77,7 @@ __device__ __forceinline__ void wave_lds_order() {
 // inclusive scan of one value per lane over the wavefront
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v) {
+    static_assert((T)0.5 == (T)0, "whole numbers");
     if constexpr (sizeof(T) == 4) {
         // rows of sixteen lanes by row shifts, then the last lane of a row to the next row and of a half to the other
         // half: six VALU instructions instead of six trips through the LDS crossbar

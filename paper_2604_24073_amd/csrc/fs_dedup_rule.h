@@ -65,7 +65,9 @@ constexpr int64_t kBucketOneWave = (int64_t)kBucketMean << 9;
 //     a place beside the row work sooner, ten steps 500 k 866 / 865, 700 k 1129 / 1093, 1 M 1585 / 1487 (200 k rows 1790 /
 //     1632), self-contained step of 400 k 121 / 124, of 700 k 160 / 156.
 //   three and more: ranges at every size they can take.  4 M rows alone 300 k 62 / 44, 786 k 77 / 73, 1 M 86 / 82 (mean of 16
-//     batches, those with a range beyond LDS among them); ten steps of 1 M 2200 / 2038; 2^30 rows alone, 1 M 118 / 88.
+//     batches, those with a range beyond LDS among them); ten steps of 1 M 2200 / 2038; 2^30 rows alone, 1 M 118 / 88.  Only
+//     batches of next to nothing but one row are the slower for it (400 k times one row 54 / 60), and those with a range beyond
+//     LDS (1 M in runs of fifty 71 / 83).
 // most_ids, key_bits: the largest batch and the widest key of the dedups that share the launches; alone: an operation of its
 // own, not part of an index half.
 inline bool dedup_by_ranges(int64_t most_ids, int key_bits, bool alone) {

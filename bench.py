@@ -279,9 +279,9 @@ def bench_config(args, ci, extras):
 
     # ---- roofline of the dominant kernel: the event pairs of the first group's context bracket what one call
     # enqueues of one kind (the class pass of one class, or the gathers) for ALL tables of that group - one launch
-    # per row width - on the stream it is launched on, inside the timed steps
+    # for eight tables - on the stream it is launched on, inside the timed steps
     grp0 = [(t, stats[bufs.index(t)]) for t in loop.groups[0]]
-    widths = len({t.dim * t.w for t, _ in grp0})
+    shared = -(-len(grp0) // fs.FS_MAX_AHEAD_BATCH)
     per_kernel = {}
     if kernel_ms.get("gather"):
         gb = sum(sum(algorithmic_bytes(t.n[b], s[b]["u"], t.n[(b + 1) % T], s[(b + 1) % T]["u"], t.dim, t.w)["gather"]
@@ -300,7 +300,7 @@ def bench_config(args, ci, extras):
     wl = f"configs[{ci}]"
 
     def traffic_of(name):
-        # measured bytes of what one event pair brackets: the launches of every row width of that kind
+        # measured bytes of what one event pair brackets: the launches of that kind
         if name == "class_pass_kernel":
             t2 = [traffic_of(name + sfx) for sfx in ("(priority_pass)", "(deferred_pass)")]
             return (t2[0] + t2[1]) / 2 if all(t2) else None
@@ -312,11 +312,11 @@ def bench_config(args, ci, extras):
         name = max(cand, key=lambda k: cand[k][0] * cand[k][2])
         ms, nbytes, launches = cand[name]
         achieved = nbytes / (ms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": name, "launches_per_step": launches * widths, "achieved": achieved,
+        roofline = {"bound": "hbm", "kernel": name, "launches_per_step": launches * shared, "achieved": achieved,
                     "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
                     "traffic": traffic_of(name), "avg_launch_us": ms * 1e3, "algorithmic_bytes_per_launch": nbytes,
-                    "note": ("per launch; " if widths == 1 and not multi else
-                             f"the {len(grp0)} tables of group 0 ({widths} launch(es) bracketed together); ") +
+                    "note": ("per launch; " if len(grp0) == 1 and not multi else
+                             f"the {len(grp0)} tables of group 0 ({shared} launch(es) bracketed together); ") +
                             "duration from HIP event pairs on the kernel's own stream inside the timed steps, one "
                             f"step in {args.time_every}; in the pipelined step the kernel shares the chip with the other "
                             "passes",

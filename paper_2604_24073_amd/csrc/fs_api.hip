@@ -908,7 +908,7 @@ int enqueue_or_consume_index_half(fs_ctx *ctx, const fs_step_args *a, bool have_
 }
 
 // update_embedding for one class of rows of iteration t (0: priority pass, 1: deferred pass) of `count`
-// tables (`use[k]`: table k has gradients); tables of one row width share their launches
+// tables (`use[k]`: table k has gradients); tables of one dtype share their launches
 fs_class_pass_job class_job(const fs_step_args *a, int cls) {
     if (cls == 2) cls = 0;                                   // both passes in one launch: the job names class 0
     return fs_class_pass_job{a->grads_t, a->n_t, a->dim, a->cperm, a->cslot, a->class_pos_dev, a->seg_offsets_t,
@@ -1397,7 +1397,7 @@ int fs_prioritized_step_two_part_multi(fs_ctx *ctx, const fs_step_args *cur, con
 
 // Bytes of gradients and looked-up rows of a call up to which the pipelined step stays on one stream: both passes of
 // every table in one launch, the lookups behind them, no wait between streams (10-12 us of host time each, with a
-// second thread to pay them) and one launch less per row width.  What it gives up is the deferred pass running beside
+// second thread to pay them) and one launch less.  What it gives up is the deferred pass running beside
 // the lookup.  Ten steps of tables of 2M x 128, two streams / one (median of three processes): one table of 32 k IDs a batch
 // (31 MB) 455 / 415 us, 102 k (100 MB) 508 / 461, 118 k (115 MB) 544 / 530, 133 k (130 MB) 599 / 569, 164 k (160 MB) 659 / 644,
 // 184 k (180 MB) 701 / 705, 205 k (200 MB) 752 / 764; two tables of 51 k (100 MB) 573 / 554, of 67 k (130 MB) 644 / 635, of 74 k

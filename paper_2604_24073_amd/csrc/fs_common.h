@@ -343,8 +343,8 @@ int launch_reduce_update(fs_ctx *, int cls, const float *grads, int64_t n, int32
                          int64_t num_rows, float lr, float eps, float *reduced, hipStream_t s,
                          const int32_t *short_rec, const int64_t *n_rows_dev);
 int launch_batch_update(fs_ctx *, const fs_batch_update_job &job, hipStream_t s);
-// the class passes (class `cls`; 2: both, the jobs name class 0) / the gathers of `count` tables: tables of one dtype and
-// row width share launches
+// the class passes (class `cls`; 2: both, the jobs name class 0) / the gathers of `count` tables: tables of one
+// dtype share launches, whatever their widths
 int launch_reduce_update_batch(fs_ctx *, int cls, int count, const fs_class_pass_job *jobs, hipStream_t s);
 int launch_gather_batch(fs_ctx *, int count, const fs_gather_job *jobs, hipStream_t s);
 // `timing`: optional event pair recorded around the main (chunk) kernel only

@@ -28,6 +28,8 @@
 // device-scope relaxed atomic stores and loads, which go through to the coherent level, ordered
 // against the counter by waiting for the stores to be acknowledged.  A device-scope fence would
 // do the same but writes back the whole dirty L2 every time - measured 10x the kernel's time.
+#include <algorithm>
+
 #include "fs_common.h"
 #include "fs_device.h"
 
@@ -180,21 +182,29 @@ struct chunk_view {
     int start[2], len[2];          // extents of the first and the last segment (positions)
 };
 
+// Every segment of the position-cut path has more than FS_SHORT_SEGMENT positions, so only a few end inside one chunk:
+// their sums wait in LDS and are all applied in one round at the end of the chunk.
+constexpr int kParkedMost = kWave / (FS_SHORT_SEGMENT + 1) + 1;
+template <int LPR>
+struct parked_rows {
+    f32x4 sum[kFusedWaves][kParkedMost * LPR];
+    int64_t row[kFusedWaves][kParkedMost];
+    int slot[kFusedWaves][kParkedMost];
+};
+
 template <bool BF16, int LPR, int UNR>
-__device__ __forceinline__ void long_chunk(const chunk_view &ch, const f32x4 *__restrict__ grads,
+__device__ __forceinline__ void long_chunk(parked_rows<LPR> &sh, const chunk_view &ch, const f32x4 *__restrict__ grads,
                                            const int64_t *__restrict__ u_t, void *table, float *state, int64_t num_rows,
                                            int gvec, float lr, float eps, f32x4 *reduced, double *part_head,
                                            double *part_last, int *cnt_seg, int *cnt_sup, bool bad, int *flags) {
     constexpr int GPW = kWave / LPR;          // rows per wavefront instruction
     constexpr int BP = GPW * UNR;             // positions per batch
-    // every segment here has more than FS_SHORT_SEGMENT positions, so only a few end inside one chunk:
-    // their sums wait in LDS and are all applied in one round at the end of the chunk
-    constexpr int CAP = kWave / (FS_SHORT_SEGMENT + 1) + 1;
+    constexpr int CAP = kParkedMost;
     constexpr int RU = FS_FUSED_RU;
     static_assert(BP <= kWave, "one tail word");
-    __shared__ f32x4 stage[kFusedWaves][CAP * LPR];
-    __shared__ int64_t stage_row[kFusedWaves][CAP];
-    __shared__ int stage_slot[kFusedWaves][CAP];
+    auto &stage = sh.sum;
+    auto &stage_row = sh.row;
+    auto &stage_slot = sh.slot;
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wib = threadIdx.x / kWave;
@@ -260,7 +270,10 @@ __device__ __forceinline__ void long_chunk(const chunk_view &ch, const f32x4 *__
 #pragma unroll
                 for (int c = 0; c < 4; ++c) acc[c] += (double)vv[u][c];
             } else {
-#pragma unroll
+                // narrow rows: written out for each of its positions the end of a segment is most of the kernel's code, and
+                // took 187 registers of rows of 32 columns where the rolled loop takes 110
+                constexpr int kUnrollGroups = GPW <= 4 ? GPW : 1;
+#pragma unroll kUnrollGroups
                 for (int g = 0; g < GPW; ++g) {
                     if (grp == g) {
 #pragma unroll
@@ -387,7 +400,7 @@ __device__ __forceinline__ void long_chunk(const chunk_view &ch, const f32x4 *__
 // The position-cut path over the class order: chunk `block * kFusedWaves + wavefront` of the class's positions.
 template <bool BF16, int LPR, int UNR>
 __device__ __forceinline__ void long_segments_body(
-    const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ cperm,
+    parked_rows<LPR> &sh, const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ cperm,
     const int32_t *__restrict__ cslot, const int32_t *__restrict__ class_pos, int cls, int n,
     const int32_t *__restrict__ seg_offsets, const int32_t *__restrict__ cstart, const int64_t *__restrict__ u_t,
     void *table, float *state, int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, double *part_head,
@@ -441,7 +454,7 @@ __device__ __forceinline__ void long_segments_body(
         ch.start[which] = __shfl(meta, which * 3 + 0, kWave);
         ch.len[which] = __shfl(meta, which * 3 + 2, kWave) - __shfl(meta, which * 3 + 1, kWave);
     }
-    long_chunk<BF16, LPR, UNR>(ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
+    long_chunk<BF16, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
                                cnt_seg, cnt_sup, bad, flags);
 }
 
@@ -450,7 +463,7 @@ __device__ __forceinline__ void long_segments_body(
 // position with a 64-ary search; its positions touch at most 64 consecutive segments, whose boundaries its lanes hold.
 template <bool BF16, int LPR, int UNR>
 __device__ __forceinline__ void long_segments_of_layout(
-    const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ perm, int n,
+    parked_rows<LPR> &sh, const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ perm, int n,
     const int32_t *__restrict__ seg_offsets, const int64_t *__restrict__ u_t, int n_u, void *table, float *state,
     int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, double *part_head, double *part_last, int *cnt_seg,
     int *cnt_sup, int *flags) {
@@ -498,7 +511,7 @@ __device__ __forceinline__ void long_segments_of_layout(
     ch.len[1] = __shfl(my_end, ch.last, kWave) - ch.start[1];
     ch.head_cut = (ch.live & 1ull) != 0 && ch.start[0] < a;
     ch.rest = ((ch.live >> ch.last) & 1ull) != 0 && ch.start[1] + ch.len[1] > a + span;
-    long_chunk<BF16, LPR, UNR>(ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
+    long_chunk<BF16, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
                                cnt_seg, cnt_sup, false, flags);
 }
 
@@ -670,16 +683,22 @@ __device__ __forceinline__ void short_rows_body(
     if (bad) atomicOr(flags, kFlagInternal);
 }
 
-// One launch per class: the first `long_blocks` workgroups walk the class order (rows with many
+template <int LPR> constexpr int fused_unr() {
+    return (kWave / (kWave / LPR)) < FS_FUSED_UNR ? kWave / (kWave / LPR) : FS_FUSED_UNR;
+}
+
+// One launch per class: the first `long_blocks` workgroups of a pass walk the class order (rows with many
 // occurrences, position-cut), the others the records of the rows with few.  The long part goes
 // first because its last arrivers have the longest dependent chains; workgroups past the end of
 // either part leave at once, so an empty part costs nothing but their dispatch.
-// A launch takes the class passes of up to kMaxBatch tables of one row width (blockIdx.y picks the table):
-// a pass is about one residency round of the chip however small it is, so the tables of a shard are
-// better walked side by side than one after the other.
+// A launch takes the class passes of up to kMaxBatch tables (blockIdx.y picks the pass): a pass is about one residency
+// round of the chip however small it is, so the tables of a shard are better walked side by side than one after the
+// other, of whatever widths: ten steps of three tables of 15 k IDs x 96, 32 and 200 columns, with their lookups, 635 us
+// with a launch per width and 509 in shared ones; of eight tables of 64, 128 and 256 columns 5474 and 4938 (nine large
+// launches a step against three, each of which ends in a tail of its own).
 struct class_pass_job {
     const f32x4 *grads;
-    int n, long_blocks, blocks, chunk_log2, gvec, cls;
+    int n, long_blocks, blocks, chunk_log2, gvec, cls, lpr;
     float lr, eps;
     const int32_t *cperm, *cslot, *class_pos, *seg_offsets, *cstart, *recs;
     const int64_t *u_t, *n_rows_dev;
@@ -694,24 +713,42 @@ struct class_pass_batch {
     class_pass_job j[kMaxBatch];
 };
 
-// CLS (0: priority pass, 1: deferred pass, 2: both of every table, one after the other in the grid) is a template
-// parameter so that the passes are kernels of their own by name in a profile; the code is the same.
-template <bool BF16, int LPR, int UNR, int SU, int CLS>
-__global__ __launch_bounds__(kFusedWaves *kWave) void class_pass_kernel(const class_pass_batch batch, int *flags) {
-    const class_pass_job &job = batch.j[blockIdx.y];
-    FS_WG_TRACE(8 + CLS);
-    if ((int)blockIdx.x >= job.blocks) return;
-    if ((int)blockIdx.x < job.long_blocks)
-        long_segments_body<BF16, LPR, UNR>((int)blockIdx.x, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos, CLS < 2 ? CLS : job.cls,
-                                                  job.n, job.seg_offsets, job.cstart, job.u_t, job.table, job.state,
-                                                  job.num_rows, job.gvec, job.lr, job.eps, job.reduced, job.part_head,
-                                                  job.part_last, job.cnt_seg, job.cnt_sup, flags);
+template <bool BF16, int LPR>
+__device__ __forceinline__ void class_pass_body(parked_rows<LPR> &sh, const class_pass_job &job, int cls, int block, int *flags) {
+    if (block < job.long_blocks)
+        long_segments_body<BF16, LPR, fused_unr<LPR>()>(sh, block, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos,
+                                                        cls, job.n, job.seg_offsets, job.cstart, job.u_t, job.table, job.state,
+                                                        job.num_rows, job.gvec, job.lr, job.eps, job.reduced, job.part_head,
+                                                        job.part_last, job.cnt_seg, job.cnt_sup, flags);
     else {
         int64_t n_rows = *job.n_rows_dev;
         if (n_rows > job.n) n_rows = job.n;
-        short_rows_body<BF16, LPR, SU, false>((int)blockIdx.x - job.long_blocks, job.blocks - job.long_blocks, job.grads,
-                                              job.n, row_source{job.recs, nullptr, nullptr, nullptr}, n_rows, job.table,
-                                              job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
+        short_rows_body<BF16, LPR, FS_SHORT_UNR, false>(block - job.long_blocks, job.blocks - job.long_blocks, job.grads, job.n,
+                                                        row_source{job.recs, nullptr, nullptr, nullptr}, n_rows, job.table,
+                                                        job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
+    }
+}
+
+// CLS (0: priority pass, 1: deferred pass, 2: both of every table, one after the other in the grid) is a template
+// parameter so that the passes are kernels of their own by name in a profile; the code is the same.
+// LPR: the lanes of a row of every table of the launch, or 0: tables of different widths from kMixedFrom lanes on, each
+// with its own (the order of a row's sums depends on it, so a table keeps its width whoever is beside it).
+constexpr int kMixedFrom = 8;
+template <bool BF16, int LPR, int CLS>
+__global__ __launch_bounds__(kFusedWaves *kWave, 4) void class_pass_kernel(const class_pass_batch batch, int *flags) {
+    FS_WG_TRACE(8 + CLS);
+    __shared__ __align__(16) char lds[sizeof(parked_rows<LPR ? LPR : kWave>)];
+    const class_pass_job &job = batch.j[blockIdx.y];
+    const int block = blockIdx.x;
+    if (block >= job.blocks) return;
+    const int cls = CLS < 2 ? CLS : job.cls;
+    if constexpr (LPR != 0) {
+        class_pass_body<BF16, LPR>(reinterpret_cast<parked_rows<LPR> &>(lds), job, cls, block, flags);
+    } else {
+#define FS_CASE(L) \
+    case L: class_pass_body<BF16, L>(reinterpret_cast<parked_rows<L> &>(lds), job, cls, block, flags); break;
+        switch (job.lpr) { FS_CASE(8) FS_CASE(16) FS_CASE(32) FS_CASE(64) }
+#undef FS_CASE
     }
 }
 
@@ -734,10 +771,11 @@ struct batch_update_job {
 template <bool BF16, int LPR, int UNR, int SU>
 __global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const batch_update_job job, int *flags) {
     FS_WG_TRACE(9);
+    __shared__ parked_rows<LPR> sh;
     int64_t n_u = *job.n_unique_dev;
     n_u = n_u < 0 ? 0 : (n_u > job.n ? job.n : n_u);
     if ((int)blockIdx.x < job.long_blocks)
-        long_segments_of_layout<BF16, LPR, UNR>((int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
+        long_segments_of_layout<BF16, LPR, UNR>(sh, (int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
                                                 job.u_t, (int)n_u, job.table, job.state, job.num_rows, job.gvec, job.lr,
                                                 job.eps, job.reduced, job.part_head, job.part_last, job.cnt_seg,
                                                 job.cnt_sup, flags);
@@ -747,17 +785,10 @@ __global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const 
                                              job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
 }
 
-template <int LPR> constexpr int fused_unr() {
-    return (kWave / (kWave / LPR)) < FS_FUSED_UNR ? kWave / (kWave / LPR) : FS_FUSED_UNR;
-}
-
-// `idx[0..m)`: the jobs of `jobs` (all of one dtype and row width, all with n > 0) that share this launch
-template <bool BF16, int LPR, int CLS>
-static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *idx, int m, hipStream_t s) {
-    constexpr int GPW = kWave / LPR;
-    constexpr int SU = FS_SHORT_UNR;
-    constexpr int UNR = fused_unr<LPR>();
-    constexpr int PER = CLS < 2 ? 1 : 2;                      // passes of a table
+// `idx[0..m)`: the jobs of `jobs` (all of one dtype, all with n > 0) that share this launch; kernel: for their width, or for any
+static void fused_launch(fs_ctx *ctx, void (*kernel)(class_pass_batch, int *), int cls, const fs_class_pass_job *jobs,
+                         const int *idx, int m, hipStream_t s) {
+    const int per = cls < 2 ? 1 : 2;                          // passes of a table
     const size_t cap_chunks = (size_t)fused_chunk_space(ctx->max_ids);
     const size_t cap_doubles = cap_chunks * (size_t)ctx->max_dim;
     int at = 0;
@@ -766,8 +797,8 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
         class_pass_batch batch;
         memset(&batch, 0, sizeof(batch));
         size_t chunks = 0, doubles = 0;
-        int k = 0, blocks = 0;
-        for (; at + k < m && (k + 1) * PER <= kMaxBatch; ++k) {
+        int k = 0;
+        for (; at + k < m && (k + 1) * per <= kMaxBatch; ++k) {
             const fs_class_pass_job &in = jobs[idx[at + k]];
             const int n = (int)in.n;
             // Both parts are sized for the worst case the host can know (every occurrence in a long
@@ -776,22 +807,22 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
             const int long_blocks = (int)ceil_div(ceil_div(n, 1 << log2), kFusedWaves);
             const size_t my_chunks = (size_t)long_blocks * kFusedWaves;
             if (k > 0 && (chunks + my_chunks > cap_chunks || doubles + my_chunks * (size_t)in.dim > cap_doubles)) break;
-            for (int c = 0; c < PER; ++c) {
-                const int cls = PER == 1 ? CLS : c;
-                class_pass_job &j = batch.j[k * PER + c];
+            for (int c = 0; c < per; ++c) {
+                const int pass = per == 1 ? cls : c;
+                class_pass_job &j = batch.j[k * per + c];
                 j.grads = (const f32x4 *)in.grads;
-                j.n = n; j.long_blocks = long_blocks; j.chunk_log2 = log2; j.cls = cls;
-                j.gvec = in.dim / 4; j.lr = in.lr; j.eps = in.eps;
+                j.n = n; j.long_blocks = long_blocks; j.chunk_log2 = log2; j.cls = pass;
+                j.gvec = in.dim / 4; j.lpr = lanes_per_row(j.gvec); j.lr = in.lr; j.eps = in.eps;
                 j.cperm = in.cperm; j.cslot = in.cslot; j.class_pos = in.class_pos; j.seg_offsets = in.seg_offsets;
                 j.cstart = in.cstart; j.u_t = in.u_t;
                 // records and row count of class 1 lie behind those of class 0 (both passes: `in` names class 0)
                 j.recs = in.short_rec + (int64_t)c * n * kShortRecInts;
                 j.n_rows_dev = in.n_rows_dev + c;
                 j.table = in.table; j.state = in.state; j.num_rows = in.num_rows; j.reduced = (f32x4 *)in.reduced;
-                j.part_head = ctx->fpart_head[cls] + doubles;
-                j.part_last = ctx->fpart_last[cls] + doubles;
-                j.cnt_seg = ctx->fcounters[cls] + chunks;
-                j.cnt_sup = ctx->fcounters_sup[cls] + chunks;
+                j.part_head = ctx->fpart_head[pass] + doubles;
+                j.part_last = ctx->fpart_last[pass] + doubles;
+                j.cnt_seg = ctx->fcounters[pass] + chunks;
+                j.cnt_sup = ctx->fcounters_sup[pass] + chunks;
             }
             chunks += my_chunks;
             doubles += my_chunks * (size_t)in.dim;
@@ -799,53 +830,66 @@ static void fused_launch(fs_ctx *ctx, const fs_class_pass_job *jobs, const int *
         // The short part walks its records with a grid stride: the tables of a launch share FS_SHORT_MAX_BLOCKS
         // workgroups (about five per compute unit, all resident from the start).  Measured on four workloads,
         // more and shorter-lived workgroups lose (16 k: +5 %, 64 k: +12 %), fewer than three per compute unit too.
-        for (int q = 0; q < k * PER; ++q) {
+        int blocks = 0;
+        for (int q = 0; q < k * per; ++q) {
             class_pass_job &j = batch.j[q];
-            int64_t short_blocks = ceil_div(j.n, (int64_t)GPW * SU * kFusedWaves);
+            int64_t short_blocks = ceil_div(j.n, (int64_t)(kWave / j.lpr) * FS_SHORT_UNR * kFusedWaves);
             const int64_t cap = FS_SHORT_MAX_BLOCKS / k > 256 ? FS_SHORT_MAX_BLOCKS / k : 256;
             if (short_blocks > cap) short_blocks = cap;
             j.blocks = j.long_blocks + (int)short_blocks;
             blocks = j.blocks > blocks ? j.blocks : blocks;
         }
-        hipLaunchKernelGGL((class_pass_kernel<BF16, LPR, UNR, SU, CLS>), dim3((unsigned)blocks, (unsigned)(k * PER)),
-                           dim3(kFusedWaves * kWave), 0, s, batch, ctx->d_flags);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, (unsigned)(k * per)), dim3(kFusedWaves * kWave), 0, s, batch, ctx->d_flags);
         at += k;
     }
 }
 
+// the kernel of a dtype, a class (2: both) and a row width (0: any)
+template <bool BF16, int CLS>
+static void (*class_pass_for(int lpr))(class_pass_batch, int *) {
+    switch (lpr) {
+        case 0: return &class_pass_kernel<BF16, 0, CLS>;
+        case 1: return &class_pass_kernel<BF16, 1, CLS>;
+        case 2: return &class_pass_kernel<BF16, 2, CLS>;
+        case 4: return &class_pass_kernel<BF16, 4, CLS>;
+        case 8: return &class_pass_kernel<BF16, 8, CLS>;
+        case 16: return &class_pass_kernel<BF16, 16, CLS>;
+        case 32: return &class_pass_kernel<BF16, 32, CLS>;
+        case 64: return &class_pass_kernel<BF16, 64, CLS>;
+        default: return nullptr;
+    }
+}
+
 int launch_reduce_update_batch(fs_ctx *ctx, int cls, int count, const fs_class_pass_job *jobs, hipStream_t s) {
-    // one launch (or as few as fit) per dtype and row width; tables keep their order inside a launch
-    bool done[FS_MAX_STEP_TABLES];
+    // one launch (or as few as fit) per dtype, and for narrow rows per width
     if (count < 0 || count > FS_MAX_STEP_TABLES) return set_err(ctx, FS_EINVAL, "reduce+update: too many tables");
-    for (int k = 0; k < count; ++k) done[k] = jobs[k].n == 0;
+    bool done[FS_MAX_STEP_TABLES];
+    for (int k = 0; k < count; ++k) {
+        done[k] = jobs[k].n == 0;
+        if (!done[k] && lanes_per_row(jobs[k].dim / 4) > kWave) return set_err(ctx, FS_EINVAL, "reduce+update: dim beyond 256");
+    }
     for (int k0 = 0; k0 < count; ++k0) {
         if (done[k0]) continue;
         const bool bf = jobs[k0].dt == FS_BF16;
-        const int lpr = lanes_per_row(jobs[k0].dim / 4);
+        int lpr = lanes_per_row(jobs[k0].dim / 4);
+        const bool wide = lpr >= kMixedFrom;
         int idx[FS_MAX_STEP_TABLES], m = 0;
-        for (int k = k0; k < count; ++k)
-            if (!done[k] && (jobs[k].dt == FS_BF16) == bf && lanes_per_row(jobs[k].dim / 4) == lpr) {
-                idx[m++] = k;
-                done[k] = true;
-            }
-#define FS_CASE(L)                                                                              \
-    case L:                                                                                     \
-        if (cls == 0) {                                                                         \
-            if (bf) fused_launch<true, L, 0>(ctx, jobs, idx, m, s);                             \
-            else fused_launch<false, L, 0>(ctx, jobs, idx, m, s);                               \
-        } else if (cls == 1) {                                                                  \
-            if (bf) fused_launch<true, L, 1>(ctx, jobs, idx, m, s);                             \
-            else fused_launch<false, L, 1>(ctx, jobs, idx, m, s);                               \
-        } else {                                                                                \
-            if (bf) fused_launch<true, L, 2>(ctx, jobs, idx, m, s);                             \
-            else fused_launch<false, L, 2>(ctx, jobs, idx, m, s);                               \
-        }                                                                                       \
-        break;
-        switch (lpr) {
-            FS_CASE(1) FS_CASE(2) FS_CASE(4) FS_CASE(8) FS_CASE(16) FS_CASE(32) FS_CASE(64)
-            default: return set_err(ctx, FS_EINVAL, "reduce+update: dim beyond 256");
+        for (int k = k0; k < count; ++k) {
+            const int mine = lanes_per_row(jobs[k].dim / 4);
+            if (done[k] || (jobs[k].dt == FS_BF16) != bf || (wide ? mine < kMixedFrom : mine != lpr)) continue;
+            lpr = lpr == mine ? lpr : 0;
+            idx[m++] = k;
+            done[k] = true;
         }
-#undef FS_CASE
+        // the largest first: the smaller ones fill the end of the launch
+        std::sort(idx, idx + m, [jobs](int a, int b) {
+            const int64_t x = jobs[a].n * jobs[a].dim, y = jobs[b].n * jobs[b].dim;
+            return x != y ? x > y : a < b;
+        });
+        auto *kernel = cls == 0 ? (bf ? class_pass_for<true, 0>(lpr) : class_pass_for<false, 0>(lpr))
+                       : cls == 1 ? (bf ? class_pass_for<true, 1>(lpr) : class_pass_for<false, 1>(lpr))
+                                  : (bf ? class_pass_for<true, 2>(lpr) : class_pass_for<false, 2>(lpr));
+        fused_launch(ctx, kernel, cls, jobs, idx, m, s);
     }
     FS_LAUNCH_CHECK(ctx, "class_pass_kernel");
     return FS_OK;

@@ -5,6 +5,8 @@
 // cover one row, so one wavefront instruction moves 64/LPR rows (2 rows of 128 fp32, 4 rows of
 // 64 fp32 or 128 bf16, 1 row of 256 fp32).  Work is flat over the N occurrences, never one
 // workgroup per user, so a 16K-item sequence costs the same per item as a short one.
+#include <algorithm>
+
 #include "fs_common.h"
 #include "fs_device.h"
 
@@ -20,53 +22,72 @@
 
 namespace fs {
 
-// one gather of a launch shared by several tables of one row width (blockIdx.y picks the table)
+// one gather of a launch shared by several tables (blockIdx.y picks the table)
 struct gather_dev_job {
     const u32x4 *table;
     int64_t num_rows;
     const int64_t *values, *offsets;
     int64_t batch, n;
     u32x4 *out;
-    int granules, blocks;
+    int granules, lpr, blocks;
     const int32_t *inverse;       // gather_part_kernel: occurrence -> slot of its row in the distinct list
     const uint8_t *row_flag;      //                     slot -> 1 for a collision row
     int which;                    //                     copy the occurrences whose flag equals this
     const int64_t *sorted_ids;    // gather_rows_kernel: row at each position of the ascending list
     const int32_t *perm;          //                     occurrence at each position of the ascending list
 };
+template <int MOST>
 struct gather_dev_batch {
-    gather_dev_job j[kMaxBatch];
+    gather_dev_job j[MOST];
 };
+constexpr int kGatherUnr = FS_GATHER_UNR;
+
+// A kernel for tables of one row width (LPR lanes a row), or with LPR = 0 for tables of any widths.
+#define FS_ANY_WIDTH(body, ...)                                                \
+    const gather_dev_job &job = jobs.j[MOST > 1 ? blockIdx.y : 0];                            \
+    const int block = blockIdx.x;                                              \
+    if (block >= job.blocks) return;                                           \
+    if constexpr (LPR != 0) body<LPR, kGatherUnr>(job, block, __VA_ARGS__);    \
+    else switch (job.lpr) {                                                    \
+        case 1: body<1, kGatherUnr>(job, block, __VA_ARGS__); break;           \
+        case 2: body<2, kGatherUnr>(job, block, __VA_ARGS__); break;           \
+        case 4: body<4, kGatherUnr>(job, block, __VA_ARGS__); break;           \
+        case 8: body<8, kGatherUnr>(job, block, __VA_ARGS__); break;           \
+        case 16: body<16, kGatherUnr>(job, block, __VA_ARGS__); break;         \
+        case 32: body<32, kGatherUnr>(job, block, __VA_ARGS__); break;         \
+        case 64: body<64, kGatherUnr>(job, block, __VA_ARGS__); break;         \
+    }
+
+// offsets validation rides along (grid-stride over the batch; almost free.  Asked for in front and looked at behind the
+// rows it takes a few registers for nothing: ten steps of 297 k IDs x 128 979 us against 970, and a lookup of 8 k IDs
+// no faster.)
+__device__ __forceinline__ void check_offsets(const gather_dev_job &job, const int block, int *__restrict__ flags) {
+    if (job.offsets == nullptr) return;
+    const int64_t gtid = (int64_t)block * blockDim.x + threadIdx.x;
+    const int64_t gsz = (int64_t)job.blocks * blockDim.x;
+    bool bad = false;
+    for (int64_t b = gtid; b < job.batch; b += gsz) bad |= job.offsets[b + 1] < job.offsets[b];
+    if (gtid == 0) bad |= (job.offsets[0] != 0) || (job.offsets[job.batch] != job.n);
+    if (bad) atomicOr(flags, kFlagOffsets);
+}
 
 template <int LPR, int UNR>
-__global__ __launch_bounds__(256) void gather_kernel(const gather_dev_batch jobs, int *__restrict__ flags) {
-    const gather_dev_job &job = jobs.j[blockIdx.y];
-    FS_WG_TRACE(10);
-    if ((int)blockIdx.x >= job.blocks) return;
+__device__ __forceinline__ void gather_body(const gather_dev_job &job, const int block, int *__restrict__ flags) {
     const u32x4 *__restrict__ table = job.table;
     const int64_t num_rows = job.num_rows;
     const int granules = job.granules;
     const int64_t *__restrict__ values = job.values;
-    const int64_t *__restrict__ offsets = job.offsets;
-    const int64_t batch = job.batch, n = job.n;
+    const int64_t n = job.n;
     u32x4 *__restrict__ out = job.out;
     constexpr int GPW = kWave / LPR;                  // rows per wavefront instruction
     constexpr int ROWS_PER_WAVE = GPW * UNR;
     const int lane = threadIdx.x & (kWave - 1);
     const int grp = lane / LPR;
     const int lig = lane % LPR;
-    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    const int64_t wave = (int64_t)block * (blockDim.x / kWave) + (threadIdx.x / kWave);
     const int64_t waves = (int64_t)job.blocks * (blockDim.x / kWave);
 
-    // offsets validation rides along (grid-stride over the batch; almost free)
-    if (offsets != nullptr) {
-        const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        const int64_t gsz = (int64_t)job.blocks * blockDim.x;
-        bool bad = false;
-        for (int64_t b = gtid; b < batch; b += gsz) bad |= offsets[b + 1] < offsets[b];
-        if (gtid == 0) bad |= (offsets[0] != 0) || (offsets[batch] != n);
-        if (bad) atomicOr(flags, kFlagOffsets);
-    }
+    check_offsets(job, block, flags);
     bool oob = false;
     for (int64_t row0 = wave * ROWS_PER_WAVE; row0 < n; row0 += waves * ROWS_PER_WAVE) {
         int64_t id[UNR];
@@ -94,6 +115,11 @@ __global__ __launch_bounds__(256) void gather_kernel(const gather_dev_batch jobs
     if (oob) atomicOr(flags, kFlagRowRange);
 }
 
+template <int LPR, int MOST>
+__global__ __launch_bounds__(256) void gather_kernel(const gather_dev_batch<MOST> jobs, int *__restrict__ flags) {
+    FS_WG_TRACE(10);
+    FS_ANY_WIDTH(gather_body, flags)
+}
 
 // The same lookup walked in ROW order: position p of the ascending ID list (every occurrence listed) holds row
 // sorted_ids[p] and belongs to occurrence perm[p] of the batch, so out[perm[p], :] = table[sorted_ids[p], :].
@@ -103,31 +129,22 @@ __global__ __launch_bounds__(256) void gather_kernel(const gather_dev_batch jobs
 // are whole 128-byte lines either way; only their order in time changes.  Offsets are validated as in the
 // batch-order kernel.
 template <int LPR, int UNR>
-__device__ __forceinline__ void gather_rows_body(const gather_dev_job &job, int *__restrict__ flags) {
-    if ((int)blockIdx.x >= job.blocks) return;
+__device__ __forceinline__ void gather_rows_body(const gather_dev_job &job, const int block, int *__restrict__ flags) {
     const u32x4 *__restrict__ table = job.table;
     const int64_t num_rows = job.num_rows;
     const int granules = job.granules;
     const int64_t *__restrict__ sorted_ids = job.sorted_ids;
     const int32_t *__restrict__ perm = job.perm;
-    const int64_t *__restrict__ offsets = job.offsets;
-    const int64_t batch = job.batch, n = job.n;
+    const int64_t n = job.n;
     u32x4 *__restrict__ out = job.out;
     constexpr int GPW = kWave / LPR;
     constexpr int ROWS_PER_WAVE = GPW * UNR;
     const int lane = threadIdx.x & (kWave - 1);
     const int grp = lane / LPR;
     const int lig = lane % LPR;
-    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    const int64_t wave = (int64_t)block * (blockDim.x / kWave) + (threadIdx.x / kWave);
     const int64_t waves = (int64_t)job.blocks * (blockDim.x / kWave);
-    if (offsets != nullptr) {
-        const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        const int64_t gsz = (int64_t)job.blocks * blockDim.x;
-        bool bad = false;
-        for (int64_t b = gtid; b < batch; b += gsz) bad |= offsets[b + 1] < offsets[b];
-        if (gtid == 0) bad |= (offsets[0] != 0) || (offsets[batch] != n);
-        if (bad) atomicOr(flags, kFlagOffsets);
-    }
+    check_offsets(job, block, flags);
     bool oob = false, bad_perm = false;
     for (int64_t p0 = wave * ROWS_PER_WAVE; p0 < n; p0 += waves * ROWS_PER_WAVE) {
         int64_t id[UNR];
@@ -159,12 +176,11 @@ __device__ __forceinline__ void gather_rows_body(const gather_dev_job &job, int 
     if (bad_perm) atomicOr(flags, kFlagInternal);
 }
 
-template <int LPR, int UNR>
-__global__ __launch_bounds__(256) void gather_rows_kernel(const gather_dev_batch jobs, int *__restrict__ flags) {
+template <int LPR, int MOST>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const gather_dev_batch<MOST> jobs, int *__restrict__ flags) {
     FS_WG_TRACE(10);
-    gather_rows_body<LPR, UNR>(jobs.j[blockIdx.y], flags);
+    FS_ANY_WIDTH(gather_rows_body, flags)
 }
-
 
 // One part of the two-part lookup of Algorithm 2 (the rows Forward fetches ahead of time, or the collision
 // rows the priority update of Backward returns): only the occurrences whose row flag equals `which` are
@@ -173,20 +189,21 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const gather_dev_batch
 // of its part into a list in LDS and then copies rows from that list exactly as the plain kernel does -
 // the row traffic stays as dense as if the other part did not exist.
 constexpr int kPartChunk = FS_PART_CHUNK;
+struct part_list {
+    int64_t id[256 / kWave][kPartChunk];
+    int32_t pos[256 / kWave][kPartChunk];
+};
 template <int LPR, int UNR>
-__global__ __launch_bounds__(256) void gather_part_kernel(const gather_dev_batch jobs, int *__restrict__ flags) {
-    const gather_dev_job &job = jobs.j[blockIdx.y];
-    FS_WG_TRACE(10);
-    if ((int)blockIdx.x >= job.blocks) return;
+__device__ __forceinline__ void gather_part_body(const gather_dev_job &job, const int block, part_list &list,
+                                                 int *__restrict__ flags) {
     const u32x4 *__restrict__ table = job.table;
     const int64_t num_rows = job.num_rows;
     const int granules = job.granules;
     const int64_t *__restrict__ values = job.values;
-    const int64_t *__restrict__ offsets = job.offsets;
     const int32_t *__restrict__ inverse = job.inverse;
     const uint8_t *__restrict__ row_flag = job.row_flag;
     const bool want = job.which != 0;
-    const int64_t batch = job.batch, n = job.n;
+    const int64_t n = job.n;
     u32x4 *__restrict__ out = job.out;
     constexpr int GPW = kWave / LPR;
     constexpr int ROWS_PER_WAVE = GPW * UNR;
@@ -195,22 +212,15 @@ __global__ __launch_bounds__(256) void gather_part_kernel(const gather_dev_batch
     const int w = threadIdx.x / kWave;
     const int grp = lane / LPR;
     const int lig = lane % LPR;
-    __shared__ int64_t l_id[WAVES][kPartChunk];
-    __shared__ int32_t l_pos[WAVES][kPartChunk];
+    auto &l_id = list.id;
+    auto &l_pos = list.pos;
 
-    if (offsets != nullptr) {
-        const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        const int64_t gsz = (int64_t)job.blocks * blockDim.x;
-        bool bad = false;
-        for (int64_t b = gtid; b < batch; b += gsz) bad |= offsets[b + 1] < offsets[b];
-        if (gtid == 0) bad |= (offsets[0] != 0) || (offsets[batch] != n);
-        if (bad) atomicOr(flags, kFlagOffsets);
-    }
+    check_offsets(job, block, flags);
     bool oob = false;
     const uint64_t lt = (1ull << lane) - 1ull;
     const int64_t chunks = (n + kPartChunk - 1) / kPartChunk;
     // every wavefront of the workgroup makes the same number of rounds (the barriers below are met by all)
-    for (int64_t c0 = (int64_t)blockIdx.x * WAVES; c0 < chunks; c0 += (int64_t)job.blocks * WAVES) {
+    for (int64_t c0 = (int64_t)block * WAVES; c0 < chunks; c0 += (int64_t)job.blocks * WAVES) {
         const int64_t base = (c0 + w) * kPartChunk;
         int count = 0;
 #pragma unroll
@@ -259,42 +269,62 @@ __global__ __launch_bounds__(256) void gather_part_kernel(const gather_dev_batch
     if (oob) atomicOr(flags, kFlagRowRange);
 }
 
-template <int LPR>
-static void gather_launch(const fs_gather_job *jobs, const int *idx, int m, bool part, bool rows, int *flags,
+template <int LPR, int MOST>
+__global__ __launch_bounds__(256) void gather_part_kernel(const gather_dev_batch<MOST> jobs, int *__restrict__ flags) {
+    FS_WG_TRACE(10);
+    __shared__ part_list list;
+    FS_ANY_WIDTH(gather_part_body, list, flags)
+}
+
+// the kernel of a form of the lookup and a row width (0: any), for a launch of up to MOST tables
+template <int LPR, int MOST>
+static void (*gather_form(bool part, bool rows))(gather_dev_batch<MOST>, int *) {
+    return part ? &gather_part_kernel<LPR, MOST> : rows ? &gather_rows_kernel<LPR, MOST> : &gather_kernel<LPR, MOST>;
+}
+template <int MOST>
+static void (*gather_for(int lpr, bool part, bool rows))(gather_dev_batch<MOST>, int *) {
+    switch (lpr) {
+        case 0: return gather_form<0, MOST>(part, rows);
+        case 1: return gather_form<1, MOST>(part, rows);
+        case 2: return gather_form<2, MOST>(part, rows);
+        case 4: return gather_form<4, MOST>(part, rows);
+        case 8: return gather_form<8, MOST>(part, rows);
+        case 16: return gather_form<16, MOST>(part, rows);
+        case 32: return gather_form<32, MOST>(part, rows);
+        default: return gather_form<64, MOST>(part, rows);
+    }
+}
+
+// `idx[0..k)`: the jobs of `jobs` that share this launch; lpr: the lanes of a row of all of them, or 0.
+// MOST: arguments for one table are a ninth of those for several, which a call has to write out whatever it uses of them.
+template <int MOST>
+static void gather_launch(int lpr, const fs_gather_job *jobs, const int *idx, int k, bool part, bool rows, int *flags,
                           hipStream_t s) {
     // One round of rows per workgroup when the cap allows: the chip writes faster the more workgroups share
     // the job (a write-only kernel: 4.6 TB/s from 1024 workgroups, 5.8 TB/s from 65536), and the small
     // latency-bound kernels that used to queue behind a long grid now run iterations ahead of it.
-    constexpr int UNR = FS_GATHER_UNR;
-    const int ROWS_PER_BLOCK = part ? 4 * kPartChunk : (kWave / LPR) * UNR * 4;
-    for (int at = 0; at < m; at += kMaxBatch) {
-        const int k = (m - at) < kMaxBatch ? (m - at) : kMaxBatch;
-        gather_dev_batch batch;
-        memset(&batch, 0, sizeof(batch));
-        // the tables of a launch share the chip: FS_GATHER_MAX_BLOCKS workgroups in all, by their sizes
-        int64_t total = 0;
-        for (int i = 0; i < k; ++i) total += jobs[idx[at + i]].n;
-        int blocks = 0;
-        for (int i = 0; i < k; ++i) {
-            const fs_gather_job &in = jobs[idx[at + i]];
-            gather_dev_job &j = batch.j[i];
-            int64_t b = ceil_div(in.n, ROWS_PER_BLOCK);
-            int64_t share = ceil_div((int64_t)FS_GATHER_MAX_BLOCKS * in.n, total);
-            if (share < 1) share = 1;
-            if (b > share) b = share;
-            j.table = (const u32x4 *)in.table; j.num_rows = in.num_rows; j.values = in.values; j.offsets = in.offsets;
-            j.batch = in.batch; j.n = in.n; j.out = (u32x4 *)in.out; j.granules = in.row_bytes / 16; j.blocks = (int)b;
-            j.inverse = in.inverse; j.row_flag = in.row_flag; j.which = in.which;
-            j.sorted_ids = in.sorted_ids; j.perm = in.perm;
-            blocks = j.blocks > blocks ? j.blocks : blocks;
-        }
-        if (part)
-            hipLaunchKernelGGL((gather_part_kernel<LPR, UNR>), dim3((unsigned)blocks, (unsigned)k), dim3(256), 0, s, batch, flags);
-        else if (rows)
-            hipLaunchKernelGGL((gather_rows_kernel<LPR, UNR>), dim3((unsigned)blocks, (unsigned)k), dim3(256), 0, s, batch, flags);
-        else
-            hipLaunchKernelGGL((gather_kernel<LPR, UNR>), dim3((unsigned)blocks, (unsigned)k), dim3(256), 0, s, batch, flags);
+    gather_dev_batch<MOST> batch;
+    memset(&batch, 0, sizeof(batch));
+    // the tables of a launch share the chip: FS_GATHER_MAX_BLOCKS workgroups in all, by their sizes
+    int64_t total = 0;
+    for (int i = 0; i < k; ++i) total += jobs[idx[i]].n;
+    int blocks = 0;
+    for (int i = 0; i < k; ++i) {
+        const fs_gather_job &in = jobs[idx[i]];
+        gather_dev_job &j = batch.j[i];
+        j.granules = in.row_bytes / 16;
+        j.lpr = lanes_per_row(j.granules);
+        int64_t b = ceil_div(in.n, part ? 4 * kPartChunk : (kWave / j.lpr) * kGatherUnr * 4);
+        int64_t share = ceil_div((int64_t)FS_GATHER_MAX_BLOCKS * in.n, total);
+        if (share < 1) share = 1;
+        if (b > share) b = share;
+        j.table = (const u32x4 *)in.table; j.num_rows = in.num_rows; j.values = in.values; j.offsets = in.offsets;
+        j.batch = in.batch; j.n = in.n; j.out = (u32x4 *)in.out; j.blocks = (int)b;
+        j.inverse = in.inverse; j.row_flag = in.row_flag; j.which = in.which;
+        j.sorted_ids = in.sorted_ids; j.perm = in.perm;
+        blocks = j.blocks > blocks ? j.blocks : blocks;
     }
+    hipLaunchKernelGGL(gather_for<MOST>(lpr, part, rows), dim3((unsigned)blocks, (unsigned)k), dim3(256), 0, s, batch, flags);
 }
 
 static bool is_part(const fs_gather_job &j) { return j.which >= 0 && j.inverse != nullptr && j.row_flag != nullptr; }
@@ -306,25 +336,27 @@ int launch_gather_batch(fs_ctx *ctx, int count, const fs_gather_job *jobs, hipSt
     for (int k = 0; k < count; ++k) done[k] = jobs[k].n == 0;
     for (int k0 = 0; k0 < count; ++k0) {
         if (done[k0]) continue;
-        const int lpr = lanes_per_row(jobs[k0].row_bytes / 16);
         const bool part = is_part(jobs[k0]), rows = is_rows(jobs[k0]);
-        int idx[FS_MAX_STEP_TABLES], m = 0;
+        int idx[FS_MAX_STEP_TABLES], m = 0, lpr = 0;
         for (int k = k0; k < count; ++k)
-            if (!done[k] && lanes_per_row(jobs[k].row_bytes / 16) == lpr && is_part(jobs[k]) == part &&
-                is_rows(jobs[k]) == rows) {
+            if (!done[k] && is_part(jobs[k]) == part && is_rows(jobs[k]) == rows) {
+                const int mine = lanes_per_row(jobs[k].row_bytes / 16);
+                if (mine > kWave) return set_err(ctx, FS_EINVAL, "gather: row wider than 1024 bytes");
+                lpr = m == 0 || lpr == mine ? mine : 0;
                 idx[m++] = k;
                 done[k] = true;
             }
-        switch (lpr) {
-            case 1: gather_launch<1>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            case 2: gather_launch<2>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            case 4: gather_launch<4>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            case 8: gather_launch<8>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            case 16: gather_launch<16>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            case 32: gather_launch<32>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            case 64: gather_launch<64>(jobs, idx, m, part, rows, ctx->d_flags, s); break;
-            default: return set_err(ctx, FS_EINVAL, "gather: row wider than 1024 bytes");
+        if (m == 1) {
+            gather_launch<1>(lpr, jobs, idx, 1, part, rows, ctx->d_flags, s);
+            continue;
         }
+        // the largest first: the smaller ones fill the end of the launch
+        std::sort(idx, idx + m, [jobs](int a, int b) {
+            const int64_t x = jobs[a].n * jobs[a].row_bytes, y = jobs[b].n * jobs[b].row_bytes;
+            return x != y ? x > y : a < b;
+        });
+        for (int at = 0; at < m; at += kMaxBatch)
+            gather_launch<kMaxBatch>(lpr, jobs, idx + at, m - at < kMaxBatch ? m - at : kMaxBatch, part, rows, ctx->d_flags, s);
     }
     FS_LAUNCH_CHECK(ctx, "gather_kernel");
     return FS_OK;

@@ -74,8 +74,9 @@ class TableBuffers:
 
 
 def group_tables(tabs: Sequence[TableBuffers], G: int) -> List[List[TableBuffers]]:
-    """The tables of a shard in G groups (one context, stream and call sequence each).  Tables of one row width
-    share the launches of their class passes and gathers inside a call, so a group should hold few widths, and
+    """The tables of a shard in G groups (one context, stream and call sequence each).  The tables of a group share
+    the launches of their class passes and gathers inside a call, and tables of one row width take the kernels
+    written for it, so a group should hold few widths, and
     the groups run side by side, so they should be about equally heavy: every assignment is tried (a shard has a
     handful of tables) and the one with the smallest (heaviest group / mean group + 0.05 x launch classes) kept."""
     tabs = list(tabs)

@@ -174,6 +174,8 @@ void carve(fs_ctx *c, char *base, size_t *total) {
     c->jag_sorted = cv.take<int32_t>(n + 16);
     c->jag_tile_sum = cv.take<int64_t>(scan_tiles);
     c->jag_sel = cv.take<int32_t>(n + 16);
+    c->jag_delta = cv.take<int64_t>(n + 16);
+    c->jag_tile_first = cv.take<int32_t>(2 * n);
     *total = align_up(cv.off, 256);
 }
 

@@ -206,6 +206,8 @@ struct fs_ctx {
     int32_t *jag_sorted;      // [max_ids] samples in ascending order of length
     int64_t *jag_tile_sum;    // [scan tiles] output elements per tile of output samples
     int32_t *jag_sel;         // [max_ids] computed segment order of a keyed shuffle
+    int64_t *jag_delta;       // [max_ids] from an output sample to its input, in elements
+    int32_t *jag_tile_first;  // [2 * max_ids] output sample that every tile of a copy starts in
 
     // the set of streams in use (fs_api.hip): the one shared with the other contexts driven from the same stream, or one
     // of its own

@@ -6,13 +6,12 @@
 // the ranks in a zig-zag - rank i takes sorted positions i, 2n-1-i, 2n+i, 4n-1-i, ...  The deal is a
 // closed form per sorted position, one thread each.
 //
-// Indexed permute: output sample k is input sample sample_of[k].  Up to 8192 samples two launches: one
+// Indexed permute: output sample k is input sample sample_of[k].  Up to 4096 samples two launches: one
 // workgroup lays out the output offsets, then the copy; beyond, lengths summed per tile of samples, the
 // output offsets by a scan with tile prefixes, and the copy.  The copy is driven
 // by the OUTPUT (every lane writes consecutive pieces of the output, so a 16K-item sample costs per
-// item what a short one costs): a workgroup takes 2048 to 8192 consecutive output pieces, finds the samples
-// they belong to with two 64-ary searches, stages their boundaries in LDS and lets every piece
-// binary-search LDS.
+// item what a short one costs): a workgroup takes 2048 to 8192 consecutive output pieces, is told which samples
+// they begin and end in, and marks the starts of its samples as bits in LDS.
 //
 // VBS: the same sort, then the sorted order is cut into n runs of about equal total weight.
 //
@@ -68,19 +67,36 @@ struct jagged_in {
     int64_t B, n_values;      // samples, elements behind them
 };
 
-// length of input sample p (0 and a flag for a sample index out of range or a sample whose boundaries are not inside
+// extent of input sample p (0 and a flag for a sample index out of range or a sample whose boundaries are not inside
 // the values: such a sample is never read)
-__device__ __forceinline__ int64_t sample_len(const jagged_in &in, int64_t p, bool &bad) {
-    if (p < 0 || p >= in.B) { bad = true; return 0; }
+struct sample_extent {
+    int64_t first, len;
+};
+__device__ __forceinline__ sample_extent extent_of(const jagged_in &in, int64_t p, bool &bad) {
+    if (p < 0 || p >= in.B) { bad = true; return {0, 0}; }
     const int64_t a = in.offsets[p], b = in.offsets[p + 1];
-    if (a < 0 || b < a || b > in.n_values) { bad = true; return 0; }
-    return b - a;
+    if (a < 0 || b < a || b > in.n_values) { bad = true; return {0, 0}; }
+    return {a, b - a};
 }
 
-// length of output sample k (0 past the end)
-__device__ __forceinline__ int64_t out_len(const jagged_in &in, const int32_t *__restrict__ sample_of, int64_t k,
-                                           int64_t n_out, bool &bad) {
-    return k < n_out ? sample_len(in, sample_of[k], bad) : 0;
+// What the copy wants to know of every output sample and every tile of the output, written down with the output
+// offsets: a workgroup of the copy then opens its tile with two dependent rounds of loads, where a search for its first
+// and last sample and a look at where they come from are six.
+struct copy_plan {
+    int64_t *delta;           // [n_out] first input element of a sample minus its first output element
+    int32_t *tile_first;      // [tiles] sample that the first piece of a tile belongs to (null: too many tiles)
+    int64_t cap_out;          // elements of the output
+    int ppe, tile_log2;       // pieces of an element, log2 of the pieces of a tile
+};
+__device__ __forceinline__ void plan_sample(const copy_plan &plan, int64_t k, int64_t start, const sample_extent &x) {
+    plan.delta[k] = x.first - start;
+    if (plan.tile_first == nullptr) return;
+    int64_t end = start + x.len;
+    if (end > plan.cap_out) end = plan.cap_out;
+    const int64_t last = end * plan.ppe;
+    const int64_t size = (int64_t)1 << plan.tile_log2;
+    for (int64_t t = (start * plan.ppe + size - 1) >> plan.tile_log2; (t << plan.tile_log2) < last; ++t)
+        plan.tile_first[t] = (int32_t)k;
 }
 
 // ---- the order of the output samples ---------------------------------------------------------------------
@@ -149,13 +165,17 @@ __device__ __forceinline__ int64_t rank_split(const sample_order &o, const int64
 // Everything the copy needs about a small number of output samples in ONE launch: their order, the output offsets
 // and the splits.  The work is a few loads a sample; what it costs is launches, about 4 us each here (four keyed
 // shuffles of 1024 segments spent three to four of them on it).  One workgroup, up to kPlanPer consecutive samples
-// a thread; beyond that one compute unit takes longer than two launches over many.
+// a thread; beyond that one compute unit takes longer than two launches over many (8192 samples 24 us against 16, 4096
+// 14.1 against 14.9).
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanPer = 8;
+#ifndef PLANPER
+#define PLANPER 8
+#endif
+constexpr int kPlanPer = 4;
 constexpr int kPlanRanks = 1024;                 // rank boundaries kept in LDS
 
 __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_in in, const sample_order order,
-                                                                   int32_t *sel, int n_out, int64_t cap_out,
+                                                                   int n_out, const copy_plan plan,
                                                                    int64_t *out_offsets, int *__restrict__ flags) {
     __shared__ int64_t s_ro[kPlanRanks + 1];
     __shared__ int64_t sh[kPlanThreads / kWave];
@@ -173,19 +193,16 @@ __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_
     for (int i = 0; i < kPlanPer; ++i) {
         p[i] = -1;
         if (i < per && k0 + i < n_out) {
-            if (order.mode == kMapGiven) {
-                p[i] = order.given[k0 + i];
-            } else {
-                p[i] = ordered_segment(order, ro, k0 + i);
-                sel[k0 + i] = p[i];
-            }
+            p[i] = order.mode == kMapGiven ? order.given[k0 + i] : ordered_segment(order, ro, k0 + i);
         }
     }
-    int64_t len[kPlanPer], v = 0;
+    sample_extent x[kPlanPer];
+    int64_t v = 0;
 #pragma unroll
     for (int i = 0; i < kPlanPer; ++i) {
-        len[i] = (i < per && k0 + i < n_out) ? sample_len(in, p[i], bad) : 0;
-        v += len[i];
+        x[i] = {0, 0};
+        if (i < per && k0 + i < n_out) x[i] = extent_of(in, p[i], bad);
+        v += x[i].len;
     }
     const int64_t inc = wave_inclusive_scan<int64_t>(v);
     if ((threadIdx.x & (kWave - 1)) == kWave - 1) sh[threadIdx.x / kWave] = inc;
@@ -198,12 +215,15 @@ __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_
     }
 #pragma unroll
     for (int i = 0; i < kPlanPer; ++i) {
-        if (i < per && k0 + i < n_out) out_offsets[k0 + i] = run;
-        run += len[i];
+        if (i < per && k0 + i < n_out) {
+            out_offsets[k0 + i] = run;
+            plan_sample(plan, k0 + i, run, x[i]);
+        }
+        run += x[i].len;
     }
     if (threadIdx.x == 0) {
         out_offsets[n_out] = total;
-        bad |= total > cap_out;                                          // the copy stops at cap_out
+        bad |= total > plan.cap_out;                                     // the copy stops there
     }
     if (bad) atomicOr(flags, kFlagOffsets);
     if (order.splits != nullptr) {
@@ -232,7 +252,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_tile_sum_kernel(const ja
                 p = ordered_segment(order, order.ro, k);
                 sel[k] = p;
             }
-            v += sample_len(in, p, bad);
+            v += extent_of(in, p, bad).len;
         }
     }
     int64_t total;
@@ -245,7 +265,8 @@ __global__ __launch_bounds__(kScanThreads) void permute_offsets_kernel(const jag
                                                                        const int32_t *__restrict__ sample_of,
                                                                        int64_t n_out,
                                                                        const int64_t *__restrict__ tile_sum,
-                                                                       int64_t cap_out, int64_t *__restrict__ out_offsets,
+                                                                       const copy_plan plan,
+                                                                       int64_t *__restrict__ out_offsets,
                                                                        int *__restrict__ flags) {
     __shared__ int64_t sh[kScanThreads / kWave];
     int64_t before = 0;
@@ -254,23 +275,28 @@ __global__ __launch_bounds__(kScanThreads) void permute_offsets_kernel(const jag
     (void)block_exclusive_scan<int64_t>(before, sh, tile_base);
     const int64_t k0 = (int64_t)blockIdx.x * kScanTile + threadIdx.x * kScanIpt;
     bool bad = false;
-    int64_t len[kScanIpt], v = 0;
+    sample_extent x[kScanIpt];
+    int64_t v = 0;
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
-        len[i] = out_len(in, sample_of, k0 + i, n_out, bad);
-        v += len[i];
+        x[i] = {0, 0};
+        if (k0 + i < n_out) x[i] = extent_of(in, sample_of[k0 + i], bad);
+        v += x[i].len;
     }
     int64_t tile_total;
     int64_t run = tile_base + block_exclusive_scan<int64_t>(v, sh, tile_total);
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
-        if (k0 + i < n_out) out_offsets[k0 + i] = run;
-        run += len[i];
+        if (k0 + i < n_out) {
+            out_offsets[k0 + i] = run;
+            plan_sample(plan, k0 + i, run, x[i]);
+        }
+        run += x[i].len;
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         const int64_t total = tile_base + tile_total;
         out_offsets[n_out] = total;
-        if (total > cap_out) atomicOr(flags, kFlagOffsets);     // the copy stops at cap_out
+        if (total > plan.cap_out) atomicOr(flags, kFlagOffsets);     // the copy stops there
     }
 }
 
@@ -281,111 +307,180 @@ __global__ __launch_bounds__(256) void dispatch_splits_kernel(const sample_order
         order.splits[r] = rank_split(order, out_offsets, r);
 }
 
-// Pieces per workgroup.  A copy of whole rows wants long stretches: the searches that open a tile are a chain of
-// dependent loads that queue behind the rows of the other workgroups (250 k rows of 512 bytes, 16-byte pieces: 50 us
-// with 128 KB a workgroup, 100 to 160 with 32 or 64 KB).  Where samples are short the walk over their boundaries
-// counts, and more, shorter-lived wavefronts hide it: 16 KB of 8-byte pieces (eight in flight per lane) against 32 KB
-// (sixteen), a whole balancer pass: samples of 1 to 200 IDs 198 -> 90 us, of 16 to 4096 IDs 108 -> 107.
-// 4-byte pieces: a large output pays for the searches with too few bytes a tile, a small one fills the chip with short
-// tiles only.  Tiles of 2048 (eight in flight) / 4096 (sixteen), one permute: 500 k pieces 22.3 / 31 us, 1 M 21.7 / 27.6,
-// 8 M 38.5 / 38.3, 9 M 42.0 / 42.1, 10 M 48.5 / 43.0, 12.5 M 51.3 / 45.1, 32 M 99.8 / 87.3.
-constexpr int kCopyTile16 = 8192, kCopyTile8 = 2048, kCopyTile4 = 2048, kCopyTile4Large = 4096;
-constexpr int64_t kCopyLargeFrom = 9 << 20;                     // 4-byte pieces of the output
+// Pieces per workgroup, and groups of sixteen bytes in flight per lane.  What bounds the copy of a large output is the rate of
+// a plain copy; what bounds a small one is the life of a workgroup, so that short tiles, many at once, are the faster ones.
+// One permute of the whole operation, tiles of 2048 pieces of 16 bytes (8 in flight) / of 8192 (4 in flight): 8 MB of output
+// 10.1 / 14.8 us, 20 MB 16.0 / 19.8, 39 MB 23.1 / 26.5, 45 MB 20.9 / 23.4, 52 MB 24.8 / 24.3, 65 MB 28.6 / 27.8, 90 MB 36.8 /
+// 36.3, 134 MB 52.9 / 50.4, 183 MB 72.2 / 71.6.  Large outputs with 8 / 4 / 2 in flight: dispatch, combine and transpose of
+// 128 MB 169.6 / 166.7 / 159.7 (tiles of 2048, 8 in flight: 164.1).
+// 8-byte pieces, tiles of 2048 (4 in flight) / of 4096: 100 k samples of 1 to 200 IDs 18.6 / 19.9, 65 k of 16 to 4096 60.8 /
+// 60.5; two in flight 64.4.  4-byte pieces: a large output pays for opening its tiles with too few bytes each; tiles of 2048
+// (2 in flight) / 4096 (4): 1 M pieces 14.4 / 14.8, 16.7 M 39.0 / 38.8.
+constexpr int kCopyTile16 = 2048, kCopyTile16Large = 8192, kCopyTile8 = 2048, kCopyTile4 = 2048, kCopyTile4Large = 4096;
+constexpr int64_t kCopyLarge16 = 3 << 20, kCopyLarge4 = 9 << 20;        // pieces of the output
 constexpr int kCopyWindow = 2048 + 2;                           // sample boundaries staged in LDS
 
-// V: the piece, the widest of 4, 8, 16 bytes that divides the element; ppe pieces per element.
-// Inside a tile everything is counted from the tile's first element in 32 bits (a 64-bit division per
-// piece would cost more than the copy).
-template <typename V, int kCopyTile, int PIECES>
-__global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__restrict__ values, const jagged_in in,
-                                                                    const int32_t *__restrict__ sample_of,
-                                                                    int64_t n_out, const int64_t *__restrict__ out_offsets,
-                                                                    int64_t cap_out, int ppe, V *__restrict__ out) {
-    __shared__ int32_t w_rel[kCopyWindow];      // out_offsets[ka + j] minus the tile's first element (at least -1)
-    __shared__ int64_t w_delta[kCopyWindow];    // first input element of sample ka + j minus its first output element
+// sixteen bytes of pieces of type V, wherever a piece may lie
+template <typename V>
+struct piece_group {
+    typedef V type __attribute__((ext_vector_type(16 / sizeof(V)), aligned(sizeof(V))));
+};
+template <>
+struct piece_group<u32x4> {
+    typedef u32x4 type;
+};
+// V: the piece, the widest of 4, 8, 16 bytes that divides the element; ppe pieces per element.  A lane moves sixteen bytes
+// of consecutive output pieces at a time, in one access each way where they belong to one sample.
+// Inside a tile everything is counted from the tile's first piece in 32 bits (a division per piece would cost more than
+// the copy).  Where samples start is a bit per piece of the tile: the sample of a piece is a matter of counting bits,
+// however short the samples are, where a walk over a list of boundaries takes a dependent step for each.
+template <typename V, int kCopyTile, int GROUPS>
+__global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__restrict__ values, int64_t n_pieces, int64_t n_out,
+                                                                    const int64_t *__restrict__ out_offsets,
+                                                                    const copy_plan plan, V *__restrict__ out) {
+    typedef typename piece_group<V>::type G;
+    constexpr int W = 16 / (int)sizeof(V);                      // pieces of a group
+    constexpr int kWords = kCopyTile / 32;
+    static_assert(kWords <= kScanThreads && kWords % kWave == 0, "a thread per word, whole wavefronts");
+    __shared__ uint32_t starts[kWords];         // a bit per piece of the tile that is the first of a sample
+    __shared__ uint32_t below[kWords];          // bits before a word
+    __shared__ int64_t w_delta[kCopyWindow];    // per bit: first input piece of the sample minus its first output piece
     __shared__ int64_t win[2];
-    const int64_t *__restrict__ offsets = in.offsets;
+    __shared__ uint32_t wave_sum[kScanThreads / kWave];
+    const int64_t *__restrict__ delta = plan.delta;
+    const int ppe = plan.ppe;
+    int64_t ka = 0, kb = n_out - 1;
+    const bool planned = plan.tile_first != nullptr;
+    if (planned) {
+        ka = plan.tile_first[blockIdx.x];                       // of a tile past the end: whatever, nobody uses it
+        if (blockIdx.x + 1 < gridDim.x) kb = plan.tile_first[blockIdx.x + 1];
+    }
     int64_t total = out_offsets[n_out];
-    if (total > cap_out) total = cap_out;
+    if (total > plan.cap_out) total = plan.cap_out;
     const int64_t pieces = total * ppe;
     const int64_t q0 = (int64_t)blockIdx.x * kCopyTile;
     if (q0 >= pieces) return;                                   // whole workgroup
-    const uint32_t tile_pieces = (uint32_t)((q0 + kCopyTile < pieces ? q0 + kCopyTile : pieces) - q0);
-    const int64_t e0 = q0 / ppe;                                // first element of the tile
-    const uint32_t rem0 = (uint32_t)(q0 - e0 * ppe);            // pieces of it that belong to the tile before
-    const int64_t e1 = (q0 + tile_pieces - 1) / ppe;            // last element of the tile
-    if (threadIdx.x < 2 * kWave) {
-        // sample of an element e: the last k with out_offsets[k] <= e (empty samples in between are skipped);
-        // the first wavefront looks for the sample of the tile's first element, the second for that of its last
-        const int w = threadIdx.x / kWave;
-        const int64_t k = wave_upper_bound<int64_t>(out_offsets, (int)(n_out + 1), w == 0 ? e0 : e1) - 1;
-        if ((threadIdx.x & (kWave - 1)) == 0) win[w] = k;
-    }
-    __syncthreads();
-    const int64_t ka = win[0], kb = win[1];
-    const bool staged = kb - ka + 1 <= kCopyWindow;             // else: the samples touched by the tile do not fit
-    const int wn = staged ? (int)(kb - ka + 1) : 0;
-    if (staged)
-        for (int j = threadIdx.x; j < wn; j += kScanThreads) {
-            const int64_t start = out_offsets[ka + j];
-            const int64_t p = sample_of[ka + j];
-            w_rel[j] = start < e0 ? -1 : (int32_t)(start - e0);                // start - e0 <= kCopyTile
-            w_delta[j] = (p >= 0 && p < in.B) ? offsets[p] - start : 0;        // a flagged sample is empty: never used
+    const int tile_pieces = (int)((q0 + kCopyTile < pieces ? q0 + kCopyTile : pieces) - q0);
+    if (q0 + kCopyTile >= pieces) kb = n_out - 1;               // the last tile: nobody wrote down what follows it
+    if (!planned || kb - ka + 1 > kCopyWindow) {
+        if (threadIdx.x < 2 * kWave) {
+            // sample of an element e: the last k with out_offsets[k] <= e (empty samples in between are skipped);
+            // the first wavefront looks for the sample of the tile's first element, the second for that of its last
+            const int w = threadIdx.x / kWave;
+            const int64_t e = (w == 0 ? q0 : q0 + tile_pieces - 1) / ppe;
+            const int64_t k = wave_upper_bound<int64_t>(out_offsets, (int)(n_out + 1), e) - 1;
+            if ((threadIdx.x & (kWave - 1)) == 0) win[w] = k;
         }
-    __syncthreads();
-    // Wavefront w copies the w-th quarter of the tile, 64 consecutive pieces per instruction, front to back:
-    // the sample of a lane's piece only moves forward, so after one binary search per lane the boundary
-    // list is walked (a step every few instructions for samples of a few hundred elements; never more
-    // steps per lane and tile than the list is long).
-    const uint32_t uppe = (uint32_t)ppe;
-    constexpr uint32_t kWavePieces = kCopyTile / (kScanThreads / kWave);
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t w0 = (threadIdx.x / kWave) * kWavePieces;
-    const int64_t wn_all = kb - ka + 1;
-    int64_t j = 0;                                              // sample ka + j holds the lane's current piece
-    {
-        const uint32_t t = rem0 + w0 + lane;
-        const int64_t le = uppe == 1 ? t : t / uppe;
-        int64_t lo = 0, hi = wn_all;                            // first j with start[j] > element
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            const bool le_mid = staged ? (w_rel[mid] <= (int32_t)le) : (out_offsets[ka + mid] <= e0 + le);
-            if (le_mid) lo = mid + 1; else hi = mid;
-        }
-        j = lo - 1;
+        __syncthreads();
+        ka = win[0];
+        kb = win[1];
     }
-    static_assert(kWavePieces % (kWave * PIECES) == 0, "a wavefront's quarter is a whole number of rounds");
-    for (uint32_t r0 = 0; r0 < kWavePieces; r0 += kWave * PIECES) {
-        if (w0 + r0 >= tile_pieces) break;                      // whole wavefront
-        V v[PIECES];                                            // in flight per lane
-        bool live[PIECES];
-#pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            const uint32_t l = w0 + r0 + (uint32_t)i * kWave + lane;                // piece of the tile
-            live[i] = l < tile_pieces;
-            if (live[i]) {
-                const uint32_t t = rem0 + l;
-                const uint32_t le = uppe == 1 ? t : t / uppe;                       // element of the tile
-                const uint32_t pin = t - le * uppe;                                 // piece of the element
-                int64_t delta;
-                if (staged) {
-                    while (j + 1 < wn_all && w_rel[j + 1] <= (int32_t)le) ++j;
-                    delta = w_delta[j];
-                } else {
-                    const int64_t e = e0 + le;
-                    while (j + 1 < wn_all && out_offsets[ka + j + 1] <= e) ++j;
-                    delta = offsets[sample_of[ka + j]] - out_offsets[ka + j];
-                }
-                // read once, written once: keeping either in the caches only pushes out the boundaries (three
-                // shuffles of 250 k rows of 512 bytes: 202 us with plain accesses, 185 with the hint on the loads
-                // only, 177 on both; at the rate of a plain copy now)
-                v[i] = __builtin_nontemporal_load(&values[(e0 + le + delta) * ppe + pin]);
+    const int64_t last = n_pieces - W;                          // the last place to read sixteen bytes from
+    if (kb - ka + 1 > kCopyWindow || last < 0) {
+        // the samples between the tile's first and last do not fit: many empty ones, or more of them than the window has
+        // places for in a tile of wide pieces (or there are no sixteen bytes).  A search per piece.
+        for (int l = threadIdx.x; l < tile_pieces; l += kScanThreads) {
+            const int64_t e = (q0 + l) / ppe;
+            int64_t lo = ka, hi = kb + 1;                       // first sample that starts behind the element
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (out_offsets[mid] <= e) lo = mid + 1; else hi = mid;
             }
+            out[q0 + l] = values[q0 + l + delta[lo > ka ? lo - 1 : ka] * ppe];
+        }
+        return;
+    }
+    const int wn = (int)(kb - ka + 1);
+    // first piece of sample ka + j in the tile; past its end: empty, or not in this tile
+    auto first_in_tile = [&](int j) -> int {
+        const int64_t start = out_offsets[ka + j], next = out_offsets[ka + j + 1], rel = start * ppe - q0;
+        return next <= start || rel >= kCopyTile ? kCopyTile : rel > 0 ? (int)rel : 0;
+    };
+    int rel0 = kCopyTile;                                       // this thread's first sample of the window
+    int64_t delta0 = 0;
+    if ((int)threadIdx.x < wn) {
+        rel0 = first_in_tile(threadIdx.x);
+        delta0 = delta[ka + threadIdx.x];
+    }
+    if ((int)threadIdx.x < kWords) starts[threadIdx.x] = 0;
+    __syncthreads();
+    for (int j = threadIdx.x; j < wn; j += kScanThreads) {
+        const int rel = j == (int)threadIdx.x ? rel0 : first_in_tile(j);
+        if (rel < kCopyTile) atomicOr(&starts[rel >> 5], 1u << (rel & 31));
+    }
+    __syncthreads();
+    {
+        const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+        const uint32_t c = (int)threadIdx.x < kWords ? (uint32_t)__popc(starts[threadIdx.x]) : 0u;
+        const uint32_t inc = wave_inclusive_scan<uint32_t>(c);
+        if (lane == kWave - 1) wave_sum[w] = inc;
+        __syncthreads();
+        uint32_t before = inc - c;
+#pragma unroll
+        for (int i = 0; i < kScanThreads / kWave; ++i) before += i < w ? wave_sum[i] : 0u;
+        if ((int)threadIdx.x < kWords) below[threadIdx.x] = before;
+    }
+    __syncthreads();
+    // the number of the sample that piece l of the tile belongs to
+    auto sample_at = [&](int l) { return (int)below[l >> 5] + __popc(starts[l >> 5] & ((2u << (l & 31)) - 1u)) - 1; };
+    for (int j = threadIdx.x; j < wn; j += kScanThreads) {
+        const bool held = j == (int)threadIdx.x;
+        const int rel = held ? rel0 : first_in_tile(j);
+        if (rel < kCopyTile) w_delta[sample_at(rel)] = (held ? delta0 : delta[ka + j]) * ppe;
+    }
+    __syncthreads();
+    // Wavefront w copies the w-th quarter of the tile, 64 consecutive groups per instruction, front to back.
+    constexpr int kWavePieces = kCopyTile / (kScanThreads / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w0 = (int)(threadIdx.x / kWave) * kWavePieces;
+    static_assert(kWavePieces % (kWave * W * GROUPS) == 0, "a wavefront's quarter is a whole number of rounds");
+#pragma unroll 1
+    for (int r0 = 0; r0 < kWavePieces; r0 += kWave * W * GROUPS) {
+        if (w0 + r0 >= tile_pieces) break;                      // whole wavefront
+        G v[GROUPS];                                            // in flight per lane
+        bool split[GROUPS];                                     // the group has the end of a sample or of the output
+        // boundaries behind the first piece of a group: bit k - 1, piece k
+        auto cuts_of = [&](int l) { return W == 1 ? 0u : (starts[l >> 5] >> (l & 31) >> 1) & ((1u << (W - 1)) - 1u); };
+        // read once, written once: keeping either in the caches only pushes out the boundaries (three
+        // shuffles of 250 k rows of 512 bytes: 202 us with plain accesses, 185 with the hint on the loads
+        // only, 177 on both; at the rate of a plain copy now)
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i) {
+            const int l = w0 + r0 + (i * kWave + lane) * W;     // first piece of the group
+            const int at = l < tile_pieces ? l : tile_pieces - 1;
+            // (every lane loads, from where sixteen bytes are: a load that only some lanes make waits for the one before)
+            const int64_t from = q0 + at + w_delta[sample_at(at)];
+            v[i] = __builtin_nontemporal_load(reinterpret_cast<const G *>(values + (from < last ? from : last)));
+            split[i] = W > 1 && l < tile_pieces && (l + W > tile_pieces || cuts_of(l) != 0);
+        }
+        if constexpr (W > 1) {
+            // the pieces of a divided group come one by one and are put together here: stored one by one they would leave
+            // gaps in the lines that the rest of the wavefront writes
+            V one[GROUPS][W];
+#pragma unroll
+            for (int i = 0; i < GROUPS; ++i)
+                if (split[i]) {
+                    const int l = w0 + r0 + (i * kWave + lane) * W;
+#pragma unroll
+                    for (int k = 0; k < W; ++k) {
+                        const int at = l + k < tile_pieces ? l + k : tile_pieces - 1;
+                        one[i][k] = __builtin_nontemporal_load(values + (q0 + at + w_delta[sample_at(at)]));
+                    }
+                }
+#pragma unroll
+            for (int i = 0; i < GROUPS; ++i)
+#pragma unroll
+                for (int k = 0; k < W; ++k) v[i][k] = split[i] ? one[i][k] : v[i][k];
         }
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            const uint32_t l = w0 + r0 + (uint32_t)i * kWave + lane;
-            if (live[i]) __builtin_nontemporal_store(v[i], &out[q0 + l]);
+        for (int i = 0; i < GROUPS; ++i) {
+            const int l = w0 + r0 + (i * kWave + lane) * W;
+            if (l + W <= tile_pieces) __builtin_nontemporal_store(v[i], reinterpret_cast<G *>(out + q0 + l));
+            else if constexpr (W > 1) {
+#pragma unroll
+                for (int k = 0; k < W; ++k)
+                    if (l + k < tile_pieces) __builtin_nontemporal_store((V)v[i][k], out + q0 + l + k);
+            }
         }
     }
 }
@@ -396,39 +491,39 @@ static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values
                                void *out_values, int64_t cap_out, int64_t *out_offsets, hipStream_t s) {
     const jagged_in in = {offsets, B, n_values};
     const int32_t *sample_of = order.mode == kMapGiven ? order.given : ctx->jag_sel;
+    const int piece = elem_bytes % 16 == 0 ? 16 : (elem_bytes % 8 == 0 ? 8 : 4);
+    const int ppe = elem_bytes / piece;
+    const bool large = piece != 8 && cap_out * ppe >= (piece == 16 ? kCopyLarge16 : kCopyLarge4);
+    const int tile = piece == 16 ? (large ? kCopyTile16Large : kCopyTile16) : piece == 8 ? kCopyTile8
+                                                                            : (large ? kCopyTile4Large : kCopyTile4);
+    const int64_t blocks = n_out > 0 ? ceil_div(cap_out * ppe, tile) : 0;
+    if (blocks > 0x7fffffffll) return set_err(ctx, FS_EINVAL, "indexed permute: output too large for one launch");
+    const copy_plan plan = {ctx->jag_delta, blocks <= 2 * ctx->max_ids ? ctx->jag_tile_first : nullptr, cap_out, ppe,
+                            31 - __builtin_clz(tile)};
     if (n_out <= (int64_t)kPlanThreads * kPlanPer) {
-        hipLaunchKernelGGL(jagged_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, in, order, ctx->jag_sel, (int)n_out,
-                           cap_out, out_offsets, ctx->d_flags);
+        hipLaunchKernelGGL(jagged_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, in, order, (int)n_out, plan, out_offsets,
+                           ctx->d_flags);
     } else {
         const int tiles = (int)ceil_div(n_out, kScanTile);
         hipLaunchKernelGGL(permute_tile_sum_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, order,
                            ctx->jag_sel, n_out, ctx->jag_tile_sum, ctx->d_flags);
         hipLaunchKernelGGL(permute_offsets_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, sample_of,
-                           n_out, ctx->jag_tile_sum, cap_out, out_offsets, ctx->d_flags);
+                           n_out, ctx->jag_tile_sum, plan, out_offsets, ctx->d_flags);
         if (order.splits != nullptr)
             hipLaunchKernelGGL(dispatch_splits_kernel, dim3((unsigned)ceil_div(order.n_ranks, 256)), dim3(256), 0, s, order,
                                out_offsets);
     }
-    if (cap_out > 0 && n_out > 0) {
-        const int piece = elem_bytes % 16 == 0 ? 16 : (elem_bytes % 8 == 0 ? 8 : 4);
-        const int ppe = elem_bytes / piece;
-        const bool large = piece == 4 && cap_out * ppe >= kCopyLargeFrom;
-        const int tile = piece == 16 ? kCopyTile16 : (piece == 8 ? kCopyTile8 : (large ? kCopyTile4Large : kCopyTile4));
-        const int64_t blocks = ceil_div(cap_out * ppe, tile);
-        if (blocks > 0x7fffffffll) return set_err(ctx, FS_EINVAL, "indexed permute: output too large for one launch");
+    if (blocks > 0) {
         const dim3 grid((unsigned)blocks);
-        if (piece == 16)
-            hipLaunchKernelGGL((permute_copy_kernel<u32x4, kCopyTile16, 8>), grid, dim3(kScanThreads), 0, s, (const u32x4 *)values,
-                               in, sample_of, n_out, out_offsets, cap_out, ppe, (u32x4 *)out_values);
-        else if (piece == 8)
-            hipLaunchKernelGGL((permute_copy_kernel<uint64_t, kCopyTile8, 8>), grid, dim3(kScanThreads), 0, s, (const uint64_t *)values,
-                               in, sample_of, n_out, out_offsets, cap_out, ppe, (uint64_t *)out_values);
-        else if (large)
-            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, kCopyTile4Large, 16>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
-                               in, sample_of, n_out, out_offsets, cap_out, ppe, (uint32_t *)out_values);
-        else
-            hipLaunchKernelGGL((permute_copy_kernel<uint32_t, kCopyTile4, 8>), grid, dim3(kScanThreads), 0, s, (const uint32_t *)values,
-                               in, sample_of, n_out, out_offsets, cap_out, ppe, (uint32_t *)out_values);
+#define FS_COPY(V, TILE, GROUPS)                                                                                       \
+    hipLaunchKernelGGL((permute_copy_kernel<V, TILE, GROUPS>), grid, dim3(kScanThreads), 0, s, (const V *)values,      \
+                       n_values * ppe, n_out, out_offsets, plan, (V *)out_values)
+        if (piece == 16 && large) FS_COPY(u32x4, kCopyTile16Large, 2);
+        else if (piece == 16) FS_COPY(u32x4, kCopyTile16, 8);
+        else if (piece == 8) FS_COPY(uint64_t, kCopyTile8, 4);
+        else if (large) FS_COPY(uint32_t, kCopyTile4Large, 4);
+        else FS_COPY(uint32_t, kCopyTile4, 2);
+#undef FS_COPY
     }
     FS_LAUNCH_CHECK(ctx, "indexed permute kernels");
     return FS_OK;

@@ -70,6 +70,8 @@ struct bucket_dev_job {
     int64_t *unique;
     int32_t *seg_offsets, *perm, *inverse;
     int64_t *n_unique_dev, *sorted_ids;
+    fs_zigzag deal;                                          // order alone: n > 0: dealt to n ranks, whose shares begin at
+    int64_t *rank_offsets;                                   // [n + 1]
 };
 struct bucket_dev_batch {
     bucket_dev_job j[kMaxBatch];
@@ -416,6 +418,11 @@ __device__ __forceinline__ uint32_t wide_exclusive_scan(uint32_t v, uint32_t *sh
     return base + inc - v;
 }
 
+// where the occurrence of a sorted position goes, where the order alone is wanted
+__device__ __forceinline__ uint32_t place_in_order(const bucket_dev_job &job, int p) {
+    return job.deal.n > 0 ? job.deal.place32((uint32_t)p) : (uint32_t)p;
+}
+
 // one position of the sorted batch
 __device__ __forceinline__ void emit(const bucket_dev_job &job, int first, int i, uint32_t key, uint32_t occurrence, bool head,
                                      int heads_before) {
@@ -430,6 +437,7 @@ __device__ __forceinline__ void emit(const bucket_dev_job &job, int first, int i
 }
 
 // A range that does not fit LDS: the same radix passes between two buffers in memory, a workgroup's width at a time.
+template <bool ORDER>
 __device__ __forceinline__ int sort_in_memory(const bucket_dev_job &job, const range_pieces &pieces, int first, int size,
                                               uint32_t lo, int bits, bucket_sort_shared &sh, uint32_t *wave_sum) {
     const int w = threadIdx.x / kWave;
@@ -490,6 +498,10 @@ __device__ __forceinline__ int sort_in_memory(const bucket_dev_job &job, const r
         }
     }
     __syncthreads();
+    if constexpr (ORDER) {
+        for (int i = threadIdx.x; i < size; i += kBucketThreads) job.perm[place_in_order(job, first + i)] = job.big_idx[0][first + i];
+        return 0;
+    }
     uint32_t heads = 0;                                      // buffer 0 holds the result; its places are perm itself
     const uint32_t *k0 = job.big_key[0] + first;
     const int32_t *v0 = job.big_idx[0] + first;
@@ -507,6 +519,8 @@ __device__ __forceinline__ int sort_in_memory(const bucket_dev_job &job, const r
     return (int)heads;
 }
 
+// ORDER: of every job the order alone is wanted (a kernel of its own: the deal costs registers)
+template <bool ORDER>
 __global__ __launch_bounds__(kBucketThreads, 8) void bucket_sort_kernel(const bucket_dev_batch batch) {
     FS_WG_TRACE(15);
     const bucket_dev_job &job = batch.j[blockIdx.y];
@@ -524,6 +538,9 @@ __global__ __launch_bounds__(kBucketThreads, 8) void bucket_sort_kernel(const bu
     const int n = job.n, tiles = job.tiles;
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x / kWave;
+    if (ORDER && job.deal.n > 0)
+        for (int64_t i = (int64_t)blockIdx.x * kBucketThreads + threadIdx.x; i <= job.deal.n; i += (int64_t)ranges * kBucketThreads)
+            job.rank_offsets[i] = job.deal.rank_start(i);
     // boundaries, what there is to do, and the table's columns: one round of loads unless this range helps another
     uint32_t lo = e > 0 ? bound_at(job.cut, e - 1) : 0u;
     const uint32_t hi = e < ranges - 1 ? bound_at(job.cut, e) : (uint32_t)job.num_rows;
@@ -587,12 +604,12 @@ __global__ __launch_bounds__(kBucketThreads, 8) void bucket_sort_kernel(const bu
             for (int k = 0; k < 4; ++k)
                 if (i + k * kBucketThreads < i1) {
                     const int p = first + i + k * kBucketThreads;
-                    job.perm[p] = tile[k] * kBucketTile + (int)place[k];
+                    job.perm[ORDER ? place_in_order(job, p) : (uint32_t)p] = tile[k] * kBucketTile + (int)place[k];
                     if (job.inverse != nullptr) job.rank[p] = part == 0 ? 1 : 0;
                     if (job.sorted_ids != nullptr) job.sorted_ids[p] = (int64_t)lo;
                 }
         }
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 0 && !ORDER) {
             const bool row = part == 0 && size > 0;
             if (row) {
                 job.row_key[first] = lo;
@@ -626,6 +643,11 @@ __global__ __launch_bounds__(kBucketThreads, 8) void bucket_sort_kernel(const bu
         }
         __syncthreads();                                     // the list of pieces gives way to the counters
         sort_any(size, bits, skey, sval, sh.sort);
+        if constexpr (ORDER) {
+            for (int i = threadIdx.x; i < size; i += kBucketThreads)
+                job.perm[place_in_order(job, first + i)] = (int32_t)(sval[i] & kPlaceMask);
+            return;
+        }
         // the distinct rows, numbered: a wavefront has consecutive elements, G rounds side by side
         constexpr int G = 4;
         const int rounds = (size + kBucketThreads - 1) / kBucketThreads;
@@ -678,9 +700,9 @@ __global__ __launch_bounds__(kBucketThreads, 8) void bucket_sort_kernel(const bu
         }
         __syncthreads();
         const range_pieces moved = {before2, at2, tiles, steps};
-        heads = sort_in_memory(job, moved, first, size, lo, bits, sh.sort, wave_sum);
+        heads = sort_in_memory<ORDER>(job, moved, first, size, lo, bits, sh.sort, wave_sum);
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && !ORDER) {
         job.first[e] = first;
         job.size[e] = size;
         job.heads[e] = heads;
@@ -725,6 +747,7 @@ int launch_bucket_unique(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipS
     bucket_dev_batch batch;
     memset(&batch, 0, sizeof(batch));
     int tiles = 0, log2 = 0;
+    bool dedup = false;                                      // else the order alone is wanted of every job
     for (int k = 0; k < count; ++k) {
         const fs_unique_job &in = jobs[k];
         const fs_sort_scratch &ws = ctx->sort[set0 + k];
@@ -744,7 +767,11 @@ int launch_bucket_unique(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipS
         j.rank = ws.idx[1];
         // a range sorted in memory ends in buffer 0: keys beside the list of its rows, places where they belong
         j.big_key[0] = k1 + ctx->max_ids; j.big_key[1] = k1;
-        j.big_idx[0] = in.perm; j.big_idx[1] = ws.idx[1];
+        // (dealt, they are spread over the output, and the list of first positions is not made)
+        j.big_idx[0] = in.deal > 0 ? j.row_seg : in.perm; j.big_idx[1] = ws.idx[1];
+        if (in.deal > 0) j.deal = fs_zigzag{in.deal, in.n / in.deal, in.n % in.deal};
+        j.rank_offsets = in.rank_offsets;
+        dedup = dedup || !in.order_only;
         j.unique = in.unique; j.seg_offsets = in.seg_offsets; j.perm = in.perm; j.inverse = in.inverse;
         j.n_unique_dev = in.n_unique_dev; j.sorted_ids = in.sorted_ids;
         tiles = j.tiles > tiles ? j.tiles : tiles;
@@ -756,9 +783,10 @@ int launch_bucket_unique(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipS
     if (tiles > 0)
         hipLaunchKernelGGL(bucket_partition_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kPartThreads), part_lds, s,
                            batch, ctx->d_flags);
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3(ranges, (unsigned)count), dim3(kBucketThreads),
-                       2 * kBucketCap * sizeof(uint32_t), s, batch);
-    hipLaunchKernelGGL(bucket_compact_kernel, dim3(ranges, (unsigned)count), dim3(kScanThreads), 0, s, batch);
+    auto *sort = dedup ? &bucket_sort_kernel<false> : &bucket_sort_kernel<true>;
+    hipLaunchKernelGGL(sort, dim3(ranges, (unsigned)count), dim3(kBucketThreads), 2 * kBucketCap * sizeof(uint32_t), s, batch);
+    if (dedup)
+        hipLaunchKernelGGL(bucket_compact_kernel, dim3(ranges, (unsigned)count), dim3(kScanThreads), 0, s, batch);
     FS_LAUNCH_CHECK(ctx, "bucket kernels");
     return FS_OK;
 }

@@ -101,6 +101,32 @@ struct fs_unique_job {
     int32_t *seg_offsets, *perm, *inverse;
     int64_t *n_unique_dev;
     int64_t *sorted_ids = nullptr;  // optional [n]: all IDs in ascending order
+    // Only the order of the IDs is wanted: unique, seg_offsets and n_unique_dev need not be written (they are scratch of the
+    // right size all the same).  By ranges the order can be dealt to ranks on the way (fs_jagged.hip): perm then holds what
+    // rank 0 gets, what rank 1 gets and so on, and rank_offsets [deal + 1] where a rank's share begins.
+    bool order_only = false;
+    int32_t deal = 0;
+    int64_t *rank_offsets = nullptr;
+};
+// The deal of B sorted samples to n ranks in a zig-zag: full rounds R = B / n, m = B % n samples in the last, partial round
+// (round R), forth if R is even (ranks 0..m-1 get one more), back if R is odd (ranks n-m..n-1 get one more).
+struct fs_zigzag {
+    int64_t n, R, m;
+    __host__ __device__ __forceinline__ int64_t rank_start(int64_t i) const {
+        const int64_t extra = (R % 2 == 0) ? (i < m ? i : m) : (i > n - m ? i - (n - m) : 0);
+        return i * R + extra;
+    }
+    // place of sorted position s
+    __device__ __forceinline__ int64_t place(int64_t s) const {
+        const int64_t r = s / n, c = s % n;
+        return rank_start((r % 2 == 0) ? c : n - 1 - c) + r;
+    }
+    // the same for up to 2^31 samples and ranks
+    __device__ __forceinline__ uint32_t place32(uint32_t s) const {
+        const uint32_t k = (uint32_t)n, r = s / k, c = s - r * k, i = (r & 1) ? k - 1 - c : c, last = (uint32_t)m;
+        const uint32_t extra = (R & 1) ? (i > k - last ? i - (k - last) : 0u) : (i < last ? i : last);
+        return i * (uint32_t)R + extra + r;
+    }
 };
 struct fs_split_job {
     const int64_t *u_t, *n_t_dev, *u_t1, *n_t1_dev;
@@ -320,6 +346,7 @@ int launch_unique(fs_ctx *, const int64_t *ids, int64_t n, int64_t num_rows, int
                   int set = 0);
 // `count` (1..kMaxBatch) independent jobs in shared launches; job k uses scratch set set0 + k; alone: an operation of its
 // own, not part of an index half
+bool unique_by_ranges(int count, const fs_unique_job *jobs, int set0, bool alone);   // the form that the next call takes
 int launch_unique_batch(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0, bool alone = false);
 // the same by ranges of keys, for jobs that dedup_by_ranges takes
 size_t bucket_table_size(int64_t max_ids);               // entries of fs_sort_scratch::range_start

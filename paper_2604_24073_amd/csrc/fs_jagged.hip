@@ -24,39 +24,36 @@
 namespace fs {
 
 // ---- FBS: the deal ------------------------------------------------------------------------------------
-// full rounds R = B / n, m = B % n samples in the last, partial round (round R): forth if R is even
-// (ranks 0..m-1 get one more), back if R is odd (ranks n-m..n-1 get one more)
-__device__ __forceinline__ int64_t fbs_rank_start(int64_t i, int64_t n, int64_t R, int64_t m) {
-    const int64_t extra = (R % 2 == 0) ? (i < m ? i : m) : (i > n - m ? i - (n - m) : 0);
-    return i * R + extra;
-}
-
-__global__ __launch_bounds__(256) void fbs_deal_kernel(const int32_t *__restrict__ sorted, int64_t B, int64_t n,
+// By ranges of keys the sort deals its positions itself and writes nothing that only a dedup needs: balancing 65 k samples
+// three launches where sort, list of the distinct lengths and deal were five.
+__global__ __launch_bounds__(256) void fbs_deal_kernel(const int32_t *__restrict__ sorted, int64_t B, const fs_zigzag deal,
                                                        int32_t *__restrict__ sample_of,
                                                        int64_t *__restrict__ rank_offsets) {
-    const int64_t R = B / n, m = B % n;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t i = gtid; i <= n; i += stride) rank_offsets[i] = fbs_rank_start(i, n, R, m);
-    for (int64_t s = gtid; s < B; s += stride) {
-        const int64_t r = s / n, c = s % n;
-        const int64_t i = (r % 2 == 0) ? c : n - 1 - c;
-        sample_of[fbs_rank_start(i, n, R, m) + r] = sorted[s];
-    }
+    for (int64_t i = gtid; i <= deal.n; i += stride) rank_offsets[i] = deal.rank_start(i);
+    for (int64_t s = gtid; s < B; s += stride) sample_of[deal.place(s)] = sorted[s];
 }
 
 int launch_partition_fbs(fs_ctx *ctx, const int64_t *lengths, int64_t B, int64_t max_len, int32_t n_ranks,
                          int32_t *sample_of, int64_t *rank_offsets, hipStream_t s) {
     if (B > 0) {
-        const int rc = launch_unique(ctx, lengths, B, max_len + 1, ctx->jag_unique, ctx->jag_seg, ctx->jag_sorted,
-                                     nullptr, ctx->jag_n, s, 0);
-        if (rc != FS_OK) return rc;
+        fs_unique_job job = {lengths, B, max_len + 1, ctx->jag_unique, ctx->jag_seg, ctx->jag_sorted, nullptr, ctx->jag_n};
+        job.order_only = true;
+        const bool dealt = unique_by_ranges(1, &job, 0, true);
+        if (dealt) {
+            job.perm = sample_of;
+            job.deal = n_ranks;
+            job.rank_offsets = rank_offsets;
+        }
+        const int rc = launch_unique_batch(ctx, 1, &job, s, 0, true);
+        if (rc != FS_OK || dealt) return rc;
     }
     const int64_t work = B > n_ranks ? B : (int64_t)n_ranks + 1;
     int64_t blocks = ceil_div(work, 256);
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(fbs_deal_kernel, dim3((unsigned)blocks), dim3(256), 0, s, ctx->jag_sorted, B, (int64_t)n_ranks,
-                       sample_of, rank_offsets);
+    hipLaunchKernelGGL(fbs_deal_kernel, dim3((unsigned)blocks), dim3(256), 0, s, ctx->jag_sorted, B,
+                       fs_zigzag{n_ranks, B / n_ranks, B % n_ranks}, sample_of, rank_offsets);
     FS_LAUNCH_CHECK(ctx, "fbs_deal_kernel");
     return FS_OK;
 }
@@ -630,8 +627,9 @@ int launch_partition_vbs(fs_ctx *ctx, const int64_t *lengths, int64_t B, const i
                          int32_t n_ranks, int32_t *sample_of, int64_t *rank_offsets, hipStream_t s) {
     const int tiles = (int)(B > 0 ? ceil_div(B, kScanTile) : 1);
     if (B > 0) {
-        const int rc = launch_unique(ctx, lengths, B, max_len + 1, ctx->jag_unique, ctx->jag_seg, sample_of, nullptr,
-                                     ctx->jag_n, s, 0);
+        fs_unique_job job = {lengths, B, max_len + 1, ctx->jag_unique, ctx->jag_seg, sample_of, nullptr, ctx->jag_n};
+        job.order_only = true;
+        const int rc = launch_unique_batch(ctx, 1, &job, s, 0, true);
         if (rc != FS_OK) return rc;
         hipLaunchKernelGGL(vbs_tile_sum_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, lengths, sample_of, B,
                            weight_of_len, max_len, ctx->jag_tile_sum, ctx->d_flags);

@@ -325,7 +325,8 @@ __global__ void unique_empty_kernel(int32_t *seg_offsets, int64_t *n_unique_dev)
 
 // ---- host side ------------------------------------------------------------------------------------------
 template <typename K>
-static int unique_batch_impl(fs_ctx *ctx, const unique_dev_batch &batch, int count, int key_bits, hipStream_t s) {
+static int unique_batch_impl(fs_ctx *ctx, const unique_dev_batch &batch, int count, int key_bits,
+                             bool order_only, hipStream_t s) {
     int tiles = 0, stiles = 0;
     for (int k = 0; k < count; ++k) {
         tiles = batch.j[k].tiles > tiles ? batch.j[k].tiles : tiles;
@@ -353,11 +354,31 @@ static int unique_batch_impl(fs_ctx *ctx, const unique_dev_batch &batch, int cou
             cur ^= 1;
         }
     }
+    if (order_only) {                                             // the last pass has written it
+        FS_LAUNCH_CHECK(ctx, "radix kernels");
+        return FS_OK;
+    }
     const dim3 sgrid((unsigned)stiles, (unsigned)count);
     hipLaunchKernelGGL((unique_count_kernel<K>), sgrid, dim3(kScanThreads), 0, s, batch, cur);
     hipLaunchKernelGGL((unique_compact_kernel<K>), sgrid, dim3(kScanThreads), 0, s, batch, cur);
     FS_LAUNCH_CHECK(ctx, "unique kernels");
     return FS_OK;
+}
+
+// one sort geometry for the whole batch: the widest key decides (sorting zero bits is harmless)
+static int widest_key(int count, const fs_unique_job *jobs) {
+    int key_bits = 1;
+    for (int k = 0; k < count; ++k) {
+        const int kb = key_bits_of(jobs[k].num_rows);
+        key_bits = kb > key_bits ? kb : key_bits;
+    }
+    return key_bits;
+}
+
+bool unique_by_ranges(int count, const fs_unique_job *jobs, int set0, bool alone) {
+    int64_t most = 0;
+    for (int k = 0; k < count; ++k) most = jobs[k].n > most ? jobs[k].n : most;
+    return most > 0 && !small_unique_fits(count, jobs, set0) && dedup_by_ranges(most, widest_key(count, jobs), alone);
 }
 
 int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipStream_t s, int set0, bool alone) {
@@ -369,15 +390,10 @@ int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipSt
         FS_LAUNCH_CHECK(ctx, "unique_empty_kernel");
         return FS_OK;
     }
-    // one sort geometry for the whole batch: the widest key decides (sorting zero bits is harmless)
-    int key_bits = 1;
-    int64_t most = 0;
-    for (int k = 0; k < count; ++k) {
-        const int kb = key_bits_of(jobs[k].num_rows);
-        key_bits = kb > key_bits ? kb : key_bits;
-        most = jobs[k].n > most ? jobs[k].n : most;
-    }
-    if (dedup_by_ranges(most, key_bits, alone)) return launch_bucket_unique(ctx, count, jobs, s, set0);
+    if (unique_by_ranges(count, jobs, set0, alone)) return launch_bucket_unique(ctx, count, jobs, s, set0);
+    const int key_bits = widest_key(count, jobs);
+    bool order_only = true;
+    for (int k = 0; k < count; ++k) order_only = order_only && jobs[k].order_only;
     unique_dev_batch batch;
     memset(&batch, 0, sizeof(batch));
     for (int k = 0; k < count; ++k) {
@@ -402,8 +418,8 @@ int launch_unique_batch(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipSt
         j.n_unique_dev = in.n_unique_dev;
         j.sorted_ids = in.sorted_ids;
     }
-    if (key_bits <= 32) return unique_batch_impl<uint32_t>(ctx, batch, count, key_bits, s);
-    return unique_batch_impl<uint64_t>(ctx, batch, count, key_bits, s);
+    if (key_bits <= 32) return unique_batch_impl<uint32_t>(ctx, batch, count, key_bits, order_only, s);
+    return unique_batch_impl<uint64_t>(ctx, batch, count, key_bits, order_only, s);
 }
 
 int launch_unique(fs_ctx *ctx, const int64_t *ids, int64_t n, int64_t num_rows, int64_t *unique,

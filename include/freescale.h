@@ -143,8 +143,7 @@ int fs_collision_split_static(const int64_t *u_t, const int64_t *n_t_dev, const 
  * accumulated in fp64 in a fixed order (results do not vary run to run) and rounded once to
  * fp32.  grads [n, dim] fp32; reduced needs *n_unique_dev rows (at most n).
  * inverse [n] is OPTIONAL (NULL allowed): the inverse map that fs_unique_ids wrote next to perm
- * and seg_offsets.  With it every wavefront reads the segment of its positions directly instead
- * of searching seg_offsets; the results are bit-identical either way. */
+ * and seg_offsets.  It is not read; the results are the same either way. */
 int fs_segment_reduce_grads(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim,
                             const int32_t *perm, const int32_t *seg_offsets, const int32_t *inverse,
                             const int64_t *n_unique_dev, float *reduced, fs_stream stream);

@@ -135,7 +135,6 @@ void carve(fs_ctx *c, char *base, size_t *total) {
     const size_t n = (size_t)c->max_ids;
     const size_t sort_tiles = (size_t)ceil_div(c->max_ids, kSortTile) + 1;
     const size_t scan_tiles = (size_t)ceil_div(c->max_ids, kScanTile) + 2;
-    const size_t chunks = (size_t)ceil_div(c->max_ids, kReduceChunk) + 2;
     c->d_flags = cv.take<int>(4);
     c->d_zero = cv.take<int64_t>(1);
     for (int k = 0; k < kSortSets; ++k) {
@@ -158,11 +157,8 @@ void carve(fs_ctx *c, char *base, size_t *total) {
         ws.tile_len = cv.take<int32_t>(2 * scan_tiles);
         ws.cidx = cv.take<int32_t>(n + 16);
     }
-    c->part_head = cv.take<double>(chunks * (size_t)c->max_dim);
-    c->part_last = cv.take<double>(chunks * (size_t)c->max_dim);
-    c->chunk_desc = cv.take<int32_t>(chunks * 4);
-    const size_t fchunks = (size_t)fused_chunk_space(c->max_ids);
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < kFusedSets; ++k) {
+        const size_t fchunks = (size_t)fused_chunk_space(c->max_ids, k);
         c->fpart_head[k] = cv.take<double>(fchunks * (size_t)c->max_dim);
         c->fpart_last[k] = cv.take<double>(fchunks * (size_t)c->max_dim);
         c->fcounters[k] = cv.take<int>(fchunks);
@@ -343,8 +339,8 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     size_t total;
     carve(c, static_cast<char *>(c->slab), &total);
     bool ok = hipMemset(c->slab, 0, 4096) == hipSuccess;
-    for (int k = 0; k < 2; ++k) {
-        const size_t bytes = (size_t)fused_chunk_space(c->max_ids) * sizeof(int);
+    for (int k = 0; k < kFusedSets; ++k) {
+        const size_t bytes = (size_t)fused_chunk_space(c->max_ids, k) * sizeof(int);
         ok = ok && hipMemset(c->fcounters[k], 0, bytes) == hipSuccess;
         ok = ok && hipMemset(c->fcounters_sup[k], 0, bytes) == hipSuccess;
     }
@@ -421,8 +417,8 @@ int fs_check_async(fs_ctx *ctx, fs_stream stream) {
     if (flags[0] & kFlagInternal) {
         // a fused pass that met an inconsistent class order left cut segments half counted in: the arrival
         // counters must stand at zero again before the next pass (every stream is idle here)
-        const size_t bytes = (size_t)fused_chunk_space(ctx->max_ids) * sizeof(int);
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < kFusedSets; ++k) {
+            const size_t bytes = (size_t)fused_chunk_space(ctx->max_ids, k) * sizeof(int);
             FS_HIP(ctx, hipMemset(ctx->fcounters[k], 0, bytes));
             FS_HIP(ctx, hipMemset(ctx->fcounters_sup[k], 0, bytes));
         }
@@ -549,10 +545,8 @@ int fs_segment_reduce_grads(fs_ctx *ctx, const float *grads, int64_t n, int32_t 
     if (n > ctx->max_ids || dim > ctx->max_dim) return set_err(ctx, FS_ENOMEM, "reduce: beyond the context capacity");
     if (n == 0) return FS_OK;
     FS_REQUIRE(ctx, grads && perm && seg_offsets && n_unique_dev && reduced, "reduce: null pointer");
-    ctx->reduce_inverse = inverse;
-    const int rc = launch_reduce(ctx, grads, n, dim, perm, seg_offsets, n_unique_dev, reduced, as_stream(stream));
-    ctx->reduce_inverse = nullptr;
-    return rc;
+    (void)inverse;
+    return launch_reduce(ctx, grads, n, dim, perm, seg_offsets, n_unique_dev, reduced, as_stream(stream));
 }
 
 int fs_rowwise_adagrad_update(fs_ctx *ctx, void *table, fs_dtype dt, float *state, int64_t num_rows, int32_t dim,

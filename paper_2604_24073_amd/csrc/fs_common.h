@@ -40,10 +40,6 @@ constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 constexpr int64_t kSmallSplitInline = 4096;
 constexpr int64_t kSmallClassesInline = 6144;
 
-// segment reduce: sorted positions owned by one wavefront (one 64-bit tail mask, one permutation
-// entry per lane).  Short chunks = many wavefronts with short dependent-load chains.
-constexpr int kReduceChunk = 64;
-constexpr int kReduceWavesPerBlock = 4;
 constexpr int kShortRecInts = 12;                         // row (2), slot, occurrences, occurrence list (FS_SHORT_SEGMENT)
 static_assert(FS_SHORT_SEGMENT == 8, "record layout");
 // Fused pass: positions of a chunk (log2) for a batch of n occurrences.  A big batch fills the chip with chunks of 64,
@@ -54,6 +50,7 @@ static_assert(FS_SHORT_SEGMENT == 8, "record layout");
 // of 60 k 1302 / 1310 / 1328, of 100 k 1892 / 1906 / 1998, of 130 k 2265 / 2335 / 2410.  It depends on the batch alone
 // and not on the tables beside it, for the order of the sums is part of the result, so the lines lie between.
 constexpr int kFusedWaves = 4;                            // wavefronts per workgroup (they never synchronise)
+constexpr int kReduceSet = 2, kFusedSets = 3;             // sets of partial rows and counters
 inline int chunk_log2(int64_t n) { return n >= 131072 ? 6 : (n >= 65536 ? 5 : 4); }
 
 // device-side error flag bits (ctx->d_flags[0])
@@ -213,17 +210,13 @@ struct fs_ctx {
     int *d_flags;             // [4] device error flags
     fs_sort_scratch sort[kSortSets];
     fs_split_scratch split[kSortSets];
-    // segment reduce
-    double *part_head;        // [chunks, max_dim] fp64 partial of the first run of each chunk
-    double *part_last;        // [chunks, max_dim] fp64 partial of the last run of each chunk
-    int32_t *chunk_desc;      // [chunks * 4]
     // fused reduce+update, one set per class (0 = collision rows, 1 = exclusive rows) so that the
-    // priority pass of one iteration and the deferred pass of another may run side by side
-    double *fpart_head[2];    // [chunks, max_dim] piece of a cut segment that came in from the previous chunk
-    double *fpart_last[2];    // [chunks, max_dim] first piece of a cut segment that continues into the next chunk
-    int *fcounters[2];        // [chunks] arrivals per cut segment (indexed by its first chunk); at 0 between launches
-    int *fcounters_sup[2];    // [chunks] arrivals per group of sixteen pieces (indexed by its first chunk)
-    const int32_t *reduce_inverse;   // host-side: the caller's optional inverse map for the launch being enqueued
+    // priority pass of one iteration and the deferred pass of another may run side by side, and kReduceSet for the
+    // segment reduce as an operation of its own
+    double *fpart_head[fs::kFusedSets];    // [chunks, max_dim] piece of a cut segment that came in from the previous chunk
+    double *fpart_last[fs::kFusedSets];    // [chunks, max_dim] first piece of a cut segment that continues into the next chunk
+    int *fcounters[fs::kFusedSets];        // [chunks] arrivals per cut segment (indexed by its first chunk); at 0 between launches
+    int *fcounters_sup[fs::kFusedSets];    // [chunks] arrivals per group of sixteen pieces (indexed by its first chunk)
     int64_t *d_zero;          // device scalar that stays 0 (stands in for a missing lookahead)
     // partitioner and jagged shuffles
     int64_t *jag_unique;      // [max_ids] by-products of sorting the lengths (distinct lengths, their extents, count)
@@ -315,8 +308,10 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // below the one from which chunks are longest (a table has the most of them just below 65536 occurrences), and four of
 // max_ids, so that the tables of a call share their launch (with room for one table a launch, ten steps of eight tables
 // of 32 k occurrences took 2105 us, with this 1535; four of 60 k 1440 and 1325).
-inline int64_t fused_chunk_space(int64_t max_ids) {
+// The segment reduce takes one batch at a time.
+inline int64_t fused_chunk_space(int64_t max_ids, int set = 0) {
     const int64_t most = max_ids < 65536 ? max_ids : 65536;
+    if (set == kReduceSet) return (most / 16 > max_ids / 64 ? most / 16 : max_ids / 64) + 2 * kFusedWaves;
     const int64_t batch = kMaxBatch * (ceil_div(most, 16) + kFusedWaves), largest = ceil_div(max_ids, 16) + 4 * kFusedWaves;
     return batch > largest ? batch : largest;
 }
@@ -376,10 +371,8 @@ int launch_batch_update(fs_ctx *, const fs_batch_update_job &job, hipStream_t s)
 // dtype share launches, whatever their widths
 int launch_reduce_update_batch(fs_ctx *, int cls, int count, const fs_class_pass_job *jobs, hipStream_t s);
 int launch_gather_batch(fs_ctx *, int count, const fs_gather_job *jobs, hipStream_t s);
-// `timing`: optional event pair recorded around the main (chunk) kernel only
 int launch_reduce(fs_ctx *, const float *grads, int64_t n, int32_t dim, const int32_t *perm,
-                  const int32_t *seg_offsets, const int64_t *n_unique_dev, float *reduced, hipStream_t s,
-                  hipEvent_t *timing = nullptr);
+                  const int32_t *seg_offsets, const int64_t *n_unique_dev, float *reduced, hipStream_t s);
 int launch_adagrad(fs_ctx *, void *table, int dt, float *state, int64_t num_rows, int32_t dim,
                    const int64_t *rows, const int32_t *slots, const int64_t *n_rows_dev, int64_t cap,
                    const float *reduced, float lr, float eps, hipStream_t s);

@@ -52,12 +52,16 @@ constexpr int kFusedSuper = 16;            // pieces of a cut segment that are a
 
 // Adagrad on `nrows` parked rows of one wavefront.  Group g of the wavefront takes rows g, g+GPW, ...
 // stage: [row][LPR] fp32 sums (4 columns per lane), stage_row: table row, stage_slot: slot in U_t.
-template <bool BF16, int LPR, int RU>
+// What is done with a row's sum: Adagrad on a table of fp32 or of bf16 rows, or nothing but writing it down.
+enum row_use { kUpdateF32, kUpdateBf16, kSumOnly };
+
+template <row_use USE, int LPR, int RU>
 __device__ __forceinline__ void update_parked(const f32x4 *stage, const int64_t *stage_row, const int *stage_slot,
                                               int nrows, void *table, float *state, int64_t num_rows, int gvec,
                                               float lr, float eps, f32x4 *reduced, bool &oob) {
 #pragma clang fp contract(off)
     constexpr int GPW = kWave / LPR;
+    constexpr bool BF16 = USE == kUpdateBf16;
     const int lane = threadIdx.x & (kWave - 1);
     const int grp = lane / LPR;
     const int lig = lane % LPR;
@@ -65,6 +69,11 @@ __device__ __forceinline__ void update_parked(const f32x4 *stage, const int64_t 
     const int dim = gvec * 4;
     u32x4 *t4 = reinterpret_cast<u32x4 *>(table);
     u32x2 *t2 = reinterpret_cast<u32x2 *>(table);
+    if constexpr (USE == kSumOnly) {
+        for (int k = grp; k < nrows; k += GPW)
+            if (col_ok) reduced[(int64_t)stage_slot[k] * gvec + lig] = stage[k * LPR + lig];
+        return;
+    }
     for (int base = 0; base < nrows; base += GPW * RU) {
         int64_t r[RU];
         int k[RU];
@@ -192,7 +201,7 @@ struct parked_rows {
     int slot[kFusedWaves][kParkedMost];
 };
 
-template <bool BF16, int LPR, int UNR>
+template <row_use USE, int LPR, int UNR>
 __device__ __forceinline__ void long_chunk(parked_rows<LPR> &sh, const chunk_view &ch, const f32x4 *__restrict__ grads,
                                            const int64_t *__restrict__ u_t, void *table, float *state, int64_t num_rows,
                                            int gvec, float lr, float eps, f32x4 *reduced, double *part_head,
@@ -298,7 +307,7 @@ __device__ __forceinline__ void long_chunk(parked_rows<LPR> &sh, const chunk_vie
     }
     if (nparked > 0) {
         wave_lds_sync();
-        update_parked<BF16, LPR, RU>(stage[wib], stage_row[wib], stage_slot[wib], nparked, table, state, num_rows,
+        update_parked<USE, LPR, RU>(stage[wib], stage_row[wib], stage_slot[wib], nparked, table, state, num_rows,
                                      gvec, lr, eps, reduced, oob);
         wave_lds_sync();
     }
@@ -367,10 +376,10 @@ __device__ __forceinline__ void long_chunk(parked_rows<LPR> &sh, const chunk_vie
         if (grp == 0 && col_ok) stage[wib][lig] = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
         if (lane == 0) {
             stage_slot[wib][0] = s;
-            stage_row[wib][0] = u_t[s];
+            stage_row[wib][0] = USE == kSumOnly ? 0 : u_t[s];
         }
         wave_lds_sync();
-        update_parked<BF16, LPR, 1>(stage[wib], stage_row[wib], stage_slot[wib], 1, table, state, num_rows, gvec, lr,
+        update_parked<USE, LPR, 1>(stage[wib], stage_row[wib], stage_slot[wib], 1, table, state, num_rows, gvec, lr,
                                     eps, reduced, oob);
         wave_lds_sync();
     };
@@ -398,7 +407,7 @@ __device__ __forceinline__ void long_chunk(parked_rows<LPR> &sh, const chunk_vie
 }
 
 // The position-cut path over the class order: chunk `block * kFusedWaves + wavefront` of the class's positions.
-template <bool BF16, int LPR, int UNR>
+template <row_use USE, int LPR, int UNR>
 __device__ __forceinline__ void long_segments_body(
     parked_rows<LPR> &sh, const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ cperm,
     const int32_t *__restrict__ cslot, const int32_t *__restrict__ class_pos, int cls, int n,
@@ -454,14 +463,14 @@ __device__ __forceinline__ void long_segments_body(
         ch.start[which] = __shfl(meta, which * 3 + 0, kWave);
         ch.len[which] = __shfl(meta, which * 3 + 2, kWave) - __shfl(meta, which * 3 + 1, kWave);
     }
-    long_chunk<BF16, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
+    long_chunk<USE, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
                                cnt_seg, cnt_sup, bad, flags);
 }
 
 // The position-cut path straight over the layout of a batch (sorted positions, segment boundaries): positions of
 // segments with at most FS_SHORT_SEGMENT occurrences take no part.  The wavefront finds the segment of its first
 // position with a 64-ary search; its positions touch at most 64 consecutive segments, whose boundaries its lanes hold.
-template <bool BF16, int LPR, int UNR>
+template <row_use USE, int LPR, int UNR>
 __device__ __forceinline__ void long_segments_of_layout(
     parked_rows<LPR> &sh, const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ perm, int n,
     const int32_t *__restrict__ seg_offsets, const int64_t *__restrict__ u_t, int n_u, void *table, float *state,
@@ -503,7 +512,7 @@ __device__ __forceinline__ void long_segments_of_layout(
         return;
     }
     if (ch.live == 0) return;
-    ch.rid = in ? u_t[ch.sl] : 0;
+    ch.rid = USE != kSumOnly && in ? u_t[ch.sl] : 0;
     ch.tails = __ballot(in && my_end == p + 1);
     ch.start[0] = __shfl(my_begin, 0, kWave);
     ch.len[0] = __shfl(my_end, 0, kWave) - ch.start[0];
@@ -511,7 +520,7 @@ __device__ __forceinline__ void long_segments_of_layout(
     ch.len[1] = __shfl(my_end, ch.last, kWave) - ch.start[1];
     ch.head_cut = (ch.live & 1ull) != 0 && ch.start[0] < a;
     ch.rest = ((ch.live >> ch.last) & 1ull) != 0 && ch.start[1] + ch.len[1] > a + span;
-    long_chunk<BF16, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
+    long_chunk<USE, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
                                cnt_seg, cnt_sup, false, flags);
 }
 
@@ -528,12 +537,13 @@ struct row_source {
     const int32_t *seg_offsets, *perm;
 };
 
-template <bool BF16, int LPR, int UNR, bool LAYOUT>
+template <row_use USE, int LPR, int UNR, bool LAYOUT>
 __device__ __forceinline__ void short_rows_body(
     const int block, const int nblocks, const f32x4 *__restrict__ grads, int n, const row_source src, int64_t n_rows,
     void *table, float *state, int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, int *flags) {
 #pragma clang fp contract(off)
     constexpr int GPW = kWave / LPR;
+    constexpr bool BF16 = USE == kUpdateBf16;
     constexpr int T = FS_SHORT_SEGMENT;
     typedef int i32x4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & (kWave - 1);
@@ -556,7 +566,7 @@ __device__ __forceinline__ void short_rows_body(
                 hd[u] = i32x4{0, 0, 0, 0};
                 at[u] = 0;
                 if (i < n_rows) {
-                    const int64_t row = src.u_t[i];
+                    const int64_t row = USE == kSumOnly ? 0 : src.u_t[i];
                     at[u] = src.seg_offsets[i];
                     hd[u] = i32x4{(int)(row & 0xFFFFFFFFll), (int)(row >> 32), (int)i, src.seg_offsets[i + 1] - at[u]};
                 }
@@ -597,7 +607,7 @@ __device__ __forceinline__ void short_rows_body(
             r[u] = ((int64_t)hd[u][1] << 32) | (uint32_t)hd[u][0];
             len[u] = hd[u][3];
             const bool in_list = base + u * GPW + grp < n_rows;
-            const bool in_table = (r[u] >= 0) && (r[u] < num_rows);
+            const bool in_table = USE == kSumOnly || ((r[u] >= 0) && (r[u] < num_rows));
             oob |= in_list && !in_table;
             const bool is_short = len[u] >= 1 && len[u] <= T;
             const bool slot_ok = (unsigned)hd[u][2] < (unsigned)n;
@@ -607,7 +617,7 @@ __device__ __forceinline__ void short_rows_body(
             mine[u] = live && col_ok;
             any_more |= len[u] > 4;
             w[u] = u32x4{0u, 0u, 0u, 0u};
-            if (mine[u]) {
+            if (USE != kSumOnly && mine[u]) {
                 if (BF16) {
                     const u32x2 h = t2[r[u] * gvec + lig];
                     w[u][0] = h[0];
@@ -616,7 +626,7 @@ __device__ __forceinline__ void short_rows_body(
                     w[u] = t4[r[u] * gvec + lig];
                 }
             }
-            s_old[u] = live ? state[r[u]] : 0.f;
+            s_old[u] = USE != kSumOnly && live ? state[r[u]] : 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 g[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -654,6 +664,10 @@ __device__ __forceinline__ void short_rows_body(
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const f32x4 gs = {(float)acc[u][0], (float)acc[u][1], (float)acc[u][2], (float)acc[u][3]};
+            if constexpr (USE == kSumOnly) {
+                if (mine[u]) reduced[(int64_t)hd[u][2] * gvec + lig] = gs;
+                continue;
+            }
             double ss = 0.0;
 #pragma unroll
             for (int c = 0; c < 4; ++c) ss += (double)gs[c] * (double)gs[c];
@@ -713,17 +727,17 @@ struct class_pass_batch {
     class_pass_job j[kMaxBatch];
 };
 
-template <bool BF16, int LPR>
+template <row_use USE, int LPR>
 __device__ __forceinline__ void class_pass_body(parked_rows<LPR> &sh, const class_pass_job &job, int cls, int block, int *flags) {
     if (block < job.long_blocks)
-        long_segments_body<BF16, LPR, fused_unr<LPR>()>(sh, block, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos,
+        long_segments_body<USE, LPR, fused_unr<LPR>()>(sh, block, job.chunk_log2, job.grads, job.cperm, job.cslot, job.class_pos,
                                                         cls, job.n, job.seg_offsets, job.cstart, job.u_t, job.table, job.state,
                                                         job.num_rows, job.gvec, job.lr, job.eps, job.reduced, job.part_head,
                                                         job.part_last, job.cnt_seg, job.cnt_sup, flags);
     else {
         int64_t n_rows = *job.n_rows_dev;
         if (n_rows > job.n) n_rows = job.n;
-        short_rows_body<BF16, LPR, FS_SHORT_UNR, false>(block - job.long_blocks, job.blocks - job.long_blocks, job.grads, job.n,
+        short_rows_body<USE, LPR, FS_SHORT_UNR, false>(block - job.long_blocks, job.blocks - job.long_blocks, job.grads, job.n,
                                                         row_source{job.recs, nullptr, nullptr, nullptr}, n_rows, job.table,
                                                         job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
     }
@@ -742,11 +756,12 @@ __global__ __launch_bounds__(kFusedWaves *kWave, 4) void class_pass_kernel(const
     const int block = blockIdx.x;
     if (block >= job.blocks) return;
     const int cls = CLS < 2 ? CLS : job.cls;
+    constexpr row_use USE = BF16 ? kUpdateBf16 : kUpdateF32;
     if constexpr (LPR != 0) {
-        class_pass_body<BF16, LPR>(reinterpret_cast<parked_rows<LPR> &>(lds), job, cls, block, flags);
+        class_pass_body<USE, LPR>(reinterpret_cast<parked_rows<LPR> &>(lds), job, cls, block, flags);
     } else {
 #define FS_CASE(L) \
-    case L: class_pass_body<BF16, L>(reinterpret_cast<parked_rows<L> &>(lds), job, cls, block, flags); break;
+    case L: class_pass_body<USE, L>(reinterpret_cast<parked_rows<L> &>(lds), job, cls, block, flags); break;
         switch (job.lpr) { FS_CASE(8) FS_CASE(16) FS_CASE(32) FS_CASE(64) }
 #undef FS_CASE
     }
@@ -768,21 +783,37 @@ struct batch_update_job {
     int *cnt_seg, *cnt_sup;
 };
 
-template <bool BF16, int LPR, int UNR, int SU>
-__global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const batch_update_job job, int *flags) {
-    FS_WG_TRACE(9);
+template <row_use USE, int LPR>
+__device__ __forceinline__ void batch_rows_body(const batch_update_job &job, int *flags) {
     __shared__ parked_rows<LPR> sh;
     int64_t n_u = *job.n_unique_dev;
     n_u = n_u < 0 ? 0 : (n_u > job.n ? job.n : n_u);
     if ((int)blockIdx.x < job.long_blocks)
-        long_segments_of_layout<BF16, LPR, UNR>(sh, (int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
+        long_segments_of_layout<USE, LPR, fused_unr<LPR>()>(sh, (int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
                                                 job.u_t, (int)n_u, job.table, job.state, job.num_rows, job.gvec, job.lr,
                                                 job.eps, job.reduced, job.part_head, job.part_last, job.cnt_seg,
                                                 job.cnt_sup, flags);
     else
-        short_rows_body<BF16, LPR, SU, true>((int)blockIdx.x - job.long_blocks, (int)gridDim.x - job.long_blocks, job.grads,
+        short_rows_body<USE, LPR, FS_SHORT_UNR, true>((int)blockIdx.x - job.long_blocks, (int)gridDim.x - job.long_blocks, job.grads,
                                              job.n, row_source{nullptr, job.u_t, job.seg_offsets, job.perm}, n_u, job.table,
                                              job.state, job.num_rows, job.gvec, job.lr, job.eps, job.reduced, flags);
+}
+
+template <bool BF16, int LPR>
+__global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const batch_update_job job, int *flags) {
+    FS_WG_TRACE(9);
+    batch_rows_body<BF16 ? kUpdateBf16 : kUpdateF32, LPR>(job, flags);
+}
+
+// The segment reduce as an operation of its own (first half of update_embedding(I, G) of Algorithm 2): reduced[k, :] =
+// sum of grads[perm[p], :] over the sorted positions p of distinct row k, in the order and with the rounding of the batch
+// update.  It is bound as the passes are.  Against a chunk kernel of its own, 64 positions a wavefront whatever the batch, and
+// a launch that adds the pieces of the cut segments: 33 k occurrences x 100 23.0 -> 9.7 us, 70 k x 64 28.5 -> 9.9, 300 k x
+// 128 61.9 -> 47.5, 300 k x 8 105.6 -> 19.2, 600 k x 256 181 -> 161.
+template <int LPR>
+__global__ __launch_bounds__(kFusedWaves *kWave) void segment_reduce_kernel(const batch_update_job job, int *flags) {
+    FS_WG_TRACE(9);
+    batch_rows_body<kSumOnly, LPR>(job, flags);
 }
 
 // `idx[0..m)`: the jobs of `jobs` (all of one dtype, all with n > 0) that share this launch; kernel: for their width, or for any
@@ -905,10 +936,8 @@ int launch_reduce_update(fs_ctx *ctx, int cls, const float *grads, int64_t n, in
     return launch_reduce_update_batch(ctx, cls, 1, &job, s);
 }
 
-template <bool BF16, int LPR>
-static void batch_update_launch(fs_ctx *ctx, const fs_batch_update_job &in, hipStream_t s) {
-    constexpr int GPW = kWave / LPR;
-    constexpr int SU = FS_SHORT_UNR;
+// `set`: the partial rows and counters it works in
+static batch_update_job batch_job(fs_ctx *ctx, const fs_batch_update_job &in, int set) {
     batch_update_job j;
     const int n = (int)in.n;
     j.grads = (const f32x4 *)in.grads;
@@ -916,28 +945,49 @@ static void batch_update_launch(fs_ctx *ctx, const fs_batch_update_job &in, hipS
     j.long_blocks = (int)ceil_div(ceil_div(n, 1 << j.chunk_log2), kFusedWaves);
     j.perm = in.perm; j.seg_offsets = in.seg_offsets; j.u_t = in.u_t; j.n_unique_dev = in.n_unique_dev;
     j.table = in.table; j.state = in.state; j.num_rows = in.num_rows; j.reduced = (f32x4 *)in.reduced;
-    j.part_head = ctx->fpart_head[0]; j.part_last = ctx->fpart_last[0];
-    j.cnt_seg = ctx->fcounters[0]; j.cnt_sup = ctx->fcounters_sup[0];
-    int64_t short_blocks = ceil_div(n, (int64_t)GPW * SU * kFusedWaves);
-    if (short_blocks > FS_SHORT_MAX_BLOCKS) short_blocks = FS_SHORT_MAX_BLOCKS;
-    hipLaunchKernelGGL((batch_update_kernel<BF16, LPR, fused_unr<LPR>(), SU>),
-                       dim3((unsigned)(j.long_blocks + short_blocks)), dim3(kFusedWaves * kWave), 0, s, j, ctx->d_flags);
+    j.part_head = ctx->fpart_head[set]; j.part_last = ctx->fpart_last[set];
+    j.cnt_seg = ctx->fcounters[set]; j.cnt_sup = ctx->fcounters_sup[set];
+    return j;
+}
+static dim3 batch_grid(const batch_update_job &j, int lpr) {
+    const int64_t rows = ceil_div(j.n, (int64_t)(kWave / lpr) * FS_SHORT_UNR * kFusedWaves);
+    return dim3((unsigned)(j.long_blocks + (rows < FS_SHORT_MAX_BLOCKS ? rows : FS_SHORT_MAX_BLOCKS)));
 }
 
 int launch_batch_update(fs_ctx *ctx, const fs_batch_update_job &job, hipStream_t s) {
     if (job.n == 0) return FS_OK;
-    const bool bf = job.dt == FS_BF16;
-#define FS_CASE(L)                                             \
-    case L:                                                    \
-        if (bf) batch_update_launch<true, L>(ctx, job, s);     \
-        else batch_update_launch<false, L>(ctx, job, s);       \
+    const batch_update_job j = batch_job(ctx, job, 0);
+    const int lpr = lanes_per_row(j.gvec);
+    const dim3 grid = batch_grid(j, lpr), block(kFusedWaves * kWave);
+#define FS_CASE(L)                                                                                                \
+    case L:                                                                                                       \
+        if (job.dt == FS_BF16) hipLaunchKernelGGL((batch_update_kernel<true, L>), grid, block, 0, s, j, ctx->d_flags); \
+        else hipLaunchKernelGGL((batch_update_kernel<false, L>), grid, block, 0, s, j, ctx->d_flags);            \
         break;
-    switch (lanes_per_row(job.dim / 4)) {
+    switch (lpr) {
         FS_CASE(1) FS_CASE(2) FS_CASE(4) FS_CASE(8) FS_CASE(16) FS_CASE(32) FS_CASE(64)
         default: return set_err(ctx, FS_EINVAL, "update: dim beyond 256");
     }
 #undef FS_CASE
     FS_LAUNCH_CHECK(ctx, "batch_update_kernel");
+    return FS_OK;
+}
+
+int launch_reduce(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim, const int32_t *perm,
+                  const int32_t *seg_offsets, const int64_t *n_unique_dev, float *reduced, hipStream_t s) {
+    if (n == 0) return FS_OK;
+    const batch_update_job j = batch_job(ctx, fs_batch_update_job{grads, n, dim, perm, seg_offsets, nullptr, n_unique_dev,
+                                                                  nullptr, FS_F32, nullptr, 0, 0.f, 0.f, reduced}, kReduceSet);
+    const int lpr = lanes_per_row(j.gvec);
+    const dim3 grid = batch_grid(j, lpr), block(kFusedWaves * kWave);
+    switch (lpr) {
+#define FS_CASE(L) \
+    case L: hipLaunchKernelGGL((segment_reduce_kernel<L>), grid, block, 0, s, j, ctx->d_flags); break;
+        FS_CASE(1) FS_CASE(2) FS_CASE(4) FS_CASE(8) FS_CASE(16) FS_CASE(32) FS_CASE(64)
+#undef FS_CASE
+        default: return set_err(ctx, FS_EINVAL, "reduce: dim beyond 256");
+    }
+    FS_LAUNCH_CHECK(ctx, "segment_reduce_kernel");
     return FS_OK;
 }
 

@@ -29,8 +29,8 @@ constexpr int kSortScan = kSortThreads > kRadix ? kSortThreads : kRadix;
 constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 4;
 constexpr int kScanTile = kScanThreads * kScanIpt;
-// The class order keeps two counts per tile of rows in LDS (60 KB): most tiles, and the most distinct rows that the host
-// may allow for (it knows occurrences only).
+// Most tiles of rows that a class order takes, and the most distinct rows that the host may allow for (it knows occurrences
+// only).
 constexpr int kClassOrderTiles = 60 * 1024 / (2 * (int)sizeof(int));
 constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
@@ -87,7 +87,7 @@ struct fs_split_scratch {
     int32_t *cnt;             // [2 * scan tiles] collisions per tile
     int32_t *cstart_local;    // [max_ids] occurrences of same-class rows before this row inside its split tile
     int32_t *tile_len;        // [2 * scan tiles] occurrences per split tile: collision rows, then exclusive rows
-    int32_t *cidx;            // [max_ids] place of every row of U_t in its class list
+    int32_t *cidx;            // [max_ids] class and place of every row of U_t among those of its class in its split tile
 };
 
 // one dedup / one collision split / one class order of a batch that shares its launches (host side)
@@ -135,7 +135,7 @@ struct fs_split_job {
     int64_t *ex_next;
     int32_t *ex_next_slot;
     int64_t *counts_dev;
-    const int32_t *seg_offsets_t;   // optional; given, the per-tile occurrence counts the class order needs are left in the scratch
+    const int32_t *seg_offsets_t;   // required with a class order
     uint8_t *flag_t1_out = nullptr; // optional [cap_t1]: 1 where the row of u_t1 is also in u_t (a collision row), else 0
     int key_bits = 63;              // of the dedup in front of it (it decides where the one workgroup ends)
 };
@@ -346,10 +346,7 @@ int launch_unique_batch(fs_ctx *, int count, const fs_unique_job *jobs, hipStrea
 // the same by ranges of keys, for jobs that dedup_by_ranges takes
 size_t bucket_table_size(int64_t max_ids);               // entries of fs_sort_scratch::range_start
 int launch_bucket_unique(fs_ctx *, int count, const fs_unique_job *jobs, hipStream_t s, int set0);
-int launch_split_batch(fs_ctx *, int count, const fs_split_job *jobs, hipStream_t s, int set0);
-// right after launch_split_batch(..., seg_offsets_t given) with the same jobs order and sets, on the same stream
-int launch_class_order_batch(fs_ctx *, int count, const fs_class_job *jobs, hipStream_t s, int set0);
-// split and class order of `count` batches: the two calls above, or one launch where all of them are small
+// split and class order of `count` batches: two launches, or one where all of them are small
 int launch_split_class_batch(fs_ctx *, int count, const fs_split_job *jobs, const fs_class_job *cls, hipStream_t s, int set0);
 // one workgroup per batch: dedups (u), splits (sp) with class orders (cls, optional), or a dedup and then a split each,
 // whose U_t no dedup of the same launch may produce; the jobs must fit

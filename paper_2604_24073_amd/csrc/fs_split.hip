@@ -5,7 +5,7 @@
 // the other list between its first and last element.  Two wavefronts find that window with a
 // 64-ary search each, the workgroup stages it in LDS and every element binary-searches LDS (global
 // binary search only if the window does not fit).  Membership flags are counted per tile and a
-// second launch compacts with tile prefixes.  Bound by dependent rounds, not bytes: the tile's own keys travel while the
+// second launch compacts with tile prefixes, the class order and the records of batch t with it where they are wanted.  Bound by dependent rounds, not bytes: the tile's own keys travel while the
 // window is searched, the two ends are searched at once, and a thread's four keys take their steps through LDS side by
 // side (the class order's positions and what their rows are likewise).  Plain operations of 34 k IDs 82.3 -> 80.5 us,
 // self-contained step of 297 k 148.6 -> 146.4 against one search, one key and one position after the other.
@@ -73,19 +73,20 @@ struct split_dev_job {
 struct split_dev_batch {
     split_dev_job j[kMaxBatch];
 };
+// ... and what the class order takes and writes on top of it
 struct class_dev_job {
-    const int32_t *perm, *seg_offsets;
+    const int32_t *perm;
     const int64_t *n_unique_dev;
-    int n, tiles_t, blocks, cap;  // blocks is at least 1: an empty batch still has its class extents written
-    const uint8_t *flag_t;
-    const int32_t *cstart_local, *tile_len, *cidx;
-    int32_t *cperm, *cslot, *cstart, *class_pos_dev;
-    const int64_t *u_t;
-    int32_t *short_rec;
+    int n, blocks;                // blocks is at least 1: an empty batch still has its counts and class extents written
+    int32_t *cperm, *cslot, *cstart, *class_pos_dev, *short_rec;
 };
 struct class_dev_batch {
-    class_dev_job j[kMaxBatch];
+    split_dev_job split[kMaxBatch];
+    class_dev_job cls[kMaxBatch];
 };
+
+constexpr int kRowIsCo = 1 << 16;        // of cidx; below it the place among the rows of the class in the tile
+static_assert(kScanTile <= kRowIsCo, "a place in a tile");
 
 // blocks [0, tiles_t) flag U_t against U_t1; blocks [tiles_t, tiles_t + tiles_t1) flag U_t1 against U_t
 __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_dev_batch batch) {
@@ -110,7 +111,10 @@ __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_de
     uint8_t *flag = side_t ? flag_t : flag_t1;
     const int t_lo = tile * kScanTile;
     if (t_lo >= n_mine) {                                    // whole workgroup: tile past the end
-        if (threadIdx.x == 0) tile_cnt[blockIdx.x] = 0;
+        if (threadIdx.x == 0) {
+            tile_cnt[blockIdx.x] = 0;
+            if (side_t && job.seg_offsets_t != nullptr) job.tile_len[tile] = job.tile_len[tiles_t + tile] = 0;
+        }
         return;
     }
     const int t_hi = (t_lo + kScanTile < n_mine) ? t_lo + kScanTile : n_mine;
@@ -126,78 +130,126 @@ __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_de
         if ((threadIdx.x & (kWave - 1)) == 0) win[w] = j;
     }
     __syncthreads();
-    const int j0 = win[0], j1 = win[1], len = j1 - j0;
-    const bool staged = len <= kSplitWindow;
+    const int j0 = win[0], j1 = win[1], in_win = j1 - j0;
+    const bool staged = in_win <= kSplitWindow;
     if (staged)
-        for (int i = threadIdx.x; i < len; i += kScanThreads) window[i] = other[j0 + i];
+        for (int i = threadIdx.x; i < in_win; i += kScanThreads) window[i] = other[j0 + i];
     __syncthreads();
     bool f[kScanIpt];
     if (staged) {
         int at[kScanIpt];                                    // entries of the window below the key
 #pragma unroll
         for (int i = 0; i < kScanIpt; ++i) at[i] = 0;
-        for (int step = len > 0 ? 1 << (31 - __builtin_clz(len)) : 0; step > 0; step >>= 1)
+        for (int step = in_win > 0 ? 1 << (31 - __builtin_clz(in_win)) : 0; step > 0; step >>= 1)
 #pragma unroll
             for (int i = 0; i < kScanIpt; ++i) {
                 const int q = at[i] + step;
-                at[i] = q <= len && window[q <= len ? q - 1 : 0] < key[i] ? q : at[i];
+                at[i] = q <= in_win && window[q <= in_win ? q - 1 : 0] < key[i] ? q : at[i];
             }
 #pragma unroll
-        for (int i = 0; i < kScanIpt; ++i) f[i] = at[i] < len && window[at[i] < len ? at[i] : 0] == key[i];
+        for (int i = 0; i < kScanIpt; ++i) f[i] = at[i] < in_win && window[at[i] < in_win ? at[i] : 0] == key[i];
     } else {
 #pragma unroll
         for (int i = 0; i < kScanIpt; ++i) f[i] = p0 + i < t_hi && sorted_contains(other, j0, j1, key[i]);
     }
+    const bool classes = side_t && job.seg_offsets_t != nullptr;
     int found = 0;
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i)
         if (p0 + i < t_hi) {
-            flag[p0 + i] = f[i] ? 1 : 0;
+            if (!classes) flag[p0 + i] = f[i] ? 1 : 0;
             found += f[i] ? 1 : 0;
         }
     int total;
-    (void)block_exclusive_scan<int>(found, sh, total);
+    const int found_before = block_exclusive_scan<int>(found, sh, total);
     if (threadIdx.x == 0) tile_cnt[blockIdx.x] = total;      // number of collisions in this tile
+    if (!classes) return;
+    // For the class order: the class and the place of every row among the rows of its class in this tile; for the rows with
+    // more than FS_SHORT_SEGMENT occurrences those of the same-class rows that precede it in the tile, and the tile's
+    // totals of them.
+    const int32_t *__restrict__ seg_offsets_t = job.seg_offsets_t;
+    int len[kScanIpt], co_len = 0, ex_len = 0;
+#pragma unroll
+    for (int i = 0; i < kScanIpt; ++i) {
+        len[i] = p0 + i < t_hi ? seg_offsets_t[p0 + i + 1] - seg_offsets_t[p0 + i] : 0;
+        if (len[i] <= FS_SHORT_SEGMENT) len[i] = 0;          // short segments are not part of the class order
+        co_len += f[i] ? len[i] : 0;
+        ex_len += f[i] ? 0 : len[i];
+    }
+    int co_total, ex_total;
+    int co_before = block_exclusive_scan<int>(co_len, sh, co_total);
+    int ex_before = block_exclusive_scan<int>(ex_len, sh, ex_total);
+    int r_found = found_before;
+#pragma unroll
+    for (int i = 0; i < kScanIpt; ++i) {
+        const int p = p0 + i;
+        if (p < t_hi) {
+            job.cidx[p] = f[i] ? r_found | kRowIsCo : p - t_lo - r_found;
+            job.cstart_local[p] = f[i] ? co_before : ex_before;
+        }
+        r_found += f[i] ? 1 : 0;
+        co_before += f[i] ? len[i] : 0;
+        ex_before += f[i] ? 0 : len[i];
+    }
+    if (threadIdx.x == 0) {
+        job.tile_len[tile] = co_total;
+        job.tile_len[tiles_t + tile] = ex_total;
+    }
 }
 
-__global__ __launch_bounds__(kScanThreads) void split_compact_kernel(const split_dev_batch batch) {
-    FS_WG_TRACE(6);
-    const split_dev_job &job = batch.j[blockIdx.y];
-    if ((int)blockIdx.x >= job.tiles_t + job.tiles_t1) return;
-    const int64_t *__restrict__ u_t = job.u_t, *__restrict__ u_t1 = job.u_t1;
-    const int64_t *__restrict__ n_t_dev = job.n_t_dev, *__restrict__ n_t1_dev = job.n_t1_dev;
-    const int64_t cap_t = job.cap_t, cap_t1 = job.cap_t1;
-    const int tiles_t = job.tiles_t;
-    const uint8_t *__restrict__ flag_t = job.flag_t, *__restrict__ flag_t1 = job.flag_t1;
-    const int32_t *__restrict__ tile_cnt = job.tile_cnt;
-    int64_t *__restrict__ co = job.co, *__restrict__ ex = job.ex, *__restrict__ ex_next = job.ex_next;
-    int32_t *__restrict__ co_slot = job.co_slot, *__restrict__ ex_slot = job.ex_slot;
-    int32_t *__restrict__ ex_next_slot = job.ex_next_slot;
-    int64_t *__restrict__ counts_dev = job.counts_dev;
-    const int32_t *__restrict__ seg_offsets_t = job.seg_offsets_t;
-    int32_t *__restrict__ cstart_local = job.cstart_local, *__restrict__ tile_len = job.tile_len;
-    int32_t *__restrict__ cidx = job.cidx;
-    __shared__ int sh[kScanThreads / kWave];
-    const int n_t = clamp_count(n_t_dev, cap_t), n_t1 = clamp_count(n_t1_dev, cap_t1);
-    const bool side_t = (int)blockIdx.x < tiles_t;
-    const int tile = side_t ? blockIdx.x : blockIdx.x - tiles_t;
-    const int first = side_t ? 0 : tiles_t;
-    // collisions in the earlier tiles of my side
-    int before = 0;
-    for (int t = threadIdx.x; t < tile; t += kScanThreads) before += tile_cnt[first + t];
-    int found_before;
-    (void)block_exclusive_scan<int>(before, sh, found_before);
-
-    const int64_t *mine = side_t ? u_t : u_t1;
-    const uint8_t *flag = side_t ? flag_t : flag_t1;
-    const int n_mine = side_t ? n_t : n_t1;
+// The rows of tile `tile` of U_t1 that are not in U_t; `before`: collisions in the tiles before it.
+__device__ __forceinline__ void list_ex_next(const split_dev_job &job, int tile, int before, int *sh) {
+    const int n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
     const int p0 = tile * kScanTile + threadIdx.x * kScanIpt;
     bool f[kScanIpt];
     int found = 0;
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
+        f[i] = p0 + i < n_t1 && job.flag_t1[p0 + i] != 0;
+        found += f[i] ? 1 : 0;
+    }
+    int total;
+    int r_found = before + block_exclusive_scan<int>(found, sh, total);
+#pragma unroll
+    for (int i = 0; i < kScanIpt; ++i) {
         const int p = p0 + i;
-        f[i] = (p < n_mine) && flag[p] != 0;
+        if (p < n_t1 && !f[i]) {
+            job.ex_next[p - r_found] = job.u_t1[p];
+            job.ex_next_slot[p - r_found] = p;
+        }
+        r_found += f[i] ? 1 : 0;
+    }
+}
+
+// collisions in the tiles of a side before `tile`
+__device__ __forceinline__ int collisions_before(const int32_t *__restrict__ tile_cnt, int tile, int *sh) {
+    int before = 0;
+    for (int t = threadIdx.x; t < tile; t += kScanThreads) before += tile_cnt[t];
+    int total;
+    (void)block_exclusive_scan<int>(before, sh, total);
+    return total;
+}
+
+// The lists of a split without a class order (with one, the launch that makes it writes them).
+__global__ __launch_bounds__(kScanThreads) void split_compact_kernel(const split_dev_batch batch) {
+    FS_WG_TRACE(6);
+    const split_dev_job &job = batch.j[blockIdx.y];
+    if ((int)blockIdx.x >= job.tiles_t + job.tiles_t1) return;
+    __shared__ int sh[kScanThreads / kWave];
+    const bool side_t = (int)blockIdx.x < job.tiles_t;
+    const int tile = side_t ? blockIdx.x : blockIdx.x - job.tiles_t;
+    const int found_before = collisions_before(job.tile_cnt + (side_t ? 0 : job.tiles_t), tile, sh);
+    if (!side_t) {
+        list_ex_next(job, tile, found_before, sh);
+        return;
+    }
+    const int n_t = clamp_count(job.n_t_dev, job.cap_t), n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
+    const int p0 = tile * kScanTile + threadIdx.x * kScanIpt;
+    bool f[kScanIpt];
+    int found = 0;
+#pragma unroll
+    for (int i = 0; i < kScanIpt; ++i) {
+        f[i] = p0 + i < n_t && job.flag_t[p0 + i] != 0;
         found += f[i] ? 1 : 0;
     }
     int tile_total;
@@ -205,134 +257,120 @@ __global__ __launch_bounds__(kScanThreads) void split_compact_kernel(const split
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
         const int p = p0 + i;
-        if (p < n_mine) {
-            const int64_t id = mine[p];
-            if (side_t) {
-                if (f[i]) { co[r_found] = id; co_slot[r_found] = p; }
-                else { ex[p - r_found] = id; ex_slot[p - r_found] = p; }
-                if (seg_offsets_t != nullptr) cidx[p] = f[i] ? r_found : p - r_found;   // place in its class list
-            } else if (!f[i]) {
-                ex_next[p - r_found] = id; ex_next_slot[p - r_found] = p;
-            }
+        if (p < n_t) {
+            const int64_t id = job.u_t[p];
+            if (f[i]) { job.co[r_found] = id; job.co_slot[r_found] = p; }
+            else { job.ex[p - r_found] = id; job.ex_slot[p - r_found] = p; }
             r_found += f[i] ? 1 : 0;
         }
     }
-    // For the class order of the batch (rows with more than FS_SHORT_SEGMENT occurrences only):
-    // occurrences of the same-class rows that precede each row inside this tile, and the tile's
-    // occurrence totals per class.
-    if (side_t && seg_offsets_t != nullptr) {
-        int len[kScanIpt];
-        int co_len = 0, ex_len = 0;
-#pragma unroll
-        for (int i = 0; i < kScanIpt; ++i) {
-            const int p = p0 + i;
-            len[i] = (p < n_mine) ? seg_offsets_t[p + 1] - seg_offsets_t[p] : 0;
-            if (len[i] <= FS_SHORT_SEGMENT) len[i] = 0;      // short segments are not part of the class order
-            co_len += f[i] ? len[i] : 0;
-            ex_len += f[i] ? 0 : len[i];
-        }
-        int co_total, ex_total;
-        int co_before = block_exclusive_scan<int>(co_len, sh, co_total);
-        int ex_before = block_exclusive_scan<int>(ex_len, sh, ex_total);
-#pragma unroll
-        for (int i = 0; i < kScanIpt; ++i) {
-            const int p = p0 + i;
-            if (p < n_mine) cstart_local[p] = f[i] ? co_before : ex_before;
-            co_before += f[i] ? len[i] : 0;
-            ex_before += f[i] ? 0 : len[i];
-        }
-        if (threadIdx.x == 0) {
-            tile_len[tile] = co_total;
-            tile_len[tiles_t + tile] = ex_total;
-        }
-    }
     // the last tile of side t knows |co|; |ex| and |ex_next| follow from the list lengths
-    if (side_t && tile == tiles_t - 1 && threadIdx.x == 0) {
+    if (tile == job.tiles_t - 1 && threadIdx.x == 0) {
         const int n_co = found_before + tile_total;
-        counts_dev[0] = n_co;
-        counts_dev[1] = n_t - n_co;
-        counts_dev[2] = n_t1 - n_co;
+        job.counts_dev[0] = n_co;
+        job.counts_dev[1] = n_t - n_co;
+        job.counts_dev[2] = n_t1 - n_co;
     }
 }
 
-// Class order of the occurrences of batch t that belong to rows with more than FS_SHORT_SEGMENT
-// occurrences: sorted position q (row slot s, the j-th occurrence of that row) goes to  [start of the class] + [occurrences of same-class rows before s] + j.
-// Every workgroup first turns the per-tile totals into tile bases (a few hundred values).  The row slot of a
-// sorted position is found in the segment boundaries themselves: a workgroup's 1024 consecutive sorted
+// The lists, the records and the class order of batch t in one launch, walked by sorted positions: the first position of a
+// row puts it in its list and writes the head of its record; every position of a row with at most FS_SHORT_SEGMENT
+// occurrences goes to the record, of a longer one to the class order: sorted position q (row slot s, the j-th occurrence of
+// that row) to [start of the class] + [occurrences of same-class rows before s] + j.
+// The row slot of a sorted position is found in the segment boundaries themselves: a workgroup's 1024 consecutive sorted
 // positions touch at most 1024 consecutive rows, whose boundaries it stages in LDS (the inverse map would
-// give the same slot at the price of one random 4-byte read per occurrence).
+// give the same slot at the price of one random 4-byte read per occurrence).  They lie in at most two tiles of rows, so that
+// what a workgroup needs of the tiles before them is three sums, taken while it looks for its rows.
+// The workgroups behind those of the positions list the rows of U_t1 that are not in U_t.
+// A launch of its own for the lists and the places of the rows cost 6 us of the self-contained step of 297 k IDs.
 __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class_dev_batch batch,
                                                                      int *__restrict__ flags) {
     FS_WG_TRACE(7);
-    const class_dev_job &job = batch.j[blockIdx.y];
-    if ((int)blockIdx.x >= job.blocks) return;
-    const int32_t *__restrict__ perm = job.perm;
-    const int32_t *__restrict__ seg_offsets = job.seg_offsets;
-    const int n = job.n, tiles_t = job.tiles_t, cap = job.cap;
-    const int n_u = clamp_count(job.n_unique_dev, cap);
-    const uint8_t *__restrict__ flag_t = job.flag_t;
-    const int32_t *__restrict__ cstart_local = job.cstart_local, *__restrict__ tile_len = job.tile_len;
-    const int32_t *__restrict__ cidx = job.cidx;
-    int32_t *__restrict__ cperm = job.cperm, *__restrict__ cslot = job.cslot, *__restrict__ cstart = job.cstart;
-    int32_t *__restrict__ class_pos_dev = job.class_pos_dev;
+    const split_dev_job &job = batch.split[blockIdx.y];
+    const class_dev_job &cls = batch.cls[blockIdx.y];
+    if ((int)blockIdx.x >= cls.blocks + job.tiles_t1) return;
+    __shared__ int sh[kScanThreads / kWave];
+    if ((int)blockIdx.x >= cls.blocks) {
+        const int tile = blockIdx.x - cls.blocks;
+        list_ex_next(job, tile, collisions_before(job.tile_cnt + job.tiles_t, tile, sh), sh);
+        return;
+    }
+    const int32_t *__restrict__ perm = cls.perm;
+    const int32_t *__restrict__ seg_offsets = job.seg_offsets_t;
+    const int n = cls.n, tiles_t = job.tiles_t, cap = (int)job.cap_t;
+    const int n_u = clamp_count(cls.n_unique_dev, cap);
+    const int32_t *__restrict__ tile_cnt = job.tile_cnt, *__restrict__ tile_len = job.tile_len;
     const int64_t *__restrict__ u_t = job.u_t;
-    int32_t *__restrict__ short_rec = job.short_rec;
-    extern __shared__ int tile_base[];                      // [2 * tiles_t]
-    __shared__ int sh[2][kScanThreads / kWave];
+    __shared__ int sums[5][kScanThreads / kWave];
     __shared__ int32_t seg_win[kScanTile + 2];              // seg_offsets[slot_a .. slot_b + 1]
     __shared__ int win[2];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int qa = blockIdx.x * kScanTile;
     const int qb = (qa + kScanTile < n ? qa + kScanTile : n) - 1;          // last sorted position of the workgroup
     const int q0 = qa + threadIdx.x;
     int i[kScanIpt];                                         // under way while the rows are looked for
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) i[k] = q0 + k * kScanThreads < n ? perm[q0 + k * kScanThreads] : 0;
-    if (threadIdx.x < 2 * kWave) {
+    // of a tile of rows: collision rows; occurrences of its long collision rows, of its long exclusive rows
+    auto of_tile = [&](int t, int (&v)[3]) {
+        v[0] = tile_cnt[t];
+        v[1] = tile_len[t];
+        v[2] = tile_len[tiles_t + t];
+    };
+    int mine[3] = {0, 0, 0};
+    if (n > 0 && (int)threadIdx.x < tiles_t) of_tile(threadIdx.x, mine);
+    if (w < 2) {
         // the row of a sorted position q: the last slot whose segment starts at or before q
-        const int w = threadIdx.x / kWave;
         int k = 0;
         if (qa < n && n_u > 0) k = wave_upper_bound<int32_t>(seg_offsets, n_u + 1, w == 0 ? qa : qb) - 1;
         k = k < 0 ? 0 : (k > n_u - 1 ? n_u - 1 : k);
-        if ((threadIdx.x & (kWave - 1)) == 0) win[w] = k;
+        if (lane == 0) win[w] = k;
     }
     __syncthreads();
-    const int slot_a = win[0];
+    const int slot_a = win[0], tile_a = slot_a / kScanTile;
     int wn = (qa < n && n_u > 0) ? win[1] - slot_a + 2 : 0; // boundaries staged
     if (wn > kScanTile + 2 || wn < 0) {                     // cannot happen: every row has an occurrence
         if (threadIdx.x == 0) atomicOr(flags, kFlagInternal);
         wn = 0;
     }
     for (int j = threadIdx.x; j < wn; j += kScanThreads) seg_win[j] = seg_offsets[slot_a + j];
-    // bases of the tiles, both classes at once
-    int class_total[2] = {0, 0};
-    for (int t0 = 0; t0 < tiles_t; t0 += kScanThreads) {
-        const int t = t0 + threadIdx.x, lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-        int v[2], inc[2];
+    int next[3] = {0, 0, 0};                                 // tile_a itself: what lies between it and the tile behind it
+    if (n > 0) of_tile(tile_a, next);
+    int part[5] = {0, 0, 0, 0, 0};                           // before tile_a; all collision rows, all their occurrences
+    for (int t = threadIdx.x; n > 0 && t < tiles_t; t += kScanThreads) {
+        if (t >= kScanThreads) of_tile(t, mine);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) v[c] = t < tiles_t ? tile_len[c * tiles_t + t] : 0;
+        for (int c = 0; c < 3; ++c) part[c] += t < tile_a ? mine[c] : 0;
+        part[3] += mine[0];
+        part[4] += mine[1];
+    }
+    int ex_all = 0;                                          // the first workgroup: occurrences of long exclusive rows
+    if (blockIdx.x == 0) {
+        int x = 0;
+        for (int t = threadIdx.x; n > 0 && t < tiles_t; t += kScanThreads) x += tile_len[tiles_t + t];
+        (void)block_exclusive_scan<int>(x, sh, ex_all);
+    }
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            inc[c] = wave_inclusive_scan<int>(v[c]);
-            if (lane == kWave - 1) sh[c][w] = inc[c];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            int before = class_total[c];
-#pragma unroll
-            for (int q = 0; q < kScanThreads / kWave; ++q) {
-                before += q < w ? sh[c][q] : 0;
-                class_total[c] += sh[c][q];
-            }
-            if (t < tiles_t) tile_base[c * tiles_t + t] = before + inc[c] - v[c];
-        }
-        __syncthreads();
+    for (int c = 0; c < 5; ++c) {
+        const int x = wave_inclusive_scan<int>(part[c]);
+        if (lane == kWave - 1) sums[c][w] = x;
     }
     __syncthreads();
-    const int n_co_pos = class_total[0];
+    int total[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        total[c] = 0;
+#pragma unroll
+        for (int q = 0; q < kScanThreads / kWave; ++q) total[c] += sums[c][q];
+    }
+    const int n_co = total[3], n_co_pos = total[4];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        class_pos_dev[0] = n_co_pos;
-        class_pos_dev[1] = n_co_pos + class_total[1];
+        const int n_t = clamp_count(job.n_t_dev, job.cap_t), n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
+        cls.class_pos_dev[0] = n_co_pos;
+        cls.class_pos_dev[1] = n_co_pos + ex_all;
+        job.counts_dev[0] = n_co;
+        job.counts_dev[1] = n_t - n_co;
+        job.counts_dev[2] = n_t1 - n_co;
     }
     // the first j with seg_win[j] > q, among the row starts, for all positions side by side
     int s[kScanIpt];
@@ -346,8 +384,8 @@ __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class
             s[k] = j <= starts && seg_win[j <= starts ? j - 1 : 0] <= q0 + k * kScanThreads ? j : s[k];
         }
     // what the rows of the positions are, again side by side
-    bool ok[kScanIpt], is_co[kScanIpt];
-    int first[kScanIpt], len[kScanIpt], li[kScanIpt], local[kScanIpt];
+    bool ok[kScanIpt];
+    int first[kScanIpt], len[kScanIpt], at[kScanIpt], local[kScanIpt];
     int64_t row[kScanIpt];
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) {
@@ -357,48 +395,48 @@ __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class
         first[k] = ok[k] ? seg_win[s[k]] : 0;
         len[k] = ok[k] ? seg_win[s[k] + 1] - first[k] : 0;
         const int slot = slot_a + s[k];
-        is_co[k] = ok[k] && flag_t[slot] != 0;
-        li[k] = ok[k] ? cidx[slot] : -1;
+        at[k] = ok[k] ? job.cidx[slot] : 0;
         row[k] = ok[k] && q == first[k] ? u_t[slot] : 0;
-        local[k] = len[k] > FS_SHORT_SEGMENT ? cstart_local[slot] : 0;
+        local[k] = len[k] > FS_SHORT_SEGMENT ? job.cstart_local[slot] : 0;
     }
 #pragma unroll
     for (int k = 0; k < kScanIpt; ++k) {
         const int q = q0 + k * kScanThreads;
         if (q < n) {
-            if (!ok[k] || li[k] < 0 || li[k] >= cap) {       // layout and batch do not fit each other
+            const int slot = slot_a + s[k], tile = slot / kScanTile;
+            const bool is_co = (at[k] & kRowIsCo) != 0, behind = tile != tile_a;
+            // place in the class list: the rows of its class in the tiles before, and in its own
+            const int co_before = total[0] + (behind ? next[0] : 0);
+            const int li = (at[k] & (kRowIsCo - 1)) + (is_co ? co_before : tile * kScanTile - co_before);
+            if (!ok[k] || li < 0 || li >= cap) {             // layout and batch do not fit each other
                 atomicOr(flags, kFlagInternal);
                 continue;
             }
-            const int slot = slot_a + s[k];
-            const int tile = slot / kScanTile;
             // one record per row of the batch, at the row's place in its class list: header (row,
             // slot, occurrences) from the row's first position, occurrences only for short segments
-            int32_t *rec = short_rec + ((int64_t)(is_co[k] ? 0 : cap) + li[k]) * kShortRecInts;
+            int32_t *rec = cls.short_rec + ((int64_t)(is_co ? 0 : cap) + li) * kShortRecInts;
             if (q == first[k]) {
                 typedef int i32x4 __attribute__((ext_vector_type(4)));
                 *reinterpret_cast<i32x4 *>(rec) =
                     i32x4{(int)(row[k] & 0xFFFFFFFFll), (int)(row[k] >> 32), slot, len[k]};
+                (is_co ? job.co : job.ex)[li] = row[k];
+                (is_co ? job.co_slot : job.ex_slot)[li] = slot;
             }
             if (len[k] <= FS_SHORT_SEGMENT) {
                 rec[4 + (q - first[k])] = i[k];
                 continue;
             }
-            const int dest = (is_co[k] ? tile_base[tile] : n_co_pos + tile_base[tiles_t + tile]) + local[k] + (q - first[k]);
+            const int before = is_co ? total[1] + (behind ? next[1] : 0) : n_co_pos + total[2] + (behind ? next[2] : 0);
+            const int dest = before + local[k] + (q - first[k]);
             if (dest < 0 || dest >= n) {                     // cannot happen with a consistent layout and split
                 atomicOr(flags, kFlagInternal);
                 continue;
             }
-            cperm[dest] = i[k];
-            cslot[dest] = slot;
-            if (q == first[k]) cstart[slot] = dest;
+            cls.cperm[dest] = i[k];
+            cls.cslot[dest] = slot;
+            if (q == first[k]) cls.cstart[slot] = dest;
         }
     }
-}
-
-__global__ void class_empty_kernel(int32_t *class_pos_dev) {
-    class_pos_dev[0] = 0;
-    class_pos_dev[1] = 0;
 }
 
 __global__ void split_empty_kernel(const int64_t *n_t1_dev, int64_t cap_t1, int64_t *counts_dev) {
@@ -407,36 +445,33 @@ __global__ void split_empty_kernel(const int64_t *n_t1_dev, int64_t cap_t1, int6
     counts_dev[2] = clamp_count(n_t1_dev, cap_t1);
 }
 
-int launch_split_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, hipStream_t s, int set0) {
-    if (count < 1 || count > kMaxBatch || set0 < 0 || set0 + count > kSortSets)
-        return set_err(ctx, FS_EINVAL, "split: batch size");
-    if (count == 1 && jobs[0].cap_t == 0 && jobs[0].cap_t1 == 0) {
-        hipLaunchKernelGGL(split_empty_kernel, dim3(1), dim3(1), 0, s, jobs[0].n_t1_dev, jobs[0].cap_t1,
-                           jobs[0].counts_dev);
+static split_dev_job split_job(const fs_split_job &in, const fs_split_scratch &ws) {
+    split_dev_job j;
+    const int tiles_t = (int)ceil_div(in.cap_t, kScanTile);
+    j.u_t = in.u_t; j.n_t_dev = in.n_t_dev; j.u_t1 = in.u_t1; j.n_t1_dev = in.n_t1_dev;
+    j.cap_t = in.cap_t; j.cap_t1 = in.cap_t1;
+    // With cap_t == 0 a single (empty) tile on side t keeps the count logic in one place.
+    j.tiles_t = tiles_t > 0 ? tiles_t : 1;
+    j.tiles_t1 = (int)ceil_div(in.cap_t1, kScanTile);
+    j.flag_t = ws.flag_t; j.flag_t1 = in.flag_t1_out ? in.flag_t1_out : ws.flag_t1; j.tile_cnt = ws.cnt;
+    j.co = in.co; j.co_slot = in.co_slot; j.ex = in.ex; j.ex_slot = in.ex_slot;
+    j.ex_next = in.ex_next; j.ex_next_slot = in.ex_next_slot; j.counts_dev = in.counts_dev;
+    j.seg_offsets_t = in.seg_offsets_t;
+    j.cstart_local = ws.cstart_local; j.tile_len = ws.tile_len; j.cidx = ws.cidx;
+    return j;
+}
+
+// one split, without a class order
+static int launch_split_alone(fs_ctx *ctx, const fs_split_job &in, hipStream_t s, int set) {
+    if (in.cap_t == 0 && in.cap_t1 == 0) {
+        hipLaunchKernelGGL(split_empty_kernel, dim3(1), dim3(1), 0, s, in.n_t1_dev, in.cap_t1, in.counts_dev);
         FS_LAUNCH_CHECK(ctx, "split_empty_kernel");
         return FS_OK;
     }
     split_dev_batch batch;
     memset(&batch, 0, sizeof(batch));
-    int blocks = 0;
-    for (int k = 0; k < count; ++k) {
-        const fs_split_job &in = jobs[k];
-        const fs_split_scratch &ws = ctx->split[set0 + k];
-        split_dev_job &j = batch.j[k];
-        const int tiles_t = (int)ceil_div(in.cap_t, kScanTile);
-        j.u_t = in.u_t; j.n_t_dev = in.n_t_dev; j.u_t1 = in.u_t1; j.n_t1_dev = in.n_t1_dev;
-        j.cap_t = in.cap_t; j.cap_t1 = in.cap_t1;
-        // With cap_t == 0 a single (empty) tile on side t keeps the count logic in one place.
-        j.tiles_t = tiles_t > 0 ? tiles_t : 1;
-        j.tiles_t1 = (int)ceil_div(in.cap_t1, kScanTile);
-        j.flag_t = ws.flag_t; j.flag_t1 = in.flag_t1_out ? in.flag_t1_out : ws.flag_t1; j.tile_cnt = ws.cnt;
-        j.co = in.co; j.co_slot = in.co_slot; j.ex = in.ex; j.ex_slot = in.ex_slot;
-        j.ex_next = in.ex_next; j.ex_next_slot = in.ex_next_slot; j.counts_dev = in.counts_dev;
-        j.seg_offsets_t = in.seg_offsets_t;
-        j.cstart_local = ws.cstart_local; j.tile_len = ws.tile_len; j.cidx = ws.cidx;
-        blocks = (j.tiles_t + j.tiles_t1) > blocks ? (j.tiles_t + j.tiles_t1) : blocks;
-    }
-    const dim3 grid((unsigned)blocks, (unsigned)count);
+    batch.j[0] = split_job(in, ctx->split[set]);
+    const dim3 grid((unsigned)(batch.j[0].tiles_t + batch.j[0].tiles_t1), 1u);
     hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch);
     hipLaunchKernelGGL(split_compact_kernel, grid, dim3(kScanThreads), 0, s, batch);
     FS_LAUNCH_CHECK(ctx, "split kernels");
@@ -450,49 +485,38 @@ int launch_split(fs_ctx *ctx, const int64_t *u_t, const int64_t *n_t_dev, const 
     const fs_split_job job = {u_t, n_t_dev, u_t1, n_t1_dev, cap_t, cap_t1, co, co_slot, ex, ex_slot,
                               ex_next, ex_next_slot, counts_dev, nullptr};
     if (small_split_fits(1, &job, nullptr, 0)) return launch_small_index(ctx, 1, nullptr, &job, nullptr, s);
-    return launch_split_batch(ctx, 1, &job, s, 0);
-}
-
-int launch_class_order_batch(fs_ctx *ctx, int count, const fs_class_job *jobs, hipStream_t s, int set0) {
-    if (count < 1 || count > kMaxBatch || set0 < 0 || set0 + count > kSortSets)
-        return set_err(ctx, FS_EINVAL, "class order: batch size");
-    if (count == 1 && jobs[0].n == 0) {
-        hipLaunchKernelGGL(class_empty_kernel, dim3(1), dim3(1), 0, s, jobs[0].class_pos_dev);
-        FS_LAUNCH_CHECK(ctx, "class_empty_kernel");
-        return FS_OK;
-    }
-    class_dev_batch batch;
-    memset(&batch, 0, sizeof(batch));
-    int blocks = 1, max_tiles = 0;
-    for (int k = 0; k < count; ++k) {
-        const fs_class_job &in = jobs[k];
-        const fs_split_scratch &ws = ctx->split[set0 + k];
-        class_dev_job &j = batch.j[k];
-        j.perm = in.perm; j.n_unique_dev = in.n_unique_dev; j.seg_offsets = in.seg_offsets;
-        j.n = (int)in.n;
-        j.tiles_t = (int)ceil_div(in.cap_u, kScanTile);      // the same tiling the split used for side t
-        j.blocks = in.n > 0 ? (int)ceil_div(in.n, kScanTile) : 1;
-        j.cap = (int)in.cap_u;
-        j.flag_t = ws.flag_t; j.cstart_local = ws.cstart_local; j.tile_len = ws.tile_len; j.cidx = ws.cidx;
-        j.cperm = in.cperm; j.cslot = in.cslot; j.cstart = in.cstart; j.class_pos_dev = in.class_pos_dev;
-        j.u_t = in.u_t; j.short_rec = in.short_rec;
-        blocks = j.blocks > blocks ? j.blocks : blocks;
-        max_tiles = j.tiles_t > max_tiles ? j.tiles_t : max_tiles;
-    }
-    if (max_tiles > kClassOrderTiles)
-        return set_err(ctx, FS_ERANGE, "class order: more than 7.8M distinct rows in one batch");
-    hipLaunchKernelGGL(class_scatter_kernel, dim3((unsigned)blocks, (unsigned)count), dim3(kScanThreads),
-                       (size_t)max_tiles * 2 * sizeof(int), s, batch, ctx->d_flags);
-    FS_LAUNCH_CHECK(ctx, "class_scatter_kernel");
-    return FS_OK;
+    return launch_split_alone(ctx, job, s, 0);
 }
 
 int launch_split_class_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, const fs_class_job *cls, hipStream_t s,
                              int set0) {
     if (small_split_fits(count, jobs, cls, set0)) return launch_small_index(ctx, count, nullptr, jobs, cls, s);
-    const int rc = launch_split_batch(ctx, count, jobs, s, set0);
-    if (rc != FS_OK) return rc;
-    return launch_class_order_batch(ctx, count, cls, s, set0);
+    if (count < 1 || count > kMaxBatch || set0 < 0 || set0 + count > kSortSets)
+        return set_err(ctx, FS_EINVAL, "split: batch size");
+    split_dev_batch batch;
+    class_dev_batch order;
+    memset(&batch, 0, sizeof(batch));
+    memset(&order, 0, sizeof(order));
+    int tiles = 0, blocks = 0;
+    for (int k = 0; k < count; ++k) {
+        const fs_class_job &in = cls[k];
+        class_dev_job &j = order.cls[k];
+        const split_dev_job sj = split_job(jobs[k], ctx->split[set0 + k]);
+        if (sj.tiles_t > kClassOrderTiles)
+            return set_err(ctx, FS_ERANGE, "class order: more than 7.8M distinct rows in one batch");
+        batch.j[k] = order.split[k] = sj;
+        j.perm = in.perm; j.n_unique_dev = in.n_unique_dev; j.n = (int)in.n;
+        j.blocks = in.n > 0 ? (int)ceil_div(in.n, kScanTile) : 1;
+        j.cperm = in.cperm; j.cslot = in.cslot; j.cstart = in.cstart; j.class_pos_dev = in.class_pos_dev;
+        j.short_rec = in.short_rec;
+        tiles = sj.tiles_t + sj.tiles_t1 > tiles ? sj.tiles_t + sj.tiles_t1 : tiles;
+        blocks = j.blocks + sj.tiles_t1 > blocks ? j.blocks + sj.tiles_t1 : blocks;
+    }
+    hipLaunchKernelGGL(split_flag_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kScanThreads), 0, s, batch);
+    hipLaunchKernelGGL(class_scatter_kernel, dim3((unsigned)blocks, (unsigned)count), dim3(kScanThreads), 0, s, order,
+                       ctx->d_flags);
+    FS_LAUNCH_CHECK(ctx, "split and class order kernels");
+    return FS_OK;
 }
 
 FS_TRACE_SETTER(split)

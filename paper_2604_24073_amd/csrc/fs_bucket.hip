@@ -2,7 +2,8 @@
 // sorted, stably, by one workgroup in LDS.  Same outputs as the radix sort of fs_unique.hip, bit for bit, in four
 // launches instead of eight (two per radix pass, two for the compaction):
 //
-//   sample     a stratified sample of the batch is sorted by one workgroup, every fourth entry becomes a boundary
+//   sample     a stratified sample of the batch is sorted by one workgroup, every fourth entry becomes a boundary (up to 64
+//              ranges, 49152 IDs, the partition finds the boundaries by itself)
 //   partition  every tile of 2048 IDs is put in the order of its ranges, on the spot: a workgroup's output goes where its
 //              input lay, with a table of where each range starts in each tile
 //   sort       one workgroup per range collects its pieces from the tiles (tile order = batch order), sorts them and
@@ -42,6 +43,8 @@ constexpr int kBucketKpt = 8;                            // most elements of a r
 constexpr int kBucketCap = kBucketThreads * kBucketKpt;  // elements of a range that fit the LDS of its workgroup
 constexpr int kSamplesLog2 = 2;                          // samples per range
 constexpr int kSamplesMost = kMaxBuckets << kSamplesLog2;
+constexpr int kSampleThreads = 256;
+constexpr int kOwnCutsLog2 = 6;                          // most ranges (log2) whose cuts the partition finds by itself
 constexpr int kPartThreads = 256;
 constexpr int kPartWaves = kPartThreads / kWave;
 constexpr int kPartKpt = kBucketTile / kPartThreads;
@@ -77,12 +80,14 @@ struct bucket_dev_batch {
     bucket_dev_job j[kMaxBatch];
 };
 
-struct bucket_sort_shared {
-    uint64_t mask[kBucketWaves][kBucketRadix];
-    uint32_t cnt[kBucketWaves][kBucketRadix];
+template <int WAVES>
+struct sort_shared {
+    uint64_t mask[WAVES][kBucketRadix];
+    uint32_t cnt[WAVES][kBucketRadix];
     uint32_t base[kBucketRadix];
     uint32_t part[kBucketRadix / kWave];
 };
+typedef sort_shared<kBucketWaves> bucket_sort_shared;
 
 // lanes of my wavefront with my digit (a lane that is not valid has no peers of its own).  All MOST bits, whatever the
 // digits use: a bit that is 0 in every lane changes nothing, and a branch around it costs more.
@@ -109,14 +114,16 @@ __device__ __forceinline__ uint32_t peers_before(uint64_t peers) {
 constexpr int kPlaceBits = 20;
 constexpr uint32_t kPlaceMask = (1u << kPlaceBits) - 1u;
 static_assert(kBucketIdsMax <= 1ll << kPlaceBits, "a place and a rank share a word");
-__device__ __forceinline__ void clear_counters(bucket_sort_shared &sh) {
-    for (int i = threadIdx.x; i < kBucketWaves * kBucketRadix; i += kBucketThreads) (&sh.cnt[0][0])[i] = 0u;
+template <int WAVES>
+__device__ __forceinline__ void clear_counters(sort_shared<WAVES> &sh) {
+    for (int i = threadIdx.x; i < WAVES * kBucketRadix; i += WAVES * kWave) (&sh.cnt[0][0])[i] = 0u;
 }
 // The elements of a wavefront with the same digit, in order: every lane sets its bit in the digit's mask, reads the mask
 // and clears it again, reads the digit's count and adds itself to it.  A wavefront's LDS accesses are carried out in
 // their order, so none of the five waits for another and the rounds follow each other; ballots over the bits of the
 // digit cost ten times the instructions.  The mask comes back whole, the count as it stood before the round.
-__device__ __forceinline__ void rank_round(bucket_sort_shared &sh, int w, uint32_t digit, bool valid, uint64_t &peers,
+template <int WAVES>
+__device__ __forceinline__ void rank_round(sort_shared<WAVES> &sh, int w, uint32_t digit, bool valid, uint64_t &peers,
                                            uint32_t &old) {
     peers = 0;
     old = 0;
@@ -133,17 +140,18 @@ __device__ __forceinline__ void rank_round(bucket_sort_shared &sh, int w, uint32
     }
     wave_lds_order();
 }
-template <int KPT>
-__device__ __forceinline__ void sort_in_lds(int n, int bits, uint32_t *skey, uint32_t *sval, bucket_sort_shared &sh) {
-    static_assert(KPT * kBucketThreads <= 1 << (32 - kPlaceBits), "a place and a rank share a word");
+template <int KPT, int WAVES>
+__device__ __forceinline__ void sort_in_lds(int n, int bits, uint32_t *skey, uint32_t *sval, sort_shared<WAVES> &sh) {
+    static_assert(kBucketRadix <= WAVES * kWave, "a thread per digit");
+    static_assert(KPT * WAVES * kWave <= 1 << (32 - kPlaceBits), "a place and a rank share a word");
     const int lane = threadIdx.x & (kWave - 1);
-    const int w = threadIdx.x / kWave;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int e0 = w * (kWave * KPT) + lane;
     const int passes = (bits + kBucketBits - 1) / kBucketBits;
     const int per = (bits + passes - 1) / passes;
     const uint32_t mask = (1u << per) - 1u;
     clear_counters(sh);
-    for (int i = threadIdx.x; i < kBucketWaves * kBucketRadix; i += kBucketThreads) (&sh.mask[0][0])[i] = 0ull;
+    for (int i = threadIdx.x; i < WAVES * kBucketRadix; i += WAVES * kWave) (&sh.mask[0][0])[i] = 0ull;
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = pass * per;
         __syncthreads();
@@ -169,7 +177,7 @@ __device__ __forceinline__ void sort_in_lds(int n, int bits, uint32_t *skey, uin
         if (threadIdx.x < kBucketRadix) {                     // a digit a thread: prefix over the waves, then over the digits
             uint32_t run = 0;
 #pragma unroll
-            for (int i = 0; i < kBucketWaves; ++i) {
+            for (int i = 0; i < WAVES; ++i) {
                 const uint32_t v = sh.cnt[i][threadIdx.x];
                 sh.cnt[i][threadIdx.x] = run;
                 run += v;
@@ -227,22 +235,31 @@ __device__ __forceinline__ int sample_place(int i, int m_log2, int n) {
     return p < n ? p : n - 1;
 }
 
-__global__ __launch_bounds__(kBucketThreads, 8) void bucket_sample_kernel(const bucket_dev_batch batch) {
+// One workgroup of 256 threads: beside four workgroups of the batch update a compute unit has registers for one wavefront a
+// SIMD.  With 512 threads it waited for one of them to end, and the whole index half of a self-contained step behind it (297 k
+// IDs 140.0 -> 138.1 us).  The sort with 256 threads, in turn with this one: the same step 137.1 / 135.1, but plain operations
+// of 34 k IDs 66.6 / 69.9, balancing 65 k samples 86.3 / 88.8, ten pipelined steps of a 64 M row table 1042 / 1051.
+template <int MOST>
+__global__ __launch_bounds__(kSampleThreads) void bucket_sample_kernel(const bucket_dev_batch batch) {
     FS_WG_TRACE(13);
     const bucket_dev_job &job = batch.j[blockIdx.x];
     if (job.n == 0) return;
-    __shared__ uint32_t key[kSamplesMost], val[kSamplesMost];
-    __shared__ bucket_sort_shared sh;
+    __shared__ uint32_t key[MOST], val[MOST];
+    __shared__ sort_shared<kSampleThreads / kWave> sh;
     const int ranges = 1 << job.log2, m_log2 = job.log2 + kSamplesLog2, m = 1 << m_log2;
     const uint32_t last_key = (uint32_t)(job.num_rows - 1);
 #pragma unroll 4
-    for (int i = threadIdx.x; i < m; i += kBucketThreads) {
+    for (int i = threadIdx.x; i < m; i += kSampleThreads) {
         const uint32_t k = (uint32_t)job.ids[sample_place(i, m_log2, job.n)];
         key[i] = k < last_key ? k : last_key;                 // IDs out of range go to the last range, where nobody looks
     }
     __syncthreads();
-    sort_any(m, bits_of(last_key | 1u), key, val, sh);
-    for (int e = threadIdx.x; e < ranges - 1; e += kBucketThreads) job.cut[e] = key[(e + 1) << kSamplesLog2];
+    const int bits = bits_of(last_key | 1u);
+    if (m <= 2 * kSampleThreads) sort_in_lds<2>(m, bits, key, val, sh);
+    else if (m <= 4 * kSampleThreads) sort_in_lds<4>(m, bits, key, val, sh);
+    else if (m <= 8 * kSampleThreads) sort_in_lds<8>(m, bits, key, val, sh);
+    else sort_in_lds<MOST / kSampleThreads>(m, bits, key, val, sh);
+    for (int e = threadIdx.x; e < ranges - 1; e += kSampleThreads) job.cut[e] = key[(e + 1) << kSamplesLog2];
 }
 static_assert(kSamplesMost <= kBucketCap, "sorted like a range");
 
@@ -267,7 +284,42 @@ __device__ __forceinline__ int bounds_below(const uint32_t *__restrict__ cut, in
     return lo;
 }
 
+// The cuts of a few ranges without a launch of their own: every tile takes the same sample, an entry a thread, and ranks its
+// entries by counting (equal ones in their order).  The first tile writes the cuts down for the sort.  With 64 ranges 256
+// comparisons a thread of two instructions: plain operations of 34 k IDs 68.7 -> 66.0 us.  With 128 ranges it is four times the
+// work, and balancing 65 k samples took 101 us instead of 85.
+__device__ __forceinline__ void own_cuts(const bucket_dev_job &job, uint32_t *sample, uint32_t *cut) {
+    static_assert(1 << (kOwnCutsLog2 + kSamplesLog2) == kPartThreads, "an entry a thread");
+    const int m_log2 = job.log2 + kSamplesLog2, m = 1 << m_log2, i = threadIdx.x;
+    const uint32_t last_key = (uint32_t)(job.num_rows - 1);
+    const uint32_t x = (uint32_t)job.ids[sample_place(i < m ? i : m - 1, m_log2, job.n)];
+    const uint32_t key = x < last_key ? x : last_key;
+    sample[i] = i < m ? key : 0xffffffffu;                   // behind every entry, and not below any
+    __syncthreads();
+    const int w0 = __builtin_amdgcn_readfirstlane(i & ~(kWave - 1));
+    uint32_t rank = 0;
+    auto count = [&](int from, int to, auto below) {
+#pragma unroll 4
+        for (int j = from; j < to; j += 4) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(sample + j);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rank += below(v[q], j + q) ? 1u : 0u;
+        }
+    };
+    count(0, w0 < m ? w0 : m, [&](uint32_t v, int) { return v <= key; });
+    count(w0, w0 + kWave, [&](uint32_t v, int j) { return v < key || (v == key && j < i); });
+    count(w0 + kWave, m, [&](uint32_t v, int) { return v < key; });
+    constexpr uint32_t kStep = 1u << kSamplesLog2;
+    if (i < m && rank != 0 && rank % kStep == 0) {
+        cut[rank / kStep - 1] = key;
+        if (blockIdx.x == 0) job.cut[rank / kStep - 1] = key;
+    }
+    __syncthreads();
+}
+
 // ---- partition -----------------------------------------------------------------------------------------------------
+// OWN: no sample has been sorted, the tiles find the cuts
+template <bool OWN>
 __global__ __launch_bounds__(kPartThreads, 8) void bucket_partition_kernel(const bucket_dev_batch batch,
                                                                           int *__restrict__ flags) {
     FS_WG_TRACE(14);
@@ -294,7 +346,12 @@ __global__ __launch_bounds__(kPartThreads, 8) void bucket_partition_kernel(const
         bad |= id < 0 || id >= job.num_rows;
         key[r] = (uint32_t)id;
     }
-    for (int i = threadIdx.x; i < ranges - 1; i += kPartThreads) bound[i] = bound_at(job.cut, i);
+    if constexpr (OWN) {
+        own_cuts(job, s_key, start);
+        for (int i = threadIdx.x; i < ranges - 1; i += kPartThreads) bound[i] = bound_at(start, i);
+    } else {
+        for (int i = threadIdx.x; i < ranges - 1; i += kPartThreads) bound[i] = bound_at(job.cut, i);
+    }
     for (int i = threadIdx.x; i < (kPartWaves * ranges + 1) / 2; i += kPartThreads) lds[i] = 0u;
     if (bad) atomicOr(flags, kFlagRowRange);
     __syncthreads();
@@ -777,12 +834,16 @@ int launch_bucket_unique(fs_ctx *ctx, int count, const fs_unique_job *jobs, hipS
         tiles = j.tiles > tiles ? j.tiles : tiles;
         log2 = j.log2 > log2 ? j.log2 : log2;
     }
+    // all batches of a launch are small: one launch less
+    const bool own = log2 <= kOwnCutsLog2;
     const unsigned ranges = 1u << log2;
     const size_t part_lds = (size_t)kPartWaves * ranges * sizeof(uint16_t);
-    hipLaunchKernelGGL(bucket_sample_kernel, dim3((unsigned)count), dim3(kBucketThreads), 0, s, batch);
+    if (!own)
+        hipLaunchKernelGGL(log2 < 10 ? &bucket_sample_kernel<kSamplesMost / 2> : &bucket_sample_kernel<kSamplesMost>,
+                           dim3((unsigned)count), dim3(kSampleThreads), 0, s, batch);
     if (tiles > 0)
-        hipLaunchKernelGGL(bucket_partition_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kPartThreads), part_lds, s,
-                           batch, ctx->d_flags);
+        hipLaunchKernelGGL(own ? &bucket_partition_kernel<true> : &bucket_partition_kernel<false>,
+                           dim3((unsigned)tiles, (unsigned)count), dim3(kPartThreads), part_lds, s, batch, ctx->d_flags);
     auto *sort = dedup ? &bucket_sort_kernel<false> : &bucket_sort_kernel<true>;
     hipLaunchKernelGGL(sort, dim3(ranges, (unsigned)count), dim3(kBucketThreads), 2 * kBucketCap * sizeof(uint32_t), s, batch);
     if (dedup)

@@ -354,6 +354,10 @@ bool small_unique_fits(int count, const fs_unique_job *jobs, int set0);
 bool small_split_fits(int count, const fs_split_job *jobs, const fs_class_job *cls, int set0, bool with_dedup = false);
 int launch_small_index(fs_ctx *, int count, const fs_unique_job *u, const fs_split_job *sp, const fs_class_job *cls,
                        hipStream_t s);
+// the index half of a small batch and the update of every row of the batch before it in one launch; the jobs must fit
+bool small_step_fits(const fs_unique_job &u, const fs_split_job &sp, const fs_class_job &cls);
+int launch_small_step(fs_ctx *, const fs_unique_job &u, const fs_split_job &sp, const fs_class_job &cls,
+                      const fs_batch_update_job &up, hipStream_t s);
 int launch_split(fs_ctx *, const int64_t *u_t, const int64_t *n_t_dev, const int64_t *u_t1,
                  const int64_t *n_t1_dev, int64_t cap_t, int64_t cap_t1, int64_t *co, int32_t *co_slot,
                  int64_t *ex, int32_t *ex_slot, int64_t *ex_next, int32_t *ex_next_slot, int64_t *counts_dev,

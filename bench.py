@@ -67,7 +67,7 @@ def device_info():
 def read_traffic(path=TRAFFIC_FILE):
     """profiles/hbm_traffic_per_launch.txt -> {(workload, kernel): HBM bytes per launch, launches per step}.
     Columns (blanks; '#' starts a comment): workload, kernel (no blanks; "/LPRnn" marks the launch of one row
-    width), dispatches averaged over, launches per step, FETCH_SIZE KiB, WRITE_SIZE KiB, the two calibration
+    width, "/any" one of tables of different widths), dispatches averaged over, launches per step, FETCH_SIZE KiB, WRITE_SIZE KiB, the two calibration
     factors.  Bytes = (FETCH * f_fetch + WRITE * f_write) * 1024 per launch."""
     out = {}
     if not os.path.exists(path):

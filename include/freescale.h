@@ -371,9 +371,9 @@ typedef struct fs_step_args {
  *                   waits for: on side stream A beside them (large batches; `stream` finally waits for A) or
  *                   behind them on `stream`
  * The step is complete when `stream` is.  Results are those of the five operations one after another, with the fp64 sums
- * of rows that occur more than FS_SHORT_SEGMENT times added in an order of its own: fixed by the layout of the batch, so
- * the same bits on every run, but another order than that of fs_segment_reduce_grads or fs_reduce_update_class, so that a
- * sum may differ from theirs by the error of fp64 addition before its one rounding to fp32. */
+ * of rows that occur more than FS_SHORT_SEGMENT times added in the order of fs_segment_reduce_grads: fixed by the layout of
+ * the batch, so the same bits on every run, but another order than that of fs_reduce_update_class, so that a sum may differ
+ * from that one's by the error of fp64 addition before its one rounding to fp32. */
 int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *args, fs_stream stream);
 
 /* The index half of an iteration alone - what Forward of Algorithm 2 does with the prefetched

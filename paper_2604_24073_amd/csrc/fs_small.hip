@@ -1,9 +1,9 @@
 // The index half of a small batch on ONE workgroup: dedup, collision split and class order of up to kSmallIdsInline IDs
 // (8192) on the caller's stream, of 10240 or 12288 ahead of time (small_index_ids in fs_dedup_rule.h).
 //
-// The kernels of fs_bucket.hip or fs_unique.hip and of fs_split.hip are a chain of up to seven launches (eleven of the radix
+// The kernels of fs_bucket.hip or fs_unique.hip and of fs_split.hip are a chain of up to six launches (ten of the radix
 // sort); on a batch of a few thousand IDs each of them is a handful of workgroups and takes 2.5 to 9 us whatever it does, so
-// a step that runs the chain takes 12 to 15 us longer up to 4 k IDs, and costs the host seven launches (one workgroup,
+// a step that runs the chain takes 12 to 15 us longer up to 4 k IDs, and costs the host six launches (one workgroup,
 // dedup, split and class order: 1 k IDs 14 us, 8 k 45 us, 16 k 96 us, three radix passes of 16 k keys on four SIMDs being
 // most of that).  Here everything the launches exchange through memory stays in the LDS of one compute unit (160 KB: room
 // for kSmallIds, 16384 IDs) and in registers, and a barrier takes the place of a launch.

@@ -12,7 +12,7 @@ from fs_workloads import CONFIGS
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 STEP_KERNELS = ["class_pass_kernel(priority_pass)", "class_pass_kernel(deferred_pass)", "gather_rows_kernel",
                 "bucket_sample_kernel", "bucket_partition_kernel", "bucket_sort_kernel", "bucket_compact_kernel",
-                "split_flag_kernel", "split_compact_kernel", "class_scatter_kernel"]
+                "split_flag_kernel", "class_scatter_kernel"]
 
 
 def test_every_timed_workload_has_the_kernels_of_the_step_and_no_others():

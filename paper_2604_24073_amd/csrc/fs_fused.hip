@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kFusedWaves *kWave, 4) void class_pass_kernel(const
 
 template <row_use USE, int LPR>
 __device__ __forceinline__ void batch_rows_body(const batch_update_job &job, int *flags) {
-    __shared__ parked_rows<LPR> sh;
+    __shared__ parked_rows<LPR, kFusedWaves, USE == kSumOnly ? 1 : kParkedMost> sh;   // a sum is written where its segment ends
     int64_t n_u = *job.n_unique_dev;
     n_u = n_u < 0 ? 0 : (n_u > job.n ? job.n : n_u);
     if ((int)blockIdx.x < job.long_blocks)
@@ -126,9 +126,14 @@ __global__ __launch_bounds__(kFusedWaves *kWave) void batch_update_kernel(const 
 
 // The segment reduce as an operation of its own (first half of update_embedding(I, G) of Algorithm 2): reduced[k, :] =
 // sum of grads[perm[p], :] over the sorted positions p of distinct row k, in the order and with the rounding of the batch
-// update.  It is bound as the passes are.  Against a chunk kernel of its own, 64 positions a wavefront whatever the batch, and
-// a launch that adds the pieces of the cut segments: 33 k occurrences x 100 23.0 -> 9.7 us, 70 k x 64 28.5 -> 9.9, 300 k x
-// 128 61.9 -> 47.5, 300 k x 8 105.6 -> 19.2, 600 k x 256 181 -> 161.
+// update.  It is bound as the passes are.  A sum is written where its segment ends: without rows parked in LDS (33 KB of the
+// widest, which is four workgroups to a compute unit) and with more workgroups of short rows than the passes, which end one
+// by one while others read, 600 k occurrences x 144 146 -> 111 us, x 256 180 -> 149, x 128 98 -> 84, 100 k x 144 31 -> 25 (1280
+// workgroups 117, 156, 88, 27; 65536 120, 157, 88, 25; four rows a round or one no better).  Against a chunk kernel of its own,
+// 64 positions a wavefront whatever the batch, and a launch that adds the pieces of the cut segments: 33 k occurrences x 100
+// 23.0 -> 9.9 us, 300 k x 8 121 -> 16, 100 k x 128 31.5 -> 19.2, x 144 26.9 -> 25.0, 600 k x 72 85 -> 71, x 144 119 -> 111, x 256
+// 175 -> 149.
+constexpr int kSumBlocks = 4096;
 template <int LPR>
 __global__ __launch_bounds__(kFusedWaves *kWave) void segment_reduce_kernel(const batch_update_job job, int *flags) {
     FS_WG_TRACE(9);
@@ -255,16 +260,16 @@ int launch_reduce_update(fs_ctx *ctx, int cls, const float *grads, int64_t n, in
     return launch_reduce_update_batch(ctx, cls, 1, &job, s);
 }
 
-static dim3 batch_grid(const batch_update_job &j, int lpr) {
+static dim3 batch_grid(const batch_update_job &j, int lpr, int64_t most) {
     const int64_t rows = ceil_div(j.n, (int64_t)(kWave / lpr) * FS_SHORT_UNR * kFusedWaves);
-    return dim3((unsigned)(j.long_blocks + (rows < FS_SHORT_MAX_BLOCKS ? rows : FS_SHORT_MAX_BLOCKS)));
+    return dim3((unsigned)(j.long_blocks + (rows < most ? rows : most)));
 }
 
 int launch_batch_update(fs_ctx *ctx, const fs_batch_update_job &job, hipStream_t s) {
     if (job.n == 0) return FS_OK;
     const batch_update_job j = batch_job(ctx, job, 0);
     const int lpr = lanes_per_row(j.gvec);
-    const dim3 grid = batch_grid(j, lpr), block(kFusedWaves * kWave);
+    const dim3 grid = batch_grid(j, lpr, FS_SHORT_MAX_BLOCKS), block(kFusedWaves * kWave);
 #define FS_CASE(L)                                                                                                \
     case L:                                                                                                       \
         if (job.dt == FS_BF16) hipLaunchKernelGGL((batch_update_kernel<true, L>), grid, block, 0, s, j, ctx->d_flags); \
@@ -285,7 +290,7 @@ int launch_reduce(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim, const
     const batch_update_job j = batch_job(ctx, fs_batch_update_job{grads, n, dim, perm, seg_offsets, nullptr, n_unique_dev,
                                                                   nullptr, FS_F32, nullptr, 0, 0.f, 0.f, reduced}, kReduceSet);
     const int lpr = lanes_per_row(j.gvec);
-    const dim3 grid = batch_grid(j, lpr), block(kFusedWaves * kWave);
+    const dim3 grid = batch_grid(j, lpr, kSumBlocks), block(kFusedWaves * kWave);
     switch (lpr) {
 #define FS_CASE(L) \
     case L: hipLaunchKernelGGL((segment_reduce_kernel<L>), grid, block, 0, s, j, ctx->d_flags); break;

@@ -221,6 +221,9 @@ __device__ __forceinline__ void long_chunk(PARKED &sh, const chunk_view &ch, con
         for (int c = 0; c < 4; ++c) t[c] = across_groups<LPR>(acc[c]);
         if (nflush == 0 && !head_complete) {
             if (grp == 0 && col_ok) store_piece(part_head + (int64_t)chunk * dim, gvec, lig, t);
+        } else if constexpr (USE == kSumOnly) {               // nothing to read first, so nothing to wait for
+            const int s_q = __shfl(ch.sl, q, kWave);
+            if (grp == 0 && col_ok) reduced[(int64_t)s_q * gvec + lig] = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
         } else {
             if (nparked < CAP) {
                 if (grp == 0 && col_ok)

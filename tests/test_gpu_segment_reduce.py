@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,rows,dim", [
     (1, 10, 4), (9, 1, 8), (63, 1, 64), (64, 3, 128), (65, 3, 256), (1000, 1, 20), (16_384, 40, 36), (65_535, 5, 4), (65_536, 5, 4),
     (65_535, 30_000, 16), (65_536, 30_000, 32), (131_071, 9, 12), (131_072, 9, 12), (131_071, 50_000, 64),
-    (131_072, 50_000, 128), (200_001, 2, 8), (300_000, 100_000, 24)])
+    (131_072, 50_000, 128), (200_001, 2, 8), (300_000, 100_000, 24), (90_000, 3_000_000, 144), (90_000, 900, 256)])
 def test_sums(n, rows, dim):
     rng = np.random.default_rng(n + dim)
     ids = dev(zipf_ids(rng, n, rows, a=1.1))

@@ -368,8 +368,11 @@ typedef struct fs_step_args {
  *                   fs_reduce_update_class; one call has nothing to gain from updating the exclusive rows later);
  *                   fs_gather_jagged(values_t1)
  *   index half    : fs_unique_ids(values_t1) -> fs_collision_split_classes(U_t, U_t1), which neither of the two
- *                   waits for: on side stream A beside them (large batches; `stream` finally waits for A) or
- *                   behind them on `stream`
+ *                   waits for: on side stream A beside them (more than 131072 IDs in the two batches; `stream`
+ *                   finally waits for A), behind them on `stream`, or (up to 8192 IDs in each) in the launch of the
+ *                   update and in front of the lookup
+ * What the index half writes must lie apart from everything that the update and the lookup read or write, or A races with
+ * them; up to 131072 IDs in the two batches it may lie there (u_t1 on values_t1, say): the index half then comes behind them.
  * The step is complete when `stream` is.  Results are those of the five operations one after another, with the fp64 sums
  * of rows that occur more than FS_SHORT_SEGMENT times added in the order of fs_segment_reduce_grads: fixed by the layout of
  * the batch, so the same bits on every run, but another order than that of fs_reduce_update_class, so that a sum may differ

@@ -900,6 +900,35 @@ int enqueue_index_work(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool hav
     return enqueue_index_work_batch(ctx, 1, a, &have_t, &have_t1, &ahead, s, set, &dedup_out, &layout_in);
 }
 
+// Nothing that the index half of a record writes lies where the update of its batch t or the lookup of its batch t+1 reads
+// or writes: the order of the two does not show.
+bool index_half_apart(const fs_step_args &x) {
+    struct span {
+        const void *p;
+        uint64_t bytes;
+    };
+    const uint64_t n_t = (uint64_t)x.n_t, n_t1 = (uint64_t)x.n_t1, w = x.dtype == FS_BF16 ? 2 : 4, dim = (uint64_t)x.dim;
+    const span written[] = {
+        {x.u_t1, 8 * n_t1}, {x.seg_offsets_t1, 4 * (n_t1 + 1)}, {x.perm_t1, 4 * n_t1}, {x.inverse_t1, 4 * n_t1},
+        {x.n_unique_t1_dev, 8}, {x.sorted_ids_t1, 8 * n_t1}, {x.co, 8 * n_t}, {x.co_slot, 4 * n_t}, {x.ex, 8 * n_t},
+        {x.ex_slot, 4 * n_t}, {x.ex_next, 8 * n_t1}, {x.ex_next_slot, 4 * n_t1}, {x.counts_dev, 24}, {x.co_flag_t1, n_t1},
+        {x.cperm, 4 * n_t}, {x.cslot, 4 * n_t}, {x.cstart, 4 * n_t}, {x.class_pos_dev, 8},
+        {x.short_rec, 2 * kShortRecInts * sizeof(int32_t) * n_t}};
+    const span row_work[] = {
+        {x.grads_t, 4 * dim * n_t}, {x.perm_t, 4 * n_t}, {x.seg_offsets_t, 4 * (n_t + 1)}, {x.u_t, 8 * n_t},
+        {x.n_unique_t_dev, 8}, {x.table, w * dim * (uint64_t)x.num_rows}, {x.state, 4 * (uint64_t)x.num_rows},
+        {x.reduced, 4 * dim * n_t}, {x.values_t1, 8 * n_t1}, {x.offsets_t1, 8 * ((uint64_t)x.batch_t1 + 1)},
+        {x.emb_t1, w * dim * n_t1}};
+    for (const span &a : written) {
+        const uintptr_t pa = (uintptr_t)a.p;
+        for (const span &b : row_work) {
+            const uintptr_t pb = (uintptr_t)b.p;
+            if (pa != 0 && pb != 0 && pa < pb + b.bytes && pb < pa + a.bytes) return false;
+        }
+    }
+    return true;
+}
+
 // The index half of one record on `s`: done ahead of time, it is only waited for.  An entry is claimed here, where
 // nothing can fail before it is given back (one that is claimed and not consumed would be lost for good).
 int enqueue_or_consume_index_half(fs_ctx *ctx, const fs_step_args *a, bool have_t, bool have_t1, hipStream_t s) {
@@ -1355,7 +1384,8 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     // row of U_t is updated straight from the layout of batch t, then the lookahead rows are read, in batch order;
     // the index half is independent of both.
     // Both batches small and nothing done ahead: the index half is a workgroup of the update's launch (a step of 1 k IDs
-    // 22.6 -> 14.5 us, of 8192 57.8 -> 46.6).  It may not write over what the update reads.
+    // 22.6 -> 14.5 us, of 8192 57.8 -> 46.6).  That puts it beside the update and in front of the lookup, so it may not
+    // write where they work; behind them it may, and stays there then.
     fs_unique_job uj;
     fs_split_job sj;
     fs_class_job cj;
@@ -1363,8 +1393,7 @@ int fs_prioritized_step(fs_ctx *ctx, const fs_step_args *a, fs_stream stream) {
     if (together) {
         index_jobs(*a, true, true, uj, sj, cj);
         together = small_step_fits(uj, sj, cj) && !find_ahead(ctx, a->counts_dev) && !find_ahead(ctx, a->u_t1) &&
-                   a->u_t1 != a->u_t && a->seg_offsets_t1 != a->seg_offsets_t && a->perm_t1 != a->perm_t &&
-                   a->n_unique_t1_dev != a->n_unique_t_dev;
+                   index_half_apart(*a);
     }
     if (side) FS_HIP(ctx, hipEventRecord(ctx->ev_fork, sp));
     if (have_t) {

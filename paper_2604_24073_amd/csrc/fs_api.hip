@@ -320,6 +320,7 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     c->max_ids = max_ids;
     c->max_dim = max_dim;
     c->use_worker = true;
+    c->reduce_tag = 1;
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) {
         delete c;

@@ -219,6 +219,7 @@ struct fs_ctx {
     double *fpart_last[fs::kFusedSets];    // [chunks, max_dim] first piece of a cut segment that continues into the next chunk
     int *fcounters[fs::kFusedSets];        // [chunks] arrivals per cut segment (indexed by its first chunk); at 0 between launches
     int *fcounters_sup[fs::kFusedSets];    // [chunks] arrivals per group of sixteen pieces (indexed by its first chunk)
+    int reduce_tag;           // of the last segment reduce (fs_fused.hip); 1 after fs_ctx_create
     int64_t *d_zero;          // device scalar that stays 0 (stands in for a missing lookahead)
     // partitioner and jagged shuffles
     int64_t *jag_unique;      // [max_ids] by-products of sorting the lengths (distinct lengths, their extents, count)

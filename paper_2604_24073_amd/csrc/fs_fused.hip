@@ -111,7 +111,7 @@ __device__ __forceinline__ void batch_rows_body(const batch_update_job &job, int
         long_segments_of_layout<USE, LPR, fused_unr<LPR>()>(sh, (int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
                                                 job.u_t, (int)n_u, job.table, job.state, job.num_rows, job.gvec, job.lr,
                                                 job.eps, job.reduced, job.part_head, job.part_last, job.cnt_seg,
-                                                job.cnt_sup, flags);
+                                                job.cnt_sup, job.tag, flags);
     else
         short_rows_body<USE, LPR, FS_SHORT_UNR, true>((int)blockIdx.x - job.long_blocks, (int)gridDim.x - job.long_blocks, job.grads,
                                              job.n, row_source{nullptr, job.u_t, job.seg_offsets, job.perm}, n_u, job.table,
@@ -284,11 +284,44 @@ int launch_batch_update(fs_ctx *ctx, const fs_batch_update_job &job, hipStream_t
     return FS_OK;
 }
 
+// The arrivals of a segment reduce are counted up from the tag of its launch, which no arrival before it has reached: a
+// layout that makes no sense can leave a counter anywhere (chunks that see it leave early), and the next call on the context
+// is right all the same.  A counter has room for the arrivals at a segment, 1 + 2^30 / (64 * 16) at most, and for 511 tags;
+// the first of them is for launches that are recorded (they can run behind any other, and clear the counters themselves),
+// and when the others are used up the counters are cleared too.
+constexpr int kTagShift = 22, kTags = 1 << (31 - kTagShift);
+static_assert((1ll << 30) / (kWave * kFusedSuper) + 1 < 1ll << kTagShift, "arrivals at the longest segment");
+
+__global__ __launch_bounds__(256) void clear_counters_kernel(int *a, int *b, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) a[i] = b[i] = 0;
+}
+
+// the tag of the next launch on `s`
+static int reduce_tag(fs_ctx *ctx, hipStream_t s, int *tag) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (s != nullptr) FS_HIP(ctx, hipStreamIsCapturing(s, &status));
+    const bool recorded = status != hipStreamCaptureStatusNone;
+    if (!recorded && ++ctx->reduce_tag < kTags) {
+        *tag = ctx->reduce_tag << kTagShift;
+        return FS_OK;
+    }
+    const int counters = (int)fused_chunk_space(ctx->max_ids, kReduceSet);
+    hipLaunchKernelGGL(clear_counters_kernel, dim3((unsigned)ceil_div(counters, 256)), dim3(256), 0, s,
+                       ctx->fcounters[kReduceSet], ctx->fcounters_sup[kReduceSet], counters);
+    FS_LAUNCH_CHECK(ctx, "clear_counters_kernel");
+    if (!recorded) ctx->reduce_tag = 2;
+    *tag = (recorded ? 1 : 2) << kTagShift;
+    return FS_OK;
+}
+
 int launch_reduce(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim, const int32_t *perm,
                   const int32_t *seg_offsets, const int64_t *n_unique_dev, float *reduced, hipStream_t s) {
     if (n == 0) return FS_OK;
-    const batch_update_job j = batch_job(ctx, fs_batch_update_job{grads, n, dim, perm, seg_offsets, nullptr, n_unique_dev,
-                                                                  nullptr, FS_F32, nullptr, 0, 0.f, 0.f, reduced}, kReduceSet);
+    batch_update_job j = batch_job(ctx, fs_batch_update_job{grads, n, dim, perm, seg_offsets, nullptr, n_unique_dev,
+                                                            nullptr, FS_F32, nullptr, 0, 0.f, 0.f, reduced}, kReduceSet);
+    const int rc = reduce_tag(ctx, s, &j.tag);
+    if (rc != FS_OK) return rc;
     const int lpr = lanes_per_row(j.gvec);
     const dim3 grid = batch_grid(j, lpr, kSumBlocks), block(kFusedWaves * kWave);
     switch (lpr) {

@@ -49,3 +49,54 @@ def test_special_values_stay_in_their_rows(special):
     slot = int((lay["unique"][:u] == hit).nonzero()[0])
     assert bad.sum() == 1 and bool(bad[slot, 5])
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [60_000, 200_000])
+@pytest.mark.parametrize("calls", [1, 3, 1200])
+def test_right_behind_a_call_whose_layout_does_not_fit(n, calls):
+    """A call that leaves early where its layout makes no sense has counted some pieces of a cut segment in and others not:
+    the next one on the context adds its own up all the same, with nothing asked in between, however often that happens."""
+    dim = 8
+    ctx = fs.Context(max_ids=n, max_dim=dim)
+    lay = fs.fs_unique_ids(ctx, torch.arange(n, device="cuda", dtype=torch.int64) // (n // 3), 10)
+    u = int(lay["n_unique"].item())
+    grads = torch.randint(-64, 65, (n, dim), device="cuda", generator=torch.Generator("cuda").manual_seed(n)).float() / 16
+    want = torch.zeros((u, dim), dtype=torch.float64).index_add_(0, lay["inverse"].cpu().long(), grads.cpu().double()).float()
+    bad = lay["perm"].clone()
+    bad[n // 2] = n                                  # one chunk in the middle of a long segment does not take part
+    out = torch.empty((n, dim), device="cuda")
+    for _ in range(calls):
+        fs.fs_segment_reduce_grads(ctx, grads, bad, lay["seg_offsets"], lay["n_unique"], out=out)
+    fs.fs_segment_reduce_grads(ctx, grads, lay["perm"], lay["seg_offsets"], lay["n_unique"], out=out)
+    assert torch.equal(out[:u].cpu(), want)
+    assert fs.fs_check_async(ctx) == fs.FS_ERANGE and "internal" in ctx.last_error()
+    ctx.close()
+
+
+def test_replayed_behind_a_call_whose_layout_does_not_fit():
+    """The same with both calls recorded: eager and recorded calls between each other."""
+    n, dim = 100_000, 8
+    ctx = fs.Context(max_ids=n, max_dim=dim)
+    lay = fs.fs_unique_ids(ctx, torch.arange(n, device="cuda", dtype=torch.int64) // (n // 3), 10)
+    u = int(lay["n_unique"].item())
+    grads = torch.randint(-64, 65, (n, dim), device="cuda", generator=torch.Generator("cuda").manual_seed(n)).float() / 16
+    want = torch.zeros((u, dim), dtype=torch.float64).index_add_(0, lay["inverse"].cpu().long(), grads.cpu().double()).float()
+    bad = lay["perm"].clone()
+    bad[n // 2] = n
+    out = torch.empty((n, dim), device="cuda")
+    good = lambda: fs.fs_segment_reduce_grads(ctx, grads, lay["perm"], lay["seg_offsets"], lay["n_unique"], out=out)  # noqa: E731
+    misfit = lambda: fs.fs_segment_reduce_grads(ctx, grads, bad, lay["seg_offsets"], lay["n_unique"], out=out)  # noqa: E731
+    graphs = []
+    torch.cuda.synchronize()
+    for call in (good, misfit):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            call()
+        graphs.append(g.replay)
+    for first, then in ((misfit, graphs[0]), (graphs[1], good), (graphs[1], graphs[0]), (good, graphs[0]), (graphs[0], good)):
+        for _ in range(2):
+            first()
+            then()
+            assert torch.equal(out[:u].cpu(), want)
+    fs.fs_check_async(ctx)
+    ctx.close()

@@ -23,8 +23,10 @@
  *     Adagrad state is one fp32 per row; gradients are fp32 [n, dim].  dim must be a
  *     multiple of 4 (fp32) or 8 (bf16) and at most FS_MAX_DIM.
  *   - One context serves one GPU and one caller thread at a time.  Calls that use the
- *     context workspace (fs_unique_ids, fs_collision_split, fs_segment_reduce_grads,
- *     fs_prioritized_step) must not overlap each other on different streams.
+ *     context workspace (fs_unique_ids, fs_collision_split with or without the classes,
+ *     fs_segment_reduce_grads, fs_split_grads, the partitioners, the jagged shuffles except
+ *     fs_jagged_indexed_permute of up to 8192 samples, the step calls) must not overlap each
+ *     other on different streams.
  */
 #ifndef FREESCALE_H
 #define FREESCALE_H
@@ -216,7 +218,7 @@ int fs_partition_vbs(fs_ctx *ctx, const int64_t *lengths, int64_t B, const int64
  *                on the number of output elements (it sizes the copy; for a permutation n_values)
  * A sample index outside [0, B), a sample whose boundaries do not lie inside the values, or more output
  * elements than cap_out (the copy stops there) are reported as FS_ERANGE by fs_check_async.
- * n_out <= context max_ids. */
+ * n_out <= context max_ids.  Of more than 8192 output samples it uses the context's workspace. */
 int fs_jagged_indexed_permute(fs_ctx *ctx, const void *values, int64_t n_values, int32_t elem_bytes,
                               const int64_t *offsets, int64_t B, const int32_t *sample_of, int64_t n_out,
                               void *out_values, int64_t cap_out, int64_t *out_offsets, fs_stream stream);
@@ -226,7 +228,7 @@ int fs_jagged_indexed_permute(fs_ctx *ctx, const void *values, int64_t n_values,
  * Feature-major: segment (f, b) is number f * B + b; batch-major: number b * F + f.  The paper states what
  * these kernels are for, not their layouts; the layouts below are this library's.  Each writes out_values
  * [n_values] and out_offsets [F * B + 1]; F * B <= context max_ids; malformed offsets or ranges are reported
- * as FS_ERANGE by fs_check_async (the segments concerned come out empty).
+ * as FS_ERANGE by fs_check_async (the segments concerned come out empty).  They use the context's workspace.
  *
  * Keyed transpose: feature-major in, batch-major out. */
 int fs_jagged_keyed_transpose(fs_ctx *ctx, const void *values, int64_t n_values, int32_t elem_bytes,

@@ -79,13 +79,16 @@ __device__ __forceinline__ sample_extent extent_of(const jagged_in &in, int64_t 
 // What the copy wants to know of every output sample and every tile of the output, written down with the output
 // offsets: a workgroup of the copy then opens its tile with two dependent rounds of loads, where a search for its first
 // and last sample and a look at where they come from are six.
+// It lies in the context, so that the calls that use it must not overlap.  The permute of up to kOwnPermute samples of a
+// caller's list has no plan: its calls share nothing and may run side by side on several streams.
 struct copy_plan {
-    int64_t *delta;           // [n_out] first input element of a sample minus its first output element
+    int64_t *delta;           // [n_out] first input element of a sample minus its first output element (null: no plan)
     int32_t *tile_first;      // [tiles] sample that the first piece of a tile belongs to (null: too many tiles)
     int64_t cap_out;          // elements of the output
     int ppe, tile_log2;       // pieces of an element, log2 of the pieces of a tile
 };
 __device__ __forceinline__ void plan_sample(const copy_plan &plan, int64_t k, int64_t start, const sample_extent &x) {
+    if (plan.delta == nullptr) return;
     plan.delta[k] = x.first - start;
     if (plan.tile_first == nullptr) return;
     int64_t end = start + x.len;
@@ -161,16 +164,16 @@ __device__ __forceinline__ int64_t rank_split(const sample_order &o, const int64
 
 // Everything the copy needs about a small number of output samples in ONE launch: their order, the output offsets
 // and the splits.  The work is a few loads a sample; what it costs is launches, about 4 us each here (four keyed
-// shuffles of 1024 segments spent three to four of them on it).  One workgroup, up to kPlanPer consecutive samples
-// a thread; beyond that one compute unit takes longer than two launches over many (8192 samples 24 us against 16, 4096
-// 14.1 against 14.9).
+// shuffles of 1024 segments spent three to four of them on it).  One workgroup, up to PER consecutive samples a thread.
+// Beyond kPlanPer one compute unit takes longer than two launches over many (a permute of 8192 samples 17.5 us against 12.3,
+// of 4096 10.8 against 11.6), but those leave sums in the context, and a permute without a plan leaves nothing there (its
+// offsets in one launch over many, each adding up the lengths in front of its samples: 17.0).
 constexpr int kPlanThreads = 1024;
-#ifndef PLANPER
-#define PLANPER 8
-#endif
-constexpr int kPlanPer = 4;
+constexpr int kPlanPer = 4, kOwnPer = 8;
+constexpr int64_t kOwnPermute = (int64_t)kPlanThreads * kOwnPer;
 constexpr int kPlanRanks = 1024;                 // rank boundaries kept in LDS
 
+template <int PER>
 __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_in in, const sample_order order,
                                                                    int n_out, const copy_plan plan,
                                                                    int64_t *out_offsets, int *__restrict__ flags) {
@@ -183,20 +186,20 @@ __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_
     __syncthreads();
     const int64_t *ro = staged ? (const int64_t *)s_ro : order.ro;
     bool bad = n_out > 0 && bad_ranks(order);
-    const int per = (n_out + kPlanThreads - 1) / kPlanThreads;           // at most kPlanPer
+    const int per = (n_out + kPlanThreads - 1) / kPlanThreads;           // at most PER
     const int k0 = (int)threadIdx.x * per;
-    int32_t p[kPlanPer];
+    int32_t p[PER];
 #pragma unroll
-    for (int i = 0; i < kPlanPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         p[i] = -1;
         if (i < per && k0 + i < n_out) {
             p[i] = order.mode == kMapGiven ? order.given[k0 + i] : ordered_segment(order, ro, k0 + i);
         }
     }
-    sample_extent x[kPlanPer];
+    sample_extent x[PER];
     int64_t v = 0;
 #pragma unroll
-    for (int i = 0; i < kPlanPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         x[i] = {0, 0};
         if (i < per && k0 + i < n_out) x[i] = extent_of(in, p[i], bad);
         v += x[i].len;
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_
         total += sh[w];
     }
 #pragma unroll
-    for (int i = 0; i < kPlanPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         if (i < per && k0 + i < n_out) {
             out_offsets[k0 + i] = run;
             plan_sample(plan, k0 + i, run, x[i]);
@@ -332,9 +335,11 @@ struct piece_group<u32x4> {
 // the copy).  Where samples start is a bit per piece of the tile: the sample of a piece is a matter of counting bits,
 // however short the samples are, where a walk over a list of boundaries takes a dependent step for each.
 template <typename V, int kCopyTile, int GROUPS>
-__global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__restrict__ values, int64_t n_pieces, int64_t n_out,
-                                                                    const int64_t *__restrict__ out_offsets,
-                                                                    const copy_plan plan, V *__restrict__ out) {
+__global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__restrict__ values, int64_t n_pieces,
+                                                                    const jagged_in in, const int32_t *__restrict__ sample_of,
+                                                                    int64_t n_out, const int64_t *__restrict__ out_offsets,
+                                                                    const copy_plan plan, V *__restrict__ out,
+                                                                    int *__restrict__ flags) {
     typedef typename piece_group<V>::type G;
     constexpr int W = 16 / (int)sizeof(V);                      // pieces of a group
     constexpr int kWords = kCopyTile / 32;
@@ -344,8 +349,13 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     __shared__ int64_t w_delta[kCopyWindow];    // per bit: first input piece of the sample minus its first output piece
     __shared__ int64_t win[2];
     __shared__ uint32_t wave_sum[kScanThreads / kWave];
-    const int64_t *__restrict__ delta = plan.delta;
     const int ppe = plan.ppe;
+    // (without a plan: of a sample that is not empty, so that the plan kernel has found its extent inside the values)
+    auto delta_of = [&](int64_t k) -> int64_t {
+        if (plan.delta != nullptr) return plan.delta[k];
+        const int64_t p = sample_of[k];
+        return p >= 0 && p < in.B ? in.offsets[p] - out_offsets[k] : 0;
+    };
     int64_t ka = 0, kb = n_out - 1;
     const bool planned = plan.tile_first != nullptr;
     if (planned) {
@@ -356,9 +366,19 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     if (total > plan.cap_out) total = plan.cap_out;
     const int64_t pieces = total * ppe;
     const int64_t q0 = (int64_t)blockIdx.x * kCopyTile;
-    if (q0 >= pieces) return;                                   // whole workgroup
+    if (q0 >= pieces || n_pieces <= 0) return;                  // whole workgroup
     const int tile_pieces = (int)((q0 + kCopyTile < pieces ? q0 + kCopyTile : pieces) - q0);
     if (q0 + kCopyTile >= pieces) kb = n_out - 1;               // the last tile: nobody wrote down what follows it
+    // What a plan says is looked at before it is used as a place: another call of the context that overlaps this one, which
+    // is not allowed, gets the flag and rows that are wrong, but no access out of range.
+    ka = ka < 0 ? 0 : ka < n_out ? ka : n_out - 1;
+    kb = kb < ka ? ka : kb < n_out ? kb : n_out - 1;
+    bool bad = false;
+    auto piece = [&](int64_t from) {
+        const bool in_range = from >= 0 && from < n_pieces;
+        bad |= !in_range;
+        return __builtin_nontemporal_load(values + (in_range ? from : 0));
+    };
     if (!planned || kb - ka + 1 > kCopyWindow) {
         if (threadIdx.x < 2 * kWave) {
             // sample of an element e: the last k with out_offsets[k] <= e (empty samples in between are skipped);
@@ -383,8 +403,9 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
                 const int64_t mid = (lo + hi) >> 1;
                 if (out_offsets[mid] <= e) lo = mid + 1; else hi = mid;
             }
-            out[q0 + l] = values[q0 + l + delta[lo > ka ? lo - 1 : ka] * ppe];
+            out[q0 + l] = piece(q0 + l + delta_of(lo > ka ? lo - 1 : ka) * ppe);
         }
+        if (bad) atomicOr(flags, kFlagOffsets);
         return;
     }
     const int wn = (int)(kb - ka + 1);
@@ -397,7 +418,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     int64_t delta0 = 0;
     if ((int)threadIdx.x < wn) {
         rel0 = first_in_tile(threadIdx.x);
-        delta0 = delta[ka + threadIdx.x];
+        delta0 = delta_of(ka + threadIdx.x);
     }
     if ((int)threadIdx.x < kWords) starts[threadIdx.x] = 0;
     __syncthreads();
@@ -423,7 +444,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     for (int j = threadIdx.x; j < wn; j += kScanThreads) {
         const bool held = j == (int)threadIdx.x;
         const int rel = held ? rel0 : first_in_tile(j);
-        if (rel < kCopyTile) w_delta[sample_at(rel)] = (held ? delta0 : delta[ka + j]) * ppe;
+        if (rel < kCopyTile) w_delta[sample_at(rel)] = (held ? delta0 : delta_of(ka + j)) * ppe;
     }
     __syncthreads();
     // Wavefront w copies the w-th quarter of the tile, 64 consecutive groups per instruction, front to back.
@@ -446,9 +467,10 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
             const int l = w0 + r0 + (i * kWave + lane) * W;     // first piece of the group
             const int at = l < tile_pieces ? l : tile_pieces - 1;
             // (every lane loads, from where sixteen bytes are: a load that only some lanes make waits for the one before)
-            const int64_t from = q0 + at + w_delta[sample_at(at)];
-            v[i] = __builtin_nontemporal_load(reinterpret_cast<const G *>(values + (from < last ? from : last)));
+            const int64_t from = q0 + at + w_delta[sample_at(at)], most = from < last ? from : last;
+            v[i] = __builtin_nontemporal_load(reinterpret_cast<const G *>(values + (most > 0 ? most : 0)));
             split[i] = W > 1 && l < tile_pieces && (l + W > tile_pieces || cuts_of(l) != 0);
+            bad |= from < 0 || (from > last && l < tile_pieces && !split[i]);
         }
         if constexpr (W > 1) {
             // the pieces of a divided group come one by one and are put together here: stored one by one they would leave
@@ -461,7 +483,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
 #pragma unroll
                     for (int k = 0; k < W; ++k) {
                         const int at = l + k < tile_pieces ? l + k : tile_pieces - 1;
-                        one[i][k] = __builtin_nontemporal_load(values + (q0 + at + w_delta[sample_at(at)]));
+                        one[i][k] = piece(q0 + at + w_delta[sample_at(at)]);
                     }
                 }
 #pragma unroll
@@ -480,6 +502,7 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
             }
         }
     }
+    if (bad) atomicOr(flags, kFlagOffsets);
 }
 
 // output samples in the order `order`, whose list is `sample_of` (written here unless the caller gave it)
@@ -495,10 +518,12 @@ static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values
                                                                             : (large ? kCopyTile4Large : kCopyTile4);
     const int64_t blocks = n_out > 0 ? ceil_div(cap_out * ppe, tile) : 0;
     if (blocks > 0x7fffffffll) return set_err(ctx, FS_EINVAL, "indexed permute: output too large for one launch");
-    const copy_plan plan = {ctx->jag_delta, blocks <= 2 * ctx->max_ids ? ctx->jag_tile_first : nullptr, cap_out, ppe,
-                            31 - __builtin_clz(tile)};
-    if (n_out <= (int64_t)kPlanThreads * kPlanPer) {
-        hipLaunchKernelGGL(jagged_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, in, order, (int)n_out, plan, out_offsets,
+    const bool own = order.mode == kMapGiven && n_out <= kOwnPermute;
+    const copy_plan plan = {own ? nullptr : ctx->jag_delta, own || blocks > 2 * ctx->max_ids ? nullptr : ctx->jag_tile_first,
+                            cap_out, ppe, 31 - __builtin_clz(tile)};
+    if (own || n_out <= (int64_t)kPlanThreads * kPlanPer) {
+        auto *kernel = n_out <= (int64_t)kPlanThreads * kPlanPer ? &jagged_plan_kernel<kPlanPer> : &jagged_plan_kernel<kOwnPer>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kPlanThreads), 0, s, in, order, (int)n_out, plan, out_offsets,
                            ctx->d_flags);
     } else {
         const int tiles = (int)ceil_div(n_out, kScanTile);
@@ -514,7 +539,8 @@ static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values
         const dim3 grid((unsigned)blocks);
 #define FS_COPY(V, TILE, GROUPS)                                                                                       \
     hipLaunchKernelGGL((permute_copy_kernel<V, TILE, GROUPS>), grid, dim3(kScanThreads), 0, s, (const V *)values,      \
-                       n_values * ppe, n_out, out_offsets, plan, (V *)out_values)
+                       n_values * ppe, in, sample_of, n_out, out_offsets, plan, (V *)out_values,  \
+                       ctx->d_flags)
         if (piece == 16 && large) FS_COPY(u32x4, kCopyTile16Large, 2);
         else if (piece == 16) FS_COPY(u32x4, kCopyTile16, 8);
         else if (piece == 8) FS_COPY(uint64_t, kCopyTile8, 4);

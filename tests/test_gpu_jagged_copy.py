@@ -1,6 +1,7 @@
 """The copy behind the jagged shuffles at the sizes where it changes: ends of tiles and of groups of sixteen bytes, values
 and outputs that lie at any multiple of the piece, inputs of less than sixteen bytes, more samples than a tile's window has
-places for, more tiles than are written down ahead, samples taken twice.  Byte work: bit-exact."""
+places for, more tiles than are written down ahead, samples taken twice; permutes side by side on streams of their own.  Byte
+work: bit-exact."""
 import numpy as np
 import pytest
 import torch
@@ -107,4 +108,35 @@ def test_sixteen_byte_pieces_around_the_size_where_the_tile_changes(pieces):
     values, offsets = jagged(rng, lens, 4)
     ctx = fs.Context(max_ids=4096, max_dim=8)
     permute(ctx, values, offsets, rng.permutation(900), 4)
+    ctx.close()
+
+
+@pytest.mark.parametrize("words", [1, 2, 4])
+@pytest.mark.parametrize("samples", [40, 4096, 4097, 8192])
+def test_permutes_of_a_list_on_two_streams_of_one_context(words, samples):
+    """Up to 8192 samples of a caller's list nothing of the context is used: calls on two streams, one of them late, do not
+    get in each other's way."""
+    rng = np.random.default_rng(samples + words)
+    ctx = fs.Context(max_ids=8192, max_dim=8)
+    calls = []
+    for k in range(24):
+        values, offsets = jagged(rng, rng.integers(0, 2 * 40_000 // samples + 2, size=samples), words)
+        order = rng.permutation(samples).astype(np.int32)
+        calls.append((values, offsets, order, torch.from_numpy(values).cuda(), torch.from_numpy(offsets).cuda(),
+                      torch.from_numpy(order).cuda()))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    slow = torch.randn(1024, 1024, device="cuda")
+    torch.cuda.synchronize()
+    got = []
+    for k, (values, _, _, v, o, sel) in enumerate(calls):
+        with torch.cuda.stream(streams[k % 2]):
+            if k % 3 == 0:
+                slow @ slow
+            got.append(fs.fs_jagged_indexed_permute(ctx, v, o, sel, len(values)))
+    torch.cuda.synchronize()
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    for (values, offsets, order, *_), (out, out_offsets) in zip(calls, got):
+        want, want_offsets = expected(values, offsets, order)
+        assert np.array_equal(out_offsets.cpu().numpy(), want_offsets)
+        assert np.array_equal(out.cpu().numpy().reshape(want.shape), want)
     ctx.close()

@@ -87,16 +87,27 @@ struct copy_plan {
     int64_t cap_out;          // elements of the output
     int ppe, tile_log2;       // pieces of an element, log2 of the pieces of a tile
 };
-__device__ __forceinline__ void plan_sample(const copy_plan &plan, int64_t k, int64_t start, const sample_extent &x) {
+// `mine`: this lane has a sample; met by whole wavefronts.  A lane writes the tiles of its sample down by itself, of a long one
+// the wavefront together: one sample of 16.7 M IDs has 8192 tiles, and a lane alone was at them for 210 us.
+constexpr int kLaneTiles = 64;
+__device__ __forceinline__ void plan_sample(const copy_plan &plan, bool mine, int64_t k, int64_t start, const sample_extent &x) {
     if (plan.delta == nullptr) return;
-    plan.delta[k] = x.first - start;
+    if (mine) plan.delta[k] = x.first - start;
     if (plan.tile_first == nullptr) return;
     int64_t end = start + x.len;
     if (end > plan.cap_out) end = plan.cap_out;
-    const int64_t last = end * plan.ppe;
     const int64_t size = (int64_t)1 << plan.tile_log2;
-    for (int64_t t = (start * plan.ppe + size - 1) >> plan.tile_log2; (t << plan.tile_log2) < last; ++t)
-        plan.tile_first[t] = (int32_t)k;
+    const int64_t t0 = (start * plan.ppe + size - 1) >> plan.tile_log2;
+    const int64_t t1 = mine ? (end * plan.ppe + size - 1) >> plan.tile_log2 : t0;        // behind the last tile that starts in it
+    const bool is_long = t1 - t0 > kLaneTiles;
+    if (!is_long)
+        for (int64_t t = t0; t < t1; ++t) plan.tile_first[t] = (int32_t)k;
+    for (uint64_t left = __ballot(is_long); left != 0; left &= left - 1) {
+        const int who = __ffsll((unsigned long long)left) - 1;
+        const int64_t from = __shfl(t0, who, kWave), to = __shfl(t1, who, kWave);
+        const int whose = __shfl((int)k, who, kWave);
+        for (int64_t t = from + (threadIdx.x & (kWave - 1)); t < to; t += kWave) plan.tile_first[t] = whose;
+    }
 }
 
 // ---- the order of the output samples ---------------------------------------------------------------------
@@ -215,9 +226,10 @@ __global__ __launch_bounds__(kPlanThreads) void jagged_plan_kernel(const jagged_
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        if (i < per && k0 + i < n_out) {
-            out_offsets[k0 + i] = run;
-            plan_sample(plan, k0 + i, run, x[i]);
+        if (i < per) {                                                   // the same for all
+            const bool mine = k0 + i < n_out;
+            if (mine) out_offsets[k0 + i] = run;
+            plan_sample(plan, mine, k0 + i, run, x[i]);
         }
         run += x[i].len;
     }
@@ -287,10 +299,9 @@ __global__ __launch_bounds__(kScanThreads) void permute_offsets_kernel(const jag
     int64_t run = tile_base + block_exclusive_scan<int64_t>(v, sh, tile_total);
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
-        if (k0 + i < n_out) {
-            out_offsets[k0 + i] = run;
-            plan_sample(plan, k0 + i, run, x[i]);
-        }
+        const bool mine = k0 + i < n_out;
+        if (mine) out_offsets[k0 + i] = run;
+        plan_sample(plan, mine, k0 + i, run, x[i]);
         run += x[i].len;
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
@@ -338,8 +349,7 @@ template <typename V, int kCopyTile, int GROUPS>
 __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__restrict__ values, int64_t n_pieces,
                                                                     const jagged_in in, const int32_t *__restrict__ sample_of,
                                                                     int64_t n_out, const int64_t *__restrict__ out_offsets,
-                                                                    const copy_plan plan, V *__restrict__ out,
-                                                                    int *__restrict__ flags) {
+                                                                    const copy_plan plan, V *__restrict__ out) {
     typedef typename piece_group<V>::type G;
     constexpr int W = 16 / (int)sizeof(V);                      // pieces of a group
     constexpr int kWords = kCopyTile / 32;
@@ -369,15 +379,12 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
     if (q0 >= pieces || n_pieces <= 0) return;                  // whole workgroup
     const int tile_pieces = (int)((q0 + kCopyTile < pieces ? q0 + kCopyTile : pieces) - q0);
     if (q0 + kCopyTile >= pieces) kb = n_out - 1;               // the last tile: nobody wrote down what follows it
-    // What a plan says is looked at before it is used as a place: another call of the context that overlaps this one, which
-    // is not allowed, gets the flag and rows that are wrong, but no access out of range.
+    // What a plan says is a place only inside the lists and the input (here, and where pieces are read): of a call that
+    // overlaps another one of its context, which is not allowed, the rows are wrong, but no access is out of range.
     ka = ka < 0 ? 0 : ka < n_out ? ka : n_out - 1;
     kb = kb < ka ? ka : kb < n_out ? kb : n_out - 1;
-    bool bad = false;
     auto piece = [&](int64_t from) {
-        const bool in_range = from >= 0 && from < n_pieces;
-        bad |= !in_range;
-        return __builtin_nontemporal_load(values + (in_range ? from : 0));
+        return __builtin_nontemporal_load(values + ((uint64_t)from < (uint64_t)n_pieces ? from : 0));
     };
     if (!planned || kb - ka + 1 > kCopyWindow) {
         if (threadIdx.x < 2 * kWave) {
@@ -405,7 +412,6 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
             }
             out[q0 + l] = piece(q0 + l + delta_of(lo > ka ? lo - 1 : ka) * ppe);
         }
-        if (bad) atomicOr(flags, kFlagOffsets);
         return;
     }
     const int wn = (int)(kb - ka + 1);
@@ -467,10 +473,9 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
             const int l = w0 + r0 + (i * kWave + lane) * W;     // first piece of the group
             const int at = l < tile_pieces ? l : tile_pieces - 1;
             // (every lane loads, from where sixteen bytes are: a load that only some lanes make waits for the one before)
-            const int64_t from = q0 + at + w_delta[sample_at(at)], most = from < last ? from : last;
-            v[i] = __builtin_nontemporal_load(reinterpret_cast<const G *>(values + (most > 0 ? most : 0)));
+            const int64_t from = q0 + at + w_delta[sample_at(at)];
+            v[i] = __builtin_nontemporal_load(reinterpret_cast<const G *>(values + ((uint64_t)from < (uint64_t)last ? from : last)));
             split[i] = W > 1 && l < tile_pieces && (l + W > tile_pieces || cuts_of(l) != 0);
-            bad |= from < 0 || (from > last && l < tile_pieces && !split[i]);
         }
         if constexpr (W > 1) {
             // the pieces of a divided group come one by one and are put together here: stored one by one they would leave
@@ -502,7 +507,6 @@ __global__ __launch_bounds__(kScanThreads) void permute_copy_kernel(const V *__r
             }
         }
     }
-    if (bad) atomicOr(flags, kFlagOffsets);
 }
 
 // output samples in the order `order`, whose list is `sample_of` (written here unless the caller gave it)
@@ -539,8 +543,7 @@ static int launch_ordered_copy(fs_ctx *ctx, const void *values, int64_t n_values
         const dim3 grid((unsigned)blocks);
 #define FS_COPY(V, TILE, GROUPS)                                                                                       \
     hipLaunchKernelGGL((permute_copy_kernel<V, TILE, GROUPS>), grid, dim3(kScanThreads), 0, s, (const V *)values,      \
-                       n_values * ppe, in, sample_of, n_out, out_offsets, plan, (V *)out_values,  \
-                       ctx->d_flags)
+                       n_values * ppe, in, sample_of, n_out, out_offsets, plan, (V *)out_values)
         if (piece == 16 && large) FS_COPY(u32x4, kCopyTile16Large, 2);
         else if (piece == 16) FS_COPY(u32x4, kCopyTile16, 8);
         else if (piece == 8) FS_COPY(uint64_t, kCopyTile8, 4);

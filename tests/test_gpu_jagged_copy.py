@@ -140,3 +140,26 @@ def test_permutes_of_a_list_on_two_streams_of_one_context(words, samples):
         assert np.array_equal(out_offsets.cpu().numpy(), want_offsets)
         assert np.array_equal(out.cpu().numpy().reshape(want.shape), want)
     ctx.close()
+
+
+@pytest.mark.parametrize("words", [1, 2, 4])
+@pytest.mark.parametrize("tiles", [63, 64, 65, 66, 700])
+@pytest.mark.parametrize("segments", [1, 40, 5000])
+def test_samples_of_many_tiles(words, tiles, segments):
+    """Samples with about as many tiles as one lane writes down, and with many more, among short ones: one in the one
+    workgroup, one each in two neighbouring lanes, one behind the others; two launches for the offsets from 4097 samples on."""
+    rng = np.random.default_rng(tiles)
+    lens = rng.integers(0, 4, size=segments)
+    lens[rng.permutation(segments)[:3]] = 2048 * tiles + rng.integers(-3, 4, size=min(3, segments))
+    lens[segments // 2:segments // 2 + 2] = 2048 * tiles + 1
+    lens[-1] = 2048 * tiles
+    values, offsets = jagged(rng, lens, words)
+    ctx = fs.Context(max_ids=8192, max_dim=8)
+    v, o = torch.from_numpy(values).cuda(), torch.from_numpy(offsets).cuda()
+    F = 4 if segments % 4 == 0 else 1
+    out, out_offsets = fs.fs_jagged_keyed_transpose(ctx, v, o, F, segments // F)
+    assert fs.fs_check_async(ctx) == fs.FS_OK, ctx.last_error()
+    want, want_offsets = expected(values, offsets, np.arange(segments).reshape(F, -1).T.reshape(-1))
+    assert np.array_equal(out_offsets.cpu().numpy(), want_offsets)
+    assert np.array_equal(out.cpu().numpy().reshape(want.shape), want)
+    ctx.close()

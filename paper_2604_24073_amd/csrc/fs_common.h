@@ -37,8 +37,9 @@ constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 // Without the dedup in front the chain is two launches, with the class order or without: IDs up to which the one workgroup
 // does those on the caller's stream.  Split alone, one workgroup against two launches: 4096 IDs 11.4 / 11.6 us, 5000
 // 13.8 / 11.4, 8192 18.9 / 11.8; with the class order against two as well: tables of 20000 rows 4000 IDs 14.8 / 17.7, 6100
-// 18.8 / 18.4; of 4 M rows 2500 13.5 / 18.2, 4000 18.3 / 18.2, 5000 21.5 / 18.6, 6100 25.7 / 18.7 (the line was drawn against
-// three launches and stays, as it also says which layouts that do not fit their batch are flagged).
+// 18.8 / 18.4; of 4 M rows 2500 13.5 / 18.2, 4000 18.3 / 18.2, 5000 21.5 / 18.6, 6100 25.7 / 18.7.  The line was drawn against
+// three launches: against two it lies where it should for small tables only.  Both report a layout that does not fit its
+// batch; the one workgroup leaves the class order empty then.
 constexpr int64_t kSmallSplitInline = 4096;
 constexpr int64_t kSmallClassesInline = 6144;
 

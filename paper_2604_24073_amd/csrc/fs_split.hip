@@ -89,7 +89,8 @@ constexpr int kRowIsCo = 1 << 16;        // of cidx; below it the place among th
 static_assert(kScanTile <= kRowIsCo, "a place in a tile");
 
 // blocks [0, tiles_t) flag U_t against U_t1; blocks [tiles_t, tiles_t + tiles_t1) flag U_t1 against U_t
-__global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_dev_batch batch) {
+// flags: looked at only with a class order
+__global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_dev_batch batch, int *__restrict__ flags) {
     FS_WG_TRACE(5);
     const split_dev_job &job = batch.j[blockIdx.y];
     if ((int)blockIdx.x >= job.tiles_t + job.tiles_t1) return;
@@ -169,13 +170,16 @@ __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_de
     // totals of them.
     const int32_t *__restrict__ seg_offsets_t = job.seg_offsets_t;
     int len[kScanIpt], co_len = 0, ex_len = 0;
+    bool bad = false;                                        // a row without an occurrence
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
         len[i] = p0 + i < t_hi ? seg_offsets_t[p0 + i + 1] - seg_offsets_t[p0 + i] : 0;
+        bad |= p0 + i < t_hi && len[i] < 1;
         if (len[i] <= FS_SHORT_SEGMENT) len[i] = 0;          // short segments are not part of the class order
         co_len += f[i] ? len[i] : 0;
         ex_len += f[i] ? 0 : len[i];
     }
+    if (bad) atomicOr(flags, kFlagInternal);
     int co_total, ex_total;
     int co_before = block_exclusive_scan<int>(co_len, sh, co_total);
     int ex_before = block_exclusive_scan<int>(ex_len, sh, ex_total);
@@ -218,6 +222,22 @@ __device__ __forceinline__ void list_ex_next(const split_dev_job &job, int tile,
             job.ex_next_slot[p - r_found] = p;
         }
         r_found += f[i] ? 1 : 0;
+    }
+}
+
+// The rows of tile `tile` of U_t, each in the list of its class; `before`: collisions in the tiles before it.
+__device__ __forceinline__ void list_classes(const split_dev_job &job, int tile, int before) {
+    const int n_t = clamp_count(job.n_t_dev, job.cap_t);
+#pragma unroll
+    for (int i = 0; i < kScanIpt; ++i) {
+        const int p = tile * kScanTile + i * kScanThreads + threadIdx.x;
+        if (p < n_t) {
+            const int at = job.cidx[p];
+            const bool is_co = (at & kRowIsCo) != 0;
+            const int li = (at & (kRowIsCo - 1)) + (is_co ? before : tile * kScanTile - before);
+            (is_co ? job.co : job.ex)[li] = job.u_t[p];
+            (is_co ? job.co_slot : job.ex_slot)[li] = p;
+        }
     }
 }
 
@@ -273,26 +293,34 @@ __global__ __launch_bounds__(kScanThreads) void split_compact_kernel(const split
     }
 }
 
-// The lists, the records and the class order of batch t in one launch, walked by sorted positions: the first position of a
-// row puts it in its list and writes the head of its record; every position of a row with at most FS_SHORT_SEGMENT
+// The lists, the records and the class order of batch t in one launch.  Records and class order are walked by sorted
+// positions: the first position of a row writes the head of its record; every position of a row with at most FS_SHORT_SEGMENT
 // occurrences goes to the record, of a longer one to the class order: sorted position q (row slot s, the j-th occurrence of
 // that row) to [start of the class] + [occurrences of same-class rows before s] + j.
 // The row slot of a sorted position is found in the segment boundaries themselves: a workgroup's 1024 consecutive sorted
 // positions touch at most 1024 consecutive rows, whose boundaries it stages in LDS (the inverse map would
 // give the same slot at the price of one random 4-byte read per occurrence).  They lie in at most two tiles of rows, so that
 // what a workgroup needs of the tiles before them is three sums, taken while it looks for its rows.
-// The workgroups behind those of the positions list the rows of U_t1 that are not in U_t.
+// The workgroups behind those of the positions write the lists, a tile of U_t or of U_t1 each: those follow from the two lists
+// of rows, whatever the layout (listed by their first positions, the rows of a layout that does not fit its batch came to be
+// missing).  A layout whose rows have an occurrence each and lie between 0 and n is a consistent one; what is not is reported
+// here and where the lengths are looked at.
 // A launch of its own for the lists and the places of the rows cost 6 us of the self-contained step of 297 k IDs.
 __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class_dev_batch batch,
                                                                      int *__restrict__ flags) {
     FS_WG_TRACE(7);
     const split_dev_job &job = batch.split[blockIdx.y];
     const class_dev_job &cls = batch.cls[blockIdx.y];
-    if ((int)blockIdx.x >= cls.blocks + job.tiles_t1) return;
+    if ((int)blockIdx.x >= cls.blocks + job.tiles_t + job.tiles_t1) return;
     __shared__ int sh[kScanThreads / kWave];
     if ((int)blockIdx.x >= cls.blocks) {
-        const int tile = blockIdx.x - cls.blocks;
-        list_ex_next(job, tile, collisions_before(job.tile_cnt + job.tiles_t, tile, sh), sh);
+        int tile = blockIdx.x - cls.blocks;
+        if (tile < job.tiles_t) {
+            list_classes(job, tile, collisions_before(job.tile_cnt, tile, sh));
+        } else {
+            tile -= job.tiles_t;
+            list_ex_next(job, tile, collisions_before(job.tile_cnt + job.tiles_t, tile, sh), sh);
+        }
         return;
     }
     const int32_t *__restrict__ perm = cls.perm;
@@ -371,6 +399,7 @@ __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class
         job.counts_dev[0] = n_co;
         job.counts_dev[1] = n_t - n_co;
         job.counts_dev[2] = n_t1 - n_co;
+        if (n > 0 && n_u > 0 && (seg_offsets[0] != 0 || seg_offsets[n_u] != n)) atomicOr(flags, kFlagInternal);
     }
     // the first j with seg_win[j] > q, among the row starts, for all positions side by side
     int s[kScanIpt];
@@ -419,8 +448,6 @@ __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class
                 typedef int i32x4 __attribute__((ext_vector_type(4)));
                 *reinterpret_cast<i32x4 *>(rec) =
                     i32x4{(int)(row[k] & 0xFFFFFFFFll), (int)(row[k] >> 32), slot, len[k]};
-                (is_co ? job.co : job.ex)[li] = row[k];
-                (is_co ? job.co_slot : job.ex_slot)[li] = slot;
             }
             if (len[k] <= FS_SHORT_SEGMENT) {
                 rec[4 + (q - first[k])] = i[k];
@@ -472,7 +499,7 @@ static int launch_split_alone(fs_ctx *ctx, const fs_split_job &in, hipStream_t s
     memset(&batch, 0, sizeof(batch));
     batch.j[0] = split_job(in, ctx->split[set]);
     const dim3 grid((unsigned)(batch.j[0].tiles_t + batch.j[0].tiles_t1), 1u);
-    hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch);
+    hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch, ctx->d_flags);
     hipLaunchKernelGGL(split_compact_kernel, grid, dim3(kScanThreads), 0, s, batch);
     FS_LAUNCH_CHECK(ctx, "split kernels");
     return FS_OK;
@@ -510,9 +537,11 @@ int launch_split_class_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, c
         j.cperm = in.cperm; j.cslot = in.cslot; j.cstart = in.cstart; j.class_pos_dev = in.class_pos_dev;
         j.short_rec = in.short_rec;
         tiles = sj.tiles_t + sj.tiles_t1 > tiles ? sj.tiles_t + sj.tiles_t1 : tiles;
-        blocks = j.blocks + sj.tiles_t1 > blocks ? j.blocks + sj.tiles_t1 : blocks;
+        const int mine = j.blocks + sj.tiles_t + sj.tiles_t1;
+        blocks = mine > blocks ? mine : blocks;
     }
-    hipLaunchKernelGGL(split_flag_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kScanThreads), 0, s, batch);
+    hipLaunchKernelGGL(split_flag_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kScanThreads), 0, s, batch,
+                       ctx->d_flags);
     hipLaunchKernelGGL(class_scatter_kernel, dim3((unsigned)blocks, (unsigned)count), dim3(kScanThreads), 0, s, order,
                        ctx->d_flags);
     FS_LAUNCH_CHECK(ctx, "split and class order kernels");
@@ -522,7 +551,7 @@ int launch_split_class_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, c
 FS_TRACE_SETTER(split)
 
 // ---- the collision split for callers that cannot allocate ----------------------------------------------------
-// Same two kernels as launch_split_batch; the membership flags and per-tile counts live in a fixed device array
+// Same two kernels as launch_split_alone; the membership flags and per-tile counts live in a fixed device array
 // instead of a context's slab.
 constexpr int64_t kStaticSplitRows = FS_STATIC_SPLIT_MAX_ROWS;
 constexpr size_t kStaticFlagBytes = ((size_t)kStaticSplitRows + 16 + 255) / 256 * 256;
@@ -601,7 +630,7 @@ extern "C" int fs_collision_split_static(const int64_t *u_t, const int64_t *n_t_
         j.ex_next = ex_next; j.ex_next_slot = ex_next_slot; j.counts_dev = counts_dev;
         j.seg_offsets_t = nullptr; j.cstart_local = nullptr; j.tile_len = nullptr; j.cidx = nullptr;
         const dim3 grid((unsigned)(j.tiles_t + j.tiles_t1), 1u);
-        hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch);
+        hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch, (int *)nullptr);
         hipLaunchKernelGGL(split_compact_kernel, grid, dim3(kScanThreads), 0, s, batch);
     }
     const hipError_t le = hipGetLastError();

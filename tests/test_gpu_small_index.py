@@ -149,3 +149,39 @@ def test_layout_that_does_not_fit_its_batch_writes_nothing_out_of_range(n, what)
     if n <= 6144:
         assert (first, end) == (0, 0)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [6144, 9000, 300_000])
+@pytest.mark.parametrize("what", ["row without occurrences", "rows behind the batch", "every other row empty", "behind the start"])
+def test_lists_are_whole_whatever_the_layout_and_a_misfit_is_reported(n, what):
+    """The lists of the split follow from the two lists of rows alone: a layout that does not fit them leaves nothing of the
+    call before in them, and is reported by one workgroup and by the chain of launches alike."""
+    ctx = fs.Context(max_ids=n, max_dim=4)
+    u = n // 9
+    seg = (np.arange(n + 1, dtype=np.int64) * 9).clip(max=n)
+    seg[u:] = n
+    if what == "row without occurrences":
+        seg[u // 2] = seg[u // 2 + 1]
+    elif what == "rows behind the batch":
+        seg[u - 40:u + 1] = n + 9 * np.arange(41)
+    elif what == "every other row empty":
+        seg[1:u:2] = seg[2:u + 1:2][:len(seg[1:u:2])]
+    else:
+        seg[0] = 3
+    lay = {"unique": dev(np.arange(n, dtype=np.int64)), "seg_offsets": dev(seg.astype(np.int32)),
+           "perm": dev(np.arange(n, dtype=np.int32)), "n_unique": dev(np.array([u], dtype=np.int64)), "n": n}
+    u1 = np.arange(0, n, 3, dtype=np.int64)
+    split = fs.alloc_split(n, n, "cuda")
+    for k in ("co", "co_slot", "ex", "ex_slot", "ex_next", "ex_next_slot"):
+        split[k].fill_(-7)
+    fs.fs_collision_split_classes(ctx, lay, dev(u1), dev(np.array([u1.size], dtype=np.int64)), n, out=split)
+    assert fs.fs_check_async(ctx) == fs.FS_ERANGE and "internal" in ctx.last_error()
+    mine = np.arange(u)
+    want = {"co": mine[mine % 3 == 0], "ex": mine[mine % 3 != 0], "ex_next": u1[u1 >= u]}
+    assert split["counts"].cpu().tolist() == [want[k].size for k in ("co", "ex", "ex_next")]
+    for k, rows in want.items():
+        got = split[k].cpu().numpy()
+        assert np.array_equal(got[:rows.size], rows) and (got[rows.size:] == -7).all(), k
+        slots = split[k + "_slot"].cpu().numpy()[:rows.size]
+        assert np.array_equal(slots, rows if k != "ex_next" else rows // 3), k
+    ctx.close()

@@ -89,7 +89,8 @@ constexpr int kRowIsCo = 1 << 16;        // of cidx; below it the place among th
 static_assert(kScanTile <= kRowIsCo, "a place in a tile");
 
 // blocks [0, tiles_t) flag U_t against U_t1; blocks [tiles_t, tiles_t + tiles_t1) flag U_t1 against U_t
-// flags: looked at only with a class order
+// CLASSES: with a class order (a kernel of its own: the split alone is over 0.8 us sooner without that code)
+template <bool CLASSES>
 __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_dev_batch batch, int *__restrict__ flags) {
     FS_WG_TRACE(5);
     const split_dev_job &job = batch.j[blockIdx.y];
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_de
     if (t_lo >= n_mine) {                                    // whole workgroup: tile past the end
         if (threadIdx.x == 0) {
             tile_cnt[blockIdx.x] = 0;
-            if (side_t && job.seg_offsets_t != nullptr) job.tile_len[tile] = job.tile_len[tiles_t + tile] = 0;
+            if (CLASSES && side_t) job.tile_len[tile] = job.tile_len[tiles_t + tile] = 0;
         }
         return;
     }
@@ -153,18 +154,17 @@ __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_de
 #pragma unroll
         for (int i = 0; i < kScanIpt; ++i) f[i] = p0 + i < t_hi && sorted_contains(other, j0, j1, key[i]);
     }
-    const bool classes = side_t && job.seg_offsets_t != nullptr;
     int found = 0;
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i)
         if (p0 + i < t_hi) {
-            if (!classes) flag[p0 + i] = f[i] ? 1 : 0;
+            if (!CLASSES || !side_t) flag[p0 + i] = f[i] ? 1 : 0;
             found += f[i] ? 1 : 0;
         }
     int total;
     const int found_before = block_exclusive_scan<int>(found, sh, total);
     if (threadIdx.x == 0) tile_cnt[blockIdx.x] = total;      // number of collisions in this tile
-    if (!classes) return;
+    if (!CLASSES || !side_t) return;
     // For the class order: the class and the place of every row among the rows of its class in this tile; for the rows with
     // more than FS_SHORT_SEGMENT occurrences those of the same-class rows that precede it in the tile, and the tile's
     // totals of them.
@@ -201,9 +201,8 @@ __global__ __launch_bounds__(kScanThreads) void split_flag_kernel(const split_de
     }
 }
 
-// The rows of tile `tile` of U_t1 that are not in U_t; `before`: collisions in the tiles before it.
-__device__ __forceinline__ void list_ex_next(const split_dev_job &job, int tile, int before, int *sh) {
-    const int n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
+// The rows of tile `tile` of U_t1 (n_t1 rows) that are not in U_t; `before`: collisions in the tiles before it.
+__device__ __forceinline__ void list_ex_next(const split_dev_job &job, int n_t1, int tile, int before, int *sh) {
     const int p0 = tile * kScanTile + threadIdx.x * kScanIpt;
     bool f[kScanIpt];
     int found = 0;
@@ -225,9 +224,8 @@ __device__ __forceinline__ void list_ex_next(const split_dev_job &job, int tile,
     }
 }
 
-// The rows of tile `tile` of U_t, each in the list of its class; `before`: collisions in the tiles before it.
-__device__ __forceinline__ void list_classes(const split_dev_job &job, int tile, int before) {
-    const int n_t = clamp_count(job.n_t_dev, job.cap_t);
+// The rows of tile `tile` of U_t (n_t rows), each in the list of its class; `before`: collisions in the tiles before it.
+__device__ __forceinline__ void list_classes(const split_dev_job &job, int n_t, int tile, int before) {
 #pragma unroll
     for (int i = 0; i < kScanIpt; ++i) {
         const int p = tile * kScanTile + i * kScanThreads + threadIdx.x;
@@ -256,14 +254,14 @@ __global__ __launch_bounds__(kScanThreads) void split_compact_kernel(const split
     const split_dev_job &job = batch.j[blockIdx.y];
     if ((int)blockIdx.x >= job.tiles_t + job.tiles_t1) return;
     __shared__ int sh[kScanThreads / kWave];
+    const int n_t = clamp_count(job.n_t_dev, job.cap_t), n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
     const bool side_t = (int)blockIdx.x < job.tiles_t;
     const int tile = side_t ? blockIdx.x : blockIdx.x - job.tiles_t;
     const int found_before = collisions_before(job.tile_cnt + (side_t ? 0 : job.tiles_t), tile, sh);
     if (!side_t) {
-        list_ex_next(job, tile, found_before, sh);
+        list_ex_next(job, n_t1, tile, found_before, sh);
         return;
     }
-    const int n_t = clamp_count(job.n_t_dev, job.cap_t), n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
     const int p0 = tile * kScanTile + threadIdx.x * kScanIpt;
     bool f[kScanIpt];
     int found = 0;
@@ -315,11 +313,12 @@ __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class
     __shared__ int sh[kScanThreads / kWave];
     if ((int)blockIdx.x >= cls.blocks) {
         int tile = blockIdx.x - cls.blocks;
+        const int n_t = clamp_count(job.n_t_dev, job.cap_t), n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
         if (tile < job.tiles_t) {
-            list_classes(job, tile, collisions_before(job.tile_cnt, tile, sh));
+            list_classes(job, n_t, tile, collisions_before(job.tile_cnt, tile, sh));
         } else {
             tile -= job.tiles_t;
-            list_ex_next(job, tile, collisions_before(job.tile_cnt + job.tiles_t, tile, sh), sh);
+            list_ex_next(job, n_t1, tile, collisions_before(job.tile_cnt + job.tiles_t, tile, sh), sh);
         }
         return;
     }
@@ -499,7 +498,7 @@ static int launch_split_alone(fs_ctx *ctx, const fs_split_job &in, hipStream_t s
     memset(&batch, 0, sizeof(batch));
     batch.j[0] = split_job(in, ctx->split[set]);
     const dim3 grid((unsigned)(batch.j[0].tiles_t + batch.j[0].tiles_t1), 1u);
-    hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch, ctx->d_flags);
+    hipLaunchKernelGGL(split_flag_kernel<false>, grid, dim3(kScanThreads), 0, s, batch, ctx->d_flags);
     hipLaunchKernelGGL(split_compact_kernel, grid, dim3(kScanThreads), 0, s, batch);
     FS_LAUNCH_CHECK(ctx, "split kernels");
     return FS_OK;
@@ -540,7 +539,7 @@ int launch_split_class_batch(fs_ctx *ctx, int count, const fs_split_job *jobs, c
         const int mine = j.blocks + sj.tiles_t + sj.tiles_t1;
         blocks = mine > blocks ? mine : blocks;
     }
-    hipLaunchKernelGGL(split_flag_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kScanThreads), 0, s, batch,
+    hipLaunchKernelGGL(split_flag_kernel<true>, dim3((unsigned)tiles, (unsigned)count), dim3(kScanThreads), 0, s, batch,
                        ctx->d_flags);
     hipLaunchKernelGGL(class_scatter_kernel, dim3((unsigned)blocks, (unsigned)count), dim3(kScanThreads), 0, s, order,
                        ctx->d_flags);
@@ -630,7 +629,7 @@ extern "C" int fs_collision_split_static(const int64_t *u_t, const int64_t *n_t_
         j.ex_next = ex_next; j.ex_next_slot = ex_next_slot; j.counts_dev = counts_dev;
         j.seg_offsets_t = nullptr; j.cstart_local = nullptr; j.tile_len = nullptr; j.cidx = nullptr;
         const dim3 grid((unsigned)(j.tiles_t + j.tiles_t1), 1u);
-        hipLaunchKernelGGL(split_flag_kernel, grid, dim3(kScanThreads), 0, s, batch, (int *)nullptr);
+        hipLaunchKernelGGL(split_flag_kernel<false>, grid, dim3(kScanThreads), 0, s, batch, (int *)nullptr);
         hipLaunchKernelGGL(split_compact_kernel, grid, dim3(kScanThreads), 0, s, batch);
     }
     const hipError_t le = hipGetLastError();

@@ -161,8 +161,8 @@ void carve(fs_ctx *c, char *base, size_t *total) {
         const size_t fchunks = (size_t)fused_chunk_space(c->max_ids, k);
         c->fpart_head[k] = cv.take<double>(fchunks * (size_t)c->max_dim);
         c->fpart_last[k] = cv.take<double>(fchunks * (size_t)c->max_dim);
-        c->fcounters[k] = cv.take<int>(fchunks);
-        c->fcounters_sup[k] = cv.take<int>(fchunks);
+        c->fcounters[k] = cv.take<int>((size_t)fused_counters(c->max_ids, k));
+        c->fcounters_sup[k] = cv.take<int>((size_t)fused_counters(c->max_ids, k));
     }
     c->jag_unique = cv.take<int64_t>(n + 16);
     c->jag_seg = cv.take<int32_t>(n + 16);
@@ -320,7 +320,6 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     c->max_ids = max_ids;
     c->max_dim = max_dim;
     c->use_worker = true;
-    c->reduce_tag = 1;
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) {
         delete c;
@@ -341,7 +340,7 @@ int fs_ctx_create(fs_ctx **out, int device, int64_t max_ids, int32_t max_dim) {
     carve(c, static_cast<char *>(c->slab), &total);
     bool ok = hipMemset(c->slab, 0, 4096) == hipSuccess;
     for (int k = 0; k < kFusedSets; ++k) {
-        const size_t bytes = (size_t)fused_chunk_space(c->max_ids, k) * sizeof(int);
+        const size_t bytes = (size_t)fused_counters(c->max_ids, k) * sizeof(int);
         ok = ok && hipMemset(c->fcounters[k], 0, bytes) == hipSuccess;
         ok = ok && hipMemset(c->fcounters_sup[k], 0, bytes) == hipSuccess;
     }
@@ -419,7 +418,7 @@ int fs_check_async(fs_ctx *ctx, fs_stream stream) {
         // a fused pass that met an inconsistent class order left cut segments half counted in: the arrival
         // counters must stand at zero again before the next pass (every stream is idle here)
         for (int k = 0; k < kFusedSets; ++k) {
-            const size_t bytes = (size_t)fused_chunk_space(ctx->max_ids, k) * sizeof(int);
+            const size_t bytes = (size_t)fused_counters(ctx->max_ids, k) * sizeof(int);
             FS_HIP(ctx, hipMemset(ctx->fcounters[k], 0, bytes));
             FS_HIP(ctx, hipMemset(ctx->fcounters_sup[k], 0, bytes));
         }

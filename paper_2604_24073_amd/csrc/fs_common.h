@@ -54,6 +54,7 @@ static_assert(FS_SHORT_SEGMENT == 8, "record layout");
 // and not on the tables beside it, for the order of the sums is part of the result, so the lines lie between.
 constexpr int kFusedWaves = 4;                            // wavefronts per workgroup (they never synchronise)
 constexpr int kReduceSet = 2, kFusedSets = 3;             // sets of partial rows and counters
+constexpr int kReduceTurns = 32;                          // counters of the segment reduce, used in turn
 inline int chunk_log2(int64_t n) { return n >= 131072 ? 6 : (n >= 65536 ? 5 : 4); }
 
 // device-side error flag bits (ctx->d_flags[0])
@@ -220,7 +221,8 @@ struct fs_ctx {
     double *fpart_last[fs::kFusedSets];    // [chunks, max_dim] first piece of a cut segment that continues into the next chunk
     int *fcounters[fs::kFusedSets];        // [chunks] arrivals per cut segment (indexed by its first chunk); at 0 between launches
     int *fcounters_sup[fs::kFusedSets];    // [chunks] arrivals per group of sixteen pieces (indexed by its first chunk)
-    int reduce_tag;           // of the last segment reduce (fs_fused.hip); 1 after fs_ctx_create
+                                           // (kReduceSet: kReduceTurns + 1 such arrays behind each other)
+    int reduce_turn;          // segment reduces since their counters were cleared (fs_fused.hip)
     int64_t *d_zero;          // device scalar that stays 0 (stands in for a missing lookahead)
     // partitioner and jagged shuffles
     int64_t *jag_unique;      // [max_ids] by-products of sorting the lengths (distinct lengths, their extents, count)
@@ -318,6 +320,9 @@ inline int64_t fused_chunk_space(int64_t max_ids, int set = 0) {
     if (set == kReduceSet) return (most / 16 > max_ids / 64 ? most / 16 : max_ids / 64) + 2 * kFusedWaves;
     const int64_t batch = kMaxBatch * (ceil_div(most, 16) + kFusedWaves), largest = ceil_div(max_ids, 16) + 4 * kFusedWaves;
     return batch > largest ? batch : largest;
+}
+inline int64_t fused_counters(int64_t max_ids, int set) {
+    return fused_chunk_space(max_ids, set) * (set == kReduceSet ? kReduceTurns + 1 : 1);
 }
 
 // launchers implemented in the kernel translation units (host side, argument-checked callers)

@@ -111,7 +111,7 @@ __device__ __forceinline__ void batch_rows_body(const batch_update_job &job, int
         long_segments_of_layout<USE, LPR, fused_unr<LPR>()>(sh, (int)blockIdx.x, job.chunk_log2, job.grads, job.perm, job.n, job.seg_offsets,
                                                 job.u_t, (int)n_u, job.table, job.state, job.num_rows, job.gvec, job.lr,
                                                 job.eps, job.reduced, job.part_head, job.part_last, job.cnt_seg,
-                                                job.cnt_sup, job.tag, flags);
+                                                job.cnt_sup, flags);
     else
         short_rows_body<USE, LPR, FS_SHORT_UNR, true>((int)blockIdx.x - job.long_blocks, (int)gridDim.x - job.long_blocks, job.grads,
                                              job.n, row_source{nullptr, job.u_t, job.seg_offsets, job.perm}, n_u, job.table,
@@ -284,34 +284,34 @@ int launch_batch_update(fs_ctx *ctx, const fs_batch_update_job &job, hipStream_t
     return FS_OK;
 }
 
-// The arrivals of a segment reduce are counted up from the tag of its launch, which no arrival before it has reached: a
-// layout that makes no sense can leave a counter anywhere (chunks that see it leave early), and the next call on the context
-// is right all the same.  A counter has room for the arrivals at a segment, 1 + 2^30 / (64 * 16) at most, and for 511 tags;
-// the first of them is for launches that are recorded (they can run behind any other, and clear the counters themselves),
-// and when the others are used up the counters are cleared too.
-constexpr int kTagShift = 22, kTags = 1 << (31 - kTagShift);
-static_assert((1ll << 30) / (kWave * kFusedSuper) + 1 < 1ll << kTagShift, "arrivals at the longest segment");
-
+// A layout that makes no sense can leave arrivals in the counters of a segment reduce (chunks that see it leave early), and
+// the next call on the context is to be right all the same.  So every call has counters that no call has used since they were
+// cleared: kReduceTurns sets in turn, all cleared by a launch when they have been used once, and a further one for launches
+// that are recorded, which can run behind any other and clear it in front.
+// Against a launch in front of every call it costs a thirty-second of one.  In the kernel itself it cost more: arrivals
+// counted up from a number of the call's own, to which the counter is raised first, are two atomics each (400 k occurrences
+// x 32 of one row 23.6 -> 26.8 us); clearing the set of the call before took registers from the sums (400 k x 32, 27.7 -> 34.1).
 __global__ __launch_bounds__(256) void clear_counters_kernel(int *a, int *b, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n) a[i] = b[i] = 0;
 }
 
-// the tag of the next launch on `s`
-static int reduce_tag(fs_ctx *ctx, hipStream_t s, int *tag) {
+static int reduce_counters(fs_ctx *ctx, batch_update_job &j, hipStream_t s) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (s != nullptr) FS_HIP(ctx, hipStreamIsCapturing(s, &status));
     const bool recorded = status != hipStreamCaptureStatusNone;
-    if (!recorded && ++ctx->reduce_tag < kTags) {
-        *tag = ctx->reduce_tag << kTagShift;
-        return FS_OK;
+    const int64_t space = fused_chunk_space(ctx->max_ids, kReduceSet);
+    const bool round = !recorded && ctx->reduce_turn == kReduceTurns;
+    if (recorded || round) {
+        const int64_t from = recorded ? kReduceTurns * space : 0, n = recorded ? space : kReduceTurns * space;
+        hipLaunchKernelGGL(clear_counters_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, j.cnt_seg + from,
+                           j.cnt_sup + from, (int)n);
+        FS_LAUNCH_CHECK(ctx, "clear_counters_kernel");
     }
-    const int counters = (int)fused_chunk_space(ctx->max_ids, kReduceSet);
-    hipLaunchKernelGGL(clear_counters_kernel, dim3((unsigned)ceil_div(counters, 256)), dim3(256), 0, s,
-                       ctx->fcounters[kReduceSet], ctx->fcounters_sup[kReduceSet], counters);
-    FS_LAUNCH_CHECK(ctx, "clear_counters_kernel");
-    if (!recorded) ctx->reduce_tag = 2;
-    *tag = (recorded ? 1 : 2) << kTagShift;
+    if (round) ctx->reduce_turn = 0;
+    const int64_t at = (recorded ? kReduceTurns : ctx->reduce_turn++) * space;
+    j.cnt_seg += at;
+    j.cnt_sup += at;
     return FS_OK;
 }
 
@@ -320,7 +320,7 @@ int launch_reduce(fs_ctx *ctx, const float *grads, int64_t n, int32_t dim, const
     if (n == 0) return FS_OK;
     batch_update_job j = batch_job(ctx, fs_batch_update_job{grads, n, dim, perm, seg_offsets, nullptr, n_unique_dev,
                                                             nullptr, FS_F32, nullptr, 0, 0.f, 0.f, reduced}, kReduceSet);
-    const int rc = reduce_tag(ctx, s, &j.tag);
+    const int rc = reduce_counters(ctx, j, s);
     if (rc != FS_OK) return rc;
     const int lpr = lanes_per_row(j.gvec);
     const dim3 grid = batch_grid(j, lpr, kSumBlocks), block(kFusedWaves * kWave);

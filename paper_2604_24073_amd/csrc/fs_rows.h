@@ -181,7 +181,7 @@ template <row_use USE, int LPR, int UNR, typename PARKED>
 __device__ __forceinline__ void long_chunk(PARKED &sh, const chunk_view &ch, const f32x4 *__restrict__ grads,
                                            const int64_t *__restrict__ u_t, void *table, float *state, int64_t num_rows,
                                            int gvec, float lr, float eps, f32x4 *reduced, double *part_head,
-                                           double *part_last, int *cnt_seg, int *cnt_sup, int tag, bool bad, int *flags) {
+                                           double *part_last, int *cnt_seg, int *cnt_sup, bool bad, int *flags) {
     constexpr int GPW = kWave / LPR;          // rows per wavefront instruction
     constexpr int BP = GPW * UNR;             // positions per batch
     constexpr int CAP = PARKED::kMost;
@@ -331,18 +331,13 @@ __device__ __forceinline__ void long_chunk(PARKED &sh, const chunk_view &ch, con
     }
     const int sup_first = c_first[0] + 1 + ((chunk - c_first[0] - 1) / kFusedSuper) * kFusedSuper;
     const int sup_last = (sup_first + kFusedSuper - 1 < c_last[0]) ? sup_first + kFusedSuper - 1 : c_last[0];
-    // What a launch whose layout makes no sense leaves in a counter is below the tag of the next one, and gives way to it.
-    auto arrive = [&](int *counter) {
-        if constexpr (USE == kSumOnly)
-            (void)__hip_atomic_fetch_max(counter, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int was = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return USE == kSumOnly ? was - tag : was;
-    };
     int old = 0;
     if (valid[0] || valid[1]) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // my pieces are acknowledged before I count myself in
-        if (lane == 0 && valid[0]) old = arrive(&cnt_sup[sup_first]);
-        if (lane == 1 && valid[1]) old = arrive(&cnt_seg[c_first[1]]);
+        if (lane == 0 && valid[0])
+            old = __hip_atomic_fetch_add(&cnt_sup[sup_first], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 1 && valid[1])
+            old = __hip_atomic_fetch_add(&cnt_seg[c_first[1]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     const int old_head = __shfl(old, 0, kWave), old_tail = __shfl(old, 1, kWave);
 
@@ -379,7 +374,7 @@ __device__ __forceinline__ void long_chunk(PARKED &sh, const chunk_view &ch, con
         const int n_sup = (c_last[0] - c_first[0] + kFusedSuper - 1) / kFusedSuper;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         int o2 = 0;
-        if (lane == 0) o2 = arrive(&cnt_seg[c_first[0]]);
+        if (lane == 0) o2 = __hip_atomic_fetch_add(&cnt_seg[c_first[0]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         o2 = __builtin_amdgcn_readfirstlane(o2);
         if (o2 == n_sup) finish_segment(seg_s[0], c_first[0], c_last[0]);   // 1 + n_sup arrivals in all
     }
@@ -450,7 +445,7 @@ __device__ __forceinline__ void long_segments_body(
     ch.head_cut = a != lo && sl_prev == __builtin_amdgcn_readfirstlane(ch.sl);
     ch.rest = ((ch.tails >> (span - 1)) & 1ull) == 0;
     long_chunk<USE, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
-                               cnt_seg, cnt_sup, 0, bad, flags);
+                               cnt_seg, cnt_sup, bad, flags);
 }
 
 // The position-cut path straight over the layout of a batch (sorted positions, segment boundaries): positions of
@@ -461,7 +456,7 @@ __device__ __forceinline__ void long_segments_of_layout(
     PARKED &sh, const int block, const int log2, const f32x4 *__restrict__ grads, const int32_t *__restrict__ perm, int n,
     const int32_t *__restrict__ seg_offsets, const int64_t *__restrict__ u_t, int n_u, void *table, float *state,
     int64_t num_rows, int gvec, float lr, float eps, f32x4 *reduced, double *part_head, double *part_last, int *cnt_seg,
-    int *cnt_sup, int tag, int *flags) {
+    int *cnt_sup, int *flags) {
     const int lane = threadIdx.x & (kWave - 1);
     const int size = 1 << log2;
     chunk_view ch;
@@ -506,7 +501,7 @@ __device__ __forceinline__ void long_segments_of_layout(
     ch.head_cut = (ch.live & 1ull) != 0 && first_begin < a;
     ch.rest = ((ch.live >> ch.last) & 1ull) != 0 && last_end > a + span;
     long_chunk<USE, LPR, UNR>(sh, ch, grads, u_t, table, state, num_rows, gvec, lr, eps, reduced, part_head, part_last,
-                               cnt_seg, cnt_sup, tag, false, flags);
+                               cnt_seg, cnt_sup, false, flags);
 }
 
 // Short path: the rows of one class whose segment has at most FS_SHORT_SEGMENT occurrences.  The
@@ -700,7 +695,6 @@ struct batch_update_job {
     f32x4 *reduced;
     double *part_head, *part_last;
     int *cnt_seg, *cnt_sup;
-    int tag;                            // sums alone: what the counters of this launch start from (0: they stand at zero)
 };
 
 // `set`: the partial rows and counters it works in
@@ -714,7 +708,6 @@ inline batch_update_job batch_job(fs_ctx *ctx, const fs_batch_update_job &in, in
     j.table = in.table; j.state = in.state; j.num_rows = in.num_rows; j.reduced = (f32x4 *)in.reduced;
     j.part_head = ctx->fpart_head[set]; j.part_last = ctx->fpart_last[set];
     j.cnt_seg = ctx->fcounters[set]; j.cnt_sup = ctx->fcounters_sup[set];
-    j.tag = 0;
     return j;
 }
 

@@ -34,7 +34,7 @@ __device__ __forceinline__ void step_rows(const batch_update_job &job, int block
         long_segments_of_layout<USE, LPR, UNR>(*reinterpret_cast<parked *>(lds), block, job.chunk_log2, job.grads, job.perm, job.n,
                                                job.seg_offsets, job.u_t, (int)n_u, job.table, job.state, job.num_rows, job.gvec,
                                                job.lr, job.eps, job.reduced, job.part_head, job.part_last, job.cnt_seg,
-                                               job.cnt_sup, 0, flags);
+                                               job.cnt_sup, flags);
     else
         short_rows_body<USE, LPR, FS_SHORT_UNR, true, kStepWaves>(block - job.long_blocks, short_blocks, job.grads, job.n,
                                                                   row_source{nullptr, job.u_t, job.seg_offsets, job.perm}, n_u,

@@ -19,7 +19,9 @@ enum { FS_TIME_REDUCE = 0, FS_TIME_GATHER = 1, FS_TIME_UPDATE_CO = 2, FS_TIME_UP
 
 /* slots > 0: one in `every` later steps (fs_prioritized_step, fs_prioritized_step_pipelined)
  * brackets its gather and its two fused reduce+update passes (FS_TIME_UPDATE_CO, FS_TIME_UPDATE_EX; one
- * launch for all rows - fs_prioritized_step, a pipelined call on one stream - counts as FS_TIME_UPDATE_CO; FS_TIME_REDUCE is not produced by the fused path) with HIP events on the stream each is
+ * launch for all rows - fs_prioritized_step, a pipelined call on one stream - counts as FS_TIME_UPDATE_CO, and where
+ * fs_prioritized_step runs its index half in that launch, up to 8192 IDs in each batch, its time is in it;
+ * FS_TIME_REDUCE is not produced by the fused path) with HIP events on the stream each is
  * launched on (ring of `slots` sampled steps).  An event record costs the
  * host more than a kernel launch: sample sparsely when the steps themselves are being timed.
  * slots == 0 turns it off (the default) and frees the events. */

@@ -827,7 +827,7 @@ void index_jobs(const fs_step_args &x, bool t, bool t1, fs_unique_job &uj, fs_sp
                       t ? x.n_t : 0, t1 ? x.n_t1 : 0, x.co, x.co_slot, x.ex, x.ex_slot, x.ex_next,
                       x.ex_next_slot, x.counts_dev, t ? x.seg_offsets_t : nullptr, t1 ? x.co_flag_t1 : nullptr,
                       key_bits_of(x.num_rows)};
-    cj = fs_class_job{x.perm_t, x.n_unique_t_dev, x.seg_offsets_t, t ? x.n_t : 0, t ? x.n_t : 0, x.cperm, x.cslot,
+    cj = fs_class_job{x.perm_t, x.n_unique_t_dev, x.seg_offsets_t, t ? x.n_t : 0, x.cperm, x.cslot,
                       x.cstart, x.class_pos_dev, x.u_t, x.short_rec};
 }
 
@@ -1126,7 +1126,7 @@ int fs_collision_split_classes(fs_ctx *ctx, const int64_t *u_t, const int64_t *n
     if (rc != FS_OK) return rc;
     const fs_split_job sj = {u_t, cap_t > 0 ? n_t_dev : nullptr, u_t1, cap_t1 > 0 ? n_t1_dev : nullptr, cap_t, cap_t1,
                              co, co_slot, ex, ex_slot, ex_next, ex_next_slot, counts_dev, cap_t > 0 ? seg_offsets_t : nullptr};
-    const fs_class_job cj = {perm_t, n_t_dev, seg_offsets_t, n_t, cap_t, cperm, cslot, cstart, class_pos_dev, u_t, short_rec};
+    const fs_class_job cj = {perm_t, n_t_dev, seg_offsets_t, n_t, cperm, cslot, cstart, class_pos_dev, u_t, short_rec};
     return launch_split_class_batch(ctx, 1, &sj, &cj, as_stream(stream), 0);
 }
 

@@ -1,6 +1,6 @@
 // Dedup of one iteration's row IDs by ranges: the batch is cut into ranges of keys of about equal weight, every range is
 // sorted, stably, by one workgroup in LDS.  Same outputs as the radix sort of fs_unique.hip, bit for bit, in four
-// launches instead of eight (two per radix pass, two for the compaction):
+// launches (up to 49152 IDs three) instead of eight (two per radix pass, two for the compaction):
 //
 //   sample     a stratified sample of the batch is sorted by one workgroup, every fourth entry becomes a boundary (up to 64
 //              ranges, 49152 IDs, the partition finds the boundaries by itself)
@@ -12,8 +12,9 @@
 //   compact    the distinct rows of the ranges, closed up
 //
 // What bounds it: launches and dependent rounds, not bytes (a few MB).  Sample, partition, sort, compact of one batch alone,
-// against the passes and the compaction of the radix sort: 34 k IDs 5 + 7 + 14 + 4 us against 54, 297 k 10 + 9 + 19 + 4
-// against 62.  Beside the class passes the smaller workgroups count as well: the passes leave a SIMD 64 registers, so
+// against the passes and the compaction of the radix sort: 34 k IDs 5 + 7 + 14 + 4 us against 54 (without the sample 10.6 + 12
+// + 4.8), 297 k 10 + 9 + 19 + 4 against 62.  Beside the class passes the smaller workgroups count as well: the passes of
+// tables of one row width leave a SIMD 64 registers (those of tables of several widths next to none, fs_fused.hip), so
 // that 512 threads of 64 registers start as soon as one workgroup of theirs ends, where the 1024 threads of a radix pass
 // wait for most of a compute unit.  Ten steps of a 4M x 128 table 1040 -> 972 us, of eight tables 5630 -> 5490.
 // Ranges of 384 IDs (256 threads) or of 768 (512 threads): the same within 1 %; 1024 threads: 1012 and 5500.
@@ -236,8 +237,9 @@ __device__ __forceinline__ int sample_place(int i, int m_log2, int n) {
 }
 
 // One workgroup of 256 threads: beside four workgroups of the batch update a compute unit has registers for one wavefront a
-// SIMD.  With 512 threads it waited for one of them to end, and the whole index half of a self-contained step behind it (297 k
-// IDs 140.0 -> 138.1 us).  The sort with 256 threads, in turn with this one: the same step 137.1 / 135.1, but plain operations
+// SIMD, and up to 512 ranges (393216 IDs) this one takes 60.  With 512 threads it waited for one of them to end, and the whole
+// index half of a self-contained step behind it (297 k IDs 140.0 -> 138.1 us).  Beyond, with 101 registers and 46 KB of LDS, it
+// waits all the same, and is 1.5 us longer alone than with 512 threads (400 k IDs 59.3 -> 60.9).  The sort with 256 threads, in turn with this one: the same step 137.1 / 135.1, but plain operations
 // of 34 k IDs 66.6 / 69.9, balancing 65 k samples 86.3 / 88.8, ten pipelined steps of a 64 M row table 1042 / 1051.
 template <int MOST>
 __global__ __launch_bounds__(kSampleThreads) void bucket_sample_kernel(const bucket_dev_batch batch) {

@@ -30,8 +30,9 @@ constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 4;
 constexpr int kScanTile = kScanThreads * kScanIpt;
 // Most tiles of rows that a class order takes, and the most distinct rows that the host may allow for (it knows occurrences
-// only).
-constexpr int kClassOrderTiles = 60 * 1024 / (2 * (int)sizeof(int));
+// only).  Every workgroup of its second launch adds up three numbers of all tiles before its own, work that grows with the
+// square of the batch: 7.7 k tiles are 60 rounds of loads a thread.
+constexpr int kClassOrderTiles = 7680;
 constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
 // Without the dedup in front the chain is two launches, with the class order or without: IDs up to which the one workgroup
@@ -147,7 +148,7 @@ struct fs_class_job {
     const int32_t *perm;
     const int64_t *n_unique_dev;    // rows of the batch (bounds seg_offsets)
     const int32_t *seg_offsets;
-    int64_t n, cap_u;
+    int64_t n;
     int32_t *cperm, *cslot, *cstart, *class_pos_dev;
     const int64_t *u_t;
     int32_t *short_rec;

@@ -55,8 +55,9 @@ inline int ranges_log2(int64_t n) {
 // IDs of a batch from which the ranges are 1024: two to a compute unit (58 KB of LDS each), 512 of them run at once.
 constexpr int64_t kBucketOneWave = (int64_t)kBucketMean << 9;
 
-// By ranges or by radix passes?  Four launches by ranges, whatever the keys; two per radix pass of up to 9 key bits and two
-// more.  Radix / ranges, us (tables of 64 fp32 columns, Zipf IDs):
+// By ranges or by radix passes?  Four launches by ranges, whatever the keys (up to 49152 IDs three; three or two where the
+// order alone is wanted); two per radix pass of up to 9 key bits and two more.  Radix / ranges, us (tables of 64 fp32 columns,
+// Zipf IDs), all of them of the form with four launches:
 //   one pass (512 rows): radix at every size.  The dedup alone, 9 k IDs 22 / 25, 131 k 23 / 29, 393 k 26 / 34, 786 k 32 / 55;
 //     ten steps of 60 k 281 / 313, of 500 k 776 / 814; self-contained step of 500 k 98 / 117; 65 k samples up to 500 long
 //     balanced 73.9 / 78.2.  (Below five rows and 34 k IDs the ranges lead, 28 / 23; no table is as small.)

@@ -6,18 +6,19 @@
 // the ranks in a zig-zag - rank i takes sorted positions i, 2n-1-i, 2n+i, 4n-1-i, ...  The deal is a
 // closed form per sorted position, one thread each.
 //
-// Indexed permute: output sample k is input sample sample_of[k].  Up to 4096 samples two launches: one
+// Indexed permute: output sample k is input sample sample_of[k].  Up to 8192 samples two launches: one
 // workgroup lays out the output offsets, then the copy; beyond, lengths summed per tile of samples, the
 // output offsets by a scan with tile prefixes, and the copy.  The copy is driven
 // by the OUTPUT (every lane writes consecutive pieces of the output, so a 16K-item sample costs per
-// item what a short one costs): a workgroup takes 2048 to 8192 consecutive output pieces, is told which samples
-// they begin and end in, and marks the starts of its samples as bits in LDS.
+// item what a short one costs): a workgroup takes 2048 to 8192 consecutive output pieces, looks up (up to 8192
+// samples, where nothing is left in the context) or is told which samples they begin and end in, and marks the
+// starts of its samples as bits in LDS.
 //
 // VBS: the same sort, then the sorted order is cut into n runs of about equal total weight.
 //
 // Keyed transpose, ranged dispatch and ranged combine (same section of the paper) are the same copy
-// under a computed order of the F x B segments of a keyed jagged tensor, written down where the lengths
-// are summed.
+// under a computed order of the F x B segments of a keyed jagged tensor, always told; the order is written down where
+// the lengths are summed, beyond the 4096 segments of one workgroup.
 #include "fs_common.h"
 #include "fs_device.h"
 

@@ -78,7 +78,9 @@ def group_tables(tabs: Sequence[TableBuffers], G: int) -> List[List[TableBuffers
     the launches of their class passes and gathers inside a call, and tables of one row width take the kernels
     written for it, so a group should hold few widths, and
     the groups run side by side, so they should be about equally heavy: every assignment is tried (a shard has a
-    handful of tables) and the one with the smallest (heaviest group / mean group + 0.05 x launch classes) kept."""
+    handful of tables) and the one with the smallest (heaviest group / mean group + 0.05 x row widths of the groups)
+    kept.  Ten steps of eight tables of 64, 128 and 256 columns in two groups, with the 0.05 / with 0 in turn: 5482,
+    5062 / 5499, 5671 us; six and four tables came out in the same groups either way."""
     tabs = list(tabs)
     if G <= 1 or len(tabs) > 12:
         return [tabs[g::max(G, 1)] for g in range(max(G, 1))]

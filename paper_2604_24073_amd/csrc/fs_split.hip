@@ -314,6 +314,8 @@ __global__ __launch_bounds__(kScanThreads) void class_scatter_kernel(const class
     if ((int)blockIdx.x >= cls.blocks) {
         int tile = blockIdx.x - cls.blocks;
         const int n_t = clamp_count(job.n_t_dev, job.cap_t), n_t1 = clamp_count(job.n_t1_dev, job.cap_t1);
+        // (the launch is sized for occurrences, of which there are several to a row: most of these have nothing to list)
+        if (tile < job.tiles_t ? tile * kScanTile >= n_t : (tile - job.tiles_t) * kScanTile >= n_t1) return;
         if (tile < job.tiles_t) {
             list_classes(job, n_t, tile, collisions_before(job.tile_cnt, tile, sh));
         } else {

@@ -591,7 +591,7 @@ def measure_extras(args, cfg, loop, t, stats, s_next, step_gbps):
             ctx, 1, t.table, t.state, cfg.lr, cfg.eps, t.grads[0], lay_a, sp_a)), cpb(1)),
         "gather_rows_kernel": (alone(lambda: fs.fs_gather_jagged(ctx, t.table, t.values[1], t.offsets[1], out=emb)), by["gather"]),
         "dedup (4 launches)": (alone(lambda: fs.fs_unique_ids(ctx, t.values[1], tab.num_rows, out=lay_b)), by["unique"]),
-        "split + class order + records (3 launches)": (alone(lambda: fs.fs_collision_split_classes(
+        "split + class order + records (2 launches)": (alone(lambda: fs.fs_collision_split_classes(
             ctx, lay_a, lay_b["unique"], lay_b["n_unique"], n[1], out=sp_a)), by["split"]),
     }
     if fs.fs_check_async(ctx) != fs.FS_OK:

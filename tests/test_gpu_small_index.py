@@ -141,8 +141,7 @@ def test_layout_that_does_not_fit_its_batch_writes_nothing_out_of_range(n, what)
         split[k] = torch.full((size[k] + GUARD,), -7, dtype=split[k].dtype, device="cuda")
     fs.fs_collision_split_classes(ctx, lay, u1, dev(np.array([u1.numel()], dtype=np.int64)), n, out=split)
     rc = fs.fs_check_async(ctx)
-    if n <= 6144 or what != "stale count":                  # the chain sees no position of a row without occurrences
-        assert rc == fs.FS_ERANGE and "internal" in ctx.last_error()
+    assert rc == fs.FS_ERANGE and "internal" in ctx.last_error()
     for k in guarded:
         assert bool((split[k][size[k]:] == -7).all()), k
     first, end = split["class_pos"].cpu().tolist()

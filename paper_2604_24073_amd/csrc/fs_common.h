@@ -30,8 +30,8 @@ constexpr int kScanThreads = 256;
 constexpr int kScanIpt = 4;
 constexpr int kScanTile = kScanThreads * kScanIpt;
 // Most tiles of rows that a class order takes, and the most distinct rows that the host may allow for (it knows occurrences
-// only).  Every workgroup of its second launch adds up three numbers of all tiles before its own, work that grows with the
-// square of the batch: 7.7 k tiles are 60 rounds of loads a thread.
+// only).  Every workgroup of its second launch adds up three numbers of all tiles, work that grows with the square of the
+// batch: 7.7 k tiles are 30 rounds of three loads a thread.
 constexpr int kClassOrderTiles = 7680;
 constexpr int64_t kClassOrderMax = (int64_t)kClassOrderTiles * kScanTile;
 
